@@ -186,8 +186,8 @@ relax_status relax_rope_table_init(const relax_layer_dims *dims, float *table, r
 
 /* out[i,r] = sum_c x[i,c] * W[r,c] with W decoded on the fly (Sec. 4.2 fused decode;
  * Sec. 5.1: the kernel is picked from the symbolic n at run time -- matrix-vector kernel
- * for one row, split-K MFMA kernel for a few rows, tiled MFMA GEMM for many).
- * x [n,k] fp16, out [n,m] fp16, fp32 accumulation.  The few-row kernel keeps its split-K
+ * for one row, streaming or split-K MFMA kernel for a few rows, tiled MFMA GEMM for many).
+ * x [n,k] fp16, out [n,m] fp16, fp32 accumulation.  The few-row kernels keep their
  * partial tiles in ws (Sec. 4.4, lifted workspace): relax_matmul_workspace_bytes(w, n_max)
  * is enough for every n <= n_max; with ws == NULL or fewer bytes the call still succeeds
  * through the other two kernels.  Errors: NULL, SHAPE (n<1, m<1, k<8, k%8),
@@ -202,6 +202,8 @@ relax_status relax_dequant_matmul(const uint16_t *x, const relax_qmat *w, uint16
  * matrix-vector kernel (the one the LM head uses) for a few rows, the tiled MFMA GEMM without its decode
  * step (k % 128 == 0, m % 4 == 0) from the row count on at which its estimated time falls below that of the
  * passes -- 24 rows on a 4096 x 4096 matrix, 8 on 22016 x 4096 (measured: bench.py --workload half_sweep).
+ * 2 .. 32 rows of up to 8192 columns (k % 128 == 0, m % 4 == 0, out 8-byte aligned; 4096 from 17 rows on) take
+ * the streaming few-row kernel instead of either: one pass over the matrix.
  * the test switch "half_matmul_gemm_rows" (relax_mi355_bench.h) with r > 0 fixes the crossover at r rows instead (0, the
  * default: by estimate).  Device pointers, x and w 16-byte aligned.  Errors: NULL, SHAPE (n<1, m<1, k<8,
  * k%8, alignment), UNSUPPORTED (k > 73728).                                                                */
@@ -322,7 +324,9 @@ relax_status relax_dequant_matmul_q3(const uint16_t *x, const relax_qmat *w, uin
  * relax_unpack_q3_native: out int8 [m,k] in -4..3 from a native matrix -- equals relax_unpack_q3 of the canonical one.
  * relax_dequant_matmul_q3_native: out[n,m] fp16 = x[n,k] times the decoded native matrix, fp32 accumulation.  Up to 15
  * rows of x are taken 4, 2 or 1 per pass over the matrix (k <= 4096: 4; k <= 8192: 2), the decode of a weight shared
- * by the rows of a pass, so a few rows cost little more than one (k <= 12288).  From 16 rows on, a matrix with
+ * by the rows of a pass, so a few rows cost little more than one (k <= 12288).  2 .. 32 rows with k % 256 == 0 (and k
+ * within what a launch without workspace holds: 12288 up to 16 rows, 6144 beyond), m % 4 == 0, s 4-byte and out 8-byte
+ * aligned take the streaming few-row MFMA kernel: one pass.  Else, from 16 rows on, a matrix with
  * k % 128 == 0 and m % 4 == 0 (out 8-byte aligned) goes through the tiled MFMA GEMM that serves the 4-bit format at
  * large n, its decode step replaced by the 3-bit one: the matrix is read once whatever n is, and k is not limited.
  * x 16-byte aligned; errors as the canonical call. */
@@ -335,10 +339,10 @@ relax_status relax_dequant_matmul_q3_native(const uint16_t *x, const relax_qmat 
  * `weights` in the GPU-native 3-bit layout above (group 0 or 32; their rows within what the 3-bit matmul takes: k % 32 == 0,
  * k <= 12288).  One row (n == 1) runs the five fused launches of the 4-bit decode layer on the 3-bit stream of the same
  * matrix-vector kernel (norms, rotary + append, attention merge, residuals and SwiGLU inside the four launches, fp32 sums
- * not rounded in between).  From two rows on the 3-bit matmuls have the plain fp16 epilogue only, so the layer is a sequence of launches of their own
- * -- RMSNorm, matmul, rotary + append, attention, matmul, residual add, RMSNorm, matmul, SwiGLU, matmul, residual add --
- * with the dispatch on n of relax_dequant_matmul_q3_native inside (matrix-vector passes below 16 rows, tiled MFMA GEMM from
- * there on); nothing is fused, a 3-bit matmul output is rounded to fp16 before the residual is added, the residual stream
+ * not rounded in between).  From two rows on the layer is a sequence of launches of their own -- RMSNorm, matmul, rotary +
+ * append, attention, matmul, residual add, RMSNorm, matmul, SwiGLU, matmul, residual add.  A matmul that the streaming few-row
+ * kernel takes (up to 32 rows, some up to 64) has the step behind it as its epilogue, on unrounded fp32 sums; the others follow
+ * the dispatch on n of relax_dequant_matmul_q3_native, their output rounded to fp16 before the step.  The residual stream
  * x1 stays fp32 between the two halves of the layer.  Its workspace is its own: relax_layer_q3_workspace_bytes(dims, n_max,
  * L_max, B_max) bytes, 256-byte aligned (0 for invalid arguments); the first 256 bytes are the flag line of
  * relax_workspace_init, which this call neither reads nor writes.  hidden % 8 == 0, ffn % 8 == 0, x and out 16-byte
@@ -352,9 +356,8 @@ relax_status relax_decoder_layer_q3(const relax_layer_dims *dims, const relax_la
  * dims, cache, descriptor and x / out conventions as relax_decoder_layer, the four matrices row-major fp16 -- wqkv
  * [(h + 2g) d, H], wo [H, h d], wgu [2F, H] (gate rows, then up rows), wdown [H, F] -- and the two norm vectors, all device
  * memory, 16-byte aligned, owned by the caller.  From two rows on it is, like the 3-bit layer, a sequence of launches of
- * their own around relax_half_matmul's dispatch on n (matrix-vector passes for a few rows, tiled MFMA GEMM from the row
- * count on at which its estimate is lower): nothing is fused, a matmul output is rounded to fp16 before the residual is
- * added, x1 stays fp32.  One row (n == 1, rows of at most 12288 columns) runs the five fused launches of the 4-bit decode
+ * their own around relax_half_matmul's dispatch on n (tiled MFMA GEMM or matrix-vector passes, the output rounded to fp16
+ * before the next step) or, up to 32 rows, around the streaming few-row kernel with that step as its epilogue; x1 stays fp32.  One row (n == 1, rows of at most 12288 columns) runs the five fused launches of the 4-bit decode
  * layer on the fp16 stream of the same matrix-vector kernel: the norms, rotary + append, the attention merge, the
  * residuals and SwiGLU happen inside the four matrix-vector launches, on fp32 sums that are not rounded in between.
  * Workspace: relax_layer_f16_workspace_bytes(dims, n_max, L_max, B_max) bytes, 256-byte aligned (0 for invalid arguments).

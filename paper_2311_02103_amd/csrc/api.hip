@@ -12,6 +12,15 @@ using namespace relax;
 namespace {
 
 inline size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
+inline bool aligned(const void *p, size_t bytes) { return (reinterpret_cast<uintptr_t>(p) & (bytes - 1)) == 0; }
+
+// k ranges of the streaming few-row kernel for a packed matrix at n rows, with at most `partial_floats` floats for the partial rows
+// of a launch that is cut along k; 0: it does not take the call.  out: whatever the epilogue writes or adds (8-byte accesses).
+int stream_ranges(int wmode, const relax_qmat &w, const void *x, const void *out, int n, int epi, size_t partial_floats, bool folded = false)
+{
+    if (!aligned(x, 16) || !aligned(w.q, 4) || !aligned(w.s, 4) || !aligned(out, 8)) return 0;
+    return fewrow_ranges(wmode, n, w.m, w.k, epi, folded, partial_floats);
+}
 
 // ---- Dynamic shape-aware memory planning (Sec. 4.3, Alg. 3) over the intermediates of one layer call ----------------------
 // The layer is a fixed sequence of destination-passing operations; every intermediate has a symbolic size in the rows n
@@ -296,6 +305,8 @@ hipError_t half_matmul_enqueue(const uint16_t *x, const uint16_t *w, uint16_t *o
 {
     bool use_gemm;
     const int gemm_rows = g_opt_half_gemm_rows.load();
+    if (gemm_rows == 0 && aligned(x, 16) && aligned(w, 16) && aligned(out, 8) && fewrow_ranges(W_F16, n, m, k, EPI_F16, false, 0))
+        return launch_fewrow_f16(x, w, n, m, k, EPI_F16, 1, out, nullptr, nullptr, nullptr, st_);
     if (gemm_rows > 0) {
         use_gemm = n >= gemm_rows;
     } else {
@@ -506,8 +517,11 @@ relax_status relax_dequant_matmul(const uint16_t *x, const relax_qmat *w, uint16
     // runtime dispatch on the symbolic n (Sec. 5.1): matrix-vector kernel for one row, split-K MFMA kernel for a few
     // (when the caller brought the workspace for its partial tiles), tiled MFMA GEMM otherwise
     const bool tiled_first = gemm_prefers_tiled(w->m, n) && gemm_mfma_eligible(*w, x, EPI_F16);
-    if (!tiled_first && n >= kSkinnyMinN && n <= kSkinnyMaxN && ws && gemm_skinny_eligible(*w, x, n, EPI_F16) &&
-        (reinterpret_cast<uintptr_t>(ws) & 15) == 0 && ws_bytes >= sizeof(float) * gemm_skinny_partial_floats(w->m, w->k, n))
+    const bool ws_fits = ws && aligned(ws, 16) && n <= kSkinnyMaxN && ws_bytes >= sizeof(float) * gemm_skinny_partial_floats(w->m, w->k, n);
+    const int kr = tiled_first || !ws_fits ? 0 : stream_ranges(W_Q4, *w, x, out, n, EPI_F16, ws_bytes / sizeof(float));
+    if (kr > 0)
+        return hip_status(launch_fewrow_q4(x, *w, n, EPI_F16, kr, out, nullptr, nullptr, static_cast<float *>(ws), static_cast<hipStream_t>(stream)));
+    if (!tiled_first && n >= kSkinnyMinN && n <= kSkinnyMaxN && ws_fits && gemm_skinny_eligible(*w, x, n, EPI_F16))
         return hip_status(launch_gemm_skinny(x, *w, n, EPI_F16, out, nullptr, nullptr, static_cast<float *>(ws),
                                              static_cast<hipStream_t>(stream)));
     if (n >= kGemmMinN && gemm_mfma_eligible(*w, x, EPI_F16))
@@ -630,14 +644,22 @@ relax_status layer_enqueue(const relax_layer_dims &dm, const relax_layer_weights
     // More than one row: matrix path (same entry point, same binary) -- the matmuls run on MFMA, as the split-K
     // few-row kernel up to kSkinnyMaxN rows and as the tiled GEMM above, with the light steps as separate kernels.
     float *skinny_ws = reinterpret_cast<float *>(base + pl.skinny);
+    // k ranges of the streaming few-row kernel where it takes this matmul (0: it does not).  Its finishing pass, if any, is the RMSNorm
+    // launch behind the output projection (and behind the down projection when the next layer's norm is known).
+    auto folds = [&](int epi) { return epi == EPI_RESID_F32 || (epi == EPI_RESID_F16 && next_norm && xn_done); };
+    auto stream = [&](const relax_qmat &wq, const void *xin, int epi) {
+        if (gemm_prefers_tiled(wq.m, n) && n >= kGemmMinN && gemm_mfma_eligible(wq, xin, epi)) return 0;
+        return stream_ranges(W_Q4, wq, xin, epi == EPI_RESID_F16 ? (const void *)out : epi == EPI_RESID_F32 ? (const void *)x : nullptr, n, epi, pl.mm_floats, folds(epi));
+    };
     auto mat_ok = [&](const relax_qmat &wq, const void *xin, int epi) {
-        return (n <= kSkinnyMaxN && gemm_skinny_eligible(wq, xin, n, epi)) || (n >= kGemmMinN && gemm_mfma_eligible(wq, xin, epi));
+        return stream(wq, xin, epi) || (n <= kSkinnyMaxN && gemm_skinny_eligible(wq, xin, n, epi)) || (n >= kGemmMinN && gemm_mfma_eligible(wq, xin, epi));
     };
     auto few_row = [&](const relax_qmat &wq, const void *xin, int epi) {      // the few-row kernel takes this matmul
         if (gemm_prefers_tiled(wq.m, n) && n >= kGemmMinN && gemm_mfma_eligible(wq, xin, epi)) return false;
         return n <= kSkinnyMaxN && gemm_skinny_eligible(wq, xin, n, epi);
     };
     auto matmul = [&](const uint16_t *xin, const relax_qmat &wq, int epi, uint16_t *o16, float *o32, const void *resid) {
+        if (const int kr = stream(wq, xin, epi)) return launch_fewrow_q4(xin, wq, n, epi, kr, o16, o32, resid, skinny_ws, st_);
         if (few_row(wq, xin, epi)) return launch_gemm_skinny(xin, wq, n, epi, o16, o32, resid, skinny_ws, st_);
         return launch_gemm_mfma(xin, wq, n, epi, o16, o32, resid, st_, skinny_ws, pl.mm_floats);
     };
@@ -660,7 +682,18 @@ relax_status layer_enqueue(const relax_layer_dims &dm, const relax_layer_weights
         hipError_t fuse_err = hipSuccess;
         const bool fuse_finish = g_opt_fuse_finish.load() != 0;
         auto fused = [&](const uint16_t *xin, const relax_qmat &wq, int epi, uint16_t *o16, float *o32, const void *resid, const SkinnyFuse &f) {
-            if (!fuse_finish || !gemm_skinny_fuse_ok(wq, epi, f)) return false;
+            if (!fuse_finish) return false;
+            const int kr = stream(wq, xin, epi);
+            if (kr == 1) {   // no finishing pass: rotary + append is its epilogue, a norm is not
+                if (epi != EPI_F16 || !fewrow_fuse_ok(dm, *cache)) return false;
+                fuse_err = launch_fewrow_q4(xin, wq, n, epi, kr, o16, o32, resid, skinny_ws, st_, &f);
+                return true;
+            }
+            if (!gemm_skinny_fuse_ok(wq, epi, f)) return false;
+            if (kr > 1) {
+                fuse_err = launch_fewrow_q4(xin, wq, n, epi, kr, o16, o32, resid, skinny_ws, st_, &f);
+                return true;
+            }
             if (few_row(wq, xin, epi)) {
                 fuse_err = launch_gemm_skinny(xin, wq, n, epi, o16, o32, resid, skinny_ws, st_, &f);
                 return true;
@@ -853,8 +886,72 @@ relax_status check_q3mat(const relax_qmat &w, int32_t m, int32_t k)
 }
 hipError_t q3_matmul(const uint16_t *x, const relax_qmat &w, int32_t n, uint16_t *out, hipStream_t st_)
 {
+    if (stream_ranges(W_Q3, w, x, out, n, EPI_F16, 0)) return launch_fewrow_q3(x, w, n, EPI_F16, 1, out, nullptr, nullptr, nullptr, st_);
     if (n >= kQ3GemmRows && gemm_q3_eligible(x, w, out)) return launch_gemm_q3(x, w, n, out, st_);
     return launch_gemv_q3_native(x, w, n, out, st_);
+}
+
+// The launches of a layer whose matmuls are not those of the 4-bit path (3-bit and fp16 weights), from two rows on.  Matrices in the
+// order wqkv, wo, wgu, wdown:
+//   plain(i, x, out)                   out = x times matrix i, fp16 epilogue, any n
+//   ranges(i, x, out, epi, floats, folded)   k ranges of the streaming few-row kernel for matrix i with this epilogue, the partial
+//                                      rows of more than one in at most `floats` floats; 0: it does not take it
+//   streamed(i, ...)                   that kernel
+// Where the streaming kernel takes a matmul, rotary + append, the residual adds and SwiGLU happen in it (or in its finishing
+// pass); the partial rows use what the workspace holds free at that point, its size is the same on either way.
+template <typename Plain, typename Ranges, typename Streamed>
+relax_status flat_layer(const relax_layer_dims &dm, const uint16_t *norm_attn, const uint16_t *norm_ffn, const uint16_t *x, const relax_kv_cache &cache,
+                        const SeqTable &st, int32_t L_max, uint16_t *out, int32_t n, char *base, const Q3Plan &pl, const Plain &plain,
+                        const Ranges &ranges, const Streamed &streamed, hipStream_t st_)
+{
+    uint16_t *xn = reinterpret_cast<uint16_t *>(base + pl.ws.xn), *qkv = reinterpret_cast<uint16_t *>(base + pl.ws.qkv);
+    uint16_t *attn = reinterpret_cast<uint16_t *>(base + pl.ws.attn), *act = reinterpret_cast<uint16_t *>(base + pl.ws.act);
+    uint16_t *gu = reinterpret_cast<uint16_t *>(base + pl.gu), *tmp = reinterpret_cast<uint16_t *>(base + pl.tmp);
+    float *x1 = reinterpret_cast<float *>(base + pl.ws.x1), *partials = reinterpret_cast<float *>(base + pl.ws.partials);
+    float *free_qkv = x1, *free_o = reinterpret_cast<float *>(act), *free_ffn = reinterpret_cast<float *>(gu);    // ... up to the end of the workspace
+    auto floats_from = [&](const float *p) { return (size_t)(base + pl.total - reinterpret_cast<const char *>(p)) / sizeof(float); };
+    const int32_t hd = dm.n_heads * dm.head_dim, qkvw = hd + 2 * dm.n_kv_heads * dm.head_dim;
+    const size_t nh = (size_t)n * dm.hidden;
+#define RELAX_TRY(call) do { if ((call) != hipSuccess) return RELAX_ERR_HIP; } while (0)
+    RELAX_TRY(launch_rmsnorm(x, norm_attn, xn, n, dm.hidden, dm.rms_eps, st_));
+    SkinnyFuse fq = {};
+    fq.dm = &dm, fq.cache = &cache, fq.st = &st;
+    const relax_qmat qkv_shape = {nullptr, nullptr, qkvw, dm.hidden, 32};
+    const int rq = ranges(0, xn, qkv, EPI_F16, floats_from(free_qkv), false);
+    if (rq == 1 ? fewrow_fuse_ok(dm, cache) : rq > 1 && gemm_skinny_fuse_ok(qkv_shape, EPI_F16, fq)) {
+        RELAX_TRY(streamed(0, xn, EPI_F16, rq, qkv, nullptr, nullptr, free_qkv, &fq));
+    } else {
+        RELAX_TRY(plain(0, xn, qkv));
+        RELAX_TRY(launch_rope_append(qkv, dm, cache, st, st_));
+    }
+    RELAX_TRY(launch_attention(qkv, qkvw, cache, dm, st, L_max, attn, partials, st_));
+    // cut along k, the finishing pass of the output projection is the second RMSNorm too
+    SkinnyFuse fo = {};
+    fo.norm_w = norm_ffn, fo.xn = xn, fo.eps = dm.rms_eps;
+    const relax_qmat o_shape = {nullptr, nullptr, dm.hidden, hd, 32};
+    const bool norm_folds = gemm_skinny_fuse_ok(o_shape, EPI_RESID_F32, fo);
+    const int ro = ranges(1, attn, x1, EPI_RESID_F32, floats_from(free_o), norm_folds);
+    if (ro) {
+        RELAX_TRY(streamed(1, attn, EPI_RESID_F32, ro, nullptr, x1, x, free_o, ro > 1 && norm_folds ? &fo : nullptr));
+    } else {
+        RELAX_TRY(plain(1, attn, tmp));
+        RELAX_TRY(launch_add_rows(x, tmp, x1, nh, st_));
+    }
+    if (!(ro > 1 && norm_folds)) RELAX_TRY(launch_rmsnorm_f32(x1, norm_ffn, xn, n, dm.hidden, dm.rms_eps, st_));
+    if (const int rg = ranges(2, xn, act, EPI_SWIGLU, floats_from(free_ffn), false)) {
+        RELAX_TRY(streamed(2, xn, EPI_SWIGLU, rg, act, nullptr, nullptr, free_ffn, nullptr));
+    } else {
+        RELAX_TRY(plain(2, xn, gu));
+        RELAX_TRY(launch_swiglu_rows(gu, act, n, dm.ffn, st_));
+    }
+    if (const int rd = ranges(3, act, out, EPI_RESID_F16, floats_from(free_ffn), false)) {
+        RELAX_TRY(streamed(3, act, EPI_RESID_F16, rd, out, nullptr, x1, free_ffn, nullptr));
+    } else {
+        RELAX_TRY(plain(3, act, tmp));
+        RELAX_TRY(launch_add_out(x1, tmp, out, nh, st_));
+    }
+#undef RELAX_TRY
+    return RELAX_OK;
 }
 }  // namespace
 
@@ -892,11 +989,9 @@ relax_status relax_decoder_layer_q3(const relax_layer_dims *dims, const relax_la
     if (rc != RELAX_OK) return rc;
 
     char *base = static_cast<char *>(ws);
-    uint16_t *xn = reinterpret_cast<uint16_t *>(base + pl.ws.xn), *qkv = reinterpret_cast<uint16_t *>(base + pl.ws.qkv);
+    uint16_t *qkv = reinterpret_cast<uint16_t *>(base + pl.ws.qkv);
     uint16_t *attn = reinterpret_cast<uint16_t *>(base + pl.ws.attn), *act = reinterpret_cast<uint16_t *>(base + pl.ws.act);
-    uint16_t *gu = reinterpret_cast<uint16_t *>(base + pl.gu), *tmp = reinterpret_cast<uint16_t *>(base + pl.tmp);
     float *x1 = reinterpret_cast<float *>(base + pl.ws.x1), *partials = reinterpret_cast<float *>(base + pl.ws.partials);
-    const size_t nh = (size_t)n * dm.hidden;
 
     // One row: the five launches of the 4-bit decode layer on the 3-bit stream of the same kernel (the norms, rotary + append,
     // the attention merge, the residuals and SwiGLU inside the four matrix-vector launches).
@@ -937,18 +1032,15 @@ relax_status relax_decoder_layer_q3(const relax_layer_dims *dims, const relax_la
             return RELAX_OK;
         }
     }
-    if (launch_rmsnorm(x, wt->norm_attn, xn, n, dm.hidden, dm.rms_eps, st_) != hipSuccess) return RELAX_ERR_HIP;
-    if (q3_matmul(xn, wt->wqkv, n, qkv, st_) != hipSuccess) return RELAX_ERR_HIP;
-    if (launch_rope_append(qkv, dm, *cache, st, st_) != hipSuccess) return RELAX_ERR_HIP;
-    if (launch_attention(qkv, qkvw, *cache, dm, st, L_max, attn, partials, st_) != hipSuccess) return RELAX_ERR_HIP;
-    if (q3_matmul(attn, wt->wo, n, tmp, st_) != hipSuccess) return RELAX_ERR_HIP;
-    if (launch_add_rows(x, tmp, x1, nh, st_) != hipSuccess) return RELAX_ERR_HIP;
-    if (launch_rmsnorm_f32(x1, wt->norm_ffn, xn, n, dm.hidden, dm.rms_eps, st_) != hipSuccess) return RELAX_ERR_HIP;
-    if (q3_matmul(xn, wt->wgu, n, gu, st_) != hipSuccess) return RELAX_ERR_HIP;
-    if (launch_swiglu_rows(gu, act, n, dm.ffn, st_) != hipSuccess) return RELAX_ERR_HIP;
-    if (q3_matmul(act, wt->wdown, n, tmp, st_) != hipSuccess) return RELAX_ERR_HIP;
-    if (launch_add_out(x1, tmp, out, nh, st_) != hipSuccess) return RELAX_ERR_HIP;
-    return RELAX_OK;
+    const relax_qmat *mats[4] = {&wt->wqkv, &wt->wo, &wt->wgu, &wt->wdown};
+    auto plain = [&](int i, const uint16_t *xin, uint16_t *o) { return q3_matmul(xin, *mats[i], n, o, st_); };
+    auto ranges = [&](int i, const void *xin, const void *o, int epi, size_t floats, bool folded) {
+        return stream_ranges(W_Q3, *mats[i], xin, o, n, epi, floats, folded);
+    };
+    auto streamed = [&](int i, const uint16_t *xin, int epi, int kr, uint16_t *o16, float *o32, const void *resid, float *part, const SkinnyFuse *f) {
+        return launch_fewrow_q3(xin, *mats[i], n, epi, kr, o16, o32, resid, part, st_, f);
+    };
+    return flat_layer(dm, wt->norm_attn, wt->norm_ffn, x, *cache, st, L_max, out, n, base, pl, plain, ranges, streamed, st_);
 }
 
 // ---- the same sequence on plain fp16 weights (the fp16 models of the paper's LLM evaluation, Sec. 5.1) -----------------
@@ -985,11 +1077,9 @@ relax_status relax_decoder_layer_f16(const relax_layer_dims *dims, const relax_l
     if (rc != RELAX_OK) return rc;
 
     char *base = static_cast<char *>(ws);
-    uint16_t *xn = reinterpret_cast<uint16_t *>(base + pl.ws.xn), *qkv = reinterpret_cast<uint16_t *>(base + pl.ws.qkv);
+    uint16_t *qkv = reinterpret_cast<uint16_t *>(base + pl.ws.qkv);
     uint16_t *attn = reinterpret_cast<uint16_t *>(base + pl.ws.attn), *act = reinterpret_cast<uint16_t *>(base + pl.ws.act);
-    uint16_t *gu = reinterpret_cast<uint16_t *>(base + pl.gu), *tmp = reinterpret_cast<uint16_t *>(base + pl.tmp);
     float *x1 = reinterpret_cast<float *>(base + pl.ws.x1), *partials = reinterpret_cast<float *>(base + pl.ws.partials);
-    const size_t nh = (size_t)n * dm.hidden;
 
     // One row: the launch sequence of the 4-bit decode layer -- five launches, the light steps folded into the matvecs'
     // prologues and epilogues -- on the fp16 stream of the same kernel.  Needs rows that fit the kernel's x registers.
@@ -1029,18 +1119,16 @@ relax_status relax_decoder_layer_f16(const relax_layer_dims *dims, const relax_l
             return RELAX_OK;
         }
     }
-    if (launch_rmsnorm(x, wt->norm_attn, xn, n, dm.hidden, dm.rms_eps, st_) != hipSuccess) return RELAX_ERR_HIP;
-    if (half_matmul_enqueue(xn, wt->wqkv, qkv, n, qkvw, dm.hidden, st_) != hipSuccess) return RELAX_ERR_HIP;
-    if (launch_rope_append(qkv, dm, *cache, st, st_) != hipSuccess) return RELAX_ERR_HIP;
-    if (launch_attention(qkv, qkvw, *cache, dm, st, L_max, attn, partials, st_) != hipSuccess) return RELAX_ERR_HIP;
-    if (half_matmul_enqueue(attn, wt->wo, tmp, n, dm.hidden, hd, st_) != hipSuccess) return RELAX_ERR_HIP;
-    if (launch_add_rows(x, tmp, x1, nh, st_) != hipSuccess) return RELAX_ERR_HIP;
-    if (launch_rmsnorm_f32(x1, wt->norm_ffn, xn, n, dm.hidden, dm.rms_eps, st_) != hipSuccess) return RELAX_ERR_HIP;
-    if (half_matmul_enqueue(xn, wt->wgu, gu, n, 2 * dm.ffn, dm.hidden, st_) != hipSuccess) return RELAX_ERR_HIP;
-    if (launch_swiglu_rows(gu, act, n, dm.ffn, st_) != hipSuccess) return RELAX_ERR_HIP;
-    if (half_matmul_enqueue(act, wt->wdown, tmp, n, dm.hidden, dm.ffn, st_) != hipSuccess) return RELAX_ERR_HIP;
-    if (launch_add_out(x1, tmp, out, nh, st_) != hipSuccess) return RELAX_ERR_HIP;
-    return RELAX_OK;
+    const uint16_t *mats[4] = {wt->wqkv, wt->wo, wt->wgu, wt->wdown};
+    const int32_t ms[4] = {qkvw, dm.hidden, 2 * dm.ffn, dm.hidden}, ks[4] = {dm.hidden, hd, dm.hidden, dm.ffn};
+    auto plain = [&](int i, const uint16_t *xin, uint16_t *o) { return half_matmul_enqueue(xin, mats[i], o, n, ms[i], ks[i], st_); };
+    auto ranges = [&](int i, const void *, const void *, int epi, size_t floats, bool folded) {      // every pointer was checked for 16 bytes above
+        return g_opt_half_gemm_rows.load() != 0 ? 0 : fewrow_ranges(W_F16, n, ms[i], ks[i], epi, folded, floats);
+    };
+    auto streamed = [&](int i, const uint16_t *xin, int epi, int kr, uint16_t *o16, float *o32, const void *resid, float *part, const SkinnyFuse *f) {
+        return launch_fewrow_f16(xin, mats[i], n, ms[i], ks[i], epi, kr, o16, o32, resid, part, st_, f);
+    };
+    return flat_layer(dm, wt->norm_attn, wt->norm_ffn, x, *cache, st, L_max, out, n, base, pl, plain, ranges, streamed, st_);
 }
 
 }  // extern "C"
@@ -1192,6 +1280,8 @@ relax_status relax_dequant_matmul_q3_native(const uint16_t *x, const relax_qmat 
         return RELAX_ERR_SHAPE;
     // From kQ3GemmRows rows on the matrix is read once by the tiled MFMA GEMM (decode on the way into LDS); below that, or
     // for a shape the GEMM does not take, it is streamed once per pass of up to four rows of x.
+    if (stream_ranges(W_Q3, *w, x, out, n, EPI_F16, 0))
+        return hip_status(launch_fewrow_q3(x, *w, n, EPI_F16, 1, out, nullptr, nullptr, nullptr, static_cast<hipStream_t>(stream)));
     if (n >= kQ3GemmRows && gemm_q3_eligible(x, *w, out))
         return hip_status(launch_gemm_q3(x, *w, n, out, static_cast<hipStream_t>(stream)));
     if (!gemv_q3_supported(w->m, w->k)) return RELAX_ERR_UNSUPPORTED;

@@ -1,0 +1,162 @@
+// Host side of the streaming few-row matmul (fewrow_kernel.h): which calls it takes, how they are cut, the launch.
+#include "fewrow_kernel.h"
+
+namespace relax {
+
+namespace fewrow {
+hipError_t launch_q4g32(int nb, int uw, const Args &a, int lds_tiles, hipStream_t stream);
+hipError_t launch_q4g64(int nb, int uw, const Args &a, int lds_tiles, hipStream_t stream);
+hipError_t launch_q4g128(int nb, int uw, const Args &a, int lds_tiles, hipStream_t stream);
+hipError_t launch_q3(int nb, int uw, const Args &a, int lds_tiles, hipStream_t stream);
+hipError_t launch_f16(int nb, int uw, const Args &a, int lds_tiles, hipStream_t stream);
+}  // namespace fewrow
+
+namespace {
+
+using namespace fewrow;
+
+bool uw_built(bool f16, int nb, int uw)                   // the instances of launch_nb
+{
+    if (f16) return uw >= 1 && (nb == 1 ? uw <= 6 || uw == 8 : nb == 2 && uw <= 4);
+    return uw >= 1 && uw <= (nb == 1 ? 6 : nb == 2 ? 3 : 1);
+}
+
+int lds_tiles(int nb) { return (int)(kLdsBytes / ((size_t)kWaves * nb * 1024)); }
+
+int blocks_of(int n) { return n <= 16 ? 1 : n <= 32 ? 2 : 4; }
+
+int tiles_of(int m, int epi) { return epi == EPI_SWIGLU ? (m / 2 + 7) / 8 : (m + kTileRows - 1) / kTileRows; }
+
+// The cut into kg k ranges; false: no instance of the kernel for it.
+bool cut(bool f16, int nb, int m, int k, int epi, int kg, Plan &p)
+{
+    const int units = k / unit_columns(f16);
+    p.kg = kg, p.uw = (units + kWaves * kg - 1) / (kWaves * kg);
+    if (!uw_built(f16, nb, p.uw)) return false;
+    p.tiles = tiles_of(m, kg > 1 ? (int)EPI_F16 : epi);
+    p.rg = std::min(p.tiles, 256 / kg);
+    // a workgroup whose epilogue is not plain partial rows keeps the sums of all its tiles in LDS: more workgroups if they don't fit
+    if (kg == 1 || nb == 1)
+        while ((p.tiles + p.rg - 1) / p.rg > lds_tiles(nb)) p.rg = std::min(p.tiles, p.rg + 256 / kg);
+    return true;
+}
+
+// The number of k ranges with the least estimated time:
+//   - 5.8 us for the launch, the first data and the sums over the wavefronts;
+//   - its share of x: every workgroup fetches n x (k / kg) values from its L2, at about 24 us per MB (measured: 4096 x 4096 at
+//     16 rows 9.4 us against 7.3 at two, 4096 x 11008 18.4 against 12.2 with one k range), so long rows and many rows of x want
+//     k ranges, and taller row ranges with them;
+//   - its row tiles, at the rate of the whole stream, or what a CU can take of it where few of them work;
+//   - with more than one k range the partial rows, written and read again, and the finishing launch (3 us; next to nothing when
+//     that launch also does a step that would be a launch of its own otherwise: `folded`).
+int best_ranges(int fmt, int n, int m, int k, int epi, bool folded, size_t partial_floats, double *time_us)
+{
+    const bool f16 = fmt == F_F16;
+    const double bytes_per_weight = f16 ? 2.0 : fmt == F_Q3 ? 0.4375 : 0.5625;
+    const double mfma = blocks_of(n) == 1 ? 1.03 : blocks_of(n) == 2 ? 1.14 : 1.3;      // two and four MFMAs per decoded word, and their sums
+    double best_us = 0.0;
+    int best = 0;
+    for (int kg = 1; kg <= 16 && (kg == 1 || (size_t)kg * n * m <= partial_floats); ++kg) {
+        Plan p;
+        if (!cut(f16, blocks_of(n), m, k, epi, kg, p)) continue;
+        const double per = (p.tiles + p.rg - 1) / p.rg, rounds = (p.rg * kg + 255) / 256, slice = (double)k / kg;
+        const double stream_us = std::max((double)m * k * bytes_per_weight / 6.1e6, rounds * per * kTileRows * slice * bytes_per_weight / 32e3);
+        const double us = (stream_us + rounds * 24e-6 * n * slice * 2.0 + (kg > 1 ? (folded ? 0.5 : 3.0) + (double)kg * n * m * 8.0 / 6e6 : 0.0)) * mfma;
+        if (best == 0 || us < best_us) best = kg, best_us = us;
+        if (p.uw == 1) break;
+    }
+    *time_us = 5.8 + best_us;
+    return best;
+}
+
+bool shape_ok(bool f16, int n, int m, int k, int epi)
+{
+    if (n < kFewRowMin || n > kFewRowMax || k < 1 || k % unit_columns(f16) != 0) return false;
+    return epi == EPI_SWIGLU ? m % 8 == 0 : m % 4 == 0;
+}
+
+constexpr size_t kMaxBuffer = 0x7FFFFFFFu;                // offsets into a buffer stay below 2^31
+
+hipError_t launch(int fmt, const uint16_t *x, const void *w, size_t w_bytes, const uint16_t *s, size_t s_bytes, int n, int m, int k, int epi, int k_ranges,
+                  uint16_t *out_f16, float *out_f32, const void *resid, float *partial, hipStream_t stream, const SkinnyFuse *fuse)
+{
+    Plan p;
+    const int nb = blocks_of(n);
+    if (!cut(fmt == F_F16, nb, m, k, epi, k_ranges, p)) return hipErrorInvalidValue;
+    Args a = {};
+    a.x = x, a.w = w, a.s = s, a.x_bytes = (uint32_t)((size_t)n * k * 2), a.w_bytes = (uint32_t)w_bytes, a.s_bytes = (uint32_t)s_bytes;
+    a.n = n, a.m = m, a.k = k, a.kg = p.kg, a.rg = p.rg, a.tiles = p.tiles;
+    a.out_f16 = out_f16, a.out_f32 = out_f32, a.resid = resid;
+    a.delta = 8;
+    const bool rope = epi == EPI_F16 && fuse;
+    if (p.kg > 1) {
+        a.epi = kPartial, a.out_f32 = partial;
+    } else if (rope) {
+        const relax_layer_dims &dm = *fuse->dm;
+        a.epi = EPI_ROPE_KV, a.delta = dm.head_dim / 2, a.ropeshift = dm.head_dim == 128 ? 3 : 2;
+        a.kc = fuse->cache->k, a.vc = fuse->cache->v, a.rope = fuse->cache->rope;
+        a.h = dm.n_heads, a.g = dm.n_kv_heads, a.d = dm.head_dim, a.cap = dm.kv_capacity, a.st = *fuse->st;
+    } else {
+        a.epi = epi;
+        if (epi == EPI_SWIGLU) a.delta = m / 2;
+    }
+    a.batch = std::min((p.tiles + p.rg - 1) / p.rg, lds_tiles(nb));
+    hipError_t e;
+    switch (fmt) {
+    case F_Q4G32: e = launch_q4g32(nb, p.uw, a, a.batch, stream); break;
+    case F_Q4G64: e = launch_q4g64(nb, p.uw, a, a.batch, stream); break;
+    case F_Q4G128: e = launch_q4g128(nb, p.uw, a, a.batch, stream); break;
+    case F_Q3: e = launch_q3(nb, p.uw, a, a.batch, stream); break;
+    default: e = launch_f16(nb, p.uw, a, a.batch, stream); break;
+    }
+    if (e != hipSuccess || p.kg == 1) return e;
+    return launch_skinny_finish(partial, p.kg, n, m, epi, out_f16, out_f32, resid, stream, fuse);
+}
+
+}  // namespace
+
+int fewrow_ranges(int wmode, int n, int m, int k, int epi, bool folded, size_t partial_floats)
+{
+    if (!shape_ok(wmode == W_F16, n, m, k, epi) || (wmode == W_F16 && n > 32)) return 0;
+    const size_t row = wmode == W_F16 ? (size_t)k * 2 : wmode == W_Q3 ? (size_t)k / 32 * 12 : (size_t)k / 2;
+    if ((size_t)m * row > kMaxBuffer) return 0;
+    double us = 0.0;
+    const int kr = best_ranges(wmode == W_F16 ? F_F16 : wmode == W_Q3 ? F_Q3 : F_Q4G32, n, m, k, epi, folded, partial_floats, &us);
+    // A 4-bit matrix may also go through the split-K few-row kernel, whose workgroups own 128 rows and an eighth of k: an eighth of the
+    // x traffic, a lower rate.  Its time with the finishing pass (7B, 13B and 70B shapes, 16 / 32 / 64 rows: 12 to 73, 13.5 to 86, 17 to
+    // 71 us) is 8.5 + 0.085 n us and 0.17 + 0.004 n us per MB; it stays the better one on long rows with few weight rows (4096 x 11008
+    // at 16 rows 15.4 against 17.3 us, 8192 x 8192 16.4 against 18.7), the stream on the others (22016 x 4096 18.8 against 22.4,
+    // 57344 x 8192 57 against 73).
+    if (wmode == W_Q4 && n > 2 && partial_floats >= gemm_skinny_partial_floats(m, k, n) && gemm_skinny_partial_floats(m, k, n) > 0) {
+        const double mb = (double)m * k * 0.5625e-6, split_us = 8.5 + 0.085 * n + (0.17 + 0.004 * n) * mb - (folded ? 3.0 : 0.0);
+        if (split_us < us) return 0;
+    }
+    return kr;
+}
+
+bool fewrow_fuse_ok(const relax_layer_dims &dm, const relax_kv_cache &cache)
+{
+    return ((reinterpret_cast<uintptr_t>(cache.k) | reinterpret_cast<uintptr_t>(cache.v)) & 7) == 0 && (reinterpret_cast<uintptr_t>(cache.rope) & 15) == 0 &&
+           (dm.head_dim == 64 || dm.head_dim == 128);
+}
+
+hipError_t launch_fewrow_q4(const uint16_t *x, const relax_qmat &w, int n, int epi, int k_ranges, uint16_t *out_f16, float *out_f32, const void *resid, float *partial,
+                            hipStream_t stream, const SkinnyFuse *fuse)
+{
+    const int gs = gshift_of(w.group);
+    return launch(gs == 0 ? F_Q4G32 : gs == 1 ? F_Q4G64 : F_Q4G128, x, w.q, (size_t)w.m * w.k / 2, w.s, (size_t)w.m * scales_per_row(w.k, gs) * 2, n, w.m, w.k,
+                  epi, k_ranges, out_f16, out_f32, resid, partial, stream, fuse);
+}
+hipError_t launch_fewrow_q3(const uint16_t *x, const relax_qmat &w, int n, int epi, int k_ranges, uint16_t *out_f16, float *out_f32, const void *resid, float *partial,
+                            hipStream_t stream, const SkinnyFuse *fuse)
+{
+    return launch(F_Q3, x, w.q, (size_t)w.m * (w.k / 32) * 12, w.s, (size_t)w.m * (w.k / 32) * 2, n, w.m, w.k, epi, k_ranges, out_f16, out_f32, resid, partial,
+                  stream, fuse);
+}
+hipError_t launch_fewrow_f16(const uint16_t *x, const uint16_t *w, int n, int m, int k, int epi, int k_ranges, uint16_t *out_f16, float *out_f32, const void *resid,
+                             float *partial, hipStream_t stream, const SkinnyFuse *fuse)
+{
+    return launch(F_F16, x, w, (size_t)m * k * 2, nullptr, 0, n, m, k, epi, k_ranges, out_f16, out_f32, resid, partial, stream, fuse);
+}
+
+}  // namespace relax

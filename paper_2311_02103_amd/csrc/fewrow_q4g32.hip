@@ -1,0 +1,8 @@
+// The streaming few-row matmul on one weight format: a code object of its own so that the formats compile side by side.
+#include "fewrow_kernel.h"
+
+namespace relax {
+namespace fewrow {
+hipError_t launch_q4g32(int nb, int uw, const Args &a, int lds_tiles, hipStream_t stream) { return launch_nb<F_Q4G32>(nb, uw, a, lds_tiles, stream); }
+}  // namespace fewrow
+}  // namespace relax

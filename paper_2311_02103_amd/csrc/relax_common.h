@@ -422,6 +422,20 @@ hipError_t launch_skinny_finish(const float *partial, int splits, int n, int m, 
                                 hipStream_t stream, const SkinnyFuse *fuse);
 hipError_t launch_gemm_skinny(const uint16_t *x, const relax_qmat &w, int n, int epi, uint16_t *out_f16, float *out_f32, const void *resid,
                               float *partial, hipStream_t stream, const SkinnyFuse *fuse = nullptr);
+// Streaming matmul for a few rows on any weight format (fewrow_kernel.h).  fewrow_ranges: how many k ranges the launch is best cut
+// into when partial_floats floats of workspace are at hand; 0: the kernel does not take the shape.  With one range the epilogues
+// (residuals, SwiGLU, and with `fuse` rotary + append) happen in the kernel and `partial` is not used; with more, `partial` holds
+// k_ranges * n * m floats and the finishing pass of the split-K kernel follows.  folded: that pass replaces a launch of its own
+// (the RMSNorm of the result), so cutting along k costs next to nothing.
+constexpr int kFewRowMin = 2, kFewRowMax = 64;
+int fewrow_ranges(int wmode, int n, int m, int k, int epi, bool folded, size_t partial_floats);
+bool fewrow_fuse_ok(const relax_layer_dims &dm, const relax_kv_cache &cache);
+hipError_t launch_fewrow_q4(const uint16_t *x, const relax_qmat &w, int n, int epi, int k_ranges, uint16_t *out_f16, float *out_f32, const void *resid, float *partial,
+                            hipStream_t stream, const SkinnyFuse *fuse = nullptr);
+hipError_t launch_fewrow_q3(const uint16_t *x, const relax_qmat &w, int n, int epi, int k_ranges, uint16_t *out_f16, float *out_f32, const void *resid, float *partial,
+                            hipStream_t stream, const SkinnyFuse *fuse = nullptr);
+hipError_t launch_fewrow_f16(const uint16_t *x, const uint16_t *w, int n, int m, int k, int epi, int k_ranges, uint16_t *out_f16, float *out_f32, const void *resid,
+                             float *partial, hipStream_t stream, const SkinnyFuse *fuse = nullptr);
 hipError_t launch_rope_append(uint16_t *qkv, const relax_layer_dims &dm, const relax_kv_cache &cache,
                               const SeqTable &st, hipStream_t stream);
 hipError_t launch_rope_table(const relax_layer_dims &dm, float *table, hipStream_t stream);

@@ -1,0 +1,124 @@
+"""GPU tests of the streaming few-row matmul (fewrow_kernel.h) at the sizes where its tiling can go wrong: rows of x around
+the blocks of 16, weight rows that do not fill a row tile, columns that do not divide over the wavefronts, one and several k
+ranges, all weight formats; and of the layers that run on it."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+pytestmark = [pytest.mark.gpu, pytest.mark.skipif(not torch.cuda.is_available(), reason="needs a GPU")]
+
+import workloads as wl  # noqa: E402
+
+
+@pytest.fixture(scope="module")
+def rx():
+    from paper_2311_02103_amd import binding
+    binding.lib()
+    return binding
+
+
+def _gen(seed):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+    return g
+
+
+def _packed(rx, fmt, m, k, group, g):
+    """(QMat, its values in float64): random codes, scales 0.001 .. 0.011."""
+    words = k // 8 if fmt == "q4" else 3 * k // 32
+    q = torch.randint(-2 ** 31, 2 ** 31 - 1, (m, words), device="cuda", dtype=torch.int32, generator=g)
+    s = (torch.rand(m, k // group, device="cuda", generator=g) * 0.01 + 0.001).half()
+    w = rx.QMat(q, s, m, k, group)
+    codes = torch.empty(m, k, dtype=torch.int8, device="cuda")
+    rx.check((rx.relax_unpack_int4 if fmt == "q4" else rx.relax_unpack_q3_native)(w, codes))
+    return w, codes.double() * s.double().repeat_interleave(group, 1)
+
+
+# m: below, at and beside a row tile of 16, one that needs several tiles per workgroup; k: one unit, units that leave wavefronts
+# idle or uneven, the 7B / 13B / 70B rows (several k ranges)
+SHAPES = [(4, 256), (20, 512), (520, 4096), (72, 11008), (36, 13824), (40, 28672), (30000, 1024), (4100, 8192)]
+# A weight is rounded once to fp16 (2^-11 of its value, the final multiply of the decode), a result once more; sums of k terms with
+# random signs keep the relative 2-norm error at that of one term: below 2 * 2^-11 = 1e-3.
+REL = 1e-3
+
+
+@pytest.mark.parametrize("m,k", SHAPES)
+@pytest.mark.parametrize("fmt,group", [("q4", 32), ("q4", 64), ("q4", 128), ("q3", 32)])
+def test_packed_formats_against_float64(rx, fmt, group, m, k):
+    if fmt == "q3" and k > 12288:
+        pytest.skip("the 3-bit call takes rows of at most 12288 columns at these row counts")
+    g = _gen(m + k + group)
+    w, ref = _packed(rx, fmt, m, k, group, g)
+    ws_bytes = rx.relax_matmul_workspace_bytes(w, 128) if fmt == "q4" else 0
+    ws = torch.empty(max(16, ws_bytes), dtype=torch.uint8, device="cuda")
+    for n in (2, 15, 16, 17, 32, 33, 64):
+        x = torch.randn(n, k, device="cuda", generator=g).half()
+        out = torch.full((n, m), float("nan"), device="cuda", dtype=torch.float16)
+        if fmt == "q4":
+            rx.check(rx.relax_dequant_matmul(x, w, out, n, ws, ws_bytes))
+        else:
+            rx.check(rx.relax_dequant_matmul_q3_native(x, w, out, n))
+        want = x.double() @ ref.t()
+        assert torch.isfinite(out.float()).all()
+        assert float((out.double() - want).norm() / want.norm()) < REL, (fmt, group, m, k, n)
+
+
+@pytest.mark.parametrize("m,k", [(4, 128), (20, 384), (520, 4096), (72, 8192), (3000, 5120)])
+def test_half_weights_against_float64(rx, m, k):
+    g = _gen(m + k)
+    w = torch.randn(m, k, device="cuda", generator=g).half() * 0.05
+    for n in (2, 15, 16, 17, 32):
+        x = torch.randn(n, k, device="cuda", generator=g).half()
+        out = torch.full((n, m), float("nan"), device="cuda", dtype=torch.float16)
+        rx.check(rx.relax_half_matmul(x, w, out, n, m, k))
+        want = x.double() @ w.double().t()
+        assert float((out.double() - want).norm() / want.norm()) < REL, (m, k, n)
+
+
+def test_infinities_stay_in_their_row(rx):
+    """A row of x with an infinity and a weight row with one change their own results only (dead units, lanes past the end of a
+    row and rows past n contribute nothing, not 0 * inf)."""
+    m, k, n = 40, 384, 5
+    g = _gen(3)
+    w = torch.randn(m, k, device="cuda", generator=g).half() * 0.05
+    x = torch.randn(n, k, device="cuda", generator=g).half()
+    clean = torch.empty(n, m, device="cuda", dtype=torch.float16)
+    rx.check(rx.relax_half_matmul(x, w, clean, n, m, k))
+    w[7, 5], x[2, 300] = float("inf"), float("inf")
+    out = torch.empty_like(clean)
+    rx.check(rx.relax_half_matmul(x, w, out, n, m, k))
+    rows, cols = torch.arange(n) != 2, torch.arange(m) != 7
+    assert torch.equal(out[rows][:, cols], clean[rows][:, cols])
+    assert not torch.isfinite(out[2].float()).any() and not torch.isfinite(out[:, 7].float()).any()
+
+
+LAYERS = [wl.LayerShape("mha-64", hidden=512, n_heads=8, n_kv_heads=8, head_dim=64, ffn=1024),
+          wl.LayerShape("gqa-128", hidden=1024, n_heads=8, n_kv_heads=2, head_dim=128, ffn=2816)]
+
+
+@pytest.mark.parametrize("si", range(len(LAYERS)))
+@pytest.mark.parametrize("fmt", ["q4", "q3", "f16"])
+def test_layers_on_it_against_the_first_rows_of_a_larger_call(rx, fmt, si):
+    """Rotary + append, residuals and SwiGLU as its epilogues (2 .. 64 rows) against the launches of their own of a call with
+    more rows than it takes: prefixes of one prompt, whose rows depend on earlier rows only."""
+    from paper_2311_02103_amd.runtime import DeviceLayer, DeviceLayerF16, DeviceLayerQ3
+    shape, n_all = LAYERS[si], 200
+    sizes = dict(hidden=shape.hidden, n_heads=shape.n_heads, n_kv_heads=shape.n_kv_heads, head_dim=shape.head_dim, ffn=shape.ffn, kv_capacity=256, n_max=n_all)
+    if fmt == "q4":
+        layer = DeviceLayer(wl.layer_weights(shape, 4), **sizes)
+    elif fmt == "q3":
+        layer = DeviceLayerQ3(wl.layer_weights3(shape, 4), **sizes)
+    else:
+        host = {name: wl.normal_f16_bits(4, i, mk, std=0.02) for i, (name, mk) in enumerate(shape.matrices().items())}
+        host.update({name: wl.normal_f16_bits(4, 10 + i, (shape.hidden,), std=0.1, mean=1.0) for i, name in enumerate(("norm_attn", "norm_ffn"))})
+        layer = DeviceLayerF16(host, **sizes)
+    x = torch.from_numpy(wl.activations(shape, 4, 0, n_all).view(np.int16)).view(torch.float16).cuda()
+    want, k_all, v_all = layer.forward(x, [n_all], [n_all]).double(), layer.k.clone(), layer.v.clone()
+    for n in (2, 5, 16, 17, 40, 64):
+        layer.k.zero_(), layer.v.zero_()
+        got = layer.forward(x[:n].contiguous(), [n], [n]).double()
+        # seven fp16 roundings (2^-11 each) on each side, independent where the two paths round at other points
+        assert float((got - want[:n]).norm() / want[:n].norm()) < 4e-3, (fmt, n)
+        for a, b in ((layer.k, k_all), (layer.v, v_all)):
+            assert float((a[0, :n].double() - b[0, :n].double()).norm() / b[0, :n].double().norm()) < 2e-3
+            assert not a[0, n:].any()
