@@ -20,10 +20,14 @@
 //     through LDS at the end).  The step count of the longest prefix sets the kernel time, and this halves it; fewer
 //     queries per workgroup cost more than they give because every workgroup stages every K/V tile of its prefix.
 //     A wavefront keeps its 32 queries' Q fragments in registers, O^T (32 x d fp32) in accumulators.  KV tiles of
-//     64 tokens are staged through registers (the next tile's global loads are in flight during the MFMAs).
+//     128 tokens (two sub-tiles per wavefront) are staged through registers into one of two LDS buffers, one barrier per
+//     tile; the next tile's global loads are in flight during the MFMAs.
+//   - The query heads of a KV head go to the same XCD, so that its K and V are fetched into one L2.
 //   - Workgroups of the longest prefixes are first in dispatch order (causal work grows with the q position).
 //   - Cache rows past a sequence's length are never read (loads are clamped to its last row); masked scores are
 //     replaced, not multiplied, so stale cache contents cannot leak in.
+#include <atomic>
+
 #include "relax_common.h"
 
 namespace relax {
@@ -31,7 +35,8 @@ namespace relax {
 namespace {
 
 typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
-typedef _Float16 half4_t __attribute__((ext_vector_type(4)));
+typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
+typedef float float2_t __attribute__((ext_vector_type(2)));
 typedef short short4_t __attribute__((ext_vector_type(4)));
 typedef float float16_t __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
@@ -65,7 +70,7 @@ __device__ __forceinline__ void lds_barrier()
 }
 
 // grid: x = query head, y = q tile (reversed: longest prefix first), z = sequence
-template <int D, int NWV, int NSUB, int TBS, int KVS>
+template <int D, int NWV, int TBS, int KVS>
 __global__ __launch_bounds__(64 * NWV) void attn_prefill_kernel(const uint16_t *__restrict__ q, int q_stride,
                                                                  const uint16_t *__restrict__ kc, const uint16_t *__restrict__ vc,
                                                                  uint16_t *__restrict__ out, SeqTable st, int h, int g, int cap)
@@ -73,58 +78,55 @@ __global__ __launch_bounds__(64 * NWV) void attn_prefill_kernel(const uint16_t *
     // NWV wavefronts = QW query groups x KVS groups along the KV length: wavefront (qw, kg) owns queries qw WQ .. + WQ of the
     // workgroup and every KVS-th 32-token sub-tile (the longest prefix is then KVS times fewer steps per wavefront);
     // the KVS states of a query group are merged through LDS at the end.
-    static_assert(TBS % KVS == 0 && NWV % KVS == 0, "sub-tiles are dealt round-robin to the KV groups");
+    static_assert(TBS == 2 * KVS && NWV % KVS == 0, "two sub-tiles of a tile for every KV group");
     constexpr int QW = NWV / KVS;
-    constexpr int kQB = QW * NSUB * 32;             // queries per workgroup
-    constexpr int kPThreads = 64 * NWV, WQ = NSUB * 32;
+    constexpr int kQB = QW * 32;             // queries per workgroup
+    constexpr int kPThreads = 64 * NWV, WQ = 32;
     constexpr int KS = D / 16;       // k steps of K Q^T
     constexpr int DB = D / 32;       // 32-wide blocks of the head dimension in O^T
+    static_assert(KS == 2 * DB, "both products of a sub-tile are KS MFMAs");
     constexpr int KP = D + 8;        // K tile pitch in halfs: 16-byte row reads of 32 rows hit distinct banks
     constexpr int VP = D + 32;       // V tile pitch in halfs: the 8-byte transpose reads of a 32-lane half hit distinct banks
     constexpr int TT = kTB * TBS;    // tokens staged per barrier pair: TBS sub-tiles of 32
     constexpr int PK = TT * (D / 8) / kPThreads;    // 16-byte packets per thread and tile, for K and for V
     constexpr int kTileHalfs = TT * KP + TT * VP;
-    constexpr int kMergeFloats = KVS > 1 ? (KVS / 2) * QW * 64 * (NSUB * (DB * 16 + 2)) : 0;   // one merge round: half of the KV groups write
-    constexpr int kSmemBytes = kTileHalfs * 2 > kMergeFloats * 4 ? kTileHalfs * 2 : kMergeFloats * 4;
-    __shared__ __align__(16) unsigned char smem[kSmemBytes];
-    uint16_t *const Ks = reinterpret_cast<uint16_t *>(smem), *const Vs = Ks + TT * KP;
+    constexpr int kMergeFloats = KVS > 1 ? (KVS / 2) * QW * 64 * (DB * 16 + 2) : 0;   // one merge round: half of the KV groups write
+    static_assert(2 * kTileHalfs * 2 >= kMergeFloats * 4, "the states to merge fit the tiles");
+    extern __shared__ __align__(16) unsigned char smem[];         // two tiles [K rows | V rows]
+    uint16_t *const tiles = reinterpret_cast<uint16_t *>(smem);
 
     const SeqInfo si = seq_info(st, blockIdx.z);
     const int qt = gridDim.y - 1 - blockIdx.y;
     const int rows = min(kQB, si.q_len - qt * kQB);
     if (rows <= 0) return;                                        // uniform for the workgroup
-    const int head = blockIdx.x, kvh = head / (h / g);
+    // heads in an order that deals the KV heads out to the XCDs (workgroups go to them round-robin): the query heads of a KV head meet
+    // in one L2
+    const int kvh = blockIdx.x % g, head = kvh * (h / g) + blockIdx.x / g;
     const int past = si.kv_len - si.q_len;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, qw = wave % QW, kg = wave / QW;
     const int i32 = lane & 31, hf = lane >> 5;
     const int pos_block_max = past + qt * kQB + rows - 1;         // last token any query of the workgroup attends to
     const int wave_rows = min(WQ, rows - qw * WQ);              // <= 0: the wavefront only helps staging
     const int pos_wave_max = wave_rows > 0 ? past + qt * kQB + qw * WQ + wave_rows - 1 : -1;
-    const float scale = 1.0f / sqrtf((float)D);
+    const int pos_wave_min = past + qt * kQB + qw * WQ;            // position of the wavefront's first query
+    const float scale = 1.0f / sqrtf((float)D), c = scale * 1.44269504088896340736f, slack = 6.0f * sqrtf((float)D);
 
     // ---- Q fragments (B operand of K Q^T): lane owns query i32 of each 32-query sub-tile, 8 d-values per k step ----
-    half8_t qf[NSUB][KS];
-    int pos_q[NSUB];
-#pragma unroll
-    for (int sub = 0; sub < NSUB; ++sub) {
-        const int local = qw * WQ + sub * 32 + i32;
-        pos_q[sub] = past + qt * kQB + local;
+    half8_t qf[KS];
+    const int local = qw * WQ + i32, pos_q = past + qt * kQB + local;
+    {
         const int row = si.q_start + qt * kQB + min(local, rows - 1);
         const uint16_t *src = q + (size_t)row * q_stride + (size_t)head * D + hf * 8;
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) qf[sub][ks] = *(const half8_t *)(src + ks * 16);
+        for (int ks = 0; ks < KS; ++ks) qf[ks] = *(const half8_t *)(src + ks * 16);
     }
 
-    float16_t O[NSUB][DB];
-    float m_run[NSUB], l_run[NSUB];
+    float16_t O[DB];
+    float m_run = -INFINITY, l_run = 0.0f;
 #pragma unroll
-    for (int sub = 0; sub < NSUB; ++sub) {
-        m_run[sub] = -INFINITY, l_run[sub] = 0.0f;
+    for (int db = 0; db < DB; ++db)
 #pragma unroll
-        for (int db = 0; db < DB; ++db)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) O[sub][db][v] = 0.0f;
-    }
+        for (int v = 0; v < 16; ++v) O[db][v] = 0.0f;
 
     // ---- KV tile staging ----
     const size_t slot_base = (size_t)si.slot * cap;
@@ -139,7 +141,8 @@ __global__ __launch_bounds__(64 * NWV) void attn_prefill_kernel(const uint16_t *
             vreg[p] = *(const u32x4_t *)(vc + at);
         }
     };
-    auto tile_store = [&]() {
+    auto tile_store = [&](int b) {
+        uint16_t *const Ks = tiles + b * kTileHalfs, *const Vs = Ks + TT * KP;
 #pragma unroll
         for (int p = 0; p < PK; ++p) {
             const int pk = tid + p * kPThreads, r = pk / (D / 8), c = pk % (D / 8);
@@ -151,120 +154,145 @@ __global__ __launch_bounds__(64 * NWV) void attn_prefill_kernel(const uint16_t *
     // lane roles of the transpose read: lane r of a 16-lane block addresses V[.. + r/4][.. + 4 (r%4)]
     const int tr_row = hf * 4 + ((lane & 15) >> 2), tr_col = ((lane >> 4) & 1) * 16 + (lane & 3) * 4;
 
+    // The two products of a sub-tile are KS MFMAs each (KS = 2 DB), and an LDS read takes as long as three or four of them: the
+    // operands of all products of a step are one stream of reads that runs PD MFMAs ahead of its use, across the softmax between
+    // the products.  (With the reads one MFMA ahead the matrix pipe was busy 30 % of the time, the wavefronts waiting 41 %.)
+    constexpr int PD = 4;
+    half8_t ring[PD];
+    auto read_k = [&](const uint16_t *Kb, int u, int i) { return *(const half8_t *)(Kb + (u * kTB + i32) * KP + hf * 8 + i * 16); };
+    auto read_v = [&](const uint16_t *Vb, int u, int i) {
+        const uint16_t *vp = Vb + (u * kTB + (i / DB) * 16 + tr_row) * VP + (i % DB) * 32 + tr_col;
+        const short4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) short4_t *)vp);
+        const short4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) short4_t *)(vp + 8 * VP));
+        return __builtin_bit_cast(half8_t, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+    };
+    // S^T = K Q^T; next(i): operand i of whatever follows this product
+    auto scores = [&](const uint16_t *Kb, int u, float16_t &S, const auto &next) {
+#pragma unroll
+        for (int v = 0; v < 16; ++v) S[v] = 0.0f;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            S = __builtin_amdgcn_mfma_f32_32x32x16_f16(ring[ks % PD], qf[ks], S, 0, 0, 0);
+            ring[ks % PD] = ks + PD < KS ? read_k(Kb, u, ks + PD) : next(ks + PD - KS);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    // O^T += V^T P^T
+    auto accumulate = [&](const uint16_t *Vb, int u, const half8_t *pf, const auto &next) {
+#pragma unroll
+        for (int i = 0; i < KS; ++i) {
+            O[i % DB] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ring[i % PD], pf[i / DB], O[i % DB], 0, 0, 0);
+            ring[i % PD] = i + PD < KS ? read_v(Vb, u, i + PD) : next(i + PD - KS);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    auto mask = [&](int t0, float16_t &S) {
+#pragma unroll
+        for (int v = 0; v < 16; ++v)
+            if (t0 + 8 * (v >> 2) + 4 * hf + (v & 3) > pos_q) S[v] = -INFINITY;
+    };
+    // Online softmax of one sub-tile in two parts: the reference point, then the exponentials (P^T packed as the B operand of the
+    // second product).  Everything stays in units of the raw scores, the softmax scale and log2(e) are one factor c of the
+    // multiply-add in front of the exponential: exp(scale (s - m)) = exp2(c s - c m).
+    auto reference = [&](const float16_t &S, float &cm, float &alpha) {
+        float mx = fmaxf(S[0], S[1]);
+#pragma unroll
+        for (int v = 2; v < 16; ++v) mx = fmaxf(mx, S[v]);
+        const float2 both = pair_xor32(mx);
+        mx = fmaxf(both.x, both.y);
+        // The reference point of the exponentials only has to stay within reach of the true maximum: it is moved (and O, l
+        // rescaled) when the scaled maximum has grown by more than 6, so that most tiles skip the rescaling of the
+        // 32 x d accumulator.  exp(6) stays far inside fp16 for P and fp32 for l.
+        const bool move = mx > m_run + slack;                     // first tile: m_run = -inf -> always
+        const float m_new = move ? mx : m_run;                    // finite from the first tile on: token 0 is visible
+        // a KV group's first sub-tiles can be masked entirely for the earlier queries of the wavefront: no reference yet,
+        // every weight is exp(-inf - 0) = 0 and the state stays empty
+        cm = m_new == -INFINITY ? 0.0f : c * m_new;
+        alpha = move ? __builtin_amdgcn_exp2f(fmaf(c, m_run, -cm)) : 1.0f;      // exp2(-inf) = 0 on the first tile
+        l_run *= alpha;
+        m_run = m_new;
+        return move;
+    };
+    auto weights = [&](const float16_t &S, float cm, half8_t *pf) {
+#pragma unroll
+        for (int v = 0; v < 16; v += 2) {
+            const float p0 = __builtin_amdgcn_exp2f(fmaf(c, S[v], -cm)), p1 = __builtin_amdgcn_exp2f(fmaf(c, S[v + 1], -cm));
+            l_run += p0;
+            l_run += p1;
+            const half2_t h = __builtin_convertvector(float2_t{p0, p1}, half2_t);
+            pf[v >> 3][v & 7] = h.x, pf[v >> 3][(v & 7) + 1] = h.y;
+        }
+    };
+    auto rescale = [&](bool move, float alpha) {
+        if (__any(move)) {
+#pragma unroll
+            for (int db = 0; db < DB; ++db)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) O[db][v] *= alpha;
+        }
+    };
     tile_load(0);
+    tile_store(0);
+    lds_barrier();
+    int buf = 0;
     for (int tb = 0; tb <= pos_block_max; tb += TT) {
-        tile_store();
-        lds_barrier();
-        tile_load(tb + TT);                                       // rows are clamped to the sequence: the tail re-reads its last row
+        const bool more = tb + TT <= pos_block_max;               // uniform for the workgroup
+        if (more) tile_load(tb + TT);
+        const uint16_t *Kb = tiles + buf * kTileHalfs, *Vb = Kb + TT * KP;
+        // this wavefront's sub-tiles of the tile: kg and kg + KVS
+        const int ua = kg, ub = kg + KVS, ta = tb + ua * kTB, tc = tb + ub * kTB;
+        half8_t pa[2], pb[2];
+        float16_t Sa, Sb;
+        float cm, alpha;
+        if (ta <= pos_wave_max) {
+            const bool two = tc <= pos_wave_max;                 // wavefront-uniform, like every branch here
 #pragma unroll
-        for (int u = 0; u < TBS; ++u) {
-        const int t0 = tb + u * kTB;
-        const uint16_t *Ku = Ks + u * kTB * KP, *Vu = Vs + u * kTB * VP;
-        if (u % KVS == kg && t0 <= pos_wave_max) {
-            // ---- S^T = K Q^T: 32 tokens x two 32-query sub-tiles ----
-            float16_t S[NSUB];
-#pragma unroll
-            for (int sub = 0; sub < NSUB; ++sub)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) S[sub][v] = 0.0f;
-#pragma unroll
-            for (int ks = 0; ks < KS; ++ks) {
-                const half8_t kf = *(const half8_t *)(Ku + i32 * KP + ks * 16 + hf * 8);
-#pragma unroll
-                for (int sub = 0; sub < NSUB; ++sub) S[sub] = __builtin_amdgcn_mfma_f32_32x32x16_f16(kf, qf[sub][ks], S[sub], 0, 0, 0);
+            for (int i = 0; i < PD; ++i) ring[i] = read_k(Kb, ua, i);
+            scores(Kb, ua, Sa, [&](int i) { return read_k(Kb, ub, i); });
+            if (ta + kTB - 1 > pos_wave_min) mask(ta, Sa);
+            scores(Kb, ub, Sb, [&](int i) { return read_v(Vb, ua, i); });
+            rescale(reference(Sa, cm, alpha), alpha);
+            weights(Sa, cm, pa);
+            accumulate(Vb, ua, pa, [&](int i) { return read_v(Vb, ub, i); });
+            if (two) {
+                if (tc + kTB - 1 > pos_wave_min) mask(tc, Sb);
+                rescale(reference(Sb, cm, alpha), alpha);
+                weights(Sb, cm, pb);
+                accumulate(Vb, ub, pb, [&](int i) { return ring[i]; });
             }
-            // ---- mask, online softmax; P^T packed as the B operand of the second product ----
-            half8_t pf[NSUB][2];
-#pragma unroll
-            for (int sub = 0; sub < NSUB; ++sub) {
-                float mx = -INFINITY;
-#pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    const int t = t0 + 8 * (v >> 2) + 4 * hf + (v & 3);
-                    const float s = t <= pos_q[sub] ? S[sub][v] * scale : -INFINITY;
-                    S[sub][v] = s;
-                    mx = fmaxf(mx, s);
-                }
-                mx = fmaxf(mx, __shfl_xor(mx, 32, kWave));
-                // The reference point of the exponentials only has to stay within reach of the true maximum: it is
-                // moved (and O, l rescaled) when the maximum has grown by more than kSlack, so that most tiles skip the
-                // rescaling of the 64 x d accumulator.  exp(kSlack) stays far inside fp16 for P and fp32 for l.
-                constexpr float kSlack = 6.0f;
-                const bool move = mx > m_run[sub] + kSlack;          // first tile: m_run = -inf -> always
-                const float m_new = move ? mx : m_run[sub];          // finite from the first tile on: token 0 is visible
-                // a KV group's first sub-tiles can be masked entirely for the earlier queries of the wavefront: no reference yet,
-                // every weight is exp(-inf - 0) = 0 and the state stays empty
-                const float m_ref = m_new == -INFINITY ? 0.0f : m_new;
-                const float alpha = move ? __expf(m_run[sub] - m_ref) : 1.0f;      // exp(-inf) = 0 on the first tile
-                float psum = 0.0f;
-#pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    const float p = __expf(S[sub][v] - m_ref);
-                    psum += p;
-                    pf[sub][v >> 3][v & 7] = (_Float16)p;
-                }
-                l_run[sub] = l_run[sub] * alpha + psum;
-                m_run[sub] = m_new;
-                if (__any(move)) {
-#pragma unroll
-                    for (int db = 0; db < DB; ++db)
-#pragma unroll
-                        for (int v = 0; v < 16; ++v) O[sub][db][v] *= alpha;
-                }
-            }
-            // ---- O^T += V^T P^T ----
-#pragma unroll
-            for (int s2 = 0; s2 < 2; ++s2)
-#pragma unroll
-                for (int db = 0; db < DB; ++db) {
-                    const uint16_t *vp = Vu + (s2 * 16 + tr_row) * VP + db * 32 + tr_col;
-                    const short4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) short4_t *)vp);
-                    const short4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) short4_t *)(vp + 8 * VP));
-                    const half8_t vf = __builtin_bit_cast(half8_t, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-#pragma unroll
-                    for (int sub = 0; sub < NSUB; ++sub)
-                        O[sub][db] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vf, pf[sub][s2], O[sub][db], 0, 0, 0);
-                }
         }
-        }
-        lds_barrier();                                            // the tile is consumed: the next store may overwrite it
+        buf ^= 1;
+        if (more) tile_store(buf);
+        lds_barrier();                                            // the next tile is there, and this one consumed
     }
 
     // ---- merge the KV groups of each query group: log2(KVS) rounds, the upper half of the groups hands its state to the lower half ----
     if (KVS > 1) {
         float *const mg = reinterpret_cast<float *>(smem);        // [writer wavefront][value][lane]: the tiles are consumed
-        constexpr int kVals = NSUB * (DB * 16 + 2);
+        constexpr int kVals = DB * 16 + 2;
 #pragma unroll
         for (int half = KVS / 2; half >= 1; half >>= 1) {
             if (kg >= half && kg < 2 * half) {
                 float *dst = mg + ((size_t)((kg - half) * QW + qw) * kVals) * 64 + lane;
+                dst[0] = m_run, dst[64] = l_run;
 #pragma unroll
-                for (int sub = 0; sub < NSUB; ++sub) {
-                    float *d2 = dst + (size_t)sub * (DB * 16 + 2) * 64;
-                    d2[0] = m_run[sub], d2[64] = l_run[sub];
+                for (int db = 0; db < DB; ++db)
 #pragma unroll
-                    for (int db = 0; db < DB; ++db)
-#pragma unroll
-                        for (int v = 0; v < 16; ++v) d2[(2 + db * 16 + v) * 64] = O[sub][db][v];
-                }
+                    for (int v = 0; v < 16; ++v) dst[(2 + db * 16 + v) * 64] = O[db][v];
             }
             __syncthreads();
             if (kg < half) {
                 const float *src = mg + ((size_t)(kg * QW + qw) * kVals) * 64 + lane;
+                const float mb = src[0], lb = src[64];
+                const float mn = fmaxf(m_run, mb);
+                const float ca = m_run == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(c * (m_run - mn));
+                const float cb = mb == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(c * (mb - mn));
+                l_run = l_run * ca + lb * cb;
+                m_run = mn;
 #pragma unroll
-                for (int sub = 0; sub < NSUB; ++sub) {
-                    const float *s2 = src + (size_t)sub * (DB * 16 + 2) * 64;
-                    const float mb = s2[0], lb = s2[64];
-                    const float mn = fmaxf(m_run[sub], mb);
-                    const float ca = m_run[sub] == -INFINITY ? 0.0f : __expf(m_run[sub] - mn);
-                    const float cb = mb == -INFINITY ? 0.0f : __expf(mb - mn);
-                    l_run[sub] = l_run[sub] * ca + lb * cb;
-                    m_run[sub] = mn;
+                for (int db = 0; db < DB; ++db)
 #pragma unroll
-                    for (int db = 0; db < DB; ++db)
-#pragma unroll
-                        for (int v = 0; v < 16; ++v) O[sub][db][v] = O[sub][db][v] * ca + s2[(2 + db * 16 + v) * 64] * cb;
-                }
+                    for (int v = 0; v < 16; ++v) O[db][v] = O[db][v] * ca + src[(2 + db * 16 + v) * 64] * cb;
             }
             __syncthreads();
         }
@@ -272,23 +300,37 @@ __global__ __launch_bounds__(64 * NWV) void attn_prefill_kernel(const uint16_t *
     }
 
     // ---- normalise and store: lane holds query i32; register v of block db is d = 32 db + 8 (v/4) + 4 hf + v%4 ----
+    const float l_tot = xor32_sum(l_run);
+    if (local >= rows) return;
+    const float inv = 1.0f / l_tot;
+    uint16_t *dst = out + (size_t)(si.q_start + qt * kQB + local) * ((size_t)h * D) + (size_t)head * D;
 #pragma unroll
-    for (int sub = 0; sub < NSUB; ++sub) {
-        const int local = qw * WQ + sub * 32 + i32;
-        const float l_tot = l_run[sub] + __shfl_xor(l_run[sub], 32, kWave);
-        if (local >= rows) continue;
-        const float inv = 1.0f / l_tot;
-        uint16_t *dst = out + (size_t)(si.q_start + qt * kQB + local) * ((size_t)h * D) + (size_t)head * D;
+    for (int db = 0; db < DB; ++db)
 #pragma unroll
-        for (int db = 0; db < DB; ++db)
-#pragma unroll
-            for (int b4 = 0; b4 < 4; ++b4) {
-                const int dd = db * 32 + b4 * 8 + hf * 4;
-                const uint32_t w0 = f2h(O[sub][db][b4 * 4] * inv) | ((uint32_t)f2h(O[sub][db][b4 * 4 + 1] * inv) << 16);
-                const uint32_t w1 = f2h(O[sub][db][b4 * 4 + 2] * inv) | ((uint32_t)f2h(O[sub][db][b4 * 4 + 3] * inv) << 16);
-                *(uint2 *)(dst + dd) = make_uint2(w0, w1);
-            }
+        for (int b4 = 0; b4 < 4; ++b4) {
+            const int dd = db * 32 + b4 * 8 + hf * 4;
+            const uint32_t w0 = f2h(O[db][b4 * 4] * inv) | ((uint32_t)f2h(O[db][b4 * 4 + 1] * inv) << 16);
+            const uint32_t w1 = f2h(O[db][b4 * 4 + 2] * inv) | ((uint32_t)f2h(O[db][b4 * 4 + 3] * inv) << 16);
+            *(uint2 *)(dst + dd) = make_uint2(w0, w1);
+        }
+}
+
+template <int D, int NWV, int TBS, int KVS>
+hipError_t launch_one(const uint16_t *q, int32_t q_stride, const relax_kv_cache &cache, const relax_layer_dims &dm, const SeqTable &st, uint16_t *out,
+                      hipStream_t stream)
+{
+    constexpr int kLds = 2 * kTB * TBS * ((D + 8) + (D + 32)) * 2;
+    static std::atomic<bool> attr_done{false};            // setting the attribute twice is harmless; the flag only has to be a defined read
+    if (!attr_done.load()) {
+        if (hipFuncSetAttribute((const void *)attn_prefill_kernel<D, NWV, TBS, KVS>, hipFuncAttributeMaxDynamicSharedMemorySize, kLds) != hipSuccess)
+            return hipErrorInvalidValue;
+        attr_done.store(true);
     }
+    const int queries = NWV / KVS * 32;
+    const dim3 grid(dm.n_heads, (st.q_max + queries - 1) / queries, st.B);
+    hipLaunchKernelGGL((attn_prefill_kernel<D, NWV, TBS, KVS>), grid, dim3(64 * NWV), kLds, stream, q, q_stride, cache.k, cache.v, out, st, dm.n_heads,
+                       dm.n_kv_heads, dm.kv_capacity);
+    return hipGetLastError();
 }
 
 }  // namespace
@@ -298,21 +340,15 @@ bool attn_prefill_supported(const relax_layer_dims &dm) { return dm.head_dim == 
 hipError_t launch_attention_prefill(const uint16_t *q, int32_t q_stride, const relax_kv_cache &cache, const relax_layer_dims &dm,
                                     const SeqTable &st, uint16_t *out, hipStream_t stream)
 {
-    // 8 wavefronts = 4 query groups of 32 x 2 KV groups, tiles of 64 tokens.  Measured at n = 2048, 32 heads of 128: 69 us; without the
-    // KV groups (8 x 32 or 4 x 32 queries) 82-84 us, 2 x 64 queries per workgroup (the first form of this kernel) 128 us, 64 queries per
-    // workgroup in any split 93-117 us (every workgroup stages every K/V tile of its prefix).
-    constexpr int kWaves = 8, kSub = 1, kKvGroups = 2;
-    const int tiles = (st.q_max + kWaves / kKvGroups * kSub * 32 - 1) / (kWaves / kKvGroups * kSub * 32);
-    const dim3 grid(dm.n_heads, tiles, st.B);
-    if (dm.head_dim == 128)
-        hipLaunchKernelGGL((attn_prefill_kernel<128, kWaves, kSub, kKvGroups, kKvGroups>), grid, dim3(64 * kWaves), 0, stream, q, q_stride, cache.k, cache.v,
-                           out, st, dm.n_heads, dm.n_kv_heads, dm.kv_capacity);
-    else if (dm.head_dim == 64)
-        hipLaunchKernelGGL((attn_prefill_kernel<64, kWaves, kSub, kKvGroups, kKvGroups>), grid, dim3(64 * kWaves), 0, stream, q, q_stride, cache.k, cache.v,
-                           out, st, dm.n_heads, dm.n_kv_heads, dm.kv_capacity);
-    else
-        return hipErrorInvalidValue;
-    return hipGetLastError();
+    // 8 wavefronts = 4 query groups of 32 x 2 KV groups, two tiles of 128 tokens in LDS.  Measured at n = 4096, 32 / 8 heads of 128: 200 us
+    // (226 with one tile of 64 tokens, the softmax in units of e and masks on every tile; 208 with the cheaper softmax alone);
+    // n = 2048, 32 heads: 63 us (72).  With the loads of the next tile left out the first takes 178 us, without its stores too 162:
+    // matrix pipe and vector unit together are busy 70 % of the time at two wavefronts per SIMD.  Ordering the exponentials of one
+    // sub-tile between the MFMAs of the other changed nothing (203 to 216 us).  Earlier forms at n = 2048: without the KV groups 82-84 us,
+    // 64 queries per wavefront 128 us, 64 queries per workgroup 93-117 us.
+    if (dm.head_dim == 128) return launch_one<128, 8, 4, 2>(q, q_stride, cache, dm, st, out, stream);
+    if (dm.head_dim == 64) return launch_one<64, 8, 4, 2>(q, q_stride, cache, dm, st, out, stream);
+    return hipErrorInvalidValue;
 }
 
 }  // namespace relax
