@@ -895,9 +895,10 @@ hipError_t q3_matmul(const uint16_t *x, const relax_qmat &w, int32_t n, uint16_t
 // order wqkv, wo, wgu, wdown:
 //   plain(i, x, out)                   out = x times matrix i, fp16 epilogue, any n
 //   ranges(i, x, out, epi, floats, folded)   k ranges of the streaming few-row kernel for matrix i with this epilogue, the partial
-//                                      rows of more than one in at most `floats` floats; 0: it does not take it
-//   streamed(i, ...)                   that kernel
-// Where the streaming kernel takes a matmul, rotary + append, the residual adds and SwiGLU happen in it (or in its finishing
+//                                      rows of more than one in at most `floats` floats; -s: it does not take the matrix, the tiled
+//                                      GEMM cut into s k ranges does; 0: plain()
+//   streamed(i, ...)                   that launch
+// Where one of the two takes a matmul, rotary + append, the residual adds and SwiGLU happen in it (or in its finishing
 // pass); the partial rows use what the workspace holds free at that point, its size is the same on either way.
 template <typename Plain, typename Ranges, typename Streamed>
 relax_status flat_layer(const relax_layer_dims &dm, const uint16_t *norm_attn, const uint16_t *norm_ffn, const uint16_t *x, const relax_kv_cache &cache,
@@ -918,8 +919,8 @@ relax_status flat_layer(const relax_layer_dims &dm, const uint16_t *norm_attn, c
     fq.dm = &dm, fq.cache = &cache, fq.st = &st;
     const relax_qmat qkv_shape = {nullptr, nullptr, qkvw, dm.hidden, 32};
     const int rq = ranges(0, xn, qkv, EPI_F16, floats_from(free_qkv), false);
-    if (rq == 1 ? fewrow_fuse_ok(dm, cache) : rq > 1 && gemm_skinny_fuse_ok(qkv_shape, EPI_F16, fq)) {
-        RELAX_TRY(streamed(0, xn, EPI_F16, rq, qkv, nullptr, nullptr, free_qkv, &fq));
+    if (rq == 1 ? fewrow_fuse_ok(dm, cache) : rq != 0 && gemm_skinny_fuse_ok(qkv_shape, EPI_F16, fq)) {
+        RELAX_TRY(streamed(0, xn, EPI_F16, rq, qkv, nullptr, nullptr, free_qkv, floats_from(free_qkv), &fq));
     } else {
         RELAX_TRY(plain(0, xn, qkv));
         RELAX_TRY(launch_rope_append(qkv, dm, cache, st, st_));
@@ -931,21 +932,22 @@ relax_status flat_layer(const relax_layer_dims &dm, const uint16_t *norm_attn, c
     const relax_qmat o_shape = {nullptr, nullptr, dm.hidden, hd, 32};
     const bool norm_folds = gemm_skinny_fuse_ok(o_shape, EPI_RESID_F32, fo);
     const int ro = ranges(1, attn, x1, EPI_RESID_F32, floats_from(free_o), norm_folds);
+    const bool norm_done = ro != 0 && ro != 1 && norm_folds;
     if (ro) {
-        RELAX_TRY(streamed(1, attn, EPI_RESID_F32, ro, nullptr, x1, x, free_o, ro > 1 && norm_folds ? &fo : nullptr));
+        RELAX_TRY(streamed(1, attn, EPI_RESID_F32, ro, nullptr, x1, x, free_o, floats_from(free_o), norm_done ? &fo : nullptr));
     } else {
         RELAX_TRY(plain(1, attn, tmp));
         RELAX_TRY(launch_add_rows(x, tmp, x1, nh, st_));
     }
-    if (!(ro > 1 && norm_folds)) RELAX_TRY(launch_rmsnorm_f32(x1, norm_ffn, xn, n, dm.hidden, dm.rms_eps, st_));
+    if (!norm_done) RELAX_TRY(launch_rmsnorm_f32(x1, norm_ffn, xn, n, dm.hidden, dm.rms_eps, st_));
     if (const int rg = ranges(2, xn, act, EPI_SWIGLU, floats_from(free_ffn), false)) {
-        RELAX_TRY(streamed(2, xn, EPI_SWIGLU, rg, act, nullptr, nullptr, free_ffn, nullptr));
+        RELAX_TRY(streamed(2, xn, EPI_SWIGLU, rg, act, nullptr, nullptr, free_ffn, floats_from(free_ffn), nullptr));
     } else {
         RELAX_TRY(plain(2, xn, gu));
         RELAX_TRY(launch_swiglu_rows(gu, act, n, dm.ffn, st_));
     }
     if (const int rd = ranges(3, act, out, EPI_RESID_F16, floats_from(free_ffn), false)) {
-        RELAX_TRY(streamed(3, act, EPI_RESID_F16, rd, out, nullptr, x1, free_ffn, nullptr));
+        RELAX_TRY(streamed(3, act, EPI_RESID_F16, rd, out, nullptr, x1, free_ffn, floats_from(free_ffn), nullptr));
     } else {
         RELAX_TRY(plain(3, act, tmp));
         RELAX_TRY(launch_add_out(x1, tmp, out, nh, st_));
@@ -1035,9 +1037,16 @@ relax_status relax_decoder_layer_q3(const relax_layer_dims *dims, const relax_la
     const relax_qmat *mats[4] = {&wt->wqkv, &wt->wo, &wt->wgu, &wt->wdown};
     auto plain = [&](int i, const uint16_t *xin, uint16_t *o) { return q3_matmul(xin, *mats[i], n, o, st_); };
     auto ranges = [&](int i, const void *xin, const void *o, int epi, size_t floats, bool folded) {
-        return stream_ranges(W_Q3, *mats[i], xin, o, n, epi, floats, folded);
+        const int kr = stream_ranges(W_Q3, *mats[i], xin, o, n, epi, floats, folded);
+        if (kr > 0 || n < kQ3GemmRows || !gemm_q3_eligible(xin, *mats[i], o)) return kr;
+        const int splits = gemm_flat_splits(n, mats[i]->m, mats[i]->k, floats);
+        return splits > 1 ? -splits : 0;
     };
-    auto streamed = [&](int i, const uint16_t *xin, int epi, int kr, uint16_t *o16, float *o32, const void *resid, float *part, const SkinnyFuse *f) {
+    auto streamed = [&](int i, const uint16_t *xin, int epi, int kr, uint16_t *o16, float *o32, const void *resid, float *part, size_t floats, const SkinnyFuse *f) {
+        if (kr < 0) {
+            const hipError_t e = launch_gemm_q3(xin, *mats[i], n, nullptr, st_, part, floats);
+            return e != hipSuccess ? e : launch_skinny_finish(part, -kr, n, mats[i]->m, epi, o16, o32, resid, st_, f);
+        }
         return launch_fewrow_q3(xin, *mats[i], n, epi, kr, o16, o32, resid, part, st_, f);
     };
     return flat_layer(dm, wt->norm_attn, wt->norm_ffn, x, *cache, st, L_max, out, n, base, pl, plain, ranges, streamed, st_);
@@ -1122,10 +1131,18 @@ relax_status relax_decoder_layer_f16(const relax_layer_dims *dims, const relax_l
     const uint16_t *mats[4] = {wt->wqkv, wt->wo, wt->wgu, wt->wdown};
     const int32_t ms[4] = {qkvw, dm.hidden, 2 * dm.ffn, dm.hidden}, ks[4] = {dm.hidden, hd, dm.hidden, dm.ffn};
     auto plain = [&](int i, const uint16_t *xin, uint16_t *o) { return half_matmul_enqueue(xin, mats[i], o, n, ms[i], ks[i], st_); };
-    auto ranges = [&](int i, const void *, const void *, int epi, size_t floats, bool folded) {      // every pointer was checked for 16 bytes above
-        return g_opt_half_gemm_rows.load() != 0 ? 0 : fewrow_ranges(W_F16, n, ms[i], ks[i], epi, folded, floats);
+    auto ranges = [&](int i, const void *xin, const void *o, int epi, size_t floats, bool folded) {      // every pointer was checked for 16 bytes above
+        if (g_opt_half_gemm_rows.load() != 0) return 0;
+        const int kr = fewrow_ranges(W_F16, n, ms[i], ks[i], epi, folded, floats);
+        if (kr > 0 || n < kGemmMinN || !gemm_f16_eligible(xin, mats[i], o, ms[i], ks[i])) return kr;
+        const int splits = gemm_flat_splits(n, ms[i], ks[i], floats);
+        return splits > 1 ? -splits : 0;
     };
-    auto streamed = [&](int i, const uint16_t *xin, int epi, int kr, uint16_t *o16, float *o32, const void *resid, float *part, const SkinnyFuse *f) {
+    auto streamed = [&](int i, const uint16_t *xin, int epi, int kr, uint16_t *o16, float *o32, const void *resid, float *part, size_t floats, const SkinnyFuse *f) {
+        if (kr < 0) {
+            const hipError_t e = launch_gemm_f16(xin, mats[i], n, ms[i], ks[i], nullptr, st_, part, floats);
+            return e != hipSuccess ? e : launch_skinny_finish(part, -kr, n, ms[i], epi, o16, o32, resid, st_, f);
+        }
         return launch_fewrow_f16(xin, mats[i], n, ms[i], ks[i], epi, kr, o16, o32, resid, part, st_, f);
     };
     return flat_layer(dm, wt->norm_attn, wt->norm_ffn, x, *cache, st, L_max, out, n, base, pl, plain, ranges, streamed, st_);

@@ -467,8 +467,8 @@ hipError_t launch_tile(const GemmArgs &a_in, hipStream_t stream, int splits)
     dim3 grid(tiles * splits);
     const size_t lds = 2 * (size_t)(BM + BN) * kPitch * sizeof(uint16_t);    // up to 147456 bytes: one workgroup per CU
     static std::atomic<bool> attr_done{false};   // setting the attribute twice is harmless; the flag only has to be a defined read
-    if constexpr (FP16W || Q3) {                          // plain matmuls only: one epilogue, one pass over k
-        if (a.epi != EPI_F16 || splits != 1) return hipErrorInvalidValue;
+    if constexpr (FP16W || Q3) {                          // plain matmuls only: one epilogue (a split launch's is the finishing pass)
+        if (a.epi != EPI_F16) return hipErrorInvalidValue;
         if (!attr_done.load()) {
             if (hipFuncSetAttribute((const void *)gemm_q4_mfma_kernel<EPI_F16, MF, NF, FP16W, WM, WN, Q3>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
                 return hipErrorInvalidValue;
@@ -510,72 +510,87 @@ bool gemm_mfma_eligible(const relax_qmat &w, const void *x, int epi)
     return w.m % 4 == 0;
 }
 
-// Tile choice for n > 128: 256 x 256, 128 x 256 or 128 x 128 (weight rows x x-rows), whichever leaves the largest
-// useful share of the rounds of workgroups over the 256 CUs (one workgroup per CU); ties go to the wider tile.
-// Small n takes narrower x tiles.  A launch whose tiles would leave more than half of the CUs idle (few weight rows, few
-// x rows: the output and down projections of a prefill chunk of a few hundred rows) is cut along k as well, into about one
-// workgroup per CU with at least 8 k blocks each; the fp32 partial tiles go to the caller's workspace and the finishing pass
-// of the few-row kernel adds them in order and applies the epilogue.
+// Tile and cut of a launch: the least estimated time over the tiles (weight rows x x-rows) and over k splits, of which there
+// may be up to kSplitKMax of at least 8 k blocks each for up to kSplitKMaxN rows; the fp32 partial tiles of a split launch go to
+// the caller's workspace (it has to hold them) and the finishing pass of the few-row kernel adds them in order and applies the
+// epilogue.  A workgroup has a CU to itself, so the time is rounds of 256 workgroups x k blocks x what a tile takes per k block:
+//   256 x 256 (eight wavefronts) 2.02 us (22016 x 4096 at n = 2048), 256 x 192 1.6; 128 x 256 1.25 (12288 x 4096), 128 x 192 1.0,
+//   128 x 128 0.83 (8192 x 28672 at n = 511), 128 x 64 0.6
+// and, with splits, the finishing launch: 3 us and the partial rows twice over at 5 TB/s.  Wide tiles with two splits beat narrow
+// ones that fill the chip by themselves (8192 x 28672 at n = 511: two splits of 128 x 256 against 256 tiles of 128 x 128),
+// and 192-wide tiles waste less on 129 to 384 rows.
 namespace {
 struct TilePlan {
     int mf, nf, splits, kb_per_split;
     int m_big;               // > 0: the first m_big weight rows go through a launch of 256 x 256 tiles of their own (whole rounds of them)
 };
-TilePlan tile_plan(int m, int k, int n, int epi)
+struct TileCost {
+    int mf, nf;
+    double us_per_kb;
+};
+constexpr TileCost kTiles[] = {{4, 4, 2.02}, {4, 3, 1.6}, {2, 4, 1.25}, {2, 3, 1.0}, {2, 2, 0.83}, {2, 1, 0.6}};
+constexpr long kCUs = 256;
+
+TilePlan tile_plan(int m, int k, int n, int epi, size_t partial_floats)
 {
     const long rows = epi == EPI_SWIGLU ? m / 2 : m;
     const long rdiv = epi == EPI_SWIGLU ? 2 : 1;
     auto blocks = [&](int mf, int nf) { return ((rows + 64 * mf / rdiv - 1) / (64 * mf / rdiv)) * (long)((n + 64 * nf - 1) / (64 * nf)); };
-    const long kCUs = 256;
-    TilePlan p = {2, 1, 1, k / BK, 0};
-    if (n > 128) {
-        // useful share of the workgroup rounds: padding rows of ragged tiles and idle CUs of the last round both count as waste,
-        // weighted by what a tile shape reaches per MFMA when the CUs are full (measured on the 7B shapes at n = 2048: the
-        // 128 x 256 tile as four wavefronts reaches about nine tenths of the 256 x 256 tile as eight)
-        auto score = [&](int mf, int nf, double tile_eff) {
-            const long b = blocks(mf, nf);
-            const double rounds = (double)((b + kCUs - 1) / kCUs);
-            return tile_eff * (double)rows * (double)n / (rounds * kCUs * (64.0 * mf / rdiv) * (64.0 * nf));
-        };
-        const double s44 = score(4, 4, 1.0), s24 = score(2, 4, 0.9), s22 = score(2, 2, 0.6);
-        if (s44 >= s24 && s44 >= s22) p.mf = 4, p.nf = 4;
-        else if (s24 >= s22) p.mf = 2, p.nf = 4;
-        else p.mf = 2, p.nf = 2;
-        // Two launches instead of one when the 128 x 256 tile was chosen only for its rounds: whole rounds of 256 x 256
-        // tiles on the first rows (the tile that reaches more per MFMA), the narrower tile on the rest.  A round of the
-        // wide tile is taken as 1.6 rounds of the narrow one (129 against 80 us per round at k = 4096, n = 2048); the
-        // split is made when the estimate gains a tenth (QKV of the 7B layer at n = 2048: 1.6 + 1 against 3 rounds).
-        if (p.mf == 2 && p.nf == 4 && epi != EPI_SWIGLU) {
-            const long tn = (n + 255) / 256;
-            if (tn <= kCUs) {
-                const long rows_round = (kCUs / tn) * 256;                       // weight rows of one full round of wide tiles
-                const double all_small = (double)((blocks(2, 4) + kCUs - 1) / kCUs);
-                double best = all_small;
-                for (long r = 1; r * rows_round < rows; ++r) {
-                    const long rem = rows - r * rows_round;
-                    const double t = 1.6 * (double)r + (double)((((rem + 127) / 128) * tn + kCUs - 1) / kCUs);
-                    if (t < best) best = t, p.m_big = (int)(r * rows_round);
-                }
-                if (best > 0.9 * all_small) p.m_big = 0;
+    const int nkb = k / BK;
+    const int most = n <= kSplitKMaxN ? kSplitKMax : 1;
+    TilePlan p = {2, 1, 1, nkb, 0};
+    double best_us = 0.0;
+    for (const TileCost &t : kTiles) {
+        if (t.nf > 2 && n <= 128) continue;               // (one x tile is enough; the wide ones were not measured there)
+        const long tiles = blocks(t.mf, t.nf);
+        for (int s = 1; s <= most && (s == 1 || nkb / s >= 8); ++s) {
+            const int per = s == 1 ? nkb : ((nkb + s - 1) / s + 1) & ~1, splits = (nkb + per - 1) / per;
+            if (splits != s || (s > 1 && (size_t)s * n * m > partial_floats)) continue;
+            const double us = (double)((tiles * s + kCUs - 1) / kCUs) * per * t.us_per_kb + (s > 1 ? 3.0 + (double)s * n * m * 8.0 / 5e6 : 0.0);
+            if (best_us == 0.0 || us < best_us) best_us = us, p.mf = t.mf, p.nf = t.nf, p.splits = s, p.kb_per_split = per;
+        }
+    }
+    // Two launches instead of one when the 128 x 256 tile was chosen only for its rounds: whole rounds of 256 x 256
+    // tiles on the first rows (the tile that reaches more per MFMA), the narrower tile on the rest.  A round of the
+    // wide tile is taken as 1.6 rounds of the narrow one (129 against 80 us per round at k = 4096, n = 2048); the
+    // split is made when the estimate gains a tenth (QKV of the 7B layer at n = 2048: 1.6 + 1 against 3 rounds).
+    if (p.mf == 2 && p.nf == 4 && p.splits == 1 && epi != EPI_SWIGLU) {
+        const long tn = (n + 255) / 256;
+        if (tn <= kCUs) {
+            const long rows_round = (kCUs / tn) * 256;                           // weight rows of one full round of wide tiles
+            const double all_small = (double)((blocks(2, 4) + kCUs - 1) / kCUs);
+            double best = all_small;
+            for (long r = 1; r * rows_round < rows; ++r) {
+                const long rem = rows - r * rows_round;
+                const double t = 1.6 * (double)r + (double)((((rem + 127) / 128) * tn + kCUs - 1) / kCUs);
+                if (t < best) best = t, p.m_big = (int)(r * rows_round);
             }
+            if (best > 0.9 * all_small) p.m_big = 0;
         }
-        const long tiles = blocks(p.mf, p.nf);
-        const int nkb = k / BK;
-        if (n <= kSplitKMaxN && tiles <= kCUs / 2) {
-            int splits = std::max(1, std::min(std::min(kSplitKMax, (int)(kCUs / tiles)), nkb / 8));
-            p.kb_per_split = ((nkb + splits - 1) / splits + 1) & ~1;
-            p.splits = (nkb + p.kb_per_split - 1) / p.kb_per_split;
-            if (p.splits < 2) p.splits = 1, p.kb_per_split = nkb;
-            if (p.splits > 1) p.m_big = 0;
-        }
-    } else if (n > 64) {
-        p.mf = 2, p.nf = 2;
     }
     return p;
 }
+
+// Splits a workspace is sized for: a launch whose tiles of the best useful share (256 x 256, 128 x 256, 128 x 128 at 1, 0.9, 0.6 per
+// MFMA) would leave more than half of the CUs idle, cut into about one workgroup per CU.  tile_plan takes what fits.
+int sized_splits(int m, int k, int n, int epi)
+{
+    const long rows = epi == EPI_SWIGLU ? m / 2 : m, rdiv = epi == EPI_SWIGLU ? 2 : 1;
+    auto blocks = [&](int mf, int nf) { return ((rows + 64 * mf / rdiv - 1) / (64 * mf / rdiv)) * (long)((n + 64 * nf - 1) / (64 * nf)); };
+    auto score = [&](int mf, int nf, double tile_eff) {
+        const double rounds = (double)((blocks(mf, nf) + kCUs - 1) / kCUs);
+        return tile_eff * (double)rows * (double)n / (rounds * kCUs * (64.0 * mf / rdiv) * (64.0 * nf));
+    };
+    const double s44 = score(4, 4, 1.0), s24 = score(2, 4, 0.9), s22 = score(2, 2, 0.6);
+    const long tiles = s44 >= s24 && s44 >= s22 ? blocks(4, 4) : s24 >= s22 ? blocks(2, 4) : blocks(2, 2);
+    const int nkb = k / BK;
+    if (tiles > kCUs / 2) return 1;
+    const int splits = std::max(1, std::min(std::min(kSplitKMax, (int)(kCUs / tiles)), nkb / 8)), per = ((nkb + splits - 1) / splits + 1) & ~1;
+    return (nkb + per - 1) / per;
+}
 }  // namespace
 
-// fp32 elements of workspace the k-split form may need for any row count up to n (0: it never splits this matrix)
+// fp32 elements of workspace a caller brings for the k-split form at any row count up to n (0: this matrix is not sized for it)
 size_t gemm_splitk_partial_floats(int m, int k, int n, int epi)
 {
     if (k % (2 * BK) != 0) return 0;
@@ -584,8 +599,8 @@ size_t gemm_splitk_partial_floats(int m, int k, int n, int epi)
     for (int nn = 256; nn <= top + 127; nn += 128) {               // splits change with the tile counts only: the top of each bracket
         const int r = nn < top ? nn : top;
         if (r <= 128) continue;
-        const TilePlan p = tile_plan(m, k, r, epi);
-        if (p.splits > 1) worst = std::max(worst, (size_t)p.splits * (size_t)r * (size_t)m);
+        const int splits = sized_splits(m, k, r, epi);
+        if (splits > 1) worst = std::max(worst, (size_t)splits * (size_t)r * (size_t)m);
     }
     return worst;
 }
@@ -593,9 +608,7 @@ size_t gemm_splitk_partial_floats(int m, int k, int n, int epi)
 // k splits the launch would make for n rows with this much workspace (1: one pass over k, no finishing pass)
 int gemm_mfma_splits(const relax_qmat &w, int n, int epi, const float *partial, size_t partial_floats)
 {
-    const TilePlan p = tile_plan(w.m, w.k, n, epi);
-    if (p.splits > 1 && (!partial || (reinterpret_cast<uintptr_t>(partial) & 15) != 0 || partial_floats < (size_t)p.splits * n * w.m)) return 1;
-    return p.splits;
+    return tile_plan(w.m, w.k, n, epi, partial && (reinterpret_cast<uintptr_t>(partial) & 15) == 0 ? partial_floats : 0).splits;
 }
 
 // out[n,m] = x[n,k] . w[m,k]^T with plain fp16 weights: the same tiles, no decode, one pass over k
@@ -605,16 +618,18 @@ bool gemm_f16_eligible(const void *x, const void *w, const void *out, int m, int
            (reinterpret_cast<uintptr_t>(out) & 7) == 0;
 }
 
-hipError_t launch_gemm_f16(const uint16_t *x, const uint16_t *w, int n, int m, int k, uint16_t *out, hipStream_t stream)
+hipError_t launch_gemm_f16(const uint16_t *x, const uint16_t *w, int n, int m, int k, uint16_t *out, hipStream_t stream, float *partial, size_t partial_floats)
 {
     GemmArgs a = {};
-    a.x = x, a.wh = w, a.n = n, a.m = m, a.k = k, a.epi = EPI_F16, a.out_f16 = out;
-    const TilePlan p = tile_plan(m, k, n, EPI_F16);
-    a.kb_per_split = k / BK;
-    if (p.mf == 4) return launch_tile<4, 4, true>(a, stream, 1);    // the fp16-weight staging needs more registers than two wavefronts per SIMD leave
-    if (p.nf == 4) return launch_tile<2, 4, true>(a, stream, 1);
-    if (p.nf == 2) return launch_tile<2, 2, true>(a, stream, 1);
-    return launch_tile<2, 1, true>(a, stream, 1);
+    a.x = x, a.wh = w, a.n = n, a.m = m, a.k = k, a.epi = EPI_F16, a.out_f16 = out, a.partial = partial;
+    const TilePlan p = tile_plan(m, k, n, EPI_F16, partial ? partial_floats : 0);
+    a.kb_per_split = p.kb_per_split;
+    if (p.mf == 4 && p.nf == 4) return launch_tile<4, 4, true>(a, stream, p.splits);    // the fp16-weight staging needs more registers than two wavefronts per SIMD leave
+    if (p.mf == 4) return launch_tile<4, 3, true>(a, stream, p.splits);
+    if (p.nf == 4) return launch_tile<2, 4, true>(a, stream, p.splits);
+    if (p.nf == 3) return launch_tile<2, 3, true>(a, stream, p.splits);
+    if (p.nf == 2) return launch_tile<2, 2, true>(a, stream, p.splits);
+    return launch_tile<2, 1, true>(a, stream, p.splits);
 }
 
 // out[n,m] = x[n,k] . w[m,k]^T with 3-bit weights in the native word layout (group 32): the same tiles, one pass over k
@@ -624,17 +639,22 @@ bool gemm_q3_eligible(const void *x, const relax_qmat &w, const void *out)
            (reinterpret_cast<uintptr_t>(w.q) & 3) == 0 && (reinterpret_cast<uintptr_t>(w.s) & 1) == 0 && (reinterpret_cast<uintptr_t>(out) & 7) == 0;
 }
 
-hipError_t launch_gemm_q3(const uint16_t *x, const relax_qmat &w, int n, uint16_t *out, hipStream_t stream)
+hipError_t launch_gemm_q3(const uint16_t *x, const relax_qmat &w, int n, uint16_t *out, hipStream_t stream, float *partial, size_t partial_floats)
 {
     GemmArgs a = {};
-    a.x = x, a.q = w.q, a.s = w.s, a.gshift = 0, a.n = n, a.m = w.m, a.k = w.k, a.epi = EPI_F16, a.out_f16 = out;
-    const TilePlan p = tile_plan(w.m, w.k, n, EPI_F16);
-    a.kb_per_split = w.k / BK;
-    if (p.mf == 4) return launch_tile<2, 4, false, 4, 2, true>(a, stream, 1);
-    if (p.nf == 4) return launch_tile<2, 4, false, 2, 2, true>(a, stream, 1);
-    if (p.nf == 2) return launch_tile<2, 2, false, 2, 2, true>(a, stream, 1);
-    return launch_tile<2, 1, false, 2, 2, true>(a, stream, 1);
+    a.x = x, a.q = w.q, a.s = w.s, a.gshift = 0, a.n = n, a.m = w.m, a.k = w.k, a.epi = EPI_F16, a.out_f16 = out, a.partial = partial;
+    const TilePlan p = tile_plan(w.m, w.k, n, EPI_F16, partial ? partial_floats : 0);
+    a.kb_per_split = p.kb_per_split;
+    if (p.mf == 4 && p.nf == 4) return launch_tile<2, 4, false, 4, 2, true>(a, stream, p.splits);
+    if (p.mf == 4) return launch_tile<2, 3, false, 4, 2, true>(a, stream, p.splits);
+    if (p.nf == 4) return launch_tile<2, 4, false, 2, 2, true>(a, stream, p.splits);
+    if (p.nf == 3) return launch_tile<2, 3, false, 2, 2, true>(a, stream, p.splits);
+    if (p.nf == 2) return launch_tile<2, 2, false, 2, 2, true>(a, stream, p.splits);
+    return launch_tile<2, 1, false, 2, 2, true>(a, stream, p.splits);
 }
+
+// k splits of the two launches above with this much workspace: more than one leaves partial rows for launch_skinny_finish
+int gemm_flat_splits(int n, int m, int k, size_t partial_floats) { return k % (2 * BK) == 0 ? tile_plan(m, k, n, EPI_F16, partial_floats).splits : 1; }
 
 hipError_t launch_gemm_mfma(const uint16_t *x, const relax_qmat &w, int n, int epi, uint16_t *out_f16, float *out_f32, const void *resid,
                             hipStream_t stream, float *partial, size_t partial_floats, const SkinnyFuse *fuse)
@@ -643,9 +663,7 @@ hipError_t launch_gemm_mfma(const uint16_t *x, const relax_qmat &w, int n, int e
     a.wh = nullptr;
     a.x = x, a.q = w.q, a.s = w.s, a.gshift = gshift_of(w.group), a.n = n, a.m = w.m, a.k = w.k, a.epi = epi;
     a.out_f16 = out_f16, a.out_f32 = out_f32, a.resid = resid;
-    TilePlan p = tile_plan(w.m, w.k, n, epi);
-    if (p.splits > 1 && gemm_mfma_splits(w, n, epi, partial, partial_floats) == 1)
-        p.splits = 1, p.kb_per_split = w.k / BK;                  // no workspace for the partial tiles: one pass over k
+    const TilePlan p = tile_plan(w.m, w.k, n, epi, partial && (reinterpret_cast<uintptr_t>(partial) & 15) == 0 ? partial_floats : 0);
     if (fuse && p.splits < 2) return hipErrorInvalidValue;        // a folded light step needs the finishing pass
     a.partial = p.splits > 1 ? partial : nullptr;
     a.kb_per_split = p.kb_per_split;
@@ -666,7 +684,9 @@ hipError_t launch_gemm_mfma(const uint16_t *x, const relax_qmat &w, int n, int e
         if (c.resid) c.resid = (epi == EPI_RESID_F32) ? (const void *)((const uint16_t *)a.resid + skip) : (const void *)((const float *)a.resid + skip);
         return launch_tile<2, 4>(c, stream, 1);
     }
-    if (p.mf == 4) e = eight ? launch_tile<2, 4, false, 4, 2>(a, stream, p.splits) : launch_tile<4, 4>(a, stream, p.splits);
+    if (p.mf == 4 && p.nf == 4) e = eight ? launch_tile<2, 4, false, 4, 2>(a, stream, p.splits) : launch_tile<4, 4>(a, stream, p.splits);
+    else if (p.mf == 4) e = eight ? launch_tile<2, 3, false, 4, 2>(a, stream, p.splits) : launch_tile<4, 3>(a, stream, p.splits);
+    else if (p.nf == 3) e = launch_tile<2, 3>(a, stream, p.splits);
     else if (p.nf == 4) e = launch_tile<2, 4>(a, stream, p.splits);        // 128 x 256: four wavefronts of 64 x 128 beat eight of 64 x 64 by 4 to 11 %
     else if (p.nf == 2) e = launch_tile<2, 2>(a, stream, p.splits);
     else e = launch_tile<2, 1>(a, stream, p.splits);

@@ -384,13 +384,16 @@ hipError_t launch_swiglu_rows(const uint16_t *gu, uint16_t *act, int n, int F, h
 constexpr int kGemmMinN = 16;        // rows from which the MFMA GEMM replaces one matvec pass per row
 bool gemm_mfma_eligible(const relax_qmat &w, const void *x, int epi);
 void gemm_set_waves_per_simd(int v);     // test switch: 2 (default) = eight wavefronts per 256 x 256 tile, 1 = four
-constexpr int kSplitKMax = 8;         // k splits of the tiled GEMM at most, when its tiles alone leave more than half of the CUs idle
+constexpr int kSplitKMax = 8;         // k splits of the tiled GEMM at most
 constexpr int kSplitKMaxN = 512;      // ... and only up to this many rows (the partial tiles are splits * n * m floats)
 size_t gemm_splitk_partial_floats(int m, int k, int n, int epi);
 // partial: optional workspace of partial_floats fp32 for the k-split form (without it the launch makes one pass over k)
 // the same tiled kernel on plain fp16 weights [m,k] (no decode)
 bool gemm_f16_eligible(const void *x, const void *w, const void *out, int m, int k);
-hipError_t launch_gemm_f16(const uint16_t *x, const uint16_t *w, int n, int m, int k, uint16_t *out, hipStream_t stream);
+// partial: with room for the partial rows of more than one k split (gemm_flat_splits) they go there and the caller finishes them
+hipError_t launch_gemm_f16(const uint16_t *x, const uint16_t *w, int n, int m, int k, uint16_t *out, hipStream_t stream, float *partial = nullptr,
+                           size_t partial_floats = 0);
+int gemm_flat_splits(int n, int m, int k, size_t partial_floats);
 struct SkinnyFuse;
 int gemm_mfma_splits(const relax_qmat &w, int n, int epi, const float *partial, size_t partial_floats);
 // fuse: only for a launch that splits (gemm_mfma_splits > 1): the light step folded into its finishing pass
@@ -451,7 +454,7 @@ hipError_t launch_gemv_q3_native(const uint16_t *x, const relax_qmat &w, int n, 
 // the tiled MFMA GEMM on native 3-bit weights (gemm_q4_mfma.hip), taken from kQ3GemmRows rows of x on
 constexpr int kQ3GemmRows = 16;
 bool gemm_q3_eligible(const void *x, const relax_qmat &w, const void *out);
-hipError_t launch_gemm_q3(const uint16_t *x, const relax_qmat &w, int n, uint16_t *out, hipStream_t stream);
+hipError_t launch_gemm_q3(const uint16_t *x, const relax_qmat &w, int n, uint16_t *out, hipStream_t stream, float *partial = nullptr, size_t partial_floats = 0);
 hipError_t launch_dequantize(const relax_qmat &w, float *out, hipStream_t stream);
 
 // Split-L attention: chunk length and split count are pure functions of the runtime shape.
