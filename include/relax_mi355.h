@@ -112,7 +112,7 @@ typedef struct {
  * of sequence b sits at position kv_lens[b] - q_lens[b] + i.  A prefill of one sequence
  * is (B=1, {n}, {L}); a batched decode step is (B=n, {1,...}, {L_b}).  Up to 16 sequences ride in kernel arguments;
  * a longer descriptor without device_table is written to a table at the front of the workspace by small kernels on
- * the call's stream (32 sequences per launch, carried in their arguments): the host arrays are not needed after the
+ * the call's stream (128 sequences per launch, carried in their arguments): the host arrays are not needed after the
  * call returns, the host never waits, and the call can be captured in a graph.                                  */
 typedef struct {
     int32_t B;

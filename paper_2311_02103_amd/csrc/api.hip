@@ -220,7 +220,7 @@ relax_status build_seqs(const relax_seqs *sq, const relax_layer_dims &dm, int32_
     return RELAX_OK;
 }
 
-// Large batches: the descriptor goes to the device table at the front of the workspace, 32 sequences per launch of a small
+// Large batches: the descriptor goes to the device table at the front of the workspace, 128 sequences per launch of a small
 // kernel that carries them in its arguments (the extra symbolic arguments of Sec. 3.3): no host buffer has to outlive the
 // call, nothing is copied from pageable memory, the host never waits, and the launches can be captured in a graph.
 relax_status upload_table(SeqTable &st, const relax_seqs *sq, bool need_table, void *ws, const WsPlan &pl, hipStream_t stream)

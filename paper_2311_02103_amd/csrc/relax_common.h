@@ -498,7 +498,7 @@ hipError_t launch_probe_mfma(float *sink, int iters, int random_data, int n_cus,
 constexpr size_t kWsFlagBytes = 256;
 hipError_t launch_ws_clear(void *base, size_t bytes, hipStream_t stream);
 // Writes a chunk of the ragged descriptor into the device table [4][B] (batches that do not ride in kernel arguments).
-constexpr int kTableChunk = 32;
+constexpr int kTableChunk = 128;       // 2 KB of the 4 KB a launch's arguments may take; a chunk of 32 cost 64 sequences a second launch (2.5 us)
 struct TableChunk {
     int32_t first, count, B;
     int32_t q_start[kTableChunk], q_len[kTableChunk], kv_len[kTableChunk], slot[kTableChunk];

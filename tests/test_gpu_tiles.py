@@ -1,0 +1,79 @@
+"""GPU tests of the tiled GEMM's plan: tiles of 64 to 256 x-rows and k splits at the row counts around their edges, and of the
+attention kernel's token tiles."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+pytestmark = [pytest.mark.gpu, pytest.mark.skipif(not torch.cuda.is_available(), reason="needs a GPU")]
+
+import workloads as wl  # noqa: E402
+
+
+@pytest.fixture(scope="module")
+def rx():
+    from paper_2311_02103_amd import binding
+    binding.lib()
+    return binding
+
+
+def _gen(seed):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+    return g
+
+
+# a weight is rounded once to fp16, a result once more: below 2 * 2^-11 in the 2-norm
+REL = 1e-3
+
+
+@pytest.mark.parametrize("m,k,group", [(4096, 4096, 32), (520, 2816, 64), (1000, 1024, 128), (8192, 2048, 32)])
+@pytest.mark.parametrize("with_ws", [True, False])
+def test_row_counts_around_the_tile_edges(rx, m, k, group, with_ws):
+    g = _gen(m + k)
+    q = torch.randint(-2 ** 31, 2 ** 31 - 1, (m, k // 8), device="cuda", dtype=torch.int32, generator=g)
+    s = (torch.rand(m, k // group, device="cuda", generator=g) * 0.01 + 0.001).half()
+    w = rx.QMat(q, s, m, k, group)
+    codes = torch.empty(m, k, dtype=torch.int8, device="cuda")
+    rx.check(rx.relax_unpack_int4(w, codes))
+    ref = codes.double() * s.double().repeat_interleave(group, 1)
+    size = rx.relax_matmul_workspace_bytes(w, 600) if with_ws else 0
+    # the workspace ends where it says: nothing behind it may change
+    ws = torch.full((size + 4096,), 7, dtype=torch.uint8, device="cuda")
+    for n in (65, 129, 192, 193, 256, 257, 300, 384, 385, 511, 512, 513):
+        x = torch.randn(n, k, device="cuda", generator=g).half()
+        out = torch.full((n, m), float("nan"), device="cuda", dtype=torch.float16)
+        rx.check(rx.relax_dequant_matmul(x, w, out, n, ws if with_ws else None, size))
+        want = x.double() @ ref.t()
+        assert float((out.double() - want).norm() / want.norm()) < REL, (m, k, n)
+        assert bool((ws[size:] == 7).all())
+
+
+@pytest.mark.parametrize("d,heads,kv_heads", [(128, 8, 2), (64, 8, 8)])
+def test_prefill_attention_around_its_token_tiles(rx, d, heads, kv_heads):
+    """Rows and cached lengths around sub-tiles of 32, tiles of 128 tokens and 128 queries, against float64; NaN behind every
+    sequence's end must not be read into a result."""
+    g = _gen(d)
+    cap = 512
+    dims = rx.make_dims(heads * d, heads, kv_heads, d, 256, cap, 2)
+    rope = torch.empty(rx.relax_rope_table_bytes(dims) // 4, dtype=torch.float32, device="cuda")
+    rx.check(rx.relax_rope_table_init(dims, rope))
+    for q_len, past, other in ((16, 0, 1), (31, 1, 33), (32, 96, 64), (33, 95, 127), (127, 1, 128), (128, 0, 129), (129, 127, 1), (200, 57, 300), (256, 256, 31)):
+        L, n = q_len + past, q_len + 1
+        k = torch.randn(2, cap, kv_heads, d, device="cuda", generator=g).half()
+        v = torch.randn(2, cap, kv_heads, d, device="cuda", generator=g).half()
+        k[0, L:], v[0, L:], k[1, other:], v[1, other:] = (float("nan"),) * 4
+        q = torch.randn(n, heads, d, device="cuda", generator=g).half()
+        out = torch.full_like(q, float("nan"))
+        size = rx.relax_workspace_bytes(dims, n, cap, 2)
+        ws = torch.empty(size, dtype=torch.uint8, device="cuda")
+        rx.check(rx.relax_attention(q, rx.KVCache(k, v, rope), rx.Seqs([q_len, 1], [L, other]), dims, out, n, ws, size))
+        want = torch.empty(n, heads, d, dtype=torch.float64, device="cuda")
+        for rows, slot, length in ((slice(0, q_len), 0, L), (slice(q_len, n), 1, other)):
+            ql = rows.stop - rows.start
+            mask = torch.arange(length, device="cuda")[None] > torch.arange(length - ql, length, device="cuda")[:, None]
+            for h in range(heads):
+                kh, vh = k[slot, :length, h * kv_heads // heads].double(), v[slot, :length, h * kv_heads // heads].double()
+                sc = (q[rows, h].double() @ kh.t() / d ** 0.5).masked_fill(mask, float("-inf"))
+                want[rows, h] = torch.softmax(sc, 1) @ vh
+        # P rounded to fp16 (2^-11 each, independent), the result once more
+        assert float((out.double() - want).norm() / want.norm()) < 1e-3, (q_len, past, other)
