@@ -121,8 +121,8 @@ WsPlan plan_ws(const relax_layer_dims &dm, int32_t n, int32_t L, int32_t B, bool
     // The intermediates of the layer, their sizes and live ranges.  xn is pinned for the whole call (allocated in front of
     // operation 0, never recycled): relax_model_step hands the next layer's normalised input over in it.  q of the one-row
     // path lives in the front of the qkv tensor.  The split-K partial tiles of the few-row matmul are one lifted workspace
-    // (the largest of the four matrices, at most kSkinnyMaxN rows), allocated and released around each matmul.
-    const int ns = n < kSkinnyMaxN ? n : kSkinnyMaxN;
+    // (the largest of the four matrices, at most kSkinnySizedN rows), allocated and released around each matmul.
+    const int ns = n < kSkinnySizedN ? n : kSkinnySizedN;
     size_t fl = gemm_skinny_partial_floats((int)qkvw, dm.hidden, ns);
     const size_t f2 = gemm_skinny_partial_floats(dm.hidden, (int)hd, ns), f3 = gemm_skinny_partial_floats(2 * dm.ffn, dm.hidden, ns),
                  f4 = gemm_skinny_partial_floats(dm.hidden, dm.ffn, ns);
@@ -503,7 +503,7 @@ relax_status relax_rope_table_init(const relax_layer_dims *dims, float *table, r
 size_t relax_matmul_workspace_bytes(const relax_qmat *w, int32_t n_max)
 {
     if (check_qmat(w) != RELAX_OK || n_max < 1) return 0;
-    const int ns = n_max < kSkinnyMaxN ? n_max : kSkinnyMaxN;
+    const int ns = n_max < kSkinnySizedN ? n_max : kSkinnySizedN;
     return align256(sizeof(float) * std::max(gemm_skinny_partial_floats(w->m, w->k, ns), gemm_splitk_partial_floats(w->m, w->k, n_max, EPI_F16)));
 }
 

@@ -32,7 +32,7 @@ typedef float float4_t __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
 
-constexpr int kRound = 256;                  // k granule every matrix has to be a multiple of (a round is 256 or 128 columns)
+constexpr int kRound = 256;                  // columns of a round; every matrix has to be a multiple of it
 constexpr int kRowsPerBlock = 128;           // 4 wavefronts x 32 weight rows
 constexpr int kMaxRounds = 16;               // rounds per task at most (the task's scales sit in LDS: 128 rows x 16 bytes per round)
 
@@ -184,9 +184,7 @@ __global__ __launch_bounds__(256) void skinny_q4_kernel(SkinnyArgs a)
     auto round = [&](const Stage &S, int r, int buf) {
         const uint16_t *xb = xs + buf * kXBuf + (row32 & (XR - 1)) * kXPitch + hf * (KR / 2);
         // the group scales of the lane's half (W/4 of them), each duplicated into both halves of a register
-        u32x2_t sc;
-        if (W == 16) sc = *(const u32x2_t *)(sc_lane + r * 8);
-        else sc = u32x2_t{*(const uint32_t *)(sc_lane + r * 4), 0u};
+        const u32x2_t sc = *(const u32x2_t *)(sc_lane + r * 8);
         const uint32_t s2[4] = {__builtin_amdgcn_perm(sc.x, sc.x, 0x01000100u), __builtin_amdgcn_perm(sc.x, sc.x, 0x03020302u),
                                 __builtin_amdgcn_perm(sc.y, sc.y, 0x01000100u), __builtin_amdgcn_perm(sc.y, sc.y, 0x03020302u)};
 #pragma unroll
@@ -441,8 +439,6 @@ SkinnyPlan skinny_plan(int m, int k, int kr)
     return p;
 }
 
-inline int skinny_round(int n) { return n <= 64 ? 256 : 128; }   // wider x tiles take narrower rounds: the x chunk has to fit LDS twice
-
 template <int NF, int XR, int KR>
 hipError_t launch_skinny(const SkinnyArgs &a, dim3 grid, hipStream_t stream)
 {
@@ -473,7 +469,7 @@ bool gemm_skinny_eligible(const relax_qmat &w, const void *x, int n, int epi)
 size_t gemm_skinny_partial_floats(int m, int k, int n)
 {
     if (k % kRound != 0) return 0;
-    size_t worst = 0;                                     // n rows may run with either round size: take the larger plan
+    size_t worst = 0;                                     // the larger of the plans with rounds of 256 and of 128 columns: what callers bring
     for (int kr : {256, 128}) {
         const size_t v = (size_t)skinny_plan(m, k, kr).splits * (size_t)n * (size_t)m;
         worst = v > worst ? v : worst;
@@ -495,7 +491,7 @@ bool gemm_skinny_fuse_ok(const relax_qmat &w, int epi, const SkinnyFuse &f)
 hipError_t launch_gemm_skinny(const uint16_t *x, const relax_qmat &w, int n, int epi, uint16_t *out_f16, float *out_f32, const void *resid,
                               float *partial, hipStream_t stream, const SkinnyFuse *fuse)
 {
-    const SkinnyPlan pl = skinny_plan(w.m, w.k, skinny_round(n));
+    const SkinnyPlan pl = skinny_plan(w.m, w.k, kRound);
     SkinnyArgs a;
     a.x = x, a.q = w.q, a.s = w.s, a.gshift = gshift_of(w.group), a.partial = partial, a.n = n, a.m = w.m, a.k = w.k, a.rounds_per_split = pl.rounds_per_split;
     dim3 grid(pl.tiles_m, pl.splits);
@@ -503,8 +499,7 @@ hipError_t launch_gemm_skinny(const uint16_t *x, const relax_qmat &w, int n, int
     const int splits = pl.splits;
     if (n <= 16) e = launch_skinny<1, 16, 256>(a, grid, stream);
     else if (n <= 32) e = launch_skinny<1, 32, 256>(a, grid, stream);
-    else if (n <= 64) e = launch_skinny<2, 64, 256>(a, grid, stream);
-    else e = launch_skinny<4, 128, 128>(a, grid, stream);
+    else e = launch_skinny<2, 64, 256>(a, grid, stream);
     if (e != hipSuccess) return e;
     return launch_skinny_finish(partial, splits, n, w.m, epi, out_f16, out_f32, resid, stream, fuse);
 }

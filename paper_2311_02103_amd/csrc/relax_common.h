@@ -401,13 +401,14 @@ hipError_t launch_gemm_mfma(const uint16_t *x, const relax_qmat &w, int n, int e
                             hipStream_t stream, float *partial = nullptr, size_t partial_floats = 0, const SkinnyFuse *fuse = nullptr);
 // MFMA matmul for a few rows, split-K with partial tiles in the workspace (gemm_q4_skinny.hip)
 constexpr int kSkinnyMinN = 2;       // rows from which the layer takes the matrix path (norm, matmuls, rope as separate launches)
-constexpr int kSkinnyMaxN = 128;     // rows up to which the few-row kernel replaces the tiled GEMM
+constexpr int kSkinnyMaxN = 64;      // rows the split-K few-row kernel takes
+constexpr int kSkinnySizedN = 128;   // ... and rows a workspace for its partial tiles is sized for (the tiled GEMM cuts its launches along k within it)
 bool gemm_skinny_eligible(const relax_qmat &w, const void *x, int n, int epi);
-// Which of the two MFMA kernels takes n rows (Sec. 5.1: the dispatch follows the runtime value of the symbolic dim).  The
-// few-row kernel streams the weights once and is the faster one up to 128 rows on matrices of up to ~12k rows; on taller
-// matrices the tiled GEMM fills the CUs with tiles of its own and wins earlier (measured, 16-row steps: 22016 x 4096 from 80
-// rows, 47 against 63 us; 57344 x 8192 from 48 rows, 146 against 158 us; 12288 x 4096 and smaller: never up to 128 rows).
-inline bool gemm_prefers_tiled(int m, int n) { return (n > 64 && m >= 16384) || (n >= 48 && m >= 49152); }
+// Whether the tiled GEMM takes n rows before the few-row kernels (Sec. 5.1: the dispatch follows the runtime value of the symbolic
+// dim): from 65 rows on, where a launch cut along k keeps its tiles wide (128 rows, few-row kernel against tiled: 8192 x 28672 126 / 95 us,
+// 5120 x 13824 57 / 40, 10240 x 8192 63 / 45, 12288 x 4096 36.8 / 34.6; layers 7B 236 / 232, 13B 325 / 289, 70B 455 / 393), and from 48
+// rows on matrices that fill the chip with tiles (57344 x 8192: 146 against 158 us).
+inline bool gemm_prefers_tiled(int m, int n) { return n > 64 || (n >= 48 && m >= 49152); }
 size_t gemm_skinny_partial_floats(int m, int k, int n);
 // Optional light step folded into the finishing pass of the few-row matmul (one launch less):
 //   residual epilogues: also xn = RMSNorm(result) * norm_w (what the next matmul of the layer, or of the next layer, reads);
