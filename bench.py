@@ -364,7 +364,7 @@ def bench_prefill_layer(args, np, torch, wl, rx):
     gemm_ms = kernel_ms["qkv"] + kernel_ms["o_proj"] + kernel_ms["gate_up"] + kernel_ms["down"]
     attn_flops = 4.0 * (n * (n + 1) / 2) * shape.n_heads * shape.head_dim
     kernel = ("gemm_q4_mfma_kernel<EPI_SWIGLU> (gate/up GEMM, m=22016, k=4096, n=%d)" % n if n > 64 else
-              "skinny_q4_kernel + skinny_finish_kernel<EPI_SWIGLU> (gate/up, m=22016, k=4096, n=%d)" % n)
+              "few-row MFMA kernel (fewrow_kernel, or skinny_q4_kernel + finishing pass; gate/up, m=22016, k=4096, n=%d)" % n)
     roofline = {"bound": "mfma", "kernel": kernel, "achieved": round(ach, 1), "peak": PEAK_MFMA_TFLOPS, "unit": "TFLOP/s",
                 "frac": round(ach / PEAK_MFMA_TFLOPS, 4), "traffic": traffic_from_profile("traffic_gate_up_gemm_7b_n%d.json" % n),
                 "algorithmic_flops_per_launch": gu_flops, "avg_launch_ms": round(kernel_ms["gate_up"], 5)}
@@ -522,7 +522,7 @@ def bench_model(args, np, torch, wl, rx, big):
     m, k = shape.matrices()["wgu"]
     gu_bytes = m * (k // 2) + m * (k // 32) * 2
     ach = gu_bytes / (kernel_ms["gate_up"] * 1e-3) / 1e9
-    kernel = ("skinny_q4_kernel<1,16> + skinny_finish_kernel<EPI_SWIGLU> (gate/up, m=57344, k=8192, n=16)" if big else
+    kernel = ("fewrow_kernel<F_Q4G32, 1, 4, 2, 4> (gate/up with SwiGLU, m=57344, k=8192, n=16)" if big else
               "gemv_q4_reg_kernel<X_F32_NORM, EPI_SWIGLU, 2> (gate/up matvec, m=22016, k=4096)")
     roofline = {"bound": "hbm", "kernel": kernel, "achieved": round(ach, 1), "peak": PEAK_HBM_GBS, "unit": "GB/s",
                 "frac": round(ach / PEAK_HBM_GBS, 4),
