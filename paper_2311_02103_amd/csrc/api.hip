@@ -295,8 +295,9 @@ int device_cus()
 }
 
 // out[n,m] = x[n,k] . w[m,k]^T on plain fp16 weights (relax_half_matmul, and the LM head of relax_model_step).
-// The same runtime dispatch on the symbolic n as the int4 path (Sec. 5.1): matvec passes for a few rows, tiled MFMA GEMM from
-// there on.  Where "there" is depends on the matrix: a pass streams the whole matrix (5.5 TB/s; passes of 8 rows are
+// 2 .. 32 rows take the streaming few-row kernel where one k range holds a row (22016 x 4096 at 8 rows 35 us, 4096 x 4096 at 16 rows 12).
+// One row, longer rows and more rows: the same runtime dispatch on the symbolic n as the int4 path (Sec. 5.1), matvec passes for a few
+// rows, tiled MFMA GEMM from there on.  Where "there" is depends on the matrix: a pass streams the whole matrix (5.5 TB/s; passes of 8 rows are
 // bound by their dot products and take twice as long), a GEMM launch with few rows costs its k loop whatever n is
 // (0.5 us per 64 columns, more when its tiles fill the device); wider passes also cost more when only one block's x rows fit
 // a CU.  Measured on 4096 x 4096: matvec up to 16 rows (33 against 36 us), GEMM from 24 (36 against 47); on 22016 x 4096:
@@ -641,8 +642,9 @@ relax_status layer_enqueue(const relax_layer_dims &dm, const relax_layer_weights
 
     float *partials = reinterpret_cast<float *>(base + pl.partials);
 
-    // More than one row: matrix path (same entry point, same binary) -- the matmuls run on MFMA, as the split-K
-    // few-row kernel up to kSkinnyMaxN rows and as the tiled GEMM above, with the light steps as separate kernels.
+    // More than one row: matrix path (same entry point, same binary) -- the matmuls run on MFMA: up to kSkinnyMaxN rows the streaming
+    // or the split-K few-row kernel, whichever is estimated faster for a matrix, the tiled GEMM above; the light steps ride in their
+    // epilogues and finishing passes or are kernels of their own.
     float *skinny_ws = reinterpret_cast<float *>(base + pl.skinny);
     // k ranges of the streaming few-row kernel where it takes this matmul (0: it does not).  Its finishing pass, if any, is the RMSNorm
     // launch behind the output projection (and behind the down projection when the next layer's norm is known).
