@@ -251,12 +251,14 @@ __global__ __launch_bounds__(64 * NWV) void attn_prefill_kernel(const uint16_t *
             scores(Kb, ua, Sa, [&](int i) { return read_k(Kb, ub, i); });
             if (ta + kTB - 1 > pos_wave_min) mask(ta, Sa);
             scores(Kb, ub, Sb, [&](int i) { return read_v(Vb, ua, i); });
-            rescale(reference(Sa, cm, alpha), alpha);
+            const bool move_a = reference(Sa, cm, alpha);         // writes alpha: a statement of its own, ahead of its use
+            rescale(move_a, alpha);
             weights(Sa, cm, pa);
             accumulate(Vb, ua, pa, [&](int i) { return read_v(Vb, ub, i); });
             if (two) {
                 if (tc + kTB - 1 > pos_wave_min) mask(tc, Sb);
-                rescale(reference(Sb, cm, alpha), alpha);
+                const bool move_b = reference(Sb, cm, alpha);
+                rescale(move_b, alpha);
                 weights(Sb, cm, pb);
                 accumulate(Vb, ub, pb, [&](int i) { return ring[i]; });
             }
