@@ -193,7 +193,11 @@ __global__ __launch_bounds__(64 * NWV) void attn_prefill_kernel(const uint16_t *
     };
     // Online softmax of one sub-tile in two parts: the reference point, then the exponentials (P^T packed as the B operand of the
     // second product).  Everything stays in units of the raw scores, the softmax scale and log2(e) are one factor c of the
-    // multiply-add in front of the exponential: exp(scale (s - m)) = exp2(c s - c m).
+    // multiply-add in front of the exponential: exp(scale (s - m)) = exp2(c s - c m).  c m is rounded, so the largest exponent is
+    // off zero by up to half a unit in the last place of c m: 2^-17 (5e-6 of a weight, the same for all weights of the row) up to
+    // c m = kFar, but 16 and more from 2^28 on, past the fp16 range of P.  Beyond kFar the reference is subtracted from the scores
+    // first, which is exact for the largest one (a subtraction more per score in all steps took 2 to 3 % at n = 4096).
+    constexpr float kFar = 256.0f;
     auto reference = [&](const float16_t &S, float &cm, float &alpha) {
         float mx = fmaxf(S[0], S[1]);
 #pragma unroll
@@ -208,7 +212,7 @@ __global__ __launch_bounds__(64 * NWV) void attn_prefill_kernel(const uint16_t *
         // a KV group's first sub-tiles can be masked entirely for the earlier queries of the wavefront: no reference yet,
         // every weight is exp(-inf - 0) = 0 and the state stays empty
         cm = m_new == -INFINITY ? 0.0f : c * m_new;
-        alpha = move ? __builtin_amdgcn_exp2f(fmaf(c, m_run, -cm)) : 1.0f;      // exp2(-inf) = 0 on the first tile
+        alpha = move ? __builtin_amdgcn_exp2f(c * (m_run - m_new)) : 1.0f;      // exp2(-inf) = 0 on the first tile
         l_run *= alpha;
         m_run = m_new;
         return move;
@@ -223,8 +227,14 @@ __global__ __launch_bounds__(64 * NWV) void attn_prefill_kernel(const uint16_t *
             pf[v >> 3][v & 7] = h.x, pf[v >> 3][(v & 7) + 1] = h.y;
         }
     };
-    auto rescale = [&](bool move, float alpha) {
-        if (__any(move)) {
+    // rare: the reference has moved, or lies beyond kFar (then the scores become differences and cm 0)
+    auto rescale = [&](bool move, float alpha, float16_t &S, float &cm) {
+        const bool far = fabsf(cm) > kFar;
+        if (__any(move || far)) {
+            const float off = far ? m_run : 0.0f;
+            cm = far ? 0.0f : cm;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) S[v] -= off;
 #pragma unroll
             for (int db = 0; db < DB; ++db)
 #pragma unroll
@@ -252,13 +262,13 @@ __global__ __launch_bounds__(64 * NWV) void attn_prefill_kernel(const uint16_t *
             if (ta + kTB - 1 > pos_wave_min) mask(ta, Sa);
             scores(Kb, ub, Sb, [&](int i) { return read_v(Vb, ua, i); });
             const bool move_a = reference(Sa, cm, alpha);         // writes alpha: a statement of its own, ahead of its use
-            rescale(move_a, alpha);
+            rescale(move_a, alpha, Sa, cm);
             weights(Sa, cm, pa);
             accumulate(Vb, ua, pa, [&](int i) { return read_v(Vb, ub, i); });
             if (two) {
                 if (tc + kTB - 1 > pos_wave_min) mask(tc, Sb);
                 const bool move_b = reference(Sb, cm, alpha);
-                rescale(move_b, alpha);
+                rescale(move_b, alpha, Sb, cm);
                 weights(Sb, cm, pb);
                 accumulate(Vb, ub, pb, [&](int i) { return ring[i]; });
             }

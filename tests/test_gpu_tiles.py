@@ -77,3 +77,39 @@ def test_prefill_attention_around_its_token_tiles(rx, d, heads, kv_heads):
                 want[rows, h] = torch.softmax(sc, 1) @ vh
         # P rounded to fp16 (2^-11 each, independent), the result once more
         assert float((out.double() - want).norm() / want.norm()) < 1e-3, (q_len, past, other)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("size", [3.0, 30.0, 300.0, 3000.0, 30000.0])
+def test_prefill_attention_on_large_scores(rx, d, size):
+    """Queries and keys of magnitude size / 2 .. size: dot products up to 1e11, all finite in fp32.  Three heads: keys equal to the
+    queries (each row sees mostly itself), keys that grow along the sequence (the reference point moves all the time), one key
+    repeated (equal scores: the mean of the values so far)."""
+    n, heads = 200, 3
+    g = _gen(int(size))
+    dims = rx.make_dims(heads * d, heads, heads, d, 256, n, 1)
+    rope = torch.empty(rx.relax_rope_table_bytes(dims) // 4, dtype=torch.float32, device="cuda")
+    rx.check(rx.relax_rope_table_init(dims, rope))
+    q = torch.randn(n, heads, d, device="cuda", generator=g)
+    q = (q.sign() * (0.5 + 0.5 * torch.rand(q.shape, device="cuda", generator=g)) * size).half()
+    k, v = q.clone(), torch.randn(n, heads, d, device="cuda", generator=g).half()
+    k[:, 1] = (k[:, 1].float() * torch.linspace(0.1, 1.0, n, device="cuda")[:, None]).half()
+    k[:, 2] = k[0, 2]
+    out, bytes_ = torch.full_like(q, float("nan")), rx.relax_workspace_bytes(dims, n, n, 1)
+    ws = torch.empty(bytes_, dtype=torch.uint8, device="cuda")
+    rx.check(rx.relax_attention(q, rx.KVCache(k.contiguous(), v, rope), rx.Seqs([n], [n]), dims, out, n, ws, bytes_))
+    assert torch.isfinite(out).all()
+    future = torch.ones(n, n, dtype=torch.bool, device="cuda").triu(1)
+    for h in range(heads):
+        scores = q[:, h].double() @ k[:, h].double().t()
+        p = torch.softmax((scores / d ** 0.5).masked_fill(future, float("-inf")), 1)
+        # what the fp32 sum of a score's products may be off by (d + 1 roundings) may turn the softmax; P and the result are rounded
+        # to fp16, 2^-11 each.  A row is checked where the first stays below the second.
+        slack = (q[:, h].double().abs() @ k[:, h].double().abs().t()).max(1).values * (d + 1) * 2.0 ** -24 / d ** 0.5
+        top2 = (scores / d ** 0.5).masked_fill(future, float("-inf")).topk(2, 1).values
+        clear = (slack < 2.0 ** -11) | (top2[:, 0] - top2[:, 1] > 2 * slack + 10.0) | (torch.arange(n, device="cuda") == 0)
+        if h == 2:                                        # equal keys have equal sums, whatever their rounding
+            clear[:] = True
+        want = p @ v[:, h].double()
+        assert clear.sum() > n // 4
+        assert float((out[clear, h].double() - want[clear]).norm() / want[clear].norm()) < 1e-3, h
