@@ -20,14 +20,14 @@
 //     through LDS at the end).  The step count of the longest prefix sets the kernel time, and this halves it; fewer
 //     queries per workgroup cost more than they give because every workgroup stages every K/V tile of its prefix.
 //     A wavefront keeps its 32 queries' Q fragments in registers, O^T (32 x d fp32) in accumulators.  KV tiles of
-//     128 tokens (two sub-tiles per wavefront) are staged through registers into one of two LDS buffers, one barrier per
-//     tile; the next tile's global loads are in flight during the MFMAs.
-//   - The query heads of a KV head go to the same XCD, so that its K and V are fetched into one L2.
+//     64 tokens (one sub-tile per wavefront) are staged through registers into one of two LDS buffers, one barrier per
+//     tile; the next tile's global loads are in flight during the MFMAs.  They are issued without a condition
+//     (behind the last tile: the sequence's last row once more), 3 to 12 % faster than behind a branch.
+//   - The query heads of a KV head get numbers that are equal modulo the number of KV heads: with 8 of them (or a multiple)
+//     they go to the same XCD, and its K and V are fetched into one L2.
 //   - Workgroups of the longest prefixes are first in dispatch order (causal work grows with the q position).
 //   - Cache rows past a sequence's length are never read (loads are clamped to its last row); masked scores are
 //     replaced, not multiplied, so stale cache contents cannot leak in.
-#include <atomic>
-
 #include "relax_common.h"
 
 namespace relax {
@@ -70,15 +70,17 @@ __device__ __forceinline__ void lds_barrier()
 }
 
 // grid: x = query head, y = q tile (reversed: longest prefix first), z = sequence
-template <int D, int NWV, int TBS, int KVS>
-__global__ __launch_bounds__(64 * NWV) void attn_prefill_kernel(const uint16_t *__restrict__ q, int q_stride,
+// MINW: wavefronts per SIMD the registers have to leave room for.  Heads of 64 fit two workgroups on a CU (4 per SIMD), which calls of
+// many short sequences live on.
+template <int D, int NWV, int KVS, int MINW>
+__global__ __launch_bounds__(64 * NWV, MINW) void attn_prefill_kernel(const uint16_t *__restrict__ q, int q_stride,
                                                                  const uint16_t *__restrict__ kc, const uint16_t *__restrict__ vc,
                                                                  uint16_t *__restrict__ out, SeqTable st, int h, int g, int cap)
 {
     // NWV wavefronts = QW query groups x KVS groups along the KV length: wavefront (qw, kg) owns queries qw WQ .. + WQ of the
     // workgroup and every KVS-th 32-token sub-tile (the longest prefix is then KVS times fewer steps per wavefront);
     // the KVS states of a query group are merged through LDS at the end.
-    static_assert(TBS == 2 * KVS && NWV % KVS == 0, "two sub-tiles of a tile for every KV group");
+    static_assert(NWV % KVS == 0, "one sub-tile of a tile for every KV group");
     constexpr int QW = NWV / KVS;
     constexpr int kQB = QW * 32;             // queries per workgroup
     constexpr int kPThreads = 64 * NWV, WQ = 32;
@@ -87,12 +89,12 @@ __global__ __launch_bounds__(64 * NWV) void attn_prefill_kernel(const uint16_t *
     static_assert(KS == 2 * DB, "both products of a sub-tile are KS MFMAs");
     constexpr int KP = D + 8;        // K tile pitch in halfs: 16-byte row reads of 32 rows hit distinct banks
     constexpr int VP = D + 32;       // V tile pitch in halfs: the 8-byte transpose reads of a 32-lane half hit distinct banks
-    constexpr int TT = kTB * TBS;    // tokens staged per barrier pair: TBS sub-tiles of 32
+    constexpr int TT = kTB * KVS;    // tokens staged per barrier
     constexpr int PK = TT * (D / 8) / kPThreads;    // 16-byte packets per thread and tile, for K and for V
     constexpr int kTileHalfs = TT * KP + TT * VP;
     constexpr int kMergeFloats = KVS > 1 ? (KVS / 2) * QW * 64 * (DB * 16 + 2) : 0;   // one merge round: half of the KV groups write
     static_assert(2 * kTileHalfs * 2 >= kMergeFloats * 4, "the states to merge fit the tiles");
-    extern __shared__ __align__(16) unsigned char smem[];         // two tiles [K rows | V rows]
+    __shared__ __align__(16) unsigned char smem[2 * kTileHalfs * 2];         // two tiles [K rows | V rows]
     uint16_t *const tiles = reinterpret_cast<uint16_t *>(smem);
 
     const SeqInfo si = seq_info(st, blockIdx.z);
@@ -159,30 +161,30 @@ __global__ __launch_bounds__(64 * NWV) void attn_prefill_kernel(const uint16_t *
     // the products.  (With the reads one MFMA ahead the matrix pipe was busy 30 % of the time, the wavefronts waiting 41 %.)
     constexpr int PD = 4;
     half8_t ring[PD];
-    auto read_k = [&](const uint16_t *Kb, int u, int i) { return *(const half8_t *)(Kb + (u * kTB + i32) * KP + hf * 8 + i * 16); };
-    auto read_v = [&](const uint16_t *Vb, int u, int i) {
-        const uint16_t *vp = Vb + (u * kTB + (i / DB) * 16 + tr_row) * VP + (i % DB) * 32 + tr_col;
+    auto read_k = [&](const uint16_t *Kb, int i) { return *(const half8_t *)(Kb + i32 * KP + hf * 8 + i * 16); };
+    auto read_v = [&](const uint16_t *Vb, int i) {
+        const uint16_t *vp = Vb + ((i / DB) * 16 + tr_row) * VP + (i % DB) * 32 + tr_col;
         const short4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) short4_t *)vp);
         const short4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) short4_t *)(vp + 8 * VP));
         return __builtin_bit_cast(half8_t, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
     };
     // S^T = K Q^T; next(i): operand i of whatever follows this product
-    auto scores = [&](const uint16_t *Kb, int u, float16_t &S, const auto &next) {
+    auto scores = [&](const uint16_t *Kb, float16_t &S, const auto &next) {
 #pragma unroll
         for (int v = 0; v < 16; ++v) S[v] = 0.0f;
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
             S = __builtin_amdgcn_mfma_f32_32x32x16_f16(ring[ks % PD], qf[ks], S, 0, 0, 0);
-            ring[ks % PD] = ks + PD < KS ? read_k(Kb, u, ks + PD) : next(ks + PD - KS);
+            ring[ks % PD] = ks + PD < KS ? read_k(Kb, ks + PD) : next(ks + PD - KS);
             __builtin_amdgcn_sched_barrier(0);
         }
     };
     // O^T += V^T P^T
-    auto accumulate = [&](const uint16_t *Vb, int u, const half8_t *pf, const auto &next) {
+    auto accumulate = [&](const uint16_t *Vb, const half8_t *pf) {
 #pragma unroll
         for (int i = 0; i < KS; ++i) {
             O[i % DB] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ring[i % PD], pf[i / DB], O[i % DB], 0, 0, 0);
-            ring[i % PD] = i + PD < KS ? read_v(Vb, u, i + PD) : next(i + PD - KS);
+            if (i + PD < KS) ring[i % PD] = read_v(Vb, i + PD);
             __builtin_amdgcn_sched_barrier(0);
         }
     };
@@ -247,31 +249,21 @@ __global__ __launch_bounds__(64 * NWV) void attn_prefill_kernel(const uint16_t *
     int buf = 0;
     for (int tb = 0; tb <= pos_block_max; tb += TT) {
         const bool more = tb + TT <= pos_block_max;               // uniform for the workgroup
-        if (more) tile_load(tb + TT);
-        const uint16_t *Kb = tiles + buf * kTileHalfs, *Vb = Kb + TT * KP;
-        // this wavefront's sub-tiles of the tile: kg and kg + KVS
-        const int ua = kg, ub = kg + KVS, ta = tb + ua * kTB, tc = tb + ub * kTB;
-        half8_t pa[2], pb[2];
-        float16_t Sa, Sb;
-        float cm, alpha;
-        if (ta <= pos_wave_max) {
-            const bool two = tc <= pos_wave_max;                 // wavefront-uniform, like every branch here
+        tile_load(tb + TT);
+        const uint16_t *Kb = tiles + buf * kTileHalfs + kg * kTB * KP, *Vb = tiles + buf * kTileHalfs + TT * KP + kg * kTB * VP;
+        const int t0 = tb + kg * kTB;                             // this wavefront's sub-tile
+        if (t0 <= pos_wave_max) {                                 // wavefront-uniform, like every branch here
+            float16_t S;
+            half8_t p[2];
+            float cm, alpha;
 #pragma unroll
-            for (int i = 0; i < PD; ++i) ring[i] = read_k(Kb, ua, i);
-            scores(Kb, ua, Sa, [&](int i) { return read_k(Kb, ub, i); });
-            if (ta + kTB - 1 > pos_wave_min) mask(ta, Sa);
-            scores(Kb, ub, Sb, [&](int i) { return read_v(Vb, ua, i); });
-            const bool move_a = reference(Sa, cm, alpha);         // writes alpha: a statement of its own, ahead of its use
-            rescale(move_a, alpha, Sa, cm);
-            weights(Sa, cm, pa);
-            accumulate(Vb, ua, pa, [&](int i) { return read_v(Vb, ub, i); });
-            if (two) {
-                if (tc + kTB - 1 > pos_wave_min) mask(tc, Sb);
-                const bool move_b = reference(Sb, cm, alpha);
-                rescale(move_b, alpha, Sb, cm);
-                weights(Sb, cm, pb);
-                accumulate(Vb, ub, pb, [&](int i) { return ring[i]; });
-            }
+            for (int i = 0; i < PD; ++i) ring[i] = read_k(Kb, i);
+            scores(Kb, S, [&](int i) { return read_v(Vb, i); });
+            if (t0 + kTB - 1 > pos_wave_min) mask(t0, S);
+            const bool move = reference(S, cm, alpha);            // writes alpha: a statement of its own, ahead of its use
+            rescale(move, alpha, S, cm);
+            weights(S, cm, p);
+            accumulate(Vb, p);
         }
         buf ^= 1;
         if (more) tile_store(buf);
@@ -327,20 +319,13 @@ __global__ __launch_bounds__(64 * NWV) void attn_prefill_kernel(const uint16_t *
         }
 }
 
-template <int D, int NWV, int TBS, int KVS>
+template <int D, int NWV, int KVS, int MINW>
 hipError_t launch_one(const uint16_t *q, int32_t q_stride, const relax_kv_cache &cache, const relax_layer_dims &dm, const SeqTable &st, uint16_t *out,
                       hipStream_t stream)
 {
-    constexpr int kLds = 2 * kTB * TBS * ((D + 8) + (D + 32)) * 2;
-    static std::atomic<bool> attr_done{false};            // setting the attribute twice is harmless; the flag only has to be a defined read
-    if (!attr_done.load()) {
-        if (hipFuncSetAttribute((const void *)attn_prefill_kernel<D, NWV, TBS, KVS>, hipFuncAttributeMaxDynamicSharedMemorySize, kLds) != hipSuccess)
-            return hipErrorInvalidValue;
-        attr_done.store(true);
-    }
     const int queries = NWV / KVS * 32;
     const dim3 grid(dm.n_heads, (st.q_max + queries - 1) / queries, st.B);
-    hipLaunchKernelGGL((attn_prefill_kernel<D, NWV, TBS, KVS>), grid, dim3(64 * NWV), kLds, stream, q, q_stride, cache.k, cache.v, out, st, dm.n_heads,
+    hipLaunchKernelGGL((attn_prefill_kernel<D, NWV, KVS, MINW>), grid, dim3(64 * NWV), 0, stream, q, q_stride, cache.k, cache.v, out, st, dm.n_heads,
                        dm.n_kv_heads, dm.kv_capacity);
     return hipGetLastError();
 }
@@ -352,14 +337,22 @@ bool attn_prefill_supported(const relax_layer_dims &dm) { return dm.head_dim == 
 hipError_t launch_attention_prefill(const uint16_t *q, int32_t q_stride, const relax_kv_cache &cache, const relax_layer_dims &dm,
                                     const SeqTable &st, uint16_t *out, hipStream_t stream)
 {
-    // 8 wavefronts = 4 query groups of 32 x 2 KV groups, two tiles of 128 tokens in LDS.  Measured at n = 4096, 32 / 8 heads of 128: 200 us
-    // (226 with one tile of 64 tokens, the softmax in units of e and masks on every tile; 208 with the cheaper softmax alone);
-    // n = 2048, 32 heads: 63 us (72).  With the loads of the next tile left out the first takes 178 us, without its stores too 162:
-    // matrix pipe and vector unit together are busy 70 % of the time at two wavefronts per SIMD.  Ordering the exponentials of one
-    // sub-tile between the MFMAs of the other changed nothing (203 to 216 us).  Earlier forms at n = 2048: without the KV groups 82-84 us,
-    // 64 queries per wavefront 128 us, 64 queries per workgroup 93-117 us.
-    if (dm.head_dim == 128) return launch_one<128, 8, 4, 2>(q, q_stride, cache, dm, st, out, stream);
-    if (dm.head_dim == 64) return launch_one<64, 8, 4, 2>(q, q_stride, cache, dm, st, out, stream);
+    // 8 wavefronts = 4 query groups of 32 x 2 KV groups, two tiles of 64 tokens in LDS (76 KB; heads of 64: 43 KB).  Measured, against one
+    // tile of 64 tokens with the softmax in units of e and masks on every tile, and against two tiles of 128 tokens (152 KB, 86 KB):
+    //   4096 rows, 32 / 8 heads of 128               181 us   214   188
+    //   2048 rows, 32 / 32 heads of 128               55       64    57
+    //   64 x 20 rows on 300 cached tokens, 32 / 32    96       97   105
+    //   16 x 1 row on 100..2000 tokens beside 16     113      114   121
+    //   64 x 20 rows, 32 / 8 heads of 64            16.9     18.2  25.8
+    //   64 x 100 rows on 200 cached, 32 / 8, 64       43       50    68
+    // Long tiles lose on cached prefixes (bursts of loads, part of the last tile empty) and, with heads of 64, the second workgroup of
+    // a CU.  One buffer instead of two: the 64-row call on 2000 cached tokens 41.7 instead of 37.9 us.  With the loads of the next
+    // tile left out 4096 rows took 178 us of 200 in an earlier form, without its stores too 162: matrix pipe and vector unit together
+    // are busy 70 % of the time at two wavefronts per SIMD.  Ordering the exponentials of one sub-tile between the MFMAs of another
+    // changed nothing.  Earlier forms at n = 2048: without the KV groups 82-84 us, 64 queries per wavefront 128 us, 64 queries per
+    // workgroup 93-117 us.
+    if (dm.head_dim == 128) return launch_one<128, 8, 2, 2>(q, q_stride, cache, dm, st, out, stream);
+    if (dm.head_dim == 64) return launch_one<64, 8, 2, 4>(q, q_stride, cache, dm, st, out, stream);
     return hipErrorInvalidValue;
 }
 

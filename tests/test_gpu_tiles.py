@@ -50,14 +50,14 @@ def test_row_counts_around_the_tile_edges(rx, m, k, group, with_ws):
 
 @pytest.mark.parametrize("d,heads,kv_heads", [(128, 8, 2), (64, 8, 8)])
 def test_prefill_attention_around_its_token_tiles(rx, d, heads, kv_heads):
-    """Rows and cached lengths around sub-tiles of 32, tiles of 128 tokens and 128 queries, against float64; NaN behind every
+    """Rows and cached lengths around sub-tiles of 32, tiles of 64 tokens and 128 queries, against float64; NaN behind every
     sequence's end must not be read into a result."""
     g = _gen(d)
     cap = 512
     dims = rx.make_dims(heads * d, heads, kv_heads, d, 256, cap, 2)
     rope = torch.empty(rx.relax_rope_table_bytes(dims) // 4, dtype=torch.float32, device="cuda")
     rx.check(rx.relax_rope_table_init(dims, rope))
-    for q_len, past, other in ((16, 0, 1), (31, 1, 33), (32, 96, 64), (33, 95, 127), (127, 1, 128), (128, 0, 129), (129, 127, 1), (200, 57, 300), (256, 256, 31)):
+    for q_len, past, other in ((16, 0, 1), (31, 1, 33), (32, 96, 64), (33, 95, 127), (127, 1, 128), (128, 0, 129), (129, 127, 1), (200, 57, 300), (256, 256, 31), (16, 47, 63), (17, 47, 65), (33, 32, 64)):
         L, n = q_len + past, q_len + 1
         k = torch.randn(2, cap, kv_heads, d, device="cuda", generator=g).half()
         v = torch.randn(2, cap, kv_heads, d, device="cuda", generator=g).half()
