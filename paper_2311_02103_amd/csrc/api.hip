@@ -16,9 +16,13 @@ inline bool aligned(const void *p, size_t bytes) { return (reinterpret_cast<uint
 
 // k ranges of the streaming few-row kernel for a packed matrix at n rows, with at most `partial_floats` floats for the partial rows
 // of a launch that is cut along k; 0: it does not take the call.  out: whatever the epilogue writes or adds (8-byte accesses).
+// The kernel reads codes and scales at 4-byte alignment.  4-bit matrices have to be aligned as the split-K kernel wants them all
+// the same: it rounds a weight to fp16, and calls that no MFMA kernel took for their alignment stay on the matvec kernels, which
+// apply the scale in fp32.
 int stream_ranges(int wmode, const relax_qmat &w, const void *x, const void *out, int n, int epi, size_t partial_floats, bool folded = false)
 {
-    if (!aligned(x, 16) || !aligned(w.q, 4) || !aligned(w.s, 4) || !aligned(out, 8)) return 0;
+    const size_t wa = wmode == W_Q4 ? 16 : 4;
+    if (!aligned(x, 16) || !aligned(w.q, wa) || !aligned(w.s, wa) || !aligned(out, 8)) return 0;
     return fewrow_ranges(wmode, n, w.m, w.k, epi, folded, partial_floats);
 }
 

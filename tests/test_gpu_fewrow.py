@@ -122,3 +122,45 @@ def test_layers_on_it_against_the_first_rows_of_a_larger_call(rx, fmt, si):
         for a, b in ((layer.k, k_all), (layer.v, v_all)):
             assert float((a[0, :n].double() - b[0, :n].double()).norm() / b[0, :n].double().norm()) < 2e-3
             assert not a[0, n:].any()
+
+
+def _shifted(t, elements):
+    """A copy of t that starts `elements` elements into its storage."""
+    buf = torch.empty(t.numel() + elements, dtype=t.dtype, device="cuda")
+    buf[elements:] = t.reshape(-1)
+    return buf[elements:].view(t.shape)
+
+
+@pytest.mark.parametrize("shift_q,shift_s", [(1, 0), (0, 2), (2, 4)])
+def test_unaligned_4bit_weights_keep_their_fp32_scales(rx, shift_q, shift_s):
+    """Codes or scales that are aligned to 4 or 8 bytes only (views into one packed checkpoint) are served by the matvec kernels at 2
+    to 15 rows, with or without a workspace: the same bits, scales applied in fp32."""
+    m, k, g = 512, 1024, _gen(9)
+    w, _ = _packed(rx, "q4", m, k, 32, g)
+    w = rx.QMat(_shifted(w.q, shift_q), _shifted(w.s, shift_s), m, k, 32)
+    ws_bytes = rx.relax_matmul_workspace_bytes(w, 64)
+    ws = torch.empty(ws_bytes, dtype=torch.uint8, device="cuda")
+    for n in (2, 5, 15):
+        x = torch.randn(n, k, device="cuda", generator=g).half()
+        with_ws, without = torch.empty(n, m, device="cuda", dtype=torch.float16), torch.empty(n, m, device="cuda", dtype=torch.float16)
+        rx.check(rx.relax_dequant_matmul(x, w, with_ws, n, ws, ws_bytes))
+        rx.check(rx.relax_dequant_matmul(x, w, without, n, None, 0))
+        assert torch.equal(with_ws, without), n
+
+
+def test_layer_on_unaligned_4bit_weights_runs_on_the_matvec_kernels(rx):
+    from paper_2311_02103_amd.runtime import DeviceLayer
+    shape = LAYERS[0]
+    layer = DeviceLayer(wl.layer_weights(shape, 4), hidden=shape.hidden, n_heads=shape.n_heads, n_kv_heads=shape.n_kv_heads, head_dim=shape.head_dim,
+                        ffn=shape.ffn, kv_capacity=64, n_max=16)
+    for mat in (layer.weights.wqkv, layer.weights.wo, layer.weights.wgu, layer.weights.wdown):
+        mat.q, mat.s = _shifted(mat.q, 1), _shifted(mat.s, 2)
+    x = torch.from_numpy(wl.activations(shape, 4, 0, 15).view(np.int16)).view(torch.float16).cuda()
+    for n in (5, 15):
+        got = layer.forward(x[:n].contiguous(), [n], [n])
+        try:                                              # the switch that keeps every call on the matvec kernels
+            rx.check(rx.relax_set_option("layer_matvec_rows", 64))
+            want = layer.forward(x[:n].contiguous(), [n], [n])
+        finally:
+            rx.check(rx.relax_set_option("layer_matvec_rows", 4))
+        assert torch.equal(got, want), n
