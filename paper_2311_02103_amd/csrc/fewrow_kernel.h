@@ -95,7 +95,9 @@ __device__ __forceinline__ u32x4_t decode_q4(uint32_t w)
     return u32x4_t{pk_add(a0, kNeg1032), pk_fma(a1, kSixteenth, kNeg72), pk_add(a2, kNeg1032), pk_fma(a3, kSixteenth, kNeg72)};
 }
 // packet j (columns 8j .. 8j+7) of a 3-bit group from its three words -> its codes less 4 as fp16: pairs (1024 + f u) with f = 1, 8
-// or 64 by class, one packed fma removes weight and offset exactly ((1024 + f u) / f - (1024 / f + 4) = u - 4)
+// or 64 by class, one packed fma removes weight and offset exactly ((1024 + f u) / f - (1024 / f + 4) = u - 4).
+// QUARTER: a quarter of that, as exact (all constants are fp16 values)
+template <bool QUARTER>
 __device__ __forceinline__ u32x4_t decode_q3(const u32x3_t &w, int j)
 {
     const uint32_t base = 0x64006400u;
@@ -112,7 +114,8 @@ __device__ __forceinline__ u32x4_t decode_q3(const u32x3_t &w, int j)
             const uint32_t v = p % 5 >= 3 ? w[p / 5] >> 9 : w[p / 5];
             pair = and_or3(v, cls == 0 ? 0x00070007u : cls == 1 ? 0x00380038u : 0x01C001C0u, base);
         }
-        r[i] = cls == 0 ? pk_add(pair, 0xE404E404u) : cls == 1 ? pk_fma(pair, 0x30003000u, 0xD820D820u) : pk_fma(pair, 0x24002400u, 0xCD00CD00u);
+        if (QUARTER) r[i] = cls == 0 ? pk_fma(pair, 0x34003400u, 0xDC04DC04u) : cls == 1 ? pk_fma(pair, 0x28002800u, 0xD020D020u) : pk_fma(pair, 0x1C001C00u, 0xC500C500u);
+        else r[i] = cls == 0 ? pk_add(pair, 0xE404E404u) : cls == 1 ? pk_fma(pair, 0x30003000u, 0xD820D820u) : pk_fma(pair, 0x24002400u, 0xCD00CD00u);
     }
     return r;
 }
@@ -152,8 +155,9 @@ __global__ __launch_bounds__(kThreads) void fewrow_kernel(Args a)
     constexpr int SG = FMT == F_Q4G64 ? 64 : FMT == F_Q4G128 ? 128 : 32;
     constexpr int SW = 128 / SG;                          // words of scales per unit and row: 4, 2 or 1
     constexpr int kNt = Q3 ? 0 : 2;                       // non-temporal
-    // 3-bit weights at up to 16 rows are exact: a scale is split into its upper eight significant bits and the rest, both products
-    // with a code fit fp16, and the second goes through MFMAs of its own (scaled by 2^8, so that nothing is subnormal).  Below 16 rows
+    // 3-bit weights at up to 16 rows are exact for every finite scale: a scale is split into its upper eight significant bits and the
+    // rest, both products with a quarter of a code (at most 1, so that nothing leaves fp16) fit its eleven bits, and the second
+    // goes through MFMAs of its own (scaled by 2^8, which its largest value, 224 x 2^8, still bears).  Below 16 rows
     // the 3-bit matvec kernels, which multiply by the scale in fp32, served these calls; with one rounding per weight the appended V
     // of a 7B layer was 3.20e-4 off the 64-bit result instead of 2.95e-4 (the split costs 4 us of 62).  Elsewhere the products are
     // rounded once, as in the split-K kernel and the tiled GEMM.
@@ -331,7 +335,7 @@ __global__ __launch_bounds__(kThreads) void fewrow_kernel(Args a)
                         af = __builtin_bit_cast(half8_t, b.w[Q3 ? 0 : u % D][F16 ? s >> 1 : 0][s & 1]);
                     } else {
                         const uint32_t sc = s2[u % 4][(s >> 2) & 1];
-                        const u32x4_t codes = Q3 ? decode_q3(b.w3[Q3 ? u % D : 0][(s >> 2) & 1], s & 3) : decode_q4(b.w[Q3 ? 0 : u % D][0][(s >> 2) & 1][s & 3]);
+                        const u32x4_t codes = Q3 ? decode_q3<EXACT>(b.w3[Q3 ? u % D : 0][(s >> 2) & 1], s & 3) : decode_q4(b.w[Q3 ? 0 : u % D][0][(s >> 2) & 1][s & 3]);
                         if (EXACT) {
                             const uint32_t upper = sc & 0xFFF8FFF8u;
                             const half8_t low = scaled(codes, pk_mul(pk_add(sc, upper ^ 0x80008000u), 0x5C005C00u));
@@ -350,7 +354,7 @@ __global__ __launch_bounds__(kThreads) void fewrow_kernel(Args a)
             else load_unit(b, next, u + D - UW);
             __builtin_amdgcn_sched_barrier(0);            // keeps decodes of later units (and their registers) out of this one
         }
-        if (EXACT) acc[0] += rest * 0x1p-8f;
+        if (EXACT) acc[0] = (acc[0] + rest * 0x1p-8f) * 4.0f;
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) red[((at_batch * kWaves + wave) * NB + nb) * 64 + lane] = acc[nb];
     };

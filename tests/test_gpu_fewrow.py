@@ -164,3 +164,23 @@ def test_layer_on_unaligned_4bit_weights_runs_on_the_matvec_kernels(rx):
         finally:
             rx.check(rx.relax_set_option("layer_matvec_rows", 4))
         assert torch.equal(got, want), n
+
+
+@pytest.mark.parametrize("low,high", [(2.0 ** -24, 2.0 ** -14), (2.0 ** -14, 1.0), (1.0, 65504.0), (16384.0, 65504.0)])
+def test_3bit_scales_over_the_whole_fp16_range(rx, low, high):
+    """2 to 16 rows of 3-bit weights, scales from the smallest subnormal to the largest fp16 value: products are exact, so what is
+    left is the fp32 sum (k roundings at most) and the rounding of the result."""
+    m, k, g = 64, 512, _gen(11)
+    q = torch.randint(-2 ** 31, 2 ** 31 - 1, (m, 3 * k // 32), device="cuda", dtype=torch.int32, generator=g)
+    s = torch.exp(torch.empty(m, k // 32, device="cuda").uniform_(float(np.log(low)), float(np.log(high)), generator=g)).clamp(low, high).half()
+    w = rx.QMat(q, s, m, k, 32)
+    codes = torch.empty(m, k, dtype=torch.int8, device="cuda")
+    rx.check(rx.relax_unpack_q3_native(w, codes))
+    ref = codes.double() * s.double().repeat_interleave(32, 1)
+    for n in (2, 3, 15, 16):
+        x = (torch.randn(n, k, device="cuda", generator=g) / min(1.0, 30 * high) if high < 1 else torch.randn(n, k, device="cuda", generator=g) / (16 * high)).half()
+        out = torch.empty(n, m, device="cuda", dtype=torch.float16)
+        rx.check(rx.relax_dequant_matmul_q3_native(x, w, out, n))
+        want, terms = x.double() @ ref.t(), x.double().abs() @ ref.abs().t()
+        bound = 2.0 ** -11 * want.abs() + 2.0 ** -25 + k * 2.0 ** -24 * terms           # 2^-25: half of the smallest fp16 step
+        assert bool(((out.double() - want).abs() <= bound).all()), n
