@@ -29,6 +29,18 @@ extern "C" {
  * Unknown name: RELAX_ERR_UNSUPPORTED.                                                                           */
 relax_status relax_set_option(const char *name, int32_t value);
 
+/* Which kernel a plain matmul of these sizes takes, for 16-byte aligned pointers: relax_dequant_matmul (format 4, group 32, with
+ * ws_bytes of workspace, 0: none), relax_dequant_matmul_q3_native (3) or relax_half_matmul (16).  Runs on the host alone; tests
+ * assert with it that a case reaches the kernel and the tile it is meant for.
+ * k_ranges: ranges the streaming kernel or the tiled GEMM cuts k into.  Tiled GEMM: tile of tile_rows weight rows x tile_cols
+ * rows of x; wide_rows > 0: the first wide_rows weight rows go through a launch of 256 x 256 tiles of their own (4-bit only).
+ * Errors: NULL, SHAPE (n, m < 1, k not a positive multiple of 32), UNSUPPORTED (format).                            */
+enum { RELAX_KERNEL_MATVEC = 0, RELAX_KERNEL_STREAM = 1, RELAX_KERNEL_SPLIT_K = 2, RELAX_KERNEL_TILED = 3 };
+typedef struct {
+    int32_t kernel, k_ranges, tile_rows, tile_cols, wide_rows;
+} relax_matmul_plan;
+relax_status relax_plan_matmul(int32_t format, int32_t n, int32_t m, int32_t k, size_t ws_bytes, relax_matmul_plan *plan);
+
 /* Measurement aids for the roofline figures: what the device at hand reaches on a plain
  * streaming read and on a bare loop of fp16 matrix-core instructions (the published
  * peaks, 8 TB/s and 2.5 PFLOP/s, are upper bounds of these).  Time them with events.

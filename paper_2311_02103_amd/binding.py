@@ -73,11 +73,18 @@ class ModelC(C.Structure):
                 ("embedding", C.c_void_p), ("norm_final", C.c_void_p), ("lm_head", C.c_void_p)]
 
 
+class MatmulPlanC(C.Structure):
+    _fields_ = [("kernel", C.c_int32), ("k_ranges", C.c_int32), ("tile_rows", C.c_int32), ("tile_cols", C.c_int32), ("wide_rows", C.c_int32)]
+
+
+KERNEL_MATVEC, KERNEL_STREAM, KERNEL_SPLIT_K, KERNEL_TILED = range(4)
+
 _lib = None
 
 _SIGNATURES = {
     "relax_build_id": (C.c_char_p, []),
     "relax_set_option": (C.c_int32, [C.c_char_p, C.c_int32]),
+    "relax_plan_matmul": (C.c_int32, [C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.c_size_t, C.POINTER(MatmulPlanC)]),
     "relax_profile_alt_gate_up": (None, [C.c_void_p, C.c_void_p]),
     "relax_workspace_init": (C.c_int32, [C.POINTER(LayerDims), C.c_void_p, C.c_size_t, C.c_void_p]),
     "relax_workspace_error": (C.c_int32, [C.POINTER(LayerDims), C.c_void_p, C.POINTER(C.c_int32)]),
@@ -431,6 +438,13 @@ def relax_profile_step_events(start: Optional[int], stop: Optional[int], step: i
 
 def relax_set_option(name: str, value: int) -> int:
     return lib().relax_set_option(name.encode(), value)
+
+
+def relax_plan_matmul(fmt: str, n: int, m: int, k: int, ws_bytes: int = 0):
+    """(status, kernel, k_ranges, tile_rows, tile_cols, wide_rows) of a plain matmul; fmt "q4", "q3" or "f16".  Host only."""
+    p = MatmulPlanC()
+    rc = lib().relax_plan_matmul({"q4": 4, "q3": 3, "f16": 16}.get(fmt, 0), n, m, k, ws_bytes, C.byref(p))
+    return rc, p.kernel, p.k_ranges, p.tile_rows, p.tile_cols, p.wide_rows
 
 
 def relax_workspace_init(dims: Optional[LayerDims], ws: Ptr, ws_bytes: int, stream=None) -> int:

@@ -26,6 +26,34 @@ int stream_ranges(int wmode, const relax_qmat &w, const void *x, const void *out
     return fewrow_ranges(wmode, n, w.m, w.k, epi, folded, partial_floats);
 }
 
+// The kernel a plain matmul takes, and for the streaming few-row kernel its k ranges (Sec. 5.1: the dispatch follows the runtime value
+// of the symbolic n).
+struct Route {
+    int kernel;                      // RELAX_KERNEL_*
+    int ranges;
+};
+
+// 4-bit: matrix-vector kernel for one row, streaming or split-K MFMA kernel for a few (when the caller brought the workspace for the
+// partial tiles), tiled MFMA GEMM otherwise
+Route q4_route(const uint16_t *x, const relax_qmat &w, const uint16_t *out, int n, const void *ws, size_t ws_bytes)
+{
+    const bool tiled_first = gemm_prefers_tiled(w.m, n) && gemm_mfma_eligible(w, x, EPI_F16);
+    const bool ws_fits = ws && aligned(ws, 16) && n <= kSkinnyMaxN && ws_bytes >= sizeof(float) * gemm_skinny_partial_floats(w.m, w.k, n);
+    const int kr = tiled_first || !ws_fits ? 0 : stream_ranges(W_Q4, w, x, out, n, EPI_F16, ws_bytes / sizeof(float));
+    if (kr > 0) return {RELAX_KERNEL_STREAM, kr};
+    if (!tiled_first && n >= kSkinnyMinN && n <= kSkinnyMaxN && ws_fits && gemm_skinny_eligible(w, x, n, EPI_F16)) return {RELAX_KERNEL_SPLIT_K, 0};
+    if (n >= kGemmMinN && gemm_mfma_eligible(w, x, EPI_F16)) return {RELAX_KERNEL_TILED, 0};
+    return {RELAX_KERNEL_MATVEC, 0};
+}
+
+// native 3-bit
+Route q3_route(const uint16_t *x, const relax_qmat &w, const uint16_t *out, int n)
+{
+    if (stream_ranges(W_Q3, w, x, out, n, EPI_F16, 0)) return {RELAX_KERNEL_STREAM, 1};
+    if (n >= kQ3GemmRows && gemm_q3_eligible(x, w, out)) return {RELAX_KERNEL_TILED, 0};
+    return {RELAX_KERNEL_MATVEC, 0};
+}
+
 // ---- Dynamic shape-aware memory planning (Sec. 4.3, Alg. 3) over the intermediates of one layer call ----------------------
 // The layer is a fixed sequence of destination-passing operations; every intermediate has a symbolic size in the rows n
 // of the call (a monomial c * n bytes) or an opaque expression of (n, L, B) (the workspaces lifted out of the attention
@@ -306,12 +334,12 @@ int device_cus()
 // (0.5 us per 64 columns, more when its tiles fill the device); wider passes also cost more when only one block's x rows fit
 // a CU.  Measured on 4096 x 4096: matvec up to 16 rows (33 against 36 us), GEMM from 24 (36 against 47); on 22016 x 4096:
 // matvec up to 4 rows (35 against 46 us), GEMM from 6 (44 against 62); on 4096 x 11008: GEMM from 16 (94 against 120).
-hipError_t half_matmul_enqueue(const uint16_t *x, const uint16_t *w, uint16_t *out, int n, int m, int k, hipStream_t st_)
+Route f16_route(const uint16_t *x, const uint16_t *w, const uint16_t *out, int n, int m, int k)
 {
     bool use_gemm;
     const int gemm_rows = g_opt_half_gemm_rows.load();
     if (gemm_rows == 0 && aligned(x, 16) && aligned(w, 16) && aligned(out, 8) && fewrow_ranges(W_F16, n, m, k, EPI_F16, false, 0))
-        return launch_fewrow_f16(x, w, n, m, k, EPI_F16, 1, out, nullptr, nullptr, nullptr, st_);
+        return {RELAX_KERNEL_STREAM, 1};
     if (gemm_rows > 0) {
         use_gemm = n >= gemm_rows;
     } else {
@@ -331,8 +359,16 @@ hipError_t half_matmul_enqueue(const uint16_t *x, const uint16_t *w, uint16_t *o
                                         (double)m * k * 2.0 / 4.3e6) + 4.0;
         use_gemm = n > 64 || gemm_us < mv_us;
     }
-    if (use_gemm && gemm_f16_eligible(x, w, out, m, k)) return launch_gemm_f16(x, w, n, m, k, out, st_);
-    return launch_lm_head(x, w, out, n, k, m, device_cus(), st_);
+    return {use_gemm && gemm_f16_eligible(x, w, out, m, k) ? RELAX_KERNEL_TILED : RELAX_KERNEL_MATVEC, 0};
+}
+
+hipError_t half_matmul_enqueue(const uint16_t *x, const uint16_t *w, uint16_t *out, int n, int m, int k, hipStream_t st_)
+{
+    switch (f16_route(x, w, out, n, m, k).kernel) {
+    case RELAX_KERNEL_STREAM: return launch_fewrow_f16(x, w, n, m, k, EPI_F16, 1, out, nullptr, nullptr, nullptr, st_);
+    case RELAX_KERNEL_TILED: return launch_gemm_f16(x, w, n, m, k, out, st_);
+    default: return launch_lm_head(x, w, out, n, k, m, device_cus(), st_);
+    }
 }
 
 // Scratch of relax_attention_static: the split-L partials of one call live in this file-scope device array instead of a
@@ -399,6 +435,20 @@ relax_status relax_set_option(const char *name, int32_t value)
         return RELAX_OK;
     }
     return RELAX_ERR_UNSUPPORTED;
+}
+
+relax_status relax_plan_matmul(int32_t format, int32_t n, int32_t m, int32_t k, size_t ws_bytes, relax_matmul_plan *plan)
+{
+    if (!plan) return RELAX_ERR_NULL;
+    if (n < 1 || m < 1 || k < 32 || k % 32 != 0) return RELAX_ERR_SHAPE;
+    if (format != 3 && format != 4 && format != 16) return RELAX_ERR_UNSUPPORTED;
+    // the dispatch looks at nothing but the alignment of pointers
+    uint16_t *const p = reinterpret_cast<uint16_t *>(static_cast<uintptr_t>(256));
+    const relax_qmat w = {reinterpret_cast<const uint32_t *>(p), p, m, k, 32};
+    const Route r = format == 4 ? q4_route(p, w, p, n, ws_bytes ? p : nullptr, ws_bytes) : format == 3 ? q3_route(p, w, p, n) : f16_route(p, p, p, n, m, k);
+    *plan = {r.kernel, r.ranges, 0, 0, 0};
+    if (r.kernel == RELAX_KERNEL_TILED) gemm_tile_plan(m, k, n, EPI_F16, format == 4 ? ws_bytes / sizeof(float) : 0, plan);
+    return RELAX_OK;
 }
 
 relax_status relax_workspace_init(const relax_layer_dims *dims, void *ws, size_t ws_bytes, relax_stream stream)
@@ -519,22 +569,16 @@ relax_status relax_dequant_matmul(const uint16_t *x, const relax_qmat *w, uint16
     relax_status rc = check_qmat(w);
     if (rc != RELAX_OK) return rc;
     if (n < 1) return RELAX_ERR_SHAPE;
-    // runtime dispatch on the symbolic n (Sec. 5.1): matrix-vector kernel for one row, split-K MFMA kernel for a few
-    // (when the caller brought the workspace for its partial tiles), tiled MFMA GEMM otherwise
-    const bool tiled_first = gemm_prefers_tiled(w->m, n) && gemm_mfma_eligible(*w, x, EPI_F16);
-    const bool ws_fits = ws && aligned(ws, 16) && n <= kSkinnyMaxN && ws_bytes >= sizeof(float) * gemm_skinny_partial_floats(w->m, w->k, n);
-    const int kr = tiled_first || !ws_fits ? 0 : stream_ranges(W_Q4, *w, x, out, n, EPI_F16, ws_bytes / sizeof(float));
-    if (kr > 0)
-        return hip_status(launch_fewrow_q4(x, *w, n, EPI_F16, kr, out, nullptr, nullptr, static_cast<float *>(ws), static_cast<hipStream_t>(stream)));
-    if (!tiled_first && n >= kSkinnyMinN && n <= kSkinnyMaxN && ws_fits && gemm_skinny_eligible(*w, x, n, EPI_F16))
-        return hip_status(launch_gemm_skinny(x, *w, n, EPI_F16, out, nullptr, nullptr, static_cast<float *>(ws),
-                                             static_cast<hipStream_t>(stream)));
-    if (n >= kGemmMinN && gemm_mfma_eligible(*w, x, EPI_F16))
-        return hip_status(launch_gemm_mfma(x, *w, n, EPI_F16, out, nullptr, nullptr, static_cast<hipStream_t>(stream), static_cast<float *>(ws),
-                                           ws ? ws_bytes / sizeof(float) : 0));
+    hipStream_t st_ = static_cast<hipStream_t>(stream);
+    float *part = static_cast<float *>(ws);
+    const Route r = q4_route(x, *w, out, n, ws, ws_bytes);
+    if (r.kernel == RELAX_KERNEL_STREAM) return hip_status(launch_fewrow_q4(x, *w, n, EPI_F16, r.ranges, out, nullptr, nullptr, part, st_));
+    if (r.kernel == RELAX_KERNEL_SPLIT_K) return hip_status(launch_gemm_skinny(x, *w, n, EPI_F16, out, nullptr, nullptr, part, st_));
+    if (r.kernel == RELAX_KERNEL_TILED)
+        return hip_status(launch_gemm_mfma(x, *w, n, EPI_F16, out, nullptr, nullptr, st_, part, ws ? ws_bytes / sizeof(float) : 0));
     GemvArgs a = {};
     a.x = x, a.q = w->q, a.s = w->s, a.m = w->m, a.k = w->k, a.n = n, a.out_f16 = out, a.gshift = gshift_of(w->group);
-    return hip_status(launch_gemv(a, X_F16, EPI_F16, static_cast<hipStream_t>(stream)));
+    return hip_status(launch_gemv(a, X_F16, EPI_F16, st_));
 }
 
 relax_status relax_rmsnorm_rope(const uint16_t *x, const uint16_t *w, uint16_t *y, int32_t n, int32_t H, float eps, uint16_t *qkv,
@@ -892,9 +936,11 @@ relax_status check_q3mat(const relax_qmat &w, int32_t m, int32_t k)
 }
 hipError_t q3_matmul(const uint16_t *x, const relax_qmat &w, int32_t n, uint16_t *out, hipStream_t st_)
 {
-    if (stream_ranges(W_Q3, w, x, out, n, EPI_F16, 0)) return launch_fewrow_q3(x, w, n, EPI_F16, 1, out, nullptr, nullptr, nullptr, st_);
-    if (n >= kQ3GemmRows && gemm_q3_eligible(x, w, out)) return launch_gemm_q3(x, w, n, out, st_);
-    return launch_gemv_q3_native(x, w, n, out, st_);
+    switch (q3_route(x, w, out, n).kernel) {
+    case RELAX_KERNEL_STREAM: return launch_fewrow_q3(x, w, n, EPI_F16, 1, out, nullptr, nullptr, nullptr, st_);
+    case RELAX_KERNEL_TILED: return launch_gemm_q3(x, w, n, out, st_);
+    default: return launch_gemv_q3_native(x, w, n, out, st_);
+    }
 }
 
 // The launches of a layer whose matmuls are not those of the 4-bit path (3-bit and fp16 weights), from two rows on.  Matrices in the
@@ -1303,12 +1349,8 @@ relax_status relax_dequant_matmul_q3_native(const uint16_t *x, const relax_qmat 
         return RELAX_ERR_SHAPE;
     // From kQ3GemmRows rows on the matrix is read once by the tiled MFMA GEMM (decode on the way into LDS); below that, or
     // for a shape the GEMM does not take, it is streamed once per pass of up to four rows of x.
-    if (stream_ranges(W_Q3, *w, x, out, n, EPI_F16, 0))
-        return hip_status(launch_fewrow_q3(x, *w, n, EPI_F16, 1, out, nullptr, nullptr, nullptr, static_cast<hipStream_t>(stream)));
-    if (n >= kQ3GemmRows && gemm_q3_eligible(x, *w, out))
-        return hip_status(launch_gemm_q3(x, *w, n, out, static_cast<hipStream_t>(stream)));
-    if (!gemv_q3_supported(w->m, w->k)) return RELAX_ERR_UNSUPPORTED;
-    return hip_status(launch_gemv_q3_native(x, *w, n, out, static_cast<hipStream_t>(stream)));
+    if (q3_route(x, *w, out, n).kernel == RELAX_KERNEL_MATVEC && !gemv_q3_supported(w->m, w->k)) return RELAX_ERR_UNSUPPORTED;
+    return hip_status(q3_matmul(x, *w, n, out, static_cast<hipStream_t>(stream)));
 }
 
 }  // extern "C"

@@ -605,6 +605,12 @@ size_t gemm_splitk_partial_floats(int m, int k, int n, int epi)
     return worst;
 }
 
+void gemm_tile_plan(int m, int k, int n, int epi, size_t partial_floats, relax_matmul_plan *plan)
+{
+    const TilePlan p = tile_plan(m, k, n, epi, partial_floats);
+    plan->k_ranges = p.splits, plan->tile_rows = 64 * p.mf, plan->tile_cols = 64 * p.nf, plan->wide_rows = p.m_big;
+}
+
 // k splits the launch would make for n rows with this much workspace (1: one pass over k, no finishing pass)
 int gemm_mfma_splits(const relax_qmat &w, int n, int epi, const float *partial, size_t partial_floats)
 {
