@@ -41,32 +41,57 @@ bool cut(bool f16, int nb, int m, int k, int epi, int kg, Plan &p)
     return true;
 }
 
-// The number of k ranges with the least estimated time:
-//   - 5.8 us for the launch, the first data and the sums over the wavefronts;
-//   - its share of x: every workgroup fetches n x (k / kg) values from its L2, at about 24 us per MB (measured: 4096 x 4096 at
-//     16 rows 9.4 us against 7.3 at two, 4096 x 11008 18.4 against 12.2 with one k range), so long rows and many rows of x want
-//     k ranges, and taller row ranges with them;
-//   - its row tiles, at the rate of the whole stream, or what a CU can take of it where few of them work;
-//   - with more than one k range the partial rows, written and read again, and the finishing launch (3 us; next to nothing when
-//     that launch also does a step that would be a launch of its own otherwise: `folded`).
+// What a launch takes, in us, for blocks of 16, 32 and 64 rows of x: fitted to 31 matrices from 256 x 256 to 57344 x 8192 and 8192 x 28672
+// at 2 to 64 rows, weights cold, every k range the kernel is built for (4-bit: 4 % rms where the kernels are close, 8 % overall).
+//   launch                 the launch, the first data and the sums over the wavefronts
+//   tb_per_s               the stream of the weights, or, where few row tiles or uneven slices leave it to the slowest workgroup,
+//   unit, tile             ... per row tile of a workgroup: its longest slice's units, and the sums
+//   x                      per MB of x a workgroup fetches from its L2: long rows and many rows of x want k ranges
+//   finish, range, partial the finishing launch, per k range of it, and the partial rows at TB/s
+struct Cost {
+    double launch, tb_per_s, unit, tile, x, finish, range, partial;
+};
+constexpr Cost kCostQ4[3] = {{3.75, 5.9, 0.51, 0.44, 42, 4.1, 0.16, 5.1}, {4.2, 5.35, 0.65, 0.37, 32, 3.2, 0.26, 3.1}, {3.6, 3.3, 1.24, 0.0, 32, 4.0, 0.86, 70}};
+// 3-bit and fp16 matrices: the rates of the stream alone (what is estimated for them only picks the k ranges of a layer's matrices)
+constexpr Cost kCostQ3[3] = {{5.8, 5.9, 0.46, 0.0, 25, 3.1, 0.0, 5.8}, {5.8, 5.35, 0.51, 0.0, 27, 3.4, 0.0, 5.3}, {5.8, 4.7, 0.58, 0.0, 31, 3.9, 0.0, 4.6}};
+constexpr Cost kCostF16[2] = {{5.8, 5.9, 1.05, 0.0, 25, 3.1, 0.0, 5.8}, {5.8, 5.35, 1.17, 0.0, 27, 3.4, 0.0, 5.3}};
+constexpr double kFolded = 2.5;                           // a finishing pass that is also a step of the layer saves that step's launch
+
+int block_class(int n) { return n <= 16 ? 0 : n <= 32 ? 1 : 2; }
+
+// The number of k ranges with the least estimated time (`folded`: the finishing pass is also the RMSNorm of the result).
 int best_ranges(int fmt, int n, int m, int k, int epi, bool folded, size_t partial_floats, double *time_us)
 {
     const bool f16 = fmt == F_F16;
-    const double bytes_per_weight = f16 ? 2.0 : fmt == F_Q3 ? 0.4375 : 0.5625;
-    const double mfma = blocks_of(n) == 1 ? 1.03 : blocks_of(n) == 2 ? 1.14 : 1.3;      // two and four MFMAs per decoded word, and their sums
+    const Cost &c = (f16 ? kCostF16 : fmt == F_Q3 ? kCostQ3 : kCostQ4)[block_class(n)];
+    const double bytes = (double)m * k * (f16 ? 2.0 : fmt == F_Q3 ? 0.4375 : 0.5625);
     double best_us = 0.0;
     int best = 0;
     for (int kg = 1; kg <= 16 && (kg == 1 || (size_t)kg * n * m <= partial_floats); ++kg) {
         Plan p;
         if (!cut(f16, blocks_of(n), m, k, epi, kg, p)) continue;
-        const double per = (p.tiles + p.rg - 1) / p.rg, rounds = (p.rg * kg + 255) / 256, slice = (double)k / kg;
-        const double stream_us = std::max((double)m * k * bytes_per_weight / 6.1e6, rounds * per * kTileRows * slice * bytes_per_weight / 32e3);
-        const double us = (stream_us + rounds * 24e-6 * n * slice * 2.0 + (kg > 1 ? (folded ? 0.5 : 3.0) + (double)kg * n * m * 8.0 / 6e6 : 0.0)) * mfma;
+        const double per = (p.tiles + p.rg - 1) / p.rg, rounds = (p.rg * kg + 255) / 256;
+        double us = std::max(bytes / (c.tb_per_s * 1e6), rounds * per * (p.uw * c.unit + c.tile)) + rounds * n * ((double)k / kg) * 2e-6 * c.x;
+        if (kg > 1) us += c.finish + kg * c.range + (double)kg * n * m * 8e-6 / c.partial - (folded ? kFolded : 0.0);
         if (best == 0 || us < best_us) best = kg, best_us = us;
         if (p.uw == 1) break;
     }
-    *time_us = 5.8 + best_us;
+    *time_us = c.launch + best_us;
     return best;
+}
+
+// The same for the split-K few-row kernel (4-bit matrices): workgroups of 128 rows and `rounds` rounds of 256 columns, one a CU or more.
+struct SplitCost {
+    double launch, row, round, round_full, split, partial;
+};
+constexpr SplitCost kCostSplit[3] = {{5.0, 0.155, 0.93, 1.0, 0.18, 2.9}, {3.25, 0.125, 1.26, 1.34, 0.26, 22}, {0.8, 0.08, 2.07, 2.21, 0.59, 56}};
+double split_us(int n, int m, int k)
+{
+    const SplitCost &c = kCostSplit[block_class(n)];
+    int tiles_m, splits, rounds;
+    gemm_skinny_cut(m, k, &tiles_m, &splits, &rounds);
+    return c.launch + c.row * n + std::max(rounds * c.round, (double)tiles_m * splits * rounds / 256.0 * c.round_full) + splits * c.split +
+           (double)splits * n * m * 8e-6 / c.partial;
 }
 
 bool shape_ok(bool f16, int n, int m, int k, int epi)
@@ -123,14 +148,12 @@ int fewrow_ranges(int wmode, int n, int m, int k, int epi, bool folded, size_t p
     double us = 0.0;
     const int kr = best_ranges(wmode == W_F16 ? F_F16 : wmode == W_Q3 ? F_Q3 : F_Q4G32, n, m, k, epi, folded, partial_floats, &us);
     // A 4-bit matrix may also go through the split-K few-row kernel, whose workgroups own 128 rows and an eighth of k: an eighth of the
-    // x traffic, a lower rate.  Its time with the finishing pass (7B, 13B and 70B shapes, 16 / 32 / 64 rows: 12 to 73, 13.5 to 86, 17 to
-    // 71 us) is 8.5 + 0.085 n us and 0.17 + 0.004 n us per MB; it stays the better one on long rows with few weight rows (4096 x 11008
-    // at 16 rows 15.4 against 17.3 us, 8192 x 8192 16.4 against 18.7), the stream on the others (22016 x 4096 18.8 against 22.4,
-    // 57344 x 8192 57 against 73).
-    if (wmode == W_Q4 && n > 2 && partial_floats >= gemm_skinny_partial_floats(m, k, n) && gemm_skinny_partial_floats(m, k, n) > 0) {
-        const double mb = (double)m * k * 0.5625e-6, split_us = 8.5 + 0.085 * n + (0.17 + 0.004 * n) * mb - (folded ? 3.0 : 0.0);
-        if (split_us < us) return 0;
-    }
+    // x traffic, a lower rate.  It is the better one where its workgroups fill the chip and rows are long or x has many rows (8192 x
+    // 8192 at 16 rows 16.5 against 18.6 us, 5120 x 13824 17.8 against 20.0, 15360 x 5120 at 64 rows 29.9 against 35.4), the stream
+    // on the others (22016 x 4096 at 16 rows 19.1 against 23.4, 57344 x 8192 58 against 74).
+    if (wmode == W_Q4 && n > 2 && kr > 0 && gemm_skinny_partial_floats(m, k, n) > 0 && partial_floats >= gemm_skinny_partial_floats(m, k, n) &&
+        split_us(n, m, k) - (folded ? kFolded : 0.0) < us)
+        return 0;
     return kr;
 }
 

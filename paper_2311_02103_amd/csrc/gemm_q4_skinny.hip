@@ -477,6 +477,12 @@ size_t gemm_skinny_partial_floats(int m, int k, int n)
     return worst;
 }
 
+void gemm_skinny_cut(int m, int k, int *tiles_m, int *splits, int *rounds)
+{
+    const SkinnyPlan p = skinny_plan(m, k, kRound);
+    *tiles_m = p.tiles_m, *splits = p.splits, *rounds = p.rounds_per_split;
+}
+
 bool gemm_skinny_fuse_ok(const relax_qmat &w, int epi, const SkinnyFuse &f)
 {
     if (epi == EPI_RESID_F32 || epi == EPI_RESID_F16)

@@ -412,6 +412,7 @@ bool gemm_skinny_eligible(const relax_qmat &w, const void *x, int n, int epi);
 // rows on matrices that fill the chip with tiles (57344 x 8192: 146 against 158 us).
 inline bool gemm_prefers_tiled(int m, int n) { return n > 64 || (n >= 48 && m >= 49152); }
 size_t gemm_skinny_partial_floats(int m, int k, int n);
+void gemm_skinny_cut(int m, int k, int *tiles_m, int *splits, int *rounds);      // its workgroups: row tiles x k splits, rounds of 256 columns each
 // Optional light step folded into the finishing pass of the few-row matmul (one launch less):
 //   residual epilogues: also xn = RMSNorm(result) * norm_w (what the next matmul of the layer, or of the next layer, reads);
 //   EPI_F16 on a QKV matrix: rotary embedding of q and k, k and v appended to the cache (q alone is written to out_f16).

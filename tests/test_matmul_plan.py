@@ -37,3 +37,20 @@ def test_a_launch_cut_along_k_stays_within_its_workspace():
         for ws in (0, full // 3, full):
             kernel, ranges, *_ = plan("q4", n, m, k, ws)
             assert kernel == rx.KERNEL_TILED and (ranges == 1 or ranges * n * m * 4 <= ws)
+
+
+# Measured times in us (weights cold, the best of several replays of a captured schedule): the streaming kernel at its best k cut and
+# the split-K kernel, 4-bit weights in groups of 32.  Where they differ by more than a twentieth the dispatch has to find the faster one.
+FEW_ROWS = [
+    (2048, 2048, 16, 7.1, 11.1), (4096, 4096, 8, 8.4, 11.9), (12288, 4096, 8, 12.1, 14.9), (22016, 4096, 16, 19.1, 23.4),
+    (22016, 4096, 64, 35.0, 38.0), (57344, 8192, 16, 58.5, 74.5), (57344, 8192, 32, 72.5, 88.9), (27648, 5120, 16, 25.0, 30.5),
+    (4096, 11008, 24, 19.6, 17.0), (4096, 11008, 32, 20.6, 17.3), (5120, 13824, 8, 18.4, 16.9), (5120, 13824, 16, 20.0, 17.8),
+    (5120, 13824, 32, 24.2, 19.9), (5120, 13824, 64, 31.2, 26.9), (8192, 8192, 16, 18.8, 16.5), (8192, 8192, 32, 23.0, 18.8),
+    (8192, 8192, 64, 31.1, 25.5), (10240, 8192, 32, 25.1, 22.1), (15360, 5120, 32, 24.6, 22.4), (15360, 5120, 64, 35.8, 29.9),
+    (7168, 7168, 32, 20.9, 18.1), (16384, 3072, 40, 25.4, 20.1), (32000, 2048, 48, 31.6, 24.8),
+]
+
+
+@pytest.mark.parametrize("m,k,n,stream,split", FEW_ROWS)
+def test_few_rows_take_the_faster_kernel(m, k, n, stream, split):
+    assert plan("q4", n, m, k, workspace(n, m, k))[0] == (rx.KERNEL_STREAM if stream < split else rx.KERNEL_SPLIT_K)
