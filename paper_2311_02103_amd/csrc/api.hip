@@ -49,7 +49,7 @@ Route q4_route(const uint16_t *x, const relax_qmat &w, const uint16_t *out, int 
 // native 3-bit
 Route q3_route(const uint16_t *x, const relax_qmat &w, const uint16_t *out, int n)
 {
-    if (stream_ranges(W_Q3, w, x, out, n, EPI_F16, 0)) return {RELAX_KERNEL_STREAM, 1};
+    if (stream_ranges(W_Q3, w, x, out, n, EPI_F16, 0) && fewrow_pays_alone(W_Q3, n, w.m, w.k)) return {RELAX_KERNEL_STREAM, 1};
     if (n >= kQ3GemmRows && gemm_q3_eligible(x, w, out)) return {RELAX_KERNEL_TILED, 0};
     return {RELAX_KERNEL_MATVEC, 0};
 }
@@ -327,7 +327,8 @@ int device_cus()
 }
 
 // out[n,m] = x[n,k] . w[m,k]^T on plain fp16 weights (relax_half_matmul, and the LM head of relax_model_step).
-// 2 .. 32 rows take the streaming few-row kernel where one k range holds a row (22016 x 4096 at 8 rows 35 us, 4096 x 4096 at 16 rows 12).
+// 2 .. 32 rows take the streaming few-row kernel where one k range holds a row (22016 x 4096 at 8 rows 35 us, 4096 x 4096 at 16 rows 12)
+// and one pass of the matvec kernel is not faster (fewrow_pays_alone).
 // One row, longer rows and more rows: the same runtime dispatch on the symbolic n as the int4 path (Sec. 5.1), matvec passes for a few
 // rows, tiled MFMA GEMM from there on.  Where "there" is depends on the matrix: a pass streams the whole matrix (5.5 TB/s; passes of 8 rows are
 // bound by their dot products and take twice as long), a GEMM launch with few rows costs its k loop whatever n is
@@ -338,7 +339,8 @@ Route f16_route(const uint16_t *x, const uint16_t *w, const uint16_t *out, int n
 {
     bool use_gemm;
     const int gemm_rows = g_opt_half_gemm_rows.load();
-    if (gemm_rows == 0 && aligned(x, 16) && aligned(w, 16) && aligned(out, 8) && fewrow_ranges(W_F16, n, m, k, EPI_F16, false, 0))
+    if (gemm_rows == 0 && aligned(x, 16) && aligned(w, 16) && aligned(out, 8) && fewrow_ranges(W_F16, n, m, k, EPI_F16, false, 0) &&
+        fewrow_pays_alone(W_F16, n, m, k))
         return {RELAX_KERNEL_STREAM, 1};
     if (gemm_rows > 0) {
         use_gemm = n >= gemm_rows;

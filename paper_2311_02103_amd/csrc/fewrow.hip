@@ -151,10 +151,39 @@ int fewrow_ranges(int wmode, int n, int m, int k, int epi, bool folded, size_t p
     // x traffic, a lower rate.  It is the better one where its workgroups fill the chip and rows are long or x has many rows (8192 x
     // 8192 at 16 rows 16.5 against 18.6 us, 5120 x 13824 17.8 against 20.0, 15360 x 5120 at 64 rows 29.9 against 35.4), the stream
     // on the others (22016 x 4096 at 16 rows 19.1 against 23.4, 57344 x 8192 58 against 74).
-    if (wmode == W_Q4 && n > 2 && kr > 0 && gemm_skinny_partial_floats(m, k, n) > 0 && partial_floats >= gemm_skinny_partial_floats(m, k, n) &&
+    if (wmode == W_Q4 && kr > 0 && gemm_skinny_partial_floats(m, k, n) > 0 && partial_floats >= gemm_skinny_partial_floats(m, k, n) &&
         split_us(n, m, k) - (folded ? kFolded : 0.0) < us)
         return 0;
     return kr;
+}
+
+// A matmul on its own (no epilogue, no workspace) on 3-bit or fp16 weights: whether the streaming kernel is at least as fast as the
+// kernels that take the call otherwise.  What those cost at few rows is passes over the matrix, so they are ahead where one pass
+// serves all rows, and on matrices so small that the launch is what counts (stream against the other kernel, us):
+//   3-bit  2 rows of up to 8192 columns are one pass: 22016 x 4096 19.2 / 14.0, 8192 x 8192 16.5 / 12.1, 57344 x 8192 59 / 52; 12288
+//          columns take two: 4096 x 11008 13.3 / 14.6.  3 and 4 rows of up to 2048 columns: 5632 x 2048 7.7 / 6.7; 4096 x 4096 8.0 / 10.2.
+//          Up to 1024 x 1024 at 8 rows 5.2 / 4.4, 256 x 768 at 15 5.2 / 4.0, 1408 x 256 at 5 4.7 / 5.3.
+//          From 17 rows on the other kernel is the tiled GEMM: 256 columns at 32 rows 5.7 / 5.3, at 64 7.1 / 5.7; 768 columns 6.3 / 9.1;
+//          from 33 rows on it is ahead on tall matrices (32000 x 2048 28.8 / 24.1, 5632 x 2048 12.4 / 19.8).
+//   fp16   2, 4 and 8 rows are one pass of the matvec kernel.  2 rows up to 190 MB: 8192 x 8192 32.6 / 28.7, 22016 x 4096 35.6 / 34.1;
+//          28672 x 4096 41.5 / 43.3.  4 rows up to 64 MB, and on very long or very short rows: 5120 x 5120 17.2 / 15.7, 10240 x 8192
+//          37.0 / 35.2, 32000 x 2048 28.2 / 26.8; 12288 x 4096 20.5 / 21.1.  8 rows up to 4 MB: 1024 x 1024 5.9 / 4.8; 2048 x 2048 a tie.
+bool fewrow_pays_alone(int wmode, int n, int m, int k)
+{
+    if (wmode == W_Q3) {
+        if (n == 2) return k > 8192;
+        if (n <= 4) return k > 2048;
+        if (n <= 8) return m > 1024 || k > 1024;
+        if (n <= 15) return m > 256 || k > 1024;
+        return n == 16 || (k > 256 && (n <= 32 || m <= 16384));
+    }
+    if (wmode == W_F16) {
+        const double mb = (double)m * k * 2e-6;
+        if (n == 2) return mb > 190.0;
+        if (n == 4) return mb > 64.0 && k > 2048 && k < 8192;
+        if (n == 8) return mb > 4.0;
+    }
+    return true;
 }
 
 bool fewrow_fuse_ok(const relax_layer_dims &dm, const relax_kv_cache &cache)

@@ -436,6 +436,7 @@ hipError_t launch_gemm_skinny(const uint16_t *x, const relax_qmat &w, int n, int
 // (the RMSNorm of the result), so cutting along k costs next to nothing.
 constexpr int kFewRowMin = 2, kFewRowMax = 64;
 int fewrow_ranges(int wmode, int n, int m, int k, int epi, bool folded, size_t partial_floats);
+bool fewrow_pays_alone(int wmode, int n, int m, int k);      // 3-bit, fp16: as fast as the other kernels without an epilogue to save a launch
 bool fewrow_fuse_ok(const relax_layer_dims &dm, const relax_kv_cache &cache);
 hipError_t launch_fewrow_q4(const uint16_t *x, const relax_qmat &w, int n, int epi, int k_ranges, uint16_t *out_f16, float *out_f32, const void *resid, float *partial,
                             hipStream_t stream, const SkinnyFuse *fuse = nullptr);

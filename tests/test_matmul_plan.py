@@ -47,10 +47,28 @@ FEW_ROWS = [
     (4096, 11008, 24, 19.6, 17.0), (4096, 11008, 32, 20.6, 17.3), (5120, 13824, 8, 18.4, 16.9), (5120, 13824, 16, 20.0, 17.8),
     (5120, 13824, 32, 24.2, 19.9), (5120, 13824, 64, 31.2, 26.9), (8192, 8192, 16, 18.8, 16.5), (8192, 8192, 32, 23.0, 18.8),
     (8192, 8192, 64, 31.1, 25.5), (10240, 8192, 32, 25.1, 22.1), (15360, 5120, 32, 24.6, 22.4), (15360, 5120, 64, 35.8, 29.9),
-    (7168, 7168, 32, 20.9, 18.1), (16384, 3072, 40, 25.4, 20.1), (32000, 2048, 48, 31.6, 24.8),
+    (5120, 13824, 2, 17.6, 15.9), (7168, 7168, 32, 20.9, 18.1), (16384, 3072, 40, 25.4, 20.1), (32000, 2048, 48, 31.6, 24.8),
 ]
 
 
 @pytest.mark.parametrize("m,k,n,stream,split", FEW_ROWS)
 def test_few_rows_take_the_faster_kernel(m, k, n, stream, split):
     assert plan("q4", n, m, k, workspace(n, m, k))[0] == (rx.KERNEL_STREAM if stream < split else rx.KERNEL_SPLIT_K)
+
+
+# The same for the calls without a workspace or an epilogue: the streaming kernel, and the matvec kernel or (from 16 rows of 3-bit
+# weights on) the tiled GEMM that takes the call otherwise.
+ALONE = [
+    ("q3", 22016, 4096, 2, 19.2, 14.0), ("q3", 8192, 8192, 2, 16.5, 12.1), ("q3", 4096, 11008, 2, 13.3, 14.6), ("q3", 5632, 2048, 4, 7.7, 6.7),
+    ("q3", 4096, 4096, 4, 8.0, 10.2), ("q3", 1024, 1024, 8, 5.2, 4.4), ("q3", 256, 768, 15, 5.2, 4.0), ("q3", 1024, 1024, 15, 5.4, 5.8),
+    ("q3", 22016, 4096, 8, 19.6, 32.1), ("q3", 768, 256, 32, 5.7, 5.3), ("q3", 256, 768, 32, 6.3, 9.1), ("q3", 768, 256, 64, 7.2, 5.8),
+    ("q3", 32000, 2048, 40, 28.8, 24.1), ("q3", 5632, 2048, 40, 12.4, 19.8),
+    ("f16", 8192, 8192, 2, 32.6, 28.7), ("f16", 22016, 4096, 3, 34.8, 54.0), ("f16", 28672, 4096, 2, 41.5, 43.3), ("f16", 5120, 5120, 4, 17.2, 15.7),
+    ("f16", 10240, 8192, 4, 37.0, 35.2), ("f16", 12288, 4096, 8, 20.5, 44.0), ("f16", 1024, 1024, 8, 5.9, 4.8), ("f16", 4096, 4096, 8, 11.4, 16.1),
+    ("f16", 4096, 4096, 32, 15.5, 42.6),
+]
+
+
+@pytest.mark.parametrize("fmt,m,k,n,stream,other", ALONE)
+def test_calls_without_a_workspace_take_the_faster_kernel(fmt, m, k, n, stream, other):
+    assert (plan(fmt, n, m, k)[0] == rx.KERNEL_STREAM) == (stream < other)
