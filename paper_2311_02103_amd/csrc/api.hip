@@ -449,7 +449,7 @@ relax_status relax_plan_matmul(int32_t format, int32_t n, int32_t m, int32_t k, 
     const relax_qmat w = {reinterpret_cast<const uint32_t *>(p), p, m, k, 32};
     const Route r = format == 4 ? q4_route(p, w, p, n, ws_bytes ? p : nullptr, ws_bytes) : format == 3 ? q3_route(p, w, p, n) : f16_route(p, p, p, n, m, k);
     *plan = {r.kernel, r.ranges, 0, 0, 0};
-    if (r.kernel == RELAX_KERNEL_TILED) gemm_tile_plan(m, k, n, EPI_F16, format == 4 ? ws_bytes / sizeof(float) : 0, plan);
+    if (r.kernel == RELAX_KERNEL_TILED) gemm_tile_plan(format == 16 ? W_F16 : format == 3 ? W_Q3 : W_Q4, m, k, n, EPI_F16, format == 4 ? ws_bytes / sizeof(float) : 0, plan);
     return RELAX_OK;
 }
 
@@ -1093,7 +1093,7 @@ relax_status relax_decoder_layer_q3(const relax_layer_dims *dims, const relax_la
     auto ranges = [&](int i, const void *xin, const void *o, int epi, size_t floats, bool folded) {
         const int kr = stream_ranges(W_Q3, *mats[i], xin, o, n, epi, floats, folded);
         if (kr > 0 || n < kQ3GemmRows || !gemm_q3_eligible(xin, *mats[i], o)) return kr;
-        const int splits = gemm_flat_splits(n, mats[i]->m, mats[i]->k, floats);
+        const int splits = gemm_flat_splits(W_Q3, n, mats[i]->m, mats[i]->k, floats);
         return splits > 1 ? -splits : 0;
     };
     auto streamed = [&](int i, const uint16_t *xin, int epi, int kr, uint16_t *o16, float *o32, const void *resid, float *part, size_t floats, const SkinnyFuse *f) {
@@ -1189,7 +1189,7 @@ relax_status relax_decoder_layer_f16(const relax_layer_dims *dims, const relax_l
         if (g_opt_half_gemm_rows.load() != 0) return 0;
         const int kr = fewrow_ranges(W_F16, n, ms[i], ks[i], epi, folded, floats);
         if (kr > 0 || n < kGemmMinN || !gemm_f16_eligible(xin, mats[i], o, ms[i], ks[i])) return kr;
-        const int splits = gemm_flat_splits(n, ms[i], ks[i], floats);
+        const int splits = gemm_flat_splits(W_F16, n, ms[i], ks[i], floats);
         return splits > 1 ? -splits : 0;
     };
     auto streamed = [&](int i, const uint16_t *xin, int epi, int kr, uint16_t *o16, float *o32, const void *resid, float *part, size_t floats, const SkinnyFuse *f) {

@@ -513,12 +513,13 @@ bool gemm_mfma_eligible(const relax_qmat &w, const void *x, int epi)
 // Tile and cut of a launch: the least estimated time over the tiles (weight rows x x-rows) and over k splits, of which there
 // may be up to kSplitKMax of at least 8 k blocks each for up to kSplitKMaxN rows; the fp32 partial tiles of a split launch go to
 // the caller's workspace (it has to hold them) and the finishing pass of the few-row kernel adds them in order and applies the
-// epilogue.  A workgroup has a CU to itself, so the time is rounds of 256 workgroups x k blocks x what a tile takes per k block:
-//   256 x 256 (eight wavefronts) 2.02 us (22016 x 4096 at n = 2048), 256 x 192 1.6; 128 x 256 1.25 (12288 x 4096), 128 x 192 1.0,
-//   128 x 128 0.83 (8192 x 28672 at n = 511), 128 x 64 0.6
-// and, with splits, the finishing launch: 3 us and the partial rows twice over at 5 TB/s.  Wide tiles with two splits beat narrow
-// ones that fill the chip by themselves (8192 x 28672 at n = 511: two splits of 128 x 256 against 256 tiles of 128 x 128),
-// and 192-wide tiles waste less on 129 to 384 rows.
+// epilogue: 3 us and the partial rows twice over at 5 TB/s.
+// A k block of a wave of 256 workgroups takes longer the more of them there are (clock and fabric), and the two small tiles fit a
+// CU twice, so a launch of 257 to 512 of them is still one round.  Fitted to 14 matrices from 2048 x 2048 to 57344 x 8192 at 48 to
+// 2048 rows, every tile, and every split up to 512 rows, of 4-bit weights (3-bit ones agree) and of fp16 weights, whose wide tiles
+// run as four wavefronts: the choice is 0.5 % (4-bit), 0.0 % and 0.1 % off the best on average, 14 %, 3 % and 9 % at most.  With one
+// figure per tile, taken on a full chip, 256 x 192 tiles were preferred to 144 of 256 x 256 or 480 of 128 x 128 (12288 x 4096 at 600 rows
+// 99 against 85 us) and wide tiles on fp16 weights (27648 x 5120 at 2048 rows 882 against 667).
 namespace {
 struct TilePlan {
     int mf, nf, splits, kb_per_split;
@@ -526,12 +527,27 @@ struct TilePlan {
 };
 struct TileCost {
     int mf, nf;
-    double us_per_kb;
+    int per_cu;              // workgroups a CU holds
+    double few[2], full[2];  // us per k block of a wave with few and with 256 workgroups; [1]: of the second workgroup of every CU, both together
 };
-constexpr TileCost kTiles[] = {{4, 4, 2.02}, {4, 3, 1.6}, {2, 4, 1.25}, {2, 3, 1.0}, {2, 2, 0.83}, {2, 1, 0.6}};
+constexpr TileCost kTiles[] = {{4, 4, 1, {1.45}, {2.05}}, {4, 3, 1, {1.18}, {1.65}}, {2, 4, 1, {0.90}, {1.18}}, {2, 3, 1, {0.74}, {0.92}},
+                               {2, 2, 2, {0.62, 1.02}, {0.73, 1.25}}, {2, 1, 2, {0.52, 0.78}, {0.58, 0.92}}};
+constexpr TileCost kTilesF16[] = {{4, 4, 1, {1.95}, {2.5}}, {4, 3, 1, {1.65}, {2.15}}, {2, 4, 1, {0.95}, {1.22}}, {2, 3, 1, {0.80}, {1.02}},
+                                  {2, 2, 2, {0.70, 1.22}, {0.85, 1.60}}, {2, 1, 2, {0.56, 1.02}, {0.70, 1.30}}};
 constexpr long kCUs = 256;
 
-TilePlan tile_plan(int m, int k, int n, int epi, size_t partial_floats)
+double tile_us(const TileCost &t, long workgroups, int k_blocks)
+{
+    const long slots = kCUs * t.per_cu, rest = workgroups % slots;
+    double us = (double)(workgroups / slots) * t.full[t.per_cu - 1];
+    if (rest > 0) {
+        const int level = rest > kCUs;
+        us += t.few[level] + (t.full[level] - t.few[level]) * (double)(rest - level * kCUs) / kCUs;
+    }
+    return us * k_blocks;
+}
+
+TilePlan tile_plan(int wmode, int m, int k, int n, int epi, size_t partial_floats)
 {
     const long rows = epi == EPI_SWIGLU ? m / 2 : m;
     const long rdiv = epi == EPI_SWIGLU ? 2 : 1;
@@ -540,34 +556,24 @@ TilePlan tile_plan(int m, int k, int n, int epi, size_t partial_floats)
     const int most = n <= kSplitKMaxN ? kSplitKMax : 1;
     TilePlan p = {2, 1, 1, nkb, 0};
     double best_us = 0.0;
-    for (const TileCost &t : kTiles) {
+    for (const TileCost &t : wmode == W_F16 ? kTilesF16 : kTiles) {
         if (t.nf > 2 && n <= 128) continue;               // (one x tile is enough; the wide ones were not measured there)
         const long tiles = blocks(t.mf, t.nf);
         for (int s = 1; s <= most && (s == 1 || nkb / s >= 8); ++s) {
             const int per = s == 1 ? nkb : ((nkb + s - 1) / s + 1) & ~1, splits = (nkb + per - 1) / per;
             if (splits != s || (s > 1 && (size_t)s * n * m > partial_floats)) continue;
-            const double us = (double)((tiles * s + kCUs - 1) / kCUs) * per * t.us_per_kb + (s > 1 ? 3.0 + (double)s * n * m * 8.0 / 5e6 : 0.0);
+            const double us = tile_us(t, tiles * s, per) + (s > 1 ? 3.0 + (double)s * n * m * 8.0 / 5e6 : 0.0);
             if (best_us == 0.0 || us < best_us) best_us = us, p.mf = t.mf, p.nf = t.nf, p.splits = s, p.kb_per_split = per;
         }
     }
-    // Two launches instead of one when the 128 x 256 tile was chosen only for its rounds: whole rounds of 256 x 256
-    // tiles on the first rows (the tile that reaches more per MFMA), the narrower tile on the rest.  A round of the
-    // wide tile is taken as 1.6 rounds of the narrow one (129 against 80 us per round at k = 4096, n = 2048); the
-    // split is made when the estimate gains a tenth (QKV of the 7B layer at n = 2048: 1.6 + 1 against 3 rounds).
-    if (p.mf == 2 && p.nf == 4 && p.splits == 1 && epi != EPI_SWIGLU) {
-        const long tn = (n + 255) / 256;
-        if (tn <= kCUs) {
-            const long rows_round = (kCUs / tn) * 256;                           // weight rows of one full round of wide tiles
-            const double all_small = (double)((blocks(2, 4) + kCUs - 1) / kCUs);
-            double best = all_small;
-            for (long r = 1; r * rows_round < rows; ++r) {
-                const long rem = rows - r * rows_round;
-                const double t = 1.6 * (double)r + (double)((((rem + 127) / 128) * tn + kCUs - 1) / kCUs);
-                if (t < best) best = t, p.m_big = (int)(r * rows_round);
-            }
-            if (best > 0.9 * all_small) p.m_big = 0;
+    // Or two launches (4-bit, plain rows): whole rounds of 256 x 256 tiles on the first weight rows, 128 x 256 tiles on the rest, and 5 us
+    // for the second launch (7B QKV at n = 2048: 227 -> 217 us; 27648 x 5120 at n = 2048 588 against 628 in one launch).
+    const long tn = (n + 255) / 256, rows_round = kCUs / std::min(tn, kCUs) * 256;      // weight rows of one round of wide tiles
+    if (wmode == W_Q4 && epi != EPI_SWIGLU && n > 128 && tn <= kCUs)
+        for (long big = rows_round; big < rows; big += rows_round) {
+            const double us = (double)(big / rows_round) * kTiles[0].full[0] * nkb + tile_us(kTiles[2], (rows - big + 127) / 128 * tn, nkb) + 5.0;
+            if (us < best_us) best_us = us, p = {2, 4, 1, nkb, (int)big};
         }
-    }
     return p;
 }
 
@@ -605,16 +611,16 @@ size_t gemm_splitk_partial_floats(int m, int k, int n, int epi)
     return worst;
 }
 
-void gemm_tile_plan(int m, int k, int n, int epi, size_t partial_floats, relax_matmul_plan *plan)
+void gemm_tile_plan(int wmode, int m, int k, int n, int epi, size_t partial_floats, relax_matmul_plan *plan)
 {
-    const TilePlan p = tile_plan(m, k, n, epi, partial_floats);
+    const TilePlan p = tile_plan(wmode, m, k, n, epi, partial_floats);
     plan->k_ranges = p.splits, plan->tile_rows = 64 * p.mf, plan->tile_cols = 64 * p.nf, plan->wide_rows = p.m_big;
 }
 
 // k splits the launch would make for n rows with this much workspace (1: one pass over k, no finishing pass)
 int gemm_mfma_splits(const relax_qmat &w, int n, int epi, const float *partial, size_t partial_floats)
 {
-    return tile_plan(w.m, w.k, n, epi, partial && (reinterpret_cast<uintptr_t>(partial) & 15) == 0 ? partial_floats : 0).splits;
+    return tile_plan(W_Q4, w.m, w.k, n, epi, partial && (reinterpret_cast<uintptr_t>(partial) & 15) == 0 ? partial_floats : 0).splits;
 }
 
 // out[n,m] = x[n,k] . w[m,k]^T with plain fp16 weights: the same tiles, no decode, one pass over k
@@ -628,7 +634,7 @@ hipError_t launch_gemm_f16(const uint16_t *x, const uint16_t *w, int n, int m, i
 {
     GemmArgs a = {};
     a.x = x, a.wh = w, a.n = n, a.m = m, a.k = k, a.epi = EPI_F16, a.out_f16 = out, a.partial = partial;
-    const TilePlan p = tile_plan(m, k, n, EPI_F16, partial ? partial_floats : 0);
+    const TilePlan p = tile_plan(W_F16, m, k, n, EPI_F16, partial ? partial_floats : 0);
     a.kb_per_split = p.kb_per_split;
     if (p.mf == 4 && p.nf == 4) return launch_tile<4, 4, true>(a, stream, p.splits);    // the fp16-weight staging needs more registers than two wavefronts per SIMD leave
     if (p.mf == 4) return launch_tile<4, 3, true>(a, stream, p.splits);
@@ -649,7 +655,7 @@ hipError_t launch_gemm_q3(const uint16_t *x, const relax_qmat &w, int n, uint16_
 {
     GemmArgs a = {};
     a.x = x, a.q = w.q, a.s = w.s, a.gshift = 0, a.n = n, a.m = w.m, a.k = w.k, a.epi = EPI_F16, a.out_f16 = out, a.partial = partial;
-    const TilePlan p = tile_plan(w.m, w.k, n, EPI_F16, partial ? partial_floats : 0);
+    const TilePlan p = tile_plan(W_Q3, w.m, w.k, n, EPI_F16, partial ? partial_floats : 0);
     a.kb_per_split = p.kb_per_split;
     if (p.mf == 4 && p.nf == 4) return launch_tile<2, 4, false, 4, 2, true>(a, stream, p.splits);
     if (p.mf == 4) return launch_tile<2, 3, false, 4, 2, true>(a, stream, p.splits);
@@ -660,7 +666,7 @@ hipError_t launch_gemm_q3(const uint16_t *x, const relax_qmat &w, int n, uint16_
 }
 
 // k splits of the two launches above with this much workspace: more than one leaves partial rows for launch_skinny_finish
-int gemm_flat_splits(int n, int m, int k, size_t partial_floats) { return k % (2 * BK) == 0 ? tile_plan(m, k, n, EPI_F16, partial_floats).splits : 1; }
+int gemm_flat_splits(int wmode, int n, int m, int k, size_t partial_floats) { return k % (2 * BK) == 0 ? tile_plan(wmode, m, k, n, EPI_F16, partial_floats).splits : 1; }
 
 hipError_t launch_gemm_mfma(const uint16_t *x, const relax_qmat &w, int n, int epi, uint16_t *out_f16, float *out_f32, const void *resid,
                             hipStream_t stream, float *partial, size_t partial_floats, const SkinnyFuse *fuse)
@@ -669,7 +675,7 @@ hipError_t launch_gemm_mfma(const uint16_t *x, const relax_qmat &w, int n, int e
     a.wh = nullptr;
     a.x = x, a.q = w.q, a.s = w.s, a.gshift = gshift_of(w.group), a.n = n, a.m = w.m, a.k = w.k, a.epi = epi;
     a.out_f16 = out_f16, a.out_f32 = out_f32, a.resid = resid;
-    const TilePlan p = tile_plan(w.m, w.k, n, epi, partial && (reinterpret_cast<uintptr_t>(partial) & 15) == 0 ? partial_floats : 0);
+    const TilePlan p = tile_plan(W_Q4, w.m, w.k, n, epi, partial && (reinterpret_cast<uintptr_t>(partial) & 15) == 0 ? partial_floats : 0);
     if (fuse && p.splits < 2) return hipErrorInvalidValue;        // a folded light step needs the finishing pass
     a.partial = p.splits > 1 ? partial : nullptr;
     a.kb_per_split = p.kb_per_split;

@@ -394,8 +394,8 @@ bool gemm_f16_eligible(const void *x, const void *w, const void *out, int m, int
 // partial: with room for the partial rows of more than one k split (gemm_flat_splits) they go there and the caller finishes them
 hipError_t launch_gemm_f16(const uint16_t *x, const uint16_t *w, int n, int m, int k, uint16_t *out, hipStream_t stream, float *partial = nullptr,
                            size_t partial_floats = 0);
-int gemm_flat_splits(int n, int m, int k, size_t partial_floats);
-void gemm_tile_plan(int m, int k, int n, int epi, size_t partial_floats, relax_matmul_plan *plan);      // tile and cut of a launch
+int gemm_flat_splits(int wmode, int n, int m, int k, size_t partial_floats);
+void gemm_tile_plan(int wmode, int m, int k, int n, int epi, size_t partial_floats, relax_matmul_plan *plan);      // tile and cut of a launch
 struct SkinnyFuse;
 int gemm_mfma_splits(const relax_qmat &w, int n, int epi, const float *partial, size_t partial_floats);
 // fuse: only for a launch that splits (gemm_mfma_splits > 1): the light step folded into its finishing pass

@@ -72,3 +72,38 @@ ALONE = [
 @pytest.mark.parametrize("fmt,m,k,n,stream,other", ALONE)
 def test_calls_without_a_workspace_take_the_faster_kernel(fmt, m, k, n, stream, other):
     assert (plan(fmt, n, m, k)[0] == rx.KERNEL_STREAM) == (stream < other)
+
+
+# The tiled GEMM's tiles (weight rows, rows of x, k splits) with their measured times in us: the fastest ones, and the one that one
+# figure per tile would pick.  The plan has to be within a tenth of the fastest.
+TILES = [
+    ("q4", 12288, 4096, 600, {(128, 128, 1): 85, (256, 192, 1): 99, (128, 192, 1): 115}),
+    ("q4", 22016, 4096, 560, {(128, 128, 1): 155, (128, 192, 1): 173, (256, 192, 1): 185}),
+    ("q4", 4096, 11008, 300, {(128, 192, 4): 52, (256, 192, 8): 54, (128, 128, 5): 57}),
+    ("q4", 8192, 28672, 511, {(256, 256, 4): 254, (128, 256, 2): 267, (256, 256, 8): 269}),
+    ("q4", 10240, 8192, 200, {(128, 256, 3): 61, (256, 256, 6): 65, (128, 128, 3): 66}),
+    ("q3", 12288, 4096, 640, {(128, 128, 1): 86, (256, 192, 1): 97, (128, 192, 1): 117}),
+    ("q3", 22016, 4096, 513, {(128, 128, 1): 152, (128, 192, 1): 174, (256, 192, 1): 181}),
+    ("f16", 12288, 4096, 600, {(128, 128, 1): 96, (128, 192, 1): 112, (256, 192, 1): 118}),
+    ("f16", 22016, 4096, 300, {(128, 192, 1): 117, (256, 192, 1): 126, (128, 256, 1): 133}),
+    ("f16", 27648, 5120, 2048, {(128, 256, 1): 667, (256, 256, 1): 741, (128, 192, 1): 795, (256, 192, 1): 882}),
+    ("f16", 32000, 4096, 700, {(128, 256, 1): 231, (128, 192, 1): 259, (256, 192, 1): 267}),
+    ("f16", 15360, 5120, 1200, {(128, 256, 1): 260, (128, 128, 1): 293, (128, 192, 1): 298, (256, 192, 1): 302}),
+]
+
+
+@pytest.mark.parametrize("fmt,m,k,n,us", TILES)
+def test_tile_plan_picks_a_fast_tile(fmt, m, k, n, us):
+    kernel, splits, rows, cols, _ = plan(fmt, n, m, k, 8 * n * m * 4 if fmt == "q4" and n <= 512 else 0)
+    assert kernel == rx.KERNEL_TILED
+    assert us[rows, cols, splits] <= 1.1 * min(us.values())
+
+
+# Two launches, whole rounds of 256 x 256 tiles first (us: two launches, the best single one): 4-bit only.
+TWO_LAUNCHES = [(12288, 4096, 2048, 8192, 217, 227), (27648, 5120, 2048, 24576, 588, 628), (22016, 4096, 1700, 18432, 343, 372), (32000, 4096, 1700, 27648, 476, 503)]
+
+
+@pytest.mark.parametrize("m,k,n,wide,us_two,us_one", TWO_LAUNCHES)
+def test_tall_matrices_are_cut_into_two_launches(m, k, n, wide, us_two, us_one):
+    assert us_two < us_one and plan("q4", n, m, k) == (rx.KERNEL_TILED, 1, 128, 256, wide)
+    assert plan("q3", n, m, k)[4] == plan("f16", n, m, k)[4] == 0
