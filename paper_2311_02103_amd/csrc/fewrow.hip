@@ -48,10 +48,12 @@ bool cut(bool f16, int nb, int m, int k, int epi, int kg, Plan &p)
 //   unit, tile             ... per row tile of a workgroup: its longest slice's units, and the sums
 //   x                      per MB of x a workgroup fetches from its L2: long rows and many rows of x want k ranges
 //   finish, range, partial the finishing launch, per k range of it, and the partial rows at TB/s
+//   full                   more where every wavefront holds four units of x or more, which leaves it two row tiles in flight (8192 columns
+//                          in one range: 8192 x 8192 at 6 rows 16.5 us, the split-K kernel 15.4)
 struct Cost {
-    double launch, tb_per_s, unit, tile, x, finish, range, partial;
+    double launch, tb_per_s, unit, tile, x, finish, range, partial, full;
 };
-constexpr Cost kCostQ4[3] = {{3.75, 5.9, 0.51, 0.44, 42, 4.1, 0.16, 5.1}, {4.2, 5.35, 0.65, 0.37, 32, 3.2, 0.26, 3.1}, {3.6, 3.3, 1.24, 0.0, 32, 4.0, 0.86, 70}};
+constexpr Cost kCostQ4[3] = {{3.75, 5.9, 0.51, 0.44, 42, 4.1, 0.16, 5.1, 2.5}, {4.2, 5.35, 0.65, 0.37, 32, 3.2, 0.26, 3.1}, {3.6, 3.3, 1.24, 0.0, 32, 4.0, 0.86, 70}};
 // 3-bit and fp16 matrices: the rates of the stream alone (what is estimated for them only picks the k ranges of a layer's matrices)
 constexpr Cost kCostQ3[3] = {{5.8, 5.9, 0.46, 0.0, 25, 3.1, 0.0, 5.8}, {5.8, 5.35, 0.51, 0.0, 27, 3.4, 0.0, 5.3}, {5.8, 4.7, 0.58, 0.0, 31, 3.9, 0.0, 4.6}};
 constexpr Cost kCostF16[2] = {{5.8, 5.9, 1.05, 0.0, 25, 3.1, 0.0, 5.8}, {5.8, 5.35, 1.17, 0.0, 27, 3.4, 0.0, 5.3}};
@@ -72,6 +74,7 @@ int best_ranges(int fmt, int n, int m, int k, int epi, bool folded, size_t parti
         if (!cut(f16, blocks_of(n), m, k, epi, kg, p)) continue;
         const double per = (p.tiles + p.rg - 1) / p.rg, rounds = (p.rg * kg + 255) / 256;
         double us = std::max(bytes / (c.tb_per_s * 1e6), rounds * per * (p.uw * c.unit + c.tile)) + rounds * n * ((double)k / kg) * 2e-6 * c.x;
+        if (p.uw >= 4 && k / unit_columns(f16) == p.uw * kWaves * kg) us += c.full;
         if (kg > 1) us += c.finish + kg * c.range + (double)kg * n * m * 8e-6 / c.partial - (folded ? kFolded : 0.0);
         if (best == 0 || us < best_us) best = kg, best_us = us;
         if (p.uw == 1) break;

@@ -47,7 +47,7 @@ FEW_ROWS = [
     (4096, 11008, 24, 19.6, 17.0), (4096, 11008, 32, 20.6, 17.3), (5120, 13824, 8, 18.4, 16.9), (5120, 13824, 16, 20.0, 17.8),
     (5120, 13824, 32, 24.2, 19.9), (5120, 13824, 64, 31.2, 26.9), (8192, 8192, 16, 18.8, 16.5), (8192, 8192, 32, 23.0, 18.8),
     (8192, 8192, 64, 31.1, 25.5), (10240, 8192, 32, 25.1, 22.1), (15360, 5120, 32, 24.6, 22.4), (15360, 5120, 64, 35.8, 29.9),
-    (5120, 13824, 2, 17.6, 15.9), (7168, 7168, 32, 20.9, 18.1), (16384, 3072, 40, 25.4, 20.1), (32000, 2048, 48, 31.6, 24.8),
+    (5120, 13824, 2, 17.6, 15.9), (8192, 8192, 4, 16.7, 15.5), (7168, 7168, 32, 20.9, 18.1), (16384, 3072, 40, 25.4, 20.1), (32000, 2048, 48, 31.6, 24.8),
 ]
 
 
