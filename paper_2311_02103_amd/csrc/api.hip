@@ -39,7 +39,7 @@ Route q4_route(const uint16_t *x, const relax_qmat &w, const uint16_t *out, int 
 {
     const bool tiled_first = gemm_prefers_tiled(w.m, n) && gemm_mfma_eligible(w, x, EPI_F16);
     const bool ws_fits = ws && aligned(ws, 16) && n <= kSkinnyMaxN && ws_bytes >= sizeof(float) * gemm_skinny_partial_floats(w.m, w.k, n);
-    const int kr = tiled_first || !ws_fits ? 0 : stream_ranges(W_Q4, w, x, out, n, EPI_F16, ws_bytes / sizeof(float));
+    const int kr = !ws_fits ? 0 : stream_ranges(W_Q4, w, x, out, n, EPI_F16, ws_bytes / sizeof(float));
     if (kr > 0) return {RELAX_KERNEL_STREAM, kr};
     if (!tiled_first && n >= kSkinnyMinN && n <= kSkinnyMaxN && ws_fits && gemm_skinny_eligible(w, x, n, EPI_F16)) return {RELAX_KERNEL_SPLIT_K, 0};
     if (n >= kGemmMinN && gemm_mfma_eligible(w, x, EPI_F16)) return {RELAX_KERNEL_TILED, 0};
@@ -700,13 +700,12 @@ relax_status layer_enqueue(const relax_layer_dims &dm, const relax_layer_weights
     // launch behind the output projection (and behind the down projection when the next layer's norm is known).
     auto folds = [&](int epi) { return epi == EPI_RESID_F32 || (epi == EPI_RESID_F16 && next_norm && xn_done); };
     auto stream = [&](const relax_qmat &wq, const void *xin, int epi) {
-        if (gemm_prefers_tiled(wq.m, n) && n >= kGemmMinN && gemm_mfma_eligible(wq, xin, epi)) return 0;
         return stream_ranges(W_Q4, wq, xin, epi == EPI_RESID_F16 ? (const void *)out : epi == EPI_RESID_F32 ? (const void *)x : nullptr, n, epi, pl.mm_floats, folds(epi));
     };
     auto mat_ok = [&](const relax_qmat &wq, const void *xin, int epi) {
         return stream(wq, xin, epi) || (n <= kSkinnyMaxN && gemm_skinny_eligible(wq, xin, n, epi)) || (n >= kGemmMinN && gemm_mfma_eligible(wq, xin, epi));
     };
-    auto few_row = [&](const relax_qmat &wq, const void *xin, int epi) {      // the few-row kernel takes this matmul
+    auto few_row = [&](const relax_qmat &wq, const void *xin, int epi) {      // the split-K few-row kernel takes this matmul, if the stream does not
         if (gemm_prefers_tiled(wq.m, n) && n >= kGemmMinN && gemm_mfma_eligible(wq, xin, epi)) return false;
         return n <= kSkinnyMaxN && gemm_skinny_eligible(wq, xin, n, epi);
     };

@@ -406,10 +406,11 @@ constexpr int kSkinnyMinN = 2;       // rows from which the layer takes the matr
 constexpr int kSkinnyMaxN = 64;      // rows the split-K few-row kernel takes
 constexpr int kSkinnySizedN = 128;   // ... and rows a workspace for its partial tiles is sized for (the tiled GEMM cuts its launches along k within it)
 bool gemm_skinny_eligible(const relax_qmat &w, const void *x, int n, int epi);
-// Whether the tiled GEMM takes n rows before the few-row kernels (Sec. 5.1: the dispatch follows the runtime value of the symbolic
-// dim): from 65 rows on, where a launch cut along k keeps its tiles wide (128 rows, few-row kernel against tiled: 8192 x 28672 126 / 95 us,
-// 5120 x 13824 57 / 40, 10240 x 8192 63 / 45, 12288 x 4096 36.8 / 34.6; layers 7B 236 / 232, 13B 325 / 289, 70B 455 / 393), and from 48
-// rows on matrices that fill the chip with tiles (57344 x 8192: 146 against 158 us).
+// Whether the tiled GEMM takes n rows before the split-K few-row kernel (Sec. 5.1: the dispatch follows the runtime value of the
+// symbolic dim): from 65 rows on, where a launch cut along k keeps its tiles wide (128 rows, few-row kernel against tiled: 8192 x 28672
+// 126 / 95 us, 5120 x 13824 57 / 40, 10240 x 8192 63 / 45, 12288 x 4096 36.8 / 34.6; layers 7B 236 / 232, 13B 325 / 289, 70B 455 / 393),
+// and from 48 rows on matrices that fill the chip with tiles (57344 x 8192: 124 against 139 us).  The streaming kernel is asked before
+// either, up to 64 rows (57344 x 8192 at 48 to 64 rows: 108 us, tiled 128).
 inline bool gemm_prefers_tiled(int m, int n) { return n > 64 || (n >= 48 && m >= 49152); }
 size_t gemm_skinny_partial_floats(int m, int k, int n);
 void gemm_skinny_cut(int m, int k, int *tiles_m, int *splits, int *rounds);      // its workgroups: row tiles x k splits, rounds of 256 columns each

@@ -107,3 +107,9 @@ TWO_LAUNCHES = [(12288, 4096, 2048, 8192, 217, 227), (27648, 5120, 2048, 24576, 
 def test_tall_matrices_are_cut_into_two_launches(m, k, n, wide, us_two, us_one):
     assert us_two < us_one and plan("q4", n, m, k) == (rx.KERNEL_TILED, 1, 128, 256, wide)
     assert plan("q3", n, m, k)[4] == plan("f16", n, m, k)[4] == 0
+
+
+@pytest.mark.parametrize("n", [47, 48, 56, 64])
+def test_tall_matrices_stay_on_the_streaming_kernel_up_to_64_rows(n):
+    """57344 x 8192 at 48 rows: the stream 108 us, the tiled GEMM 128, the split-K kernel 139."""
+    assert plan("q4", n, 57344, 8192, workspace(n, 57344, 8192))[0] == rx.KERNEL_STREAM
