@@ -41,8 +41,9 @@ bool cut(bool f16, int nb, int m, int k, int epi, int kg, Plan &p)
     return true;
 }
 
-// What a launch takes, in us, for blocks of 16, 32 and 64 rows of x: fitted to 31 matrices from 256 x 256 to 57344 x 8192 and 8192 x 28672
-// at 2 to 64 rows, weights cold, every k range the kernel is built for (4-bit: 4 % rms where the kernels are close, 8 % overall).
+// What a launch takes, in us, for blocks of 16, 32 and 64 rows of x: fitted to 73 matrices from 256 x 256 to 128256 x 4096 and 12288 x
+// 12288 at 2 to 64 rows, weights cold, every k range the kernel is built for.  What the 4-bit figures and the ones of the split-K kernel
+// below choose is 0.4, 0.6 and 0.6 % off the fastest launch on average, 15, 13 and 11 % at most.
 //   launch                 the launch, the first data and the sums over the wavefronts
 //   tb_per_s               the stream of the weights, or, where few row tiles or uneven slices leave it to the slowest workgroup,
 //   unit, tile             ... per row tile of a workgroup: its longest slice's units, and the sums
@@ -50,10 +51,11 @@ bool cut(bool f16, int nb, int m, int k, int epi, int kg, Plan &p)
 //   finish, range, partial the finishing launch, per k range of it, and the partial rows at TB/s
 //   full                   more where every wavefront holds four units of x or more, which leaves it two row tiles in flight (8192 columns
 //                          in one range: 8192 x 8192 at 6 rows 16.5 us, the split-K kernel 15.4)
+//   round                  more per wave of workgroups behind the first, which begins with x and the first data again
 struct Cost {
-    double launch, tb_per_s, unit, tile, x, finish, range, partial, full;
+    double launch, tb_per_s, unit, tile, x, finish, range, partial, full, round;
 };
-constexpr Cost kCostQ4[3] = {{3.75, 5.9, 0.51, 0.44, 42, 4.1, 0.16, 5.1, 2.5}, {4.2, 5.35, 0.65, 0.37, 32, 3.2, 0.26, 3.1}, {3.6, 3.3, 1.24, 0.0, 32, 4.0, 0.86, 70}};
+constexpr Cost kCostQ4[3] = {{4.2, 9.5, 0.65, 0.17, 35, 3.1, 0.33, 3.3, 3.4}, {4.6, 5.4, 0.79, 0.0, 32, 2.2, 0.57, 2.7, 0.0, 8.0}, {4.8, 3.1, 1.39, 0.05, 25, 2.6, 0.79, 38}};
 // 3-bit and fp16 matrices: the rates of the stream alone (what is estimated for them only picks the k ranges of a layer's matrices)
 constexpr Cost kCostQ3[3] = {{5.8, 5.9, 0.46, 0.0, 25, 3.1, 0.0, 5.8}, {5.8, 5.35, 0.51, 0.0, 27, 3.4, 0.0, 5.3}, {5.8, 4.7, 0.58, 0.0, 31, 3.9, 0.0, 4.6}};
 constexpr Cost kCostF16[2] = {{5.8, 5.9, 1.05, 0.0, 25, 3.1, 0.0, 5.8}, {5.8, 5.35, 1.17, 0.0, 27, 3.4, 0.0, 5.3}};
@@ -73,7 +75,7 @@ int best_ranges(int fmt, int n, int m, int k, int epi, bool folded, size_t parti
         Plan p;
         if (!cut(f16, blocks_of(n), m, k, epi, kg, p)) continue;
         const double per = (p.tiles + p.rg - 1) / p.rg, rounds = (p.rg * kg + 255) / 256;
-        double us = std::max(bytes / (c.tb_per_s * 1e6), rounds * per * (p.uw * c.unit + c.tile)) + rounds * n * ((double)k / kg) * 2e-6 * c.x;
+        double us = std::max(bytes / (c.tb_per_s * 1e6), rounds * per * (p.uw * c.unit + c.tile)) + rounds * n * ((double)k / kg) * 2e-6 * c.x + (rounds - 1) * c.round;
         if (p.uw >= 4 && k / unit_columns(f16) == p.uw * kWaves * kg) us += c.full;
         if (kg > 1) us += c.finish + kg * c.range + (double)kg * n * m * 8e-6 / c.partial - (folded ? kFolded : 0.0);
         if (best == 0 || us < best_us) best = kg, best_us = us;
@@ -83,17 +85,19 @@ int best_ranges(int fmt, int n, int m, int k, int epi, bool folded, size_t parti
     return best;
 }
 
-// The same for the split-K few-row kernel (4-bit matrices): workgroups of 128 rows and `rounds` rounds of 256 columns, one a CU or more.
+// The same for the split-K few-row kernel (4-bit matrices): workgroups of 128 rows and `rounds` rounds of 256 columns, whole waves of 256
+// of them (12288 x 12288 has 288: 34.8 us at 6 rows, the stream 23.6) or what the chip makes of all of them.
 struct SplitCost {
-    double launch, row, round, round_full, split, partial;
+    double launch, row, wave, chip, split, partial;
 };
-constexpr SplitCost kCostSplit[3] = {{5.0, 0.155, 0.93, 1.0, 0.18, 2.9}, {3.25, 0.125, 1.26, 1.34, 0.26, 22}, {0.8, 0.08, 2.07, 2.21, 0.59, 56}};
+constexpr SplitCost kCostSplit[3] = {{7.0, 0.054, 0.81, 0.65, 0.2, 2.1}, {4.9, 0.09, 1.1, 0.48, 0.27, 4.3}, {5.1, 0.01, 1.7, 1.55, 0.6, 4.0}};
 double split_us(int n, int m, int k)
 {
     const SplitCost &c = kCostSplit[block_class(n)];
     int tiles_m, splits, rounds;
     gemm_skinny_cut(m, k, &tiles_m, &splits, &rounds);
-    return c.launch + c.row * n + std::max(rounds * c.round, (double)tiles_m * splits * rounds / 256.0 * c.round_full) + splits * c.split +
+    const int workgroups = tiles_m * splits;
+    return c.launch + c.row * n + std::max((workgroups + 255) / 256 * rounds * c.wave, workgroups / 256.0 * rounds * c.chip) + splits * c.split +
            (double)splits * n * m * 8e-6 / c.partial;
 }
 
@@ -157,6 +161,8 @@ int fewrow_ranges(int wmode, int n, int m, int k, int epi, bool folded, size_t p
     if (wmode == W_Q4 && kr > 0 && gemm_skinny_partial_floats(m, k, n) > 0 && partial_floats >= gemm_skinny_partial_floats(m, k, n) &&
         split_us(n, m, k) - (folded ? kFolded : 0.0) < us)
         return 0;
+    // ... and on matrices that fill the chip with tiles through the tiled GEMM (48 rows: 49152 x 2048 32.6 against 44.5 us)
+    if (wmode == W_Q4 && gemm_prefers_tiled(m, n) && gemm_tile_us(m, k, n, epi, partial_floats) < us) return 0;
     return kr;
 }
 
@@ -165,26 +171,27 @@ int fewrow_ranges(int wmode, int n, int m, int k, int epi, bool folded, size_t p
 // serves all rows, and on matrices so small that the launch is what counts (stream against the other kernel, us):
 //   3-bit  2 rows of up to 8192 columns are one pass: 22016 x 4096 19.2 / 14.0, 8192 x 8192 16.5 / 12.1, 57344 x 8192 59 / 52; 12288
 //          columns take two: 4096 x 11008 13.3 / 14.6.  3 and 4 rows of up to 2048 columns: 5632 x 2048 7.7 / 6.7; 4096 x 4096 8.0 / 10.2.
-//          Up to 1024 x 1024 at 8 rows 5.2 / 4.4, 256 x 768 at 15 5.2 / 4.0, 1408 x 256 at 5 4.7 / 5.3.
+//          Up to 1024 rows of 4096 columns at 8 rows: 1024 x 1024 5.2 / 4.4, 1000 x 3584 7.4 / 6.3, 1408 x 256 at 5 4.7 / 5.3; 256 x
+//          768 at 15 5.2 / 4.0.
 //          From 17 rows on the other kernel is the tiled GEMM: 256 columns at 32 rows 5.7 / 5.3, at 64 7.1 / 5.7; 768 columns 6.3 / 9.1;
 //          from 33 rows on it is ahead on tall matrices (32000 x 2048 28.8 / 24.1, 5632 x 2048 12.4 / 19.8).
 //   fp16   2, 4 and 8 rows are one pass of the matvec kernel.  2 rows up to 190 MB: 8192 x 8192 32.6 / 28.7, 22016 x 4096 35.6 / 34.1;
-//          28672 x 4096 41.5 / 43.3.  4 rows up to 64 MB, and on very long or very short rows: 5120 x 5120 17.2 / 15.7, 10240 x 8192
-//          37.0 / 35.2, 32000 x 2048 28.2 / 26.8; 12288 x 4096 20.5 / 21.1.  8 rows up to 4 MB: 1024 x 1024 5.9 / 4.8; 2048 x 2048 a tie.
+//          28672 x 4096 41.5 / 43.3.  4 rows up to 72 MB, and on very long or very short rows: 5120 x 5120 17.2 / 15.7, 10240 x 8192
+//          37.0 / 35.2, 32000 x 2048 28.2 / 26.8; 12288 x 4096 20.5 / 21.1.  8 rows up to 8 MB: 1024 x 1024 5.9 / 4.8, 1000 x 3584 8.9 / 7.2; 2048 x 2048 a tie.
 bool fewrow_pays_alone(int wmode, int n, int m, int k)
 {
     if (wmode == W_Q3) {
         if (n == 2) return k > 8192;
-        if (n <= 4) return k > 2048;
-        if (n <= 8) return m > 1024 || k > 1024;
+        if (n <= 4 && k <= 2048) return false;
+        if (n <= 8) return m > 1024 || k > 4096;
         if (n <= 15) return m > 256 || k > 1024;
         return n == 16 || (k > 256 && (n <= 32 || m <= 16384));
     }
     if (wmode == W_F16) {
         const double mb = (double)m * k * 2e-6;
         if (n == 2) return mb > 190.0;
-        if (n == 4) return mb > 64.0 && k > 2048 && k < 8192;
-        if (n == 8) return mb > 4.0;
+        if (n == 4) return mb > 72.0 && k > 2048 && k < 8192;
+        if (n == 8) return mb > 8.0;
     }
     return true;
 }

@@ -513,27 +513,28 @@ bool gemm_mfma_eligible(const relax_qmat &w, const void *x, int epi)
 // Tile and cut of a launch: the least estimated time over the tiles (weight rows x x-rows) and over k splits, of which there
 // may be up to kSplitKMax of at least 8 k blocks each for up to kSplitKMaxN rows; the fp32 partial tiles of a split launch go to
 // the caller's workspace (it has to hold them) and the finishing pass of the few-row kernel adds them in order and applies the
-// epilogue: 3 us and the partial rows twice over at 5 TB/s.
+// epilogue: 1.6 us, 0.4 per split and the partial rows twice over at 5 TB/s.
 // A k block of a wave of 256 workgroups takes longer the more of them there are (clock and fabric), and the two small tiles fit a
-// CU twice, so a launch of 257 to 512 of them is still one round.  Fitted to 14 matrices from 2048 x 2048 to 57344 x 8192 at 48 to
-// 2048 rows, every tile, and every split up to 512 rows, of 4-bit weights (3-bit ones agree) and of fp16 weights, whose wide tiles
-// run as four wavefronts: the choice is 0.5 % (4-bit), 0.0 % and 0.1 % off the best on average, 14 %, 3 % and 9 % at most.  With one
-// figure per tile, taken on a full chip, 256 x 192 tiles were preferred to 144 of 256 x 256 or 480 of 128 x 128 (12288 x 4096 at 600 rows
-// 99 against 85 us) and wide tiles on fp16 weights (27648 x 5120 at 2048 rows 882 against 667).
+// CU twice, so a launch of 257 to 512 of them is still one round.  The figures are the ones whose choice is closest to the fastest launch
+// over 28 matrices from 1024 x 1024 to 57344 x 8192 at 48 to 2048 rows, every tile, and every split up to 512 rows, of 4-bit weights (3-bit
+// ones agree) and of fp16 weights, whose wide tiles run as four wavefronts: 0.3 % (4-bit, whatever the workspace) and 0.1 % off on average, 12 % and 9 % at most.
+// With one figure per tile, taken on a full chip, 256 x 192 tiles were preferred to 144 of 256 x 256 or 480 of 128 x 128 (12288 x 4096
+// at 600 rows 99 against 85 us) and wide tiles on fp16 weights (27648 x 5120 at 2048 rows 882 against 667).
 namespace {
 struct TilePlan {
     int mf, nf, splits, kb_per_split;
     int m_big;               // > 0: the first m_big weight rows go through a launch of 256 x 256 tiles of their own (whole rounds of them)
+    double us;               // estimated time less the launch
 };
 struct TileCost {
     int mf, nf;
     int per_cu;              // workgroups a CU holds
     double few[2], full[2];  // us per k block of a wave with few and with 256 workgroups; [1]: of the second workgroup of every CU, both together
 };
-constexpr TileCost kTiles[] = {{4, 4, 1, {1.45}, {2.05}}, {4, 3, 1, {1.18}, {1.65}}, {2, 4, 1, {0.90}, {1.18}}, {2, 3, 1, {0.74}, {0.92}},
-                               {2, 2, 2, {0.62, 1.02}, {0.73, 1.25}}, {2, 1, 2, {0.52, 0.78}, {0.58, 0.92}}};
-constexpr TileCost kTilesF16[] = {{4, 4, 1, {1.95}, {2.5}}, {4, 3, 1, {1.65}, {2.15}}, {2, 4, 1, {0.95}, {1.22}}, {2, 3, 1, {0.80}, {1.02}},
-                                  {2, 2, 2, {0.70, 1.22}, {0.85, 1.60}}, {2, 1, 2, {0.56, 1.02}, {0.70, 1.30}}};
+constexpr TileCost kTiles[] = {{4, 4, 1, {1.67}, {1.85}}, {4, 3, 1, {1.25}, {1.50}}, {2, 4, 1, {0.90}, {1.08}}, {2, 3, 1, {0.74}, {0.88}},
+                               {2, 2, 2, {0.59, 1.04}, {0.70, 1.22}}, {2, 1, 2, {0.475, 0.78}, {0.515, 0.90}}};
+constexpr TileCost kTilesF16[] = {{4, 4, 1, {1.85}, {2.56}}, {4, 3, 1, {1.94}, {2.10}}, {2, 4, 1, {0.985}, {1.13}}, {2, 3, 1, {0.85}, {0.96}},
+                                  {2, 2, 2, {0.70, 1.45}, {0.82, 1.60}}, {2, 1, 2, {0.58, 1.05}, {0.67, 1.43}}};
 constexpr long kCUs = 256;
 
 double tile_us(const TileCost &t, long workgroups, int k_blocks)
@@ -554,7 +555,7 @@ TilePlan tile_plan(int wmode, int m, int k, int n, int epi, size_t partial_float
     auto blocks = [&](int mf, int nf) { return ((rows + 64 * mf / rdiv - 1) / (64 * mf / rdiv)) * (long)((n + 64 * nf - 1) / (64 * nf)); };
     const int nkb = k / BK;
     const int most = n <= kSplitKMaxN ? kSplitKMax : 1;
-    TilePlan p = {2, 1, 1, nkb, 0};
+    TilePlan p = {2, 1, 1, nkb, 0, 0.0};
     double best_us = 0.0;
     for (const TileCost &t : wmode == W_F16 ? kTilesF16 : kTiles) {
         if (t.nf > 2 && n <= 128) continue;               // (one x tile is enough; the wide ones were not measured there)
@@ -562,7 +563,7 @@ TilePlan tile_plan(int wmode, int m, int k, int n, int epi, size_t partial_float
         for (int s = 1; s <= most && (s == 1 || nkb / s >= 8); ++s) {
             const int per = s == 1 ? nkb : ((nkb + s - 1) / s + 1) & ~1, splits = (nkb + per - 1) / per;
             if (splits != s || (s > 1 && (size_t)s * n * m > partial_floats)) continue;
-            const double us = tile_us(t, tiles * s, per) + (s > 1 ? 3.0 + (double)s * n * m * 8.0 / 5e6 : 0.0);
+            const double us = tile_us(t, tiles * s, per) + (s > 1 ? 1.6 + 0.4 * s + (double)s * n * m * 8.0 / 5e6 : 0.0);
             if (best_us == 0.0 || us < best_us) best_us = us, p.mf = t.mf, p.nf = t.nf, p.splits = s, p.kb_per_split = per;
         }
     }
@@ -572,8 +573,9 @@ TilePlan tile_plan(int wmode, int m, int k, int n, int epi, size_t partial_float
     if (wmode == W_Q4 && epi != EPI_SWIGLU && n > 128 && tn <= kCUs)
         for (long big = rows_round; big < rows; big += rows_round) {
             const double us = (double)(big / rows_round) * kTiles[0].full[0] * nkb + tile_us(kTiles[2], (rows - big + 127) / 128 * tn, nkb) + 5.0;
-            if (us < best_us) best_us = us, p = {2, 4, 1, nkb, (int)big};
+            if (us < best_us) best_us = us, p = {2, 4, 1, nkb, (int)big, 0.0};
         }
+    p.us = best_us;
     return p;
 }
 
@@ -610,6 +612,8 @@ size_t gemm_splitk_partial_floats(int m, int k, int n, int epi)
     }
     return worst;
 }
+
+double gemm_tile_us(int m, int k, int n, int epi, size_t partial_floats) { return 4.5 + tile_plan(W_Q4, m, k, n, epi, partial_floats).us; }
 
 void gemm_tile_plan(int wmode, int m, int k, int n, int epi, size_t partial_floats, relax_matmul_plan *plan)
 {

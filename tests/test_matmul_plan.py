@@ -48,6 +48,8 @@ FEW_ROWS = [
     (5120, 13824, 32, 24.2, 19.9), (5120, 13824, 64, 31.2, 26.9), (8192, 8192, 16, 18.8, 16.5), (8192, 8192, 32, 23.0, 18.8),
     (8192, 8192, 64, 31.1, 25.5), (10240, 8192, 32, 25.1, 22.1), (15360, 5120, 32, 24.6, 22.4), (15360, 5120, 64, 35.8, 29.9),
     (5120, 13824, 2, 17.6, 15.9), (8192, 8192, 4, 16.7, 15.5), (7168, 7168, 32, 20.9, 18.1), (16384, 3072, 40, 25.4, 20.1), (32000, 2048, 48, 31.6, 24.8),
+    (12288, 12288, 8, 25.4, 35.4), (30000, 1024, 15, 10.6, 12.4), (5120, 25600, 8, 24.7, 29.4), (2560, 10240, 5, 12.2, 13.9),
+    (9216, 9216, 24, 25.2, 22.1), (36864, 4608, 40, 50.5, 61.2), (51200, 5120, 17, 47.2, 56.2), (11264, 2048, 48, 15.1, 17.8),
 ]
 
 
@@ -113,3 +115,8 @@ def test_tall_matrices_are_cut_into_two_launches(m, k, n, wide, us_two, us_one):
 def test_tall_matrices_stay_on_the_streaming_kernel_up_to_64_rows(n):
     """57344 x 8192 at 48 rows: the stream 108 us, the tiled GEMM 128, the split-K kernel 139."""
     assert plan("q4", n, 57344, 8192, workspace(n, 57344, 8192))[0] == rx.KERNEL_STREAM
+
+
+def test_short_rows_of_tall_matrices_go_to_the_tiled_gemm_at_48_rows():
+    """49152 x 2048 at 48 rows: the tiled GEMM 32.6 us, the stream 44.5."""
+    assert plan("q4", 48, 49152, 2048, workspace(48, 49152, 2048))[0] == rx.KERNEL_TILED
