@@ -517,9 +517,11 @@ bool gemm_mfma_eligible(const relax_qmat &w, const void *x, int epi)
 // A k block of a wave of 256 workgroups takes longer the more of them there are (clock and fabric), and the two small tiles fit a
 // CU twice, so a launch of 257 to 512 of them is still one round.  The figures are the ones whose choice is closest to the fastest launch
 // over 28 matrices from 1024 x 1024 to 57344 x 8192 at 48 to 2048 rows, every tile, and every split up to 512 rows, of 4-bit weights (3-bit
-// ones agree) and of fp16 weights, whose wide tiles run as four wavefronts: 0.3 % (4-bit, whatever the workspace) and 0.1 % off on average, 12 % and 9 % at most.
+// ones agree) and of fp16 weights: 0.3 % (4-bit, whatever the workspace) and 0.1 % off on average, 12 % and 9 % at most.
 // With one figure per tile, taken on a full chip, 256 x 192 tiles were preferred to 144 of 256 x 256 or 480 of 128 x 128 (12288 x 4096
-// at 600 rows 99 against 85 us) and wide tiles on fp16 weights (27648 x 5120 at 2048 rows 882 against 667).
+// at 600 rows 99 against 85 us).  Fp16 weights have no tiles of 256 weight rows: their staging needs more registers than two wavefronts
+// per SIMD leave, and as four wavefronts they lost to two of 128 rows on all but the longest rows (27648 x 5120 at 2048 rows 741 to 882
+// against 667 us; 8192 x 28672 at 1200 877 against 943).
 namespace {
 struct TilePlan {
     int mf, nf, splits, kb_per_split;
@@ -533,8 +535,7 @@ struct TileCost {
 };
 constexpr TileCost kTiles[] = {{4, 4, 1, {1.67}, {1.85}}, {4, 3, 1, {1.25}, {1.50}}, {2, 4, 1, {0.90}, {1.08}}, {2, 3, 1, {0.74}, {0.88}},
                                {2, 2, 2, {0.59, 1.04}, {0.70, 1.22}}, {2, 1, 2, {0.475, 0.78}, {0.515, 0.90}}};
-constexpr TileCost kTilesF16[] = {{4, 4, 1, {1.85}, {2.56}}, {4, 3, 1, {1.94}, {2.10}}, {2, 4, 1, {0.985}, {1.13}}, {2, 3, 1, {0.85}, {0.96}},
-                                  {2, 2, 2, {0.70, 1.45}, {0.82, 1.60}}, {2, 1, 2, {0.58, 1.05}, {0.67, 1.43}}};
+constexpr TileCost kTilesF16[] = {{2, 4, 1, {0.985}, {1.13}}, {2, 3, 1, {0.85}, {0.96}}, {2, 2, 2, {0.70, 1.45}, {0.82, 1.60}}, {2, 1, 2, {0.58, 1.05}, {0.67, 1.43}}};
 constexpr long kCUs = 256;
 
 double tile_us(const TileCost &t, long workgroups, int k_blocks)
@@ -640,8 +641,6 @@ hipError_t launch_gemm_f16(const uint16_t *x, const uint16_t *w, int n, int m, i
     a.x = x, a.wh = w, a.n = n, a.m = m, a.k = k, a.epi = EPI_F16, a.out_f16 = out, a.partial = partial;
     const TilePlan p = tile_plan(W_F16, m, k, n, EPI_F16, partial ? partial_floats : 0);
     a.kb_per_split = p.kb_per_split;
-    if (p.mf == 4 && p.nf == 4) return launch_tile<4, 4, true>(a, stream, p.splits);    // the fp16-weight staging needs more registers than two wavefronts per SIMD leave
-    if (p.mf == 4) return launch_tile<4, 3, true>(a, stream, p.splits);
     if (p.nf == 4) return launch_tile<2, 4, true>(a, stream, p.splits);
     if (p.nf == 3) return launch_tile<2, 3, true>(a, stream, p.splits);
     if (p.nf == 2) return launch_tile<2, 2, true>(a, stream, p.splits);

@@ -17,6 +17,7 @@
 //     several times over even when m is small; every task writes its fp32 partial tile to the workspace and a small
 //     finishing kernel adds the partials IN A FIXED ORDER and applies the epilogue (plain fp16, residual adds,
 //     SwiGLU).  No atomics: results are reproducible run to run.
+#include <algorithm>
 #include <atomic>
 
 #include "relax_common.h"
@@ -85,22 +86,22 @@ struct SkinnyArgs {
 // grid: x = 128-row tile of weight rows, y = k split.  NF = 32-wide column blocks of the MFMA tile, XR = x rows kept
 // in LDS (n <= XR <= 32 NF).  MFMA columns beyond n compute on whatever the LDS rows hold (for XR = 16 the lanes of
 // columns 16..31 re-read rows 0..15) and are never stored: a column of the result depends on its own x row only.
-template <int NF, int XR, int KR>
+template <int NF, int XR>
 __global__ __launch_bounds__(256) void skinny_q4_kernel(SkinnyArgs a)
 {
-    constexpr int kXPitch = KR + 8;                       // LDS row pitch of the x chunk in halfs (16-byte fragment reads of 32 rows hit distinct banks)
-    constexpr int W = KR / 16;                            // packed words (= MFMA k steps) per lane and round: the lane's half of the round
-    constexpr int XP = XR * (KR / 8) / 256;               // 16-byte x packets a thread stages per round
+    constexpr int kXPitch = kRound + 8;                   // LDS row pitch of the x chunk in halfs (16-byte fragment reads of 32 rows hit distinct banks)
+    constexpr int W = kRound / 16;                        // packed words (= MFMA k steps) per lane and round: the lane's half of the round
+    constexpr int XP = XR * (kRound / 8) / 256;           // 16-byte x packets a thread stages per round
     constexpr int kXBuf = XR * kXPitch;
     extern __shared__ __align__(16) uint16_t lds[];       // x chunks [2][XR][kXPitch], then the scale tile [128][sc_pitch]
     uint16_t *const xs = lds, *const scs = lds + 2 * kXBuf;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int row32 = lane & 31, hf = lane >> 5;
     const int kw = a.k >> 3, SG = a.k >> (5 + a.gshift);   // packed words and scales per weight row
-    const int total_rounds = a.k / KR;
+    const int total_rounds = a.k / kRound;
     const int r_begin = blockIdx.y * a.rounds_per_split, r_end = min(total_rounds, r_begin + a.rounds_per_split);
     const int nr = r_end - r_begin;                       // >= 1 by construction of the grid
-    const int spr = a.rounds_per_split * KR / 256;        // 16-byte scale packets (8 groups = 256 columns) per row of the task
+    const int spr = a.rounds_per_split;                   // 16-byte scale packets (8 groups = 256 columns) per row of the task
     const int sc_pitch = spr * 8 + 8;                     // halfs per row of the scale tile (+16 bytes: rows start in different banks)
 
     // ---- group scales of the whole task, once: 128 rows x (8 nr) fp16, 16-byte packets, coalesced along each row ----
@@ -112,7 +113,7 @@ __global__ __launch_bounds__(256) void skinny_q4_kernel(SkinnyArgs a)
     for (int i = 0; i < kMaxRounds / 2; ++i) {
         const int pk = tid + i * 256, row = pk / spr, pp = pk - row * spr;
         const int grow = min(blockIdx.x * kRowsPerBlock + min(row, kRowsPerBlock - 1), a.m - 1);
-        const size_t sub = (size_t)r_begin * (KR / 32) + (size_t)min(pp, nr * KR / 256 - 1) * 8;      // first 32-column sub-group of the packet
+        const size_t sub = (size_t)r_begin * (kRound / 32) + (size_t)min(pp, nr - 1) * 8;      // first 32-column sub-group of the packet
         const uint16_t *src = a.s + (size_t)grow * SG + (sub >> a.gshift);
         if (a.gshift == 0) {
             screg[i] = *(const u32x4_t *)src;
@@ -128,15 +129,15 @@ __global__ __launch_bounds__(256) void skinny_q4_kernel(SkinnyArgs a)
     }
 
     const int wrow = min(blockIdx.x * kRowsPerBlock + wave * 32 + row32, a.m - 1);
-    const uint32_t *qsrc = a.q + (size_t)wrow * kw + (size_t)r_begin * (KR / 8) + hf * W;
-    // x staging roles: packet pk = tid + p * 256 -> x row pk / (KR/8), packet pk % (KR/8) of the round
+    const uint32_t *qsrc = a.q + (size_t)wrow * kw + (size_t)r_begin * (kRound / 8) + hf * W;
+    // x staging roles: packet pk = tid + p * 256 -> x row pk / (kRound/8), packet pk % (kRound/8) of the round
     const uint16_t *xsrc[XP];
     bool xon[XP];
 #pragma unroll
     for (int p = 0; p < XP; ++p) {
-        const int pk = tid + p * 256, xr = pk / (KR / 8);
+        const int pk = tid + p * 256, xr = pk / (kRound / 8);
         xon[p] = xr < a.n;
-        xsrc[p] = a.x + (size_t)min(xr, a.n - 1) * a.k + (size_t)r_begin * KR + (pk % (KR / 8)) * 8;
+        xsrc[p] = a.x + (size_t)min(xr, a.n - 1) * a.k + (size_t)r_begin * kRound + (pk % (kRound / 8)) * 8;
     }
 
     // Registers of one round in flight: the thread's share of the x chunk and the lane's 64 bytes of codes.
@@ -148,10 +149,10 @@ __global__ __launch_bounds__(256) void skinny_q4_kernel(SkinnyArgs a)
     auto stage_load = [&](Stage &S, int r) {              // r relative to r_begin, clamped: the tail re-reads the last round
         r = min(r, nr - 1);
 #pragma unroll
-        for (int p = 0; p < XP; ++p) S.x[p] = *(const u32x4_t *)(xsrc[p] + (size_t)r * KR);
+        for (int p = 0; p < XP; ++p) S.x[p] = *(const u32x4_t *)(xsrc[p] + (size_t)r * kRound);
 #pragma unroll
         // (plain loads: the four 16-byte pieces of a lane's 64 bytes and its neighbour's share 128-byte lines, which have to stay cached between them)
-        for (int i = 0; i < W / 4; ++i) S.w[i] = *(const u32x4_t *)(qsrc + (size_t)r * (KR / 8) + i * 4);
+        for (int i = 0; i < W / 4; ++i) S.w[i] = *(const u32x4_t *)(qsrc + (size_t)r * (kRound / 8) + i * 4);
     };
     auto x_store = [&](const Stage &S, int buf) {
 #pragma unroll
@@ -164,7 +165,7 @@ __global__ __launch_bounds__(256) void skinny_q4_kernel(SkinnyArgs a)
             o.y = __builtin_amdgcn_perm(S.x[p].z, S.x[p].x, 0x07060302u);
             o.z = __builtin_amdgcn_perm(S.x[p].w, S.x[p].y, 0x05040100u);
             o.w = __builtin_amdgcn_perm(S.x[p].w, S.x[p].y, 0x07060302u);
-            *(u32x4_t *)(xs + buf * kXBuf + (pk / (KR / 8)) * kXPitch + (pk % (KR / 8)) * 8) = o;
+            *(u32x4_t *)(xs + buf * kXBuf + (pk / (kRound / 8)) * kXPitch + (pk % (kRound / 8)) * 8) = o;
         }
     };
     auto lds_barrier = [&]() {                            // LDS only: global loads stay in flight across it
@@ -182,7 +183,7 @@ __global__ __launch_bounds__(256) void skinny_q4_kernel(SkinnyArgs a)
     // one round: W k steps; word W hf + s of the lane's codes against x packet W hf + s of the chunk
     const uint16_t *sc_lane = scs + (wave * 32 + row32) * sc_pitch + hf * (W / 4);
     auto round = [&](const Stage &S, int r, int buf) {
-        const uint16_t *xb = xs + buf * kXBuf + (row32 & (XR - 1)) * kXPitch + hf * (KR / 2);
+        const uint16_t *xb = xs + buf * kXBuf + (row32 & (XR - 1)) * kXPitch + hf * (kRound / 2);
         // the group scales of the lane's half (W/4 of them), each duplicated into both halves of a register
         const u32x2_t sc = *(const u32x2_t *)(sc_lane + r * 8);
         const uint32_t s2[4] = {__builtin_amdgcn_perm(sc.x, sc.x, 0x01000100u), __builtin_amdgcn_perm(sc.x, sc.x, 0x03020302u),
@@ -422,34 +423,46 @@ struct SkinnyPlan {
     int tiles_m, splits, rounds_per_split;
 };
 
-// Split count: about one workgroup per CU when the row tiles alone do not give that many, no k range shorter than 4 rounds (unless k itself is),
-// none longer than kMaxRounds; with 128-wide rounds every task has an even number of them (its scales come in packets of 256 columns).
-SkinnyPlan skinny_plan(int m, int k, int kr)
+// Splits of `rounds` rounds for tiles_m row tiles: about one workgroup per CU when the row tiles alone do not give that many (more of them
+// in flight measured slower: 7B and 70B shapes, 16 and 64 rows), no k range shorter than 4 rounds (unless k itself is), none longer
+// than kMaxRounds.
+int split_count(int tiles_m, int rounds)
+{
+    const int most = rounds >= 4 ? rounds / 4 : 1, least = (rounds + kMaxRounds - 1) / kMaxRounds;
+    return std::max(std::min(256 / tiles_m, most), least);
+}
+
+SkinnyPlan skinny_plan(int m, int k)
 {
     SkinnyPlan p;
     p.tiles_m = (m + kRowsPerBlock - 1) / kRowsPerBlock;
-    const int rounds = k / kr;
-    int splits = 256 / p.tiles_m;                         // about one workgroup per CU: more of them in flight measured slower (7B and 70B shapes, 16 and 64 rows)
-    const int max_splits = rounds >= 4 ? rounds / 4 : 1, min_splits = (rounds + kMaxRounds - 1) / kMaxRounds;
-    splits = splits > max_splits ? max_splits : splits;
-    splits = splits < min_splits ? min_splits : splits;
+    const int rounds = k / kRound, splits = split_count(p.tiles_m, rounds);
     p.rounds_per_split = (rounds + splits - 1) / splits;
-    if (kr == 128) p.rounds_per_split = (p.rounds_per_split + 1) & ~1;
     p.splits = (rounds + p.rounds_per_split - 1) / p.rounds_per_split;
     return p;
 }
 
-template <int NF, int XR, int KR>
+// Splits a workspace is sized for: those of the plan, or of a cut into rounds of 128 columns, an even number per task, if that is more.
+// Only the first is launched here.  The size is what programs have been told and the streaming kernel's k ranges and the
+// tiled GEMM's k splits live within it, so it stays.
+int sized_splits(int m, int k)
+{
+    const int tiles_m = (m + kRowsPerBlock - 1) / kRowsPerBlock, rounds = k / 128, splits = split_count(tiles_m, rounds);
+    const int per = ((rounds + splits - 1) / splits + 1) & ~1;
+    return std::max(skinny_plan(m, k).splits, (rounds + per - 1) / per);
+}
+
+template <int NF, int XR>
 hipError_t launch_skinny(const SkinnyArgs &a, dim3 grid, hipStream_t stream)
 {
-    const size_t lds = (size_t)2 * XR * (KR + 8) * sizeof(uint16_t) + (size_t)kRowsPerBlock * (a.rounds_per_split * KR / 256 * 8 + 8) * sizeof(uint16_t);
+    const size_t lds = (size_t)2 * XR * (kRound + 8) * sizeof(uint16_t) + (size_t)kRowsPerBlock * (a.rounds_per_split * 8 + 8) * sizeof(uint16_t);
     static std::atomic<bool> attr_done{false};   // setting the attribute twice is harmless; the flag only has to be a defined read
     if (!attr_done.load()) {
-        if (hipFuncSetAttribute((const void *)skinny_q4_kernel<NF, XR, KR>, hipFuncAttributeMaxDynamicSharedMemorySize, 112 * 1024) != hipSuccess)
+        if (hipFuncSetAttribute((const void *)skinny_q4_kernel<NF, XR>, hipFuncAttributeMaxDynamicSharedMemorySize, 112 * 1024) != hipSuccess)
             return hipErrorInvalidValue;
         attr_done.store(true);
     }
-    hipLaunchKernelGGL((skinny_q4_kernel<NF, XR, KR>), grid, dim3(256), lds, stream, a);
+    hipLaunchKernelGGL((skinny_q4_kernel<NF, XR>), grid, dim3(256), lds, stream, a);
     return hipGetLastError();
 }
 
@@ -469,17 +482,12 @@ bool gemm_skinny_eligible(const relax_qmat &w, const void *x, int n, int epi)
 size_t gemm_skinny_partial_floats(int m, int k, int n)
 {
     if (k % kRound != 0) return 0;
-    size_t worst = 0;                                     // the larger of the plans with rounds of 256 and of 128 columns: what callers bring
-    for (int kr : {256, 128}) {
-        const size_t v = (size_t)skinny_plan(m, k, kr).splits * (size_t)n * (size_t)m;
-        worst = v > worst ? v : worst;
-    }
-    return worst;
+    return (size_t)sized_splits(m, k) * (size_t)n * (size_t)m;
 }
 
 void gemm_skinny_cut(int m, int k, int *tiles_m, int *splits, int *rounds)
 {
-    const SkinnyPlan p = skinny_plan(m, k, kRound);
+    const SkinnyPlan p = skinny_plan(m, k);
     *tiles_m = p.tiles_m, *splits = p.splits, *rounds = p.rounds_per_split;
 }
 
@@ -497,15 +505,15 @@ bool gemm_skinny_fuse_ok(const relax_qmat &w, int epi, const SkinnyFuse &f)
 hipError_t launch_gemm_skinny(const uint16_t *x, const relax_qmat &w, int n, int epi, uint16_t *out_f16, float *out_f32, const void *resid,
                               float *partial, hipStream_t stream, const SkinnyFuse *fuse)
 {
-    const SkinnyPlan pl = skinny_plan(w.m, w.k, kRound);
+    const SkinnyPlan pl = skinny_plan(w.m, w.k);
     SkinnyArgs a;
     a.x = x, a.q = w.q, a.s = w.s, a.gshift = gshift_of(w.group), a.partial = partial, a.n = n, a.m = w.m, a.k = w.k, a.rounds_per_split = pl.rounds_per_split;
     dim3 grid(pl.tiles_m, pl.splits);
     hipError_t e;
     const int splits = pl.splits;
-    if (n <= 16) e = launch_skinny<1, 16, 256>(a, grid, stream);
-    else if (n <= 32) e = launch_skinny<1, 32, 256>(a, grid, stream);
-    else e = launch_skinny<2, 64, 256>(a, grid, stream);
+    if (n <= 16) e = launch_skinny<1, 16>(a, grid, stream);
+    else if (n <= 32) e = launch_skinny<1, 32>(a, grid, stream);
+    else e = launch_skinny<2, 64>(a, grid, stream);
     if (e != hipSuccess) return e;
     return launch_skinny_finish(partial, splits, n, w.m, epi, out_f16, out_f32, resid, stream, fuse);
 }
