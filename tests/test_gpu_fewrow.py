@@ -1,6 +1,6 @@
-"""GPU tests of the streaming few-row matmul (fewrow_kernel.h) at the sizes where its tiling can go wrong: rows of x around
-the blocks of 16, weight rows that do not fill a row tile, columns that do not divide over the wavefronts, one and several k
-ranges, all weight formats; and of the layers that run on it."""
+"""GPU tests of the few-row matmuls, above all the streaming kernel (fewrow_kernel.h), at the sizes where its tiling can go wrong:
+rows of x around the blocks of 16, weight rows that do not fill a row tile, columns that do not divide over the wavefronts, one k
+range in all weight formats, several with more row tiles than LDS holds; and of the layers that run on it."""
 import numpy as np
 import pytest
 
@@ -35,7 +35,8 @@ def _packed(rx, fmt, m, k, group, g):
 
 
 # m: below, at and beside a row tile of 16, one that needs several tiles per workgroup; k: one unit, units that leave wavefronts
-# idle or uneven, the 7B / 13B / 70B rows (several k ranges)
+# idle or uneven, the 7B / 13B / 70B rows.  Which kernel a row count takes is the dispatch's choice here (3-bit calls have one k
+# range; 30000 and 4100 rows of 4-bit weights go to the split-K kernel); the tests below say which one they reach.
 SHAPES = [(4, 256), (20, 512), (520, 4096), (72, 11008), (36, 13824), (40, 28672), (30000, 1024), (4100, 8192)]
 # A weight is rounded once to fp16 (2^-11 of its value, the final multiply of the decode), a result once more; sums of k terms with
 # random signs keep the relative 2-norm error at that of one term: below 2 * 2^-11 = 1e-3.
@@ -184,3 +185,82 @@ def test_3bit_scales_over_the_whole_fp16_range(rx, low, high):
         want, terms = x.double() @ ref.t(), x.double().abs() @ ref.abs().t()
         bound = 2.0 ** -11 * want.abs() + 2.0 ** -25 + k * 2.0 ** -24 * terms           # 2^-25: half of the smallest fp16 step
         assert bool(((out.double() - want).abs() <= bound).all()), n
+
+
+def _more_tiles_than_lds(n, m, ranges):
+    """Whether a workgroup of the streaming kernel gets more row tiles than its 152 KB of LDS hold sums of."""
+    blocks, tiles = (1 if n <= 16 else 2 if n <= 32 else 4), -(-m // 16)
+    return -(-tiles // min(tiles, 256 // ranges)) > 152 // (8 * blocks)
+
+
+# (m, k, n, k ranges, sums flushed inside the loop): blocks of 16, 32 and 64 rows
+RANGES = [(20, 5120, 15, 3, False), (20, 28672, 16, 14, False), (20, 6656, 17, 4, False), (11264, 6656, 17, 4, True), (11264, 8192, 32, 4, True),
+          (12292, 11008, 17, 3, True), (20, 5120, 33, 3, False), (11264, 4096, 33, 2, True), (16388, 2816, 64, 2, True), (11264, 5632, 48, 3, True)]
+
+
+@pytest.mark.parametrize("m,k,n,ranges,flush", RANGES)
+@pytest.mark.parametrize("group", [32, 128])
+def test_several_k_ranges_against_float64(rx, group, m, k, n, ranges, flush):
+    g = _gen(m + k + n)
+    w, ref = _packed(rx, "q4", m, k, group, g)
+    size = rx.relax_matmul_workspace_bytes(w, 128)
+    assert rx.relax_plan_matmul("q4", n, m, k, size)[:3] == (rx.OK, rx.KERNEL_STREAM, ranges) and _more_tiles_than_lds(n, m, ranges) == flush
+    ws = torch.full((size + 4096,), 7, dtype=torch.uint8, device="cuda")
+    x = torch.randn(n, k, device="cuda", generator=g).half()
+    out = [torch.full((n, m), float("nan"), device="cuda", dtype=torch.float16) for _ in range(2)]
+    for o in out:
+        rx.check(rx.relax_dequant_matmul(x, w, o, n, ws, size))
+    want = x.double() @ ref.t()
+    assert float((out[0].double() - want).norm() / want.norm()) < REL
+    assert torch.equal(out[0], out[1]) and bool((ws[size:] == 7).all())
+
+
+@pytest.mark.parametrize("fmt,m,k,n", [("q3", 520, 4096, 15), ("q3", 72, 11008, 2), ("q3", 3000, 5120, 17), ("q3", 520, 2048, 64),
+                                       ("f16", 520, 4096, 16), ("f16", 3000, 4096, 32), ("f16", 72, 8192, 3), ("f16", 4100, 12288, 2)])
+def test_one_k_range_of_the_other_formats(rx, fmt, m, k, n):
+    """... reaches the streaming kernel (fp16 rows of 12288 columns have no instance of it); 3-bit codes and scales aligned to 4 bytes."""
+    g = _gen(m + k + n)
+    x = torch.randn(n, k, device="cuda", generator=g).half()
+    out = torch.full((n, m), float("nan"), device="cuda", dtype=torch.float16)
+    assert rx.relax_plan_matmul(fmt, n, m, k)[:2] == (rx.OK, rx.KERNEL_MATVEC if k == 12288 else rx.KERNEL_STREAM)
+    if fmt == "q3":
+        w, ref = _packed(rx, fmt, m, k, 32, g)
+        w = rx.QMat(_shifted(w.q, 1), _shifted(w.s, 2), m, k, 32)
+        rx.check(rx.relax_dequant_matmul_q3_native(x, w, out, n))
+    else:
+        w = torch.randn(m, k, device="cuda", generator=g).half() * 0.05
+        ref = w.double()
+        rx.check(rx.relax_half_matmul(x, w, out, n, m, k))
+    want = x.double() @ ref.t()
+    assert float((out.double() - want).norm() / want.norm()) < REL
+
+
+def test_fp16_instances_leave_out_seven_units_per_wavefront(rx):
+    """One k range of 6145 to 7168 columns would need it: these rows take the kernels they took without the streaming kernel."""
+    for k, stream in ((6144, True), (6656, False), (7168, False), (7296, True), (8192, True)):
+        assert (rx.relax_plan_matmul("f16", 16, 4096, k)[1] == rx.KERNEL_STREAM) == stream, k
+
+
+@pytest.mark.parametrize("fmt,shape,rows", [("q3", wl.LLAMA7B, (17, 33, 64)), ("f16", wl.LLAMA7B, (17, 32)),
+                                            ("q4", wl.LayerShape("w13b", hidden=5120, n_heads=40, n_kv_heads=40, head_dim=128, ffn=13824), (17, 32, 64))])
+def test_wide_layers_against_the_first_rows_of_a_larger_call(rx, fmt, shape, rows):
+    """Partial rows in workspace that is dead at that point, and more row tiles than LDS holds: the down projection in fp16 and the QKV
+    and gate/up projections of 33 rows and more in 3 bits run several k ranges.  As above, on random codes."""
+    from paper_2311_02103_amd.runtime import DeviceLayer, DeviceLayerF16, DeviceLayerQ3
+    n_all, r, host = 130, np.random.RandomState(7), {}
+    for name, (m, k) in shape.matrices().items():
+        if fmt == "f16":
+            host[name] = (r.standard_normal((m, k)).astype(np.float32) * 0.02).astype(np.float16).view(np.uint16)
+        else:
+            host[name + ".q"] = r.randint(0, 2 ** 32, (m, k // 8 if fmt == "q4" else 3 * k // 32), dtype=np.uint32)
+            host[name + ".s"] = (r.random_sample((m, k // 32)) * 0.006 + 0.001).astype(np.float16).view(np.uint16)
+    host.update({name: wl.normal_f16_bits(4, 10 + i, (shape.hidden,), std=0.1, mean=1.0) for i, name in enumerate(("norm_attn", "norm_ffn"))})
+    layer = {"q4": DeviceLayer, "q3": DeviceLayerQ3, "f16": DeviceLayerF16}[fmt](
+        host, hidden=shape.hidden, n_heads=shape.n_heads, n_kv_heads=shape.n_kv_heads, head_dim=shape.head_dim, ffn=shape.ffn, kv_capacity=192, n_max=n_all)
+    x = torch.from_numpy(wl.activations(shape, 4, 0, n_all).view(np.int16)).view(torch.float16).cuda()
+    want, k_all = layer.forward(x, [n_all], [n_all]).double(), layer.k.clone()
+    for n in rows:
+        layer.k.zero_(), layer.v.zero_()
+        got = layer.forward(x[:n].contiguous(), [n], [n]).double()
+        assert float((got - want[:n]).norm() / want[:n].norm()) < 4e-3, (fmt, n)
+        assert float((layer.k[0, :n].double() - k_all[0, :n].double()).norm() / k_all[0, :n].double().norm()) < 2e-3

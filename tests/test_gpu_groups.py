@@ -55,7 +55,7 @@ def test_exact_cases_bitwise(rx, m, k, n, group):
     q, s = wl.pack_codes(codes), sc.view(np.uint16)
     ref = oracle.dequant_matmul(x, q, s, m, k, group)
     assert np.abs(ref).max() <= 2048 and np.abs(ref).max() > 0
-    for with_ws in (False, True):               # with a workspace 2..128 rows take the few-row split-K kernel
+    for with_ws in (False, True):               # with a workspace 2..64 rows take a few-row kernel
         got = gpu_matmul(rx, x.astype(np.float16).view(np.uint16), q, s, m, k, with_ws=with_ws, group=group).view(np.float16).astype(np.float32)
         assert np.array_equal(got, ref), with_ws
     codes = np.full((m, k), 8, dtype=np.uint8)

@@ -382,8 +382,7 @@ def test_repeated_decode_call_is_reproducible_and_raises_no_flag(rx):
 
 # ------------------------------------------------------------------------- MFMA GEMM path (n >= 16, k % 128 == 0)
 @pytest.mark.parametrize("m,k,n", [(64, 128, 16), (260, 256, 33), (512, 4096, 128), (256, 11008, 17), (1024, 1024, 511),
-                                   # two launches: the first 8192 weight rows on 256 x 256 tiles (one full round of them at 2048
-                                   # rows of x), the last 256 on 128 x 256 tiles
+                                   # (each tile, and the form of two launches, is met in test_gpu_tiles.py)
                                    (8448, 256, 2048)])
 def test_gemm_integer_valued_bitwise(rx, m, k, n):
     r = np.random.RandomState(m + k + n)
@@ -435,7 +434,7 @@ def test_skinny_integer_valued_bitwise(rx, m, k, n):
 
 @pytest.mark.parametrize("m,k,n", [(768, 256, 3), (4096, 4096, 16), (8192, 8192, 16), (512, 28672, 7), (12288, 4096, 40), (1000, 1024, 64),
                                    (4096, 4096, 128), (1000, 11008, 97), (768, 256, 65),
-                                   (4096, 4096, 200), (4096, 11008, 130), (8192, 1024, 511)])     # k-split tiled GEMM (8, 8 and 2 splits)
+                                   (4096, 4096, 200), (4096, 11008, 130), (8192, 1024, 511)])     # tiled GEMM, the first two cut along k
 def test_skinny_random_against_oracle_and_reproducible(rx, m, k, n):
     q, s = wl.qmat(8, m * 7 + k, m, k)
     x = wl.normal_f16_bits(8, n, (n, k))
@@ -528,9 +527,9 @@ def test_llama7b_layer_two_to_five_decode_rows_on_both_paths(rx, matvec_rows):
 
 def test_llama7b_layer_row_counts_around_the_dispatch_boundaries(rx):
     """The same binary picks the kernels from n: up to four rows of a small model stay on the matvec kernels (two or
-    four rows of x share one pass over the weights), five take the few-row path; at 64 rows every matmul is the few-row
-    kernel, at 65 and 96 the tall gate/up matrix goes to the tiled GEMM while the other three stay (their finishing
-    passes still fold the light steps)."""
+    four rows of x share one pass over the weights), five take the few-row path; at 64 rows every matmul is a few-row
+    kernel, at 65 and 96 all four go to the tiled GEMM, cut along k where its tiles are few (the finishing passes
+    still fold the light steps)."""
     calls = [([40, 25], [40, 25], [0, 1]),            # 65 rows, two prefills
              ([1, 1], [41, 26], [0, 1]),              # two decode rows
              ([1, 1, 1], [42, 27, 1], [0, 1, 2]),     # three
@@ -545,8 +544,8 @@ def test_llama7b_layer_row_counts_around_the_dispatch_boundaries(rx):
 @pytest.mark.parametrize("n", [200, 511, 2048])
 def test_llama7b_layer_prefill_full_sizes(rx, n):
     """The remaining row counts of the symbolic-n configuration, every row and the whole appended cache against the
-    oracle (200: the tiled GEMM of the output and down projections is cut along k into 4 splits, finished by the few-row
-    kernel's finishing pass; 511: ragged tiles everywhere, 2 splits; 2048: the size the prefill figures are quoted on)."""
+    oracle (200: the tiled GEMM of the output and down projections is cut along k, finished by the few-row kernel's
+    finishing pass; 511: ragged tiles everywhere; 2048: the size the prefill figures are quoted on, QKV in two launches)."""
     outs, (Kg, Vg), (Ko, Vo) = run_schedule(rx, wl.LLAMA7B, 2, n, [([n], [n], None)])
     assert_close(*outs[0], "7B prefill n=%d" % n)
     assert_close(Kg[0, :n], Ko[0, :n], "appended K", atol=5e-3, rtol=5e-3)
@@ -568,7 +567,7 @@ def gpu_half_matmul(rx, x_bits, w_bits):
                                    (700, 1024, 513), (250, 1000, 40), (1000, 4096 + 64, 40)])      # the last two: shapes the GEMM cannot take
 def test_half_matmul_against_oracle(rx, m, k, n):
     """Plain fp16 weights through the same dispatch on n: passes of up to 8 rows through the matvec kernel below the
-    crossover, the tiled MFMA GEMM without its decode step from there on (every tile shape, ragged edges), and the
+    crossover, the tiled MFMA GEMM without its decode step from there on (ragged edges), and the
     matvec passes again for matrices the GEMM cannot take (m % 4 != 0, k % 128 != 0)."""
     w = wl.normal_f16_bits(9, m * 3 + k, (m, k))
     w = (wl.f16_bits_to_f32(w) * 0.02).astype(np.float16).view(np.uint16)          # weight scale of the int4 workloads

@@ -1,5 +1,5 @@
-"""GPU tests of the tiled GEMM's plan: tiles of 64 to 256 x-rows and k splits at the row counts around their edges, and of the
-attention kernel's token tiles."""
+"""GPU tests of the tiled GEMM: every tile, k cut and the two-launch form on its own, row counts around the tiles' edges; and of the
+attention kernel's token tiles and softmax."""
 import numpy as np
 import pytest
 
@@ -46,6 +46,47 @@ def test_row_counts_around_the_tile_edges(rx, m, k, group, with_ws):
         want = x.double() @ ref.t()
         assert float((out.double() - want).norm() / want.norm()) < REL, (m, k, n)
         assert bool((ws[size:] == 7).all())
+
+
+# (m, k, n, tile rows, tile columns, k splits, weight rows of a launch of wide tiles in front); a weight row, and where it can be a row of x,
+# beside the edge of a tile
+ONE_PASS = [(132, 256, 33, 128, 64, 1, 0), (16388, 256, 65, 128, 128, 1, 0), (16388, 256, 129, 128, 192, 1, 0), (16388, 256, 200, 128, 256, 1, 0),
+            (22020, 256, 257, 256, 192, 1, 0), (16388, 256, 600, 256, 256, 1, 0), (16388, 4096, 1200, 128, 256, 1, 13056)]
+SPLIT = [(132, 1024, 65, 128, 64, 2, 0), (132, 4096, 65, 128, 64, 8, 0), (4100, 2048, 65, 128, 128, 4, 0), (4100, 5632, 128, 128, 128, 5, 0),
+         (8196, 4096, 129, 128, 192, 2, 0), (4100, 11008, 129, 128, 192, 6, 0), (8196, 11008, 200, 128, 256, 3, 0), (12292, 11008, 257, 256, 192, 2, 0)]
+
+
+@pytest.mark.parametrize("fmt,case", [("q4", c) for c in ONE_PASS + SPLIT] + [("q3", c) for c in ONE_PASS[:6]] + [("f16", c) for c in ONE_PASS[:4]])
+def test_every_tile_exactly(rx, fmt, case):
+    """Small integers: every sum is a whole number below 2048, so the result is exact whatever the order of the sums."""
+    m, k, n, *planned = case
+    g = _gen(m + k + n)
+    if fmt == "f16":
+        w = torch.randint(-8, 8, (m, k), device="cuda", generator=g).half()
+        ref, size = w.double(), 0
+    else:
+        q = torch.randint(-2 ** 31, 2 ** 31 - 1, (m, k // 8 if fmt == "q4" else 3 * k // 32), device="cuda", dtype=torch.int32, generator=g)
+        s = torch.randint(1, 3, (m, k // 32), device="cuda", generator=g).half()
+        w = rx.QMat(q, s, m, k, 32)
+        codes = torch.empty(m, k, dtype=torch.int8, device="cuda")
+        rx.check((rx.relax_unpack_int4 if fmt == "q4" else rx.relax_unpack_q3_native)(w, codes))
+        ref = codes.double() * s.double().repeat_interleave(32, 1)
+        size = rx.relax_matmul_workspace_bytes(w, n) if planned[2] > 1 else 0
+    rc, kernel, splits, rows, cols, wide = rx.relax_plan_matmul(fmt, n, m, k, size)
+    assert (rc, kernel, [rows, cols, splits, wide]) == (rx.OK, rx.KERNEL_TILED, planned)
+    x = torch.zeros(n, k, device="cuda")
+    x.scatter_(1, torch.randint(0, k, (n, 20), device="cuda", generator=g), torch.randint(-3, 4, (n, 20), device="cuda", generator=g).float())
+    x, out = x.half(), torch.full((n, m), float("nan"), device="cuda", dtype=torch.float16)
+    ws = torch.full((size + 4096,), 7, dtype=torch.uint8, device="cuda")
+    if fmt == "q4":
+        rx.check(rx.relax_dequant_matmul(x, w, out, n, ws if size else None, size))
+    elif fmt == "q3":
+        rx.check(rx.relax_dequant_matmul_q3_native(x, w, out, n))
+    else:
+        rx.check(rx.relax_half_matmul(x, w, out, n, m, k))
+    want = x.double() @ ref.t()
+    assert float(want.abs().max()) <= 2048 and torch.equal(out.double(), want)
+    assert bool((ws[size:] == 7).all())
 
 
 @pytest.mark.parametrize("d,heads,kv_heads", [(128, 8, 2), (64, 8, 8)])

@@ -99,7 +99,7 @@ def run_schedule(rx, shape, seed, cap, calls, slots=1):
 
 @pytest.mark.gpu
 def test_gpu_layer_small_prefill_decode_and_ragged_batch(rx):
-    """Grouped heads, k = 256 and 704 (matvec passes only: 704 is not a multiple of 128): a prefill, decode steps, a ragged
+    """Grouped heads, k = 256 and 704 (704 is not a multiple of 128: matvec passes): a prefill, decode steps, a ragged
     batch over three slots."""
     calls = [([21], [21], [0]), ([1], [22], [0]), ([1], [23], [0]), ([3, 1, 5], [3, 24, 5], [1, 0, 2]), ([1, 1, 1], [4, 25, 6], [1, 0, 2])]
     run_schedule(rx, F16_SMALL, 13, 40, calls, slots=3)
@@ -107,7 +107,7 @@ def test_gpu_layer_small_prefill_decode_and_ragged_batch(rx):
 
 @pytest.mark.gpu
 def test_gpu_layer_mid_through_matvec_and_gemm(rx):
-    """k = 2048 and 5632: one decode row and a few rows through the matvec passes, 40 and 130 rows through the tiled GEMM."""
+    """k = 2048 and 5632: one decode row through the fused launches, a few rows through the streaming kernel, 40 and 130 rows through the tiled GEMM."""
     calls = [([40], [40], None), ([1], [41], None), ([3], [44], None), ([130], [174], None), ([1], [175], None)]
     run_schedule(rx, F16_MID, 17, 192, calls)
 

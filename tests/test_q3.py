@@ -239,7 +239,7 @@ def test_gpu_native_matmul_random(rx, m, k, n):
 
 
 # From 16 rows of x on, a matrix with k % 128 == 0 and m % 4 == 0 goes through the tiled MFMA GEMM (3-bit decode on the way
-# into LDS); every tile shape of it is met below (n <= 64: 128 x 64; <= 128: 128 x 128; above: 128 x 256 and 256 x 256).
+# into LDS) unless the streaming few-row kernel takes it; each tile is met in test_gpu_tiles.py.
 @pytest.mark.gpu
 @pytest.mark.parametrize("m,k,n", [(128, 256, 16), (64, 4096, 40), (260, 1024, 100), (512, 2048, 200), (1024, 1024, 300), (96, 16384, 17)])
 def test_gpu_native_gemm_integer_valued_bitwise(rx, m, k, n):
@@ -338,7 +338,7 @@ def test_gpu_q3_layer_small_prefill_decode_and_ragged_batch(rx):
 
 @pytest.mark.gpu
 def test_gpu_q3_layer_mid_through_matvec_and_gemm(rx):
-    """k = 2048 and 5632: one decode row and a few rows through the matvec passes, 40 and 130 rows through the tiled GEMM."""
+    """k = 2048 and 5632: one decode row through the fused launches, a few rows through the streaming kernel, 40 and 130 rows through the tiled GEMM."""
     calls = [([40], [40], None), ([1], [41], None), ([3], [44], None), ([130], [174], None), ([1], [175], None)]
     run_q3_schedule(rx, Q3_MID, 17, 192, calls)
 
