@@ -202,9 +202,10 @@ relax_status relax_dequant_matmul(const uint16_t *x, const relax_qmat *w, uint16
  * matrix-vector kernel (the one the LM head uses) for a few rows, the tiled MFMA GEMM without its decode
  * step (k % 128 == 0, m % 4 == 0) from the row count on at which its estimated time falls below that of the
  * passes -- 24 rows on a 4096 x 4096 matrix, 8 on 22016 x 4096 (measured: bench.py --workload half_sweep).
- * 2 .. 32 rows of up to 8192 columns (k % 128 == 0, m % 4 == 0, out 8-byte aligned; 4096 from 17 rows on) take
- * the streaming few-row kernel instead of either: one pass over the matrix.
- * the test switch "half_matmul_gemm_rows" (relax_mi355_bench.h) with r > 0 fixes the crossover at r rows instead (0, the
+ * 2 .. 32 rows of up to 6144 or of 7169 .. 8192 columns (k % 128 == 0, m % 4 == 0, out 8-byte aligned; up to 4096 from
+ * 17 rows on) take the streaming few-row kernel instead of either, one pass over the matrix, unless 2, 4 or 8 rows are
+ * served faster by a pass of the matrix-vector kernel (relax_plan_matmul in relax_mi355_bench.h tells).
+ * The test switch "half_matmul_gemm_rows" (relax_mi355_bench.h) with r > 0 fixes the crossover at r rows instead (0, the
  * default: by estimate).  Device pointers, x and w 16-byte aligned.  Errors: NULL, SHAPE (n<1, m<1, k<8,
  * k%8, alignment), UNSUPPORTED (k > 73728).                                                                */
 relax_status relax_half_matmul(const uint16_t *x, const uint16_t *w, uint16_t *out, int32_t n, int32_t m,
@@ -324,9 +325,10 @@ relax_status relax_dequant_matmul_q3(const uint16_t *x, const relax_qmat *w, uin
  * relax_unpack_q3_native: out int8 [m,k] in -4..3 from a native matrix -- equals relax_unpack_q3 of the canonical one.
  * relax_dequant_matmul_q3_native: out[n,m] fp16 = x[n,k] times the decoded native matrix, fp32 accumulation.  Up to 15
  * rows of x are taken 4, 2 or 1 per pass over the matrix (k <= 4096: 4; k <= 8192: 2), the decode of a weight shared
- * by the rows of a pass, so a few rows cost little more than one (k <= 12288).  2 .. 32 rows with k % 256 == 0 (and k
- * within what a launch without workspace holds: 12288 up to 16 rows, 6144 beyond), m % 4 == 0, s 4-byte and out 8-byte
- * aligned take the streaming few-row MFMA kernel: one pass.  Else, from 16 rows on, a matrix with
+ * by the rows of a pass, so a few rows cost little more than one (k <= 12288).  2 .. 64 rows with k % 256 == 0 (and k
+ * within what a launch without workspace holds: 12288 up to 16 rows, 6144 up to 32, 2048 beyond), m % 4 == 0, s 4-byte and
+ * out 8-byte aligned take the streaming few-row MFMA kernel, one pass, except where one matrix-vector pass or the GEMM is
+ * faster (two rows of up to 8192 columns, small matrices).  Else, from 16 rows on, a matrix with
  * k % 128 == 0 and m % 4 == 0 (out 8-byte aligned) goes through the tiled MFMA GEMM that serves the 4-bit format at
  * large n, its decode step replaced by the 3-bit one: the matrix is read once whatever n is, and k is not limited.
  * x 16-byte aligned; errors as the canonical call. */
@@ -341,7 +343,8 @@ relax_status relax_dequant_matmul_q3_native(const uint16_t *x, const relax_qmat 
  * matrix-vector kernel (norms, rotary + append, attention merge, residuals and SwiGLU inside the four launches, fp32 sums
  * not rounded in between).  From two rows on the layer is a sequence of launches of their own -- RMSNorm, matmul, rotary +
  * append, attention, matmul, residual add, RMSNorm, matmul, SwiGLU, matmul, residual add.  A matmul that the streaming few-row
- * kernel takes (up to 32 rows, some up to 64) has the step behind it as its epilogue, on unrounded fp32 sums; the others follow
+ * kernel takes (up to 64 rows), or the tiled GEMM cut along k, has the step behind it as its epilogue or in its finishing
+ * pass, on unrounded fp32 sums; the others follow
  * the dispatch on n of relax_dequant_matmul_q3_native, their output rounded to fp16 before the step.  The residual stream
  * x1 stays fp32 between the two halves of the layer.  Its workspace is its own: relax_layer_q3_workspace_bytes(dims, n_max,
  * L_max, B_max) bytes, 256-byte aligned (0 for invalid arguments); the first 256 bytes are the flag line of

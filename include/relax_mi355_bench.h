@@ -15,10 +15,11 @@ extern "C" {
 #endif
 
 /* Test switches.
- * "fuse_finish" (default 1): in the few-row path (2 <= n <= 128: batched decode, short prefills) the finishing pass of a
- * split-K matmul also does the light step that follows it (rotary embedding + KV append after QKV, the RMSNorm after
- * the output projection, and in relax_model_step the first RMSNorm of the next layer after the down projection:
- * Sec. 4.2 operator fusion); 0 runs them as launches of their own.  Results are identical bit for bit either way.
+ * "fuse_finish" (default 1): in relax_decoder_layer and relax_model_step on the matrix path (from two rows on) the finishing
+ * pass of a matmul that is cut along k, or the epilogue of a streaming one, also does the light step that follows it (rotary
+ * embedding + KV append after QKV; in a finishing pass the RMSNorm after the output projection, and in relax_model_step
+ * the first RMSNorm of the next layer after the down projection: Sec. 4.2 operator fusion); 0 runs them as launches of
+ * their own.  Results are identical bit for bit either way.
  * "gemm_waves_per_simd" (default 2): the 256 x 256 tile of the tiled GEMM runs as eight wavefronts (two per SIMD) or, with 1,
  * as four (one per SIMD); identical results.
  * "layer_matvec_rows" (default 4, 1 .. 64): relax_decoder_layer and relax_model_step keep a call of up to this many rows on

@@ -897,9 +897,10 @@ relax_status relax_decoder_layer(const relax_layer_dims *dims, const relax_layer
 }  // extern "C"
 
 // ---- one decoder layer on 3-bit weights (native layout) ---------------------------------------------------------------
-// The same layer, composed of launches of their own: the 3-bit matmuls have the plain fp16 epilogue only, so the light
-// steps run between them (RMSNorm, rotary + append, attention, residual adds, SwiGLU).  Its workspace is laid out one
-// intermediate after the other (nothing is shared: the schedule differs from the one the planner of the 4-bit layer walks).
+// The same layer, composed of launches of their own (RMSNorm, matmul, rotary + append, attention, residual adds, SwiGLU); a matmul on the
+// streaming few-row kernel, or cut along k, does the step behind it as its epilogue or in its finishing pass (flat_layer below).
+// Its workspace is laid out one intermediate after the other (the schedule differs from the one the planner of the 4-bit layer
+// walks); partial rows use what is dead at that point.
 // The layer on plain fp16 weights further down is the same sequence around relax_half_matmul's dispatch and shares the layout.
 namespace {
 struct Q3Plan {
