@@ -28,6 +28,7 @@
 //     Narrower tiles (64 weight rows per wavefront; 32 or 64 x-rows per wavefront) are picked by the launcher
 //     when the wide one would leave CUs idle.
 #include <atomic>
+#include <iterator>
 
 #include "relax_common.h"
 
@@ -558,7 +559,10 @@ TilePlan tile_plan(int wmode, int m, int k, int n, int epi, size_t partial_float
     const int most = n <= kSplitKMaxN ? kSplitKMax : 1;
     TilePlan p = {2, 1, 1, nkb, 0, 0.0};
     double best_us = 0.0;
-    for (const TileCost &t : wmode == W_F16 ? kTilesF16 : kTiles) {
+    const TileCost *const first = wmode == W_F16 ? std::begin(kTilesF16) : std::begin(kTiles);
+    const TileCost *const last = wmode == W_F16 ? std::end(kTilesF16) : std::end(kTiles);
+    for (const TileCost *c = first; c != last; ++c) {
+        const TileCost &t = *c;
         if (t.nf > 2 && n <= 128) continue;               // (one x tile is enough; the wide ones were not measured there)
         const long tiles = blocks(t.mf, t.nf);
         for (int s = 1; s <= most && (s == 1 || nkb / s >= 8); ++s) {
