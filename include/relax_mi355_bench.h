@@ -20,8 +20,7 @@ extern "C" {
  * embedding + KV append after QKV; in a finishing pass the RMSNorm after the output projection, and in relax_model_step
  * the first RMSNorm of the next layer after the down projection: Sec. 4.2 operator fusion); 0 runs them as launches of
  * their own.  Results are identical bit for bit either way.
- * "gemm_waves_per_simd" (default 2): the 256 x 256 tile of the tiled GEMM runs as eight wavefronts (two per SIMD) or, with 1,
- * as four (one per SIMD); identical results.
+ * "gemm_waves_per_simd" (1 or 2): accepted, without effect (the tiled GEMM has one form per tile).
  * "layer_matvec_rows" (default 4, 1 .. 64): relax_decoder_layer and relax_model_step keep a call of up to this many rows on
  * the matrix-vector kernels (two or four rows of x share one pass over the weights): two rows on every model, more when
  * every matrix of the layer is at most "layer_matvec_mb" MB of packed codes (default 96, 0 .. 4096) -- a model that mostly

@@ -2,8 +2,11 @@
 from __future__ import annotations
 
 import os
+import re
+import shutil
 import subprocess
 import sys
+import tempfile
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -45,11 +48,70 @@ def scratch_users(remarks: str, name_part: str):
     return bad
 
 
+# Sources that write their MFMAs as inline asm (accumulators in place): the compiler does not see to the distances the matrix
+# instructions need there, so the build checks them in the assembly.
+MFMA_ASM = "gemm_packed_"
+OPERAND_SLOTS = 2        # issue slots between a vector operation and an MFMA that reads what it wrote
+RESULT_SLOTS = 18        # ... and between an MFMA and another instruction that touches its result
+
+
+def _registers(operand: str):
+    m = re.match(r"^([va])(?:\[(\d+):(\d+)\]|(\d+))$", operand)
+    if not m:
+        return set()
+    lo, hi = (int(m[2]), int(m[3])) if m[2] else (int(m[4]), int(m[4]))
+    return {(m[1], i) for i in range(lo, hi + 1)}
+
+
+def mfma_hazards(assembly: str):
+    """Instructions of an assembly listing that come too soon behind or in front of an MFMA, as texts."""
+    bad, recent = [], []                                     # recent: (name, operands, text), oldest first
+    for line in assembly.splitlines():
+        text = line.split(";")[0].strip()
+        if not text or text.startswith(".") or text.endswith(":"):
+            continue
+        name, _, rest = text.partition(" ")
+        ops = [o.strip() for o in rest.split(",")]
+        touched = set().union(*(_registers(o) for o in ops))
+        is_mfma = name.startswith("v_mfma")
+        slots = 0
+        for pname, pops, ptext in reversed(recent):
+            if slots >= RESULT_SLOTS:
+                break
+            if pname == "s_nop":
+                slots += int(pops[0], 0) + 1
+                continue
+            if pname.startswith("v_mfma"):
+                if not is_mfma and _registers(pops[0]) & touched:
+                    bad.append("%s -> %s" % (ptext, text))
+            elif is_mfma and slots < OPERAND_SLOTS and pname.startswith("v_") and not pname.startswith("v_cmp") and _registers(pops[0]) & touched:
+                bad.append("%s -> %s" % (ptext, text))
+            slots += 1
+        recent = (recent + [(name, ops, text)])[-RESULT_SLOTS - 2:]
+    return bad
+
+
+def _check_mfma_asm(src: str, folder: str) -> None:
+    listings = [f for f in os.listdir(folder) if f.endswith("gfx950.s")]
+    if len(listings) != 1:
+        raise RuntimeError("%s: no assembly listing to check (%s)" % (src, ", ".join(listings)))
+    with open(os.path.join(folder, listings[0])) as f:
+        bad = mfma_hazards(f.read())
+    if bad:
+        raise RuntimeError("%s: instructions too close to an MFMA: %s" % (src, "; ".join(bad[:8])))
+
+
 def _compile(src: str) -> str:
     obj = os.path.join(OBJ, src[:-4] + ".o")
     guarded = src in NO_SCRATCH
-    cmd = [HIPCC] + FLAGS + ([REMARK] if guarded else []) + ["-c", os.path.join(CSRC, src), "-o", obj]
-    res = subprocess.run(cmd, capture_output=True, text=True)
+    cmd = [HIPCC] + FLAGS + ([REMARK] if guarded else [])
+    with tempfile.TemporaryDirectory() as folder:            # of the intermediate files where the assembly is checked
+        checked = src.startswith(MFMA_ASM)
+        kept = os.path.join(folder, os.path.basename(obj)) if checked else obj
+        res = subprocess.run(cmd + (["--save-temps=obj"] if checked else []) + ["-c", os.path.join(CSRC, src), "-o", kept], capture_output=True, text=True)
+        if checked and res.returncode == 0:
+            _check_mfma_asm(src, folder)
+            shutil.move(kept, obj)
     if res.returncode != 0:
         raise RuntimeError("hipcc failed on %s:\n%s\n%s" % (src, res.stdout, res.stderr))
     if guarded:

@@ -418,8 +418,7 @@ relax_status relax_set_option(const char *name, int32_t value)
     }
     if (std::strcmp(name, "gemm_waves_per_simd") == 0) {
         if (value != 1 && value != 2) return RELAX_ERR_SHAPE;
-        gemm_set_waves_per_simd(value);
-        return RELAX_OK;
+        return RELAX_OK;                                 // (no kernel has two forms any more)
     }
     if (std::strcmp(name, "layer_matvec_rows") == 0) {
         if (value < 1 || value > 64) return RELAX_ERR_SHAPE;

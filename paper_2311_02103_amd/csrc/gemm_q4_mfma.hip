@@ -1,42 +1,28 @@
-// Fused int4-decode GEMM for large n (prefill): out[i,r] = sum_c x[i,c] * (u(r,c) - 8) * s[r, c/32].
+// Tiled MFMA GEMM on native 3-bit and on plain fp16 weights for large n (prefill), out[i,r] = sum_c x[i,c] * W(r,c), and the tile plan of
+// these and of the 4-bit kernel (gemm_packed.hip).
 //
-// At large n the contraction is dense and MFMA-bound (Relax, Sec. 5.1: library-grade GEMM for batch sizes
-// other than 1; Sec. 4.2: the 4-bit decode stays fused into the matmul).  Mapping for gfx950:
-//   - v_mfma_f32_32x32x16_f16, fp32 accumulate.  The 256 x 256 tile (weight rows x x-rows) runs as eight wavefronts,
-//     two per SIMD with up to 256 registers each (64 x 128 outputs per wavefront), so that one wavefront's decode, LDS
+//   - v_mfma_f32_32x32x16_f16, fp32 accumulate.  The 256-row tiles (weight rows x x-rows) run as eight wavefronts,
+//     two per SIMD with up to 256 registers each, so that one wavefront's decode, LDS
 //     traffic and waits run under the other's MFMAs; the narrower tiles and the fp16-weight variant run as four
 //     wavefronts (2 x 2), one per SIMD (128 x 256 as eight wavefronts of 64 x 64 was measured 4 to 11 % slower than as
 //     four of 64 x 128: twice the fragment reads per MFMA).
 //   - Both operands go through LDS in 64-wide k blocks, double buffered with ONE LDS-only barrier per block
-//     (global loads of the next block stay in flight across it).  The packed weights are decoded on the way in,
+//     (global loads of the next block stay in flight across it).  3-bit weights are decoded on the way in,
 //     once per workgroup: every thread loads its share of the codes and the group scale of one weight row, turns
-//     them into fp16 values and writes them to LDS.  Decode = merge the nibbles into the mantissa of fp16
-//     1024.0, remove the offset exactly (1024+u-1032, (1024+16u)/16-72), multiply by the group scale: 13
-//     packed-fp16 VALU ops per 8 weights.  A quarter of a block's loads, decode and LDS writes is placed next to the
+//     them into fp16 values and writes them to LDS.  A quarter of a block's loads, decode and LDS writes is placed next to the
 //     MFMAs of each of its four k steps.
-//   - What bounds it: with realistic operand values the matrix pipes of this chip run well below the rate they reach on
-//     all-zero operands (the vendor's fp16 GEMM: 1.5 against 2.3 PFLOP/s at 8192^3; 0.86 to 1.19 PFLOP/s on the four
-//     shapes of the 7B layer at n = 2048), so timing a variant on dummy LDS contents says nothing about its staging cost.
-//   - Each 8-wide k packet is kept in LDS in the order [e0 e4 e1 e5 e2 e6 e3 e7] -- the nibble pairs the decode
-//     produces; the x tile is permuted the same way when it is staged.  The order of k inside an MFMA is free
-//     as long as A and B agree.  Rows are padded to 144 bytes: 16-byte reads and writes of consecutive rows hit
-//     distinct banks.
-//   - For the gate/up matrix a workgroup tile is 128 gate rows + the 128 matching up rows and a wavefront owns
-//     matching fragments of both, so SwiGLU is an element-wise epilogue on the accumulators.
+//   - Rows are padded to 144 bytes: 16-byte reads and writes of consecutive rows hit distinct banks.  fp16 weights and their x tile keep
+//     the packet order [e0 e4 e1 e5 e2 e6 e3 e7] (the order of k inside an MFMA is free as long as A and B agree); 3-bit ones the natural order.
 //   - n, m need not be multiples of the tile: rows are clamped on load and masked on store (one binary for
 //     every n: 17, 511, 2048 ...).  k must be a multiple of 128 (else the matvec path serves the call).
-//     Narrower tiles (64 weight rows per wavefront; 32 or 64 x-rows per wavefront) are picked by the launcher
-//     when the wide one would leave CUs idle.
 #include <atomic>
 #include <iterator>
 
-#include "relax_common.h"
+#include "gemm_tile.h"
 
 namespace relax {
 
 namespace {
-
-std::atomic<int> g_waves_per_simd{2};
 
 typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
 typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
@@ -45,10 +31,6 @@ typedef float float16_t __attribute__((ext_vector_type(16)));
 constexpr int BK = 64;                  // k per main-loop step
 constexpr int kPitch = BK + 8;          // LDS row pitch in halfs (144 bytes)
 
-__device__ __forceinline__ uint32_t pk_add(uint32_t a, uint32_t b)
-{
-    return __builtin_bit_cast(uint32_t, __builtin_bit_cast(half2_t, a) + __builtin_bit_cast(half2_t, b));
-}
 __device__ __forceinline__ uint32_t pk_mul(uint32_t a, uint32_t b)
 {
     return __builtin_bit_cast(uint32_t, __builtin_bit_cast(half2_t, a) * __builtin_bit_cast(half2_t, b));
@@ -66,24 +48,6 @@ __device__ __forceinline__ uint32_t and_or(uint32_t w, uint32_t mask, uint32_t b
     uint32_t r;
     asm("v_and_or_b32 %0, %1, %2, %3" : "=v"(r) : "v"(w), "s"(mask), "v"(bits));
     return r;
-}
-
-// one packed word (8 codes, elements 0..7) and its group scale (fp16 pair s,s) -> 8 fp16 weights in the packet
-// order [e0 e4 e1 e5 e2 e6 e3 e7]; every step is exact except the final multiply by the scale
-__device__ __forceinline__ half8_t decode_word(uint32_t w, uint32_t s2)
-{
-    const uint32_t w8 = w >> 8;
-    const uint32_t a0 = and_or(w, 0x000F000Fu, 0x64006400u);   // 1024 + u   : e0, e4
-    const uint32_t a1 = and_or(w, 0x00F000F0u, 0x64006400u);   // 1024 + 16u : e1, e5
-    const uint32_t a2 = and_or(w8, 0x000F000Fu, 0x64006400u);  // e2, e6
-    const uint32_t a3 = and_or(w8, 0x00F000F0u, 0x64006400u);  // e3, e7
-    const uint32_t kNeg1032 = 0xE408E408u, kSixteenth = 0x2C002C00u, kNeg72 = 0xD480D480u;
-    uint4 r;
-    r.x = pk_mul(pk_add(a0, kNeg1032), s2);
-    r.y = pk_mul(pk_fma(a1, kSixteenth, kNeg72), s2);
-    r.z = pk_mul(pk_add(a2, kNeg1032), s2);
-    r.w = pk_mul(pk_fma(a3, kSixteenth, kNeg72), s2);
-    return __builtin_bit_cast(half8_t, r);
 }
 
 // 3-bit weights in the native word layout (three words per group of 32 columns: word w, position j holds column 2(5w+j)
@@ -120,40 +84,17 @@ __device__ __forceinline__ half8_t decode_q3_packet(uint32_t w0, uint32_t w1, ui
     return __builtin_bit_cast(half8_t, o);
 }
 
-struct GemmArgs {
-    const uint16_t *x;       // [n,k] fp16
-    const uint32_t *q;       // [m,k/8]; Q3 kernels: [m, 3 k / 32] words of the native 3-bit layout
-    const uint16_t *s;       // [m, k / (32 << gshift)]
-    int32_t gshift;          // 32-column sub-group index >> gshift = scale index (quantisation group 32, 64 or 128)
-    const uint16_t *wh;      // FP16W kernels: plain fp16 weights [m,k] instead of q, s
-    int32_t n, m, k;
-    int32_t ldm;             // row pitch of out / resid in elements; 0: m (a launch on a range of the weight rows brings the matrix's m here)
-    int32_t epi;
-    int32_t tiles_m;         // weight-row tiles of the launch (the grid is one-dimensional: tiles_m * x-row tiles * k splits)
-    int32_t tiles_n;         // x-row tiles
-    int32_t kb_per_split;    // k blocks (of BK columns) per k split, even; one split: all of them
-    float *partial;          // more than one k split: [split][n][m] fp32 partial tiles, finished by the few-row kernel's finishing pass
-    uint16_t *out_f16;       // EPI_F16: [n,m]; EPI_RESID_F16: [n,m]; EPI_SWIGLU: [n,m/2]
-    float *out_f32;          // EPI_RESID_F32: [n,m]
-    const void *resid;       // EPI_RESID_F32: fp16 [n,m]; EPI_RESID_F16: fp32 [n,m]
-};
-
-// One-dimensional grid of tiles_m * (x-row tiles) workgroups.  Wavefront w owns MF fragments of 32 weight rows (w & 1 picks which)
-// and NF fragments of 32 x-rows (w >> 1 picks which) of the workgroup tile of 64 MF weight rows x 64 NF x-rows.
-// LDS row r of the weight tile is weight row m0 + r, except for EPI_SWIGLU: rows [0, 32 MF) are gate rows
-// g0 + r and rows [32 MF, 64 MF) the up rows F + g0 + (r - 32 MF).
-// FP16W: the weights are plain fp16 (the fp16-weight configurations of the paper's LLM charts, Sec. 5.1): the staging copies
-// 16-byte packets instead of decoding words, everything else is the same kernel.
-// WM x WN: wavefronts along the weight rows and along the x rows.  2 x 2: four wavefronts, one per SIMD, each with up to 512
-// registers.  4 x 2: eight wavefronts, two per SIMD with up to 256 registers each, so that one wavefront's decode, LDS
-// traffic and waits run under the other's MFMAs (with one wavefront per SIMD the matrix pipe was busy 37 % of the time:
-// counters in profiles/).
-// Q3: 3-bit weights in the native word layout (Sec. 5.3 of the paper deploys 3-bit models): a thread stages whole groups of 32
+// One-dimensional grid of tiles_m * (x-row tiles) workgroups.  Wavefront w owns MF fragments of 32 weight rows (w % WM picks which)
+// and NF fragments of 32 x-rows (w / WM picks which) of the workgroup tile of 32 MF WM weight rows x 32 NF WN x-rows.
+// FP16W: plain fp16 weights (the fp16-weight configurations of the paper's LLM charts, Sec. 5.1): the staging copies 16-byte packets.
+// Otherwise 3-bit weights in the native word layout (Sec. 5.3 of the paper deploys 3-bit models): a thread stages whole groups of 32
 // columns (three words), the decode yields the columns in natural order, so the x tile is staged unpermuted.
-template <int EPI, int MF, int NF, bool FP16W = false, int WM = 2, int WN = 2, bool Q3 = false>
-__global__ __launch_bounds__(WM * WN * 64) void gemm_q4_mfma_kernel(GemmArgs a)
+// WM x WN: wavefronts along the weight rows and along the x rows.  2 x 2: four wavefronts, one per SIMD, each with up to 512
+// registers.  4 x 2: eight wavefronts, two per SIMD with up to 256 registers each.
+template <int MF, int NF, bool FP16W, int WM = 2, int WN = 2>
+__global__ __launch_bounds__(WM * WN * 64) void gemm_mfma_kernel(GemmArgs a)
 {
-    static_assert(!(FP16W && Q3), "one weight format per kernel");
+    constexpr bool Q3 = !FP16W;
     constexpr int ST = 2;                                 // register stages; four were measured and gained nothing
     constexpr int kThreadsG = WM * WN * 64;
     constexpr int BM = 32 * MF * WM, BN = 32 * NF * WN;
@@ -184,20 +125,11 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_q4_mfma_kernel(GemmArgs a)
     const bool whole = 2 * pair + 1 < a.tiles_n;          // the last pair of an odd count is a single tile
     const int tile_m = whole ? r2 >> 1 : r2, tile_n = whole ? 2 * pair + (r2 & 1) : 2 * pair;
     const int n0 = tile_n * BN;
-    const int kw = a.k >> 3;
-    const int F = a.m >> 1;
-    const int ldm = a.ldm > 0 ? a.ldm : a.m;
 
     // ---- staging roles ----
     const int arow = tid / TPR, aword0 = (tid % TPR) * W;
-    int grow;
-    if (EPI == EPI_SWIGLU) {
-        const int g0 = tile_m * (BM / 2);
-        grow = arow < BM / 2 ? min(g0 + arow, F - 1) : F + min(g0 + arow - BM / 2, F - 1);
-    } else {
-        grow = min(tile_m * BM + arow, a.m - 1);
-    }
-    const uint32_t *qsrc = FP16W ? nullptr : Q3 ? a.q + ((size_t)grow * (a.k >> 5) + (aword0 >> 2)) * 3 : a.q + (size_t)grow * kw + aword0;
+    const int grow = min(tile_m * BM + arow, a.m - 1);
+    const uint32_t *qsrc = FP16W ? nullptr : a.q + ((size_t)grow * (a.k >> 5) + (aword0 >> 2)) * 3;
     const uint16_t *ssrc = FP16W ? nullptr : a.s + (size_t)grow * scales_per_row(a.k, a.gshift);
     const int sub0 = aword0 >> 2;                         // first 32-column sub-group of this thread's words inside a k block
     const uint16_t *hsrc = FP16W ? a.wh + (size_t)grow * a.k + aword0 * 8 : nullptr;
@@ -230,15 +162,8 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_q4_mfma_kernel(GemmArgs a)
 #pragma unroll
             for (int i = 0; i < WV; ++i) {
                 if (i * 2 != part) continue;
-                if (Q3) {                                 // group i of this thread: three words, 4-byte aligned
-                    const uint32_t *g3 = qsrc + (kb * (BK / 32) + i) * 3;
-                    S.wq[i].x = g3[0], S.wq[i].y = g3[1], S.wq[i].z = g3[2];
-                } else if (W == 2) {
-                    const uint2 two = *(const uint2 *)(qsrc + kb * (BK / 8));
-                    S.wq[0].x = two.x, S.wq[0].y = two.y;
-                } else {
-                    S.wq[i] = *(const uint4 *)(qsrc + kb * (BK / 8) + i * 4);
-                }
+                const uint32_t *g3 = qsrc + (kb * (BK / 32) + i) * 3;      // group i of this thread: three words, 4-byte aligned
+                S.wq[i].x = g3[0], S.wq[i].y = g3[1], S.wq[i].z = g3[2];
             }
             if (part == 1) {
                 // scale of sub-group g: ssrc[g >> gshift] (neighbouring sub-groups share it when the group is wider than 32)
@@ -277,10 +202,8 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_q4_mfma_kernel(GemmArgs a)
                 continue;
             }
             const uint4 &wv = S.wq[i >> 2];
-            const uint32_t word = (i & 3) == 0 ? wv.x : (i & 3) == 1 ? wv.y : (i & 3) == 2 ? wv.z : wv.w;
             const uint32_t sc = (W == 8 && i >= 4) ? (S.wsc >> 16) : (S.wsc & 0xFFFFu);
-            if (Q3) *(half8_t *)(ad + i * 8) = decode_q3_packet(wv.x, wv.y, wv.z, i & 3, sc | (sc << 16));
-            else *(half8_t *)(ad + i * 8) = decode_word(word, sc | (sc << 16));
+            *(half8_t *)(ad + i * 8) = decode_q3_packet(wv.x, wv.y, wv.z, i & 3, sc | (sc << 16));
         }
         uint16_t *bd = Bs + buf * kBBuf;
 #pragma unroll
@@ -308,12 +231,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_q4_mfma_kernel(GemmArgs a)
     // ---- MFMA roles ----
     int afrag_off[MF];                                    // offset of this lane's fragment rows inside a weight tile
 #pragma unroll
-    for (int f = 0; f < MF; ++f) {
-        int rb;
-        if (EPI == EPI_SWIGLU) rb = (f / (MF / 2)) * (BM / 2) + (wm * (MF / 2) + f % (MF / 2)) * 32;
-        else rb = (wm * MF + f) * 32;
-        afrag_off[f] = (rb + row32) * kPitch + hf * 8;
-    }
+    for (int f = 0; f < MF; ++f) afrag_off[f] = ((wm * MF + f) * 32 + row32) * kPitch + hf * 8;
     const int bfrag_off = (wn * NF * 32 + row32) * kPitch + hf * 8;
 
     float16_t acc[MF][NF];
@@ -377,129 +295,43 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_q4_mfma_kernel(GemmArgs a)
     }
 
     // ---- epilogue.  acc[f][j][v]: tile row of fragment f + 8 (v/4) + 4 (lane/32) + v%4, x row n0 + 32 (NF wn + j) + lane%32 ----
-    if (a.partial) {
-        // k split: the raw fp32 tile goes to partial[split][x row][weight row] (gate rows first, up rows from F on, as in the
-        // matrix), and the finishing pass adds the splits in order and applies the epilogue
-#pragma unroll
-        for (int j = 0; j < NF; ++j) {
-            const int xrow = n0 + (wn * NF + j) * 32 + row32;
-            if (xrow >= a.n) continue;
-            float *dst = a.partial + ((size_t)split * a.n + xrow) * a.m;
-#pragma unroll
-            for (int f = 0; f < MF; ++f)
-#pragma unroll
-                for (int b = 0; b < 4; ++b) {
-                    const int off = b * 8 + hf * 4;
-                    int row;                                     // matrix row of this granule of four
-                    bool ok;
-                    if (EPI == EPI_SWIGLU) {
-                        const int g = tile_m * (BM / 2) + (wm * (MF / 2) + f % (MF / 2)) * 32 + off;
-                        row = (f / (MF / 2)) * F + g, ok = g < F;
-                    } else {
-                        row = tile_m * BM + (wm * MF + f) * 32 + off, ok = row < a.m;
-                    }
-                    if (ok)
-                        *(float4 *)(dst + row) = make_float4(acc[f][j][b * 4], acc[f][j][b * 4 + 1], acc[f][j][b * 4 + 2], acc[f][j][b * 4 + 3]);
-                }
-        }
-        return;
-    }
+    // k split: the raw fp32 tile goes to partial[split][x row][weight row], and the finishing pass adds the splits in order and applies the epilogue
 #pragma unroll
     for (int j = 0; j < NF; ++j) {
         const int xrow = n0 + (wn * NF + j) * 32 + row32;
         if (xrow >= a.n) continue;
 #pragma unroll
-        for (int b = 0; b < 4; ++b) {
-            const int off = b * 8 + hf * 4;
-            if (EPI == EPI_SWIGLU) {
+        for (int f = 0; f < MF; ++f)
 #pragma unroll
-                for (int f = 0; f < MF / 2; ++f) {
-                    const int g = tile_m * (BM / 2) + (wm * (MF / 2) + f) * 32 + off;
-                    if (g < F) {                                 // F % 4 == 0 is checked by the launcher
-                        uint16_t o[4];
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) {
-                            const float gte = acc[f][j][b * 4 + r], up = acc[f + MF / 2][j][b * 4 + r];
-                            o[r] = f2h(gte / (1.0f + __expf(-gte)) * up);
-                        }
-                        *(uint2 *)(a.out_f16 + (size_t)xrow * F + g) = make_uint2(o[0] | ((uint32_t)o[1] << 16), o[2] | ((uint32_t)o[3] << 16));
-                    }
-                }
-            } else {
-#pragma unroll
-                for (int f = 0; f < MF; ++f) {
-                    const int r0 = tile_m * BM + (wm * MF + f) * 32 + off;
-                    if (r0 < a.m) {                              // m % 4 == 0 is checked by the launcher
-                        const size_t at = (size_t)xrow * ldm + r0;
-                        float v[4];
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) v[r] = acc[f][j][b * 4 + r];
-                        if (EPI == EPI_RESID_F32) {
-                            const uint2 xx = *(const uint2 *)((const uint16_t *)a.resid + at);
-                            float4 o;
-                            o.x = h2f((uint16_t)(xx.x & 0xFFFFu)) + v[0], o.y = h2f((uint16_t)(xx.x >> 16)) + v[1];
-                            o.z = h2f((uint16_t)(xx.y & 0xFFFFu)) + v[2], o.w = h2f((uint16_t)(xx.y >> 16)) + v[3];
-                            *(float4 *)(a.out_f32 + at) = o;
-                        } else {
-                            if (EPI == EPI_RESID_F16) {
-                                const float4 rr = *(const float4 *)((const float *)a.resid + at);
-                                v[0] += rr.x, v[1] += rr.y, v[2] += rr.z, v[3] += rr.w;
-                            }
-                            *(uint2 *)(a.out_f16 + at) =
-                                make_uint2(f2h(v[0]) | ((uint32_t)f2h(v[1]) << 16), f2h(v[2]) | ((uint32_t)f2h(v[3]) << 16));
-                        }
-                    }
-                }
+            for (int b = 0; b < 4; ++b) {
+                const int row = tile_m * BM + (wm * MF + f) * 32 + b * 8 + hf * 4;
+                if (row >= a.m) continue;                        // m % 4 == 0 is checked by the launcher
+                const float v0 = acc[f][j][b * 4], v1 = acc[f][j][b * 4 + 1], v2 = acc[f][j][b * 4 + 2], v3 = acc[f][j][b * 4 + 3];
+                if (a.partial) *(float4 *)(a.partial + ((size_t)split * a.n + xrow) * a.m + row) = make_float4(v0, v1, v2, v3);
+                else *(uint2 *)(a.out_f16 + (size_t)xrow * a.m + row) = make_uint2(f2h(v0) | ((uint32_t)f2h(v1) << 16), f2h(v2) | ((uint32_t)f2h(v3) << 16));
             }
-        }
     }
 }
 
-template <int MF, int NF, bool FP16W = false, int WM = 2, int WN = 2, bool Q3 = false>
+template <int MF, int NF, bool FP16W, int WM = 2, int WN = 2>
 hipError_t launch_tile(const GemmArgs &a_in, hipStream_t stream, int splits)
 {
     constexpr int BM = 32 * MF * WM, BN = 32 * NF * WN, kThreadsG = WM * WN * 64;
-    const int rows = a_in.epi == EPI_SWIGLU ? a_in.m / 2 : a_in.m, per_block = a_in.epi == EPI_SWIGLU ? BM / 2 : BM;
     GemmArgs a = a_in;
-    a.tiles_m = (rows + per_block - 1) / per_block;
-    a.tiles_n = (a.n + BN - 1) / BN;
-    const int nkb = a.k / BK, tiles = a.tiles_m * a.tiles_n;
-    if (splits < 2) a.partial = nullptr, a.kb_per_split = nkb, splits = 1;
-    dim3 grid(tiles * splits);
+    if (a.epi != EPI_F16) return hipErrorInvalidValue;   // plain matmuls only: a split launch's epilogue is the finishing pass
+    const dim3 grid(gemm_tile_grid(a, BM, BN, splits));
     const size_t lds = 2 * (size_t)(BM + BN) * kPitch * sizeof(uint16_t);    // up to 147456 bytes: one workgroup per CU
     static std::atomic<bool> attr_done{false};   // setting the attribute twice is harmless; the flag only has to be a defined read
-    if constexpr (FP16W || Q3) {                          // plain matmuls only: one epilogue (a split launch's is the finishing pass)
-        if (a.epi != EPI_F16) return hipErrorInvalidValue;
-        if (!attr_done.load()) {
-            if (hipFuncSetAttribute((const void *)gemm_q4_mfma_kernel<EPI_F16, MF, NF, FP16W, WM, WN, Q3>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
-                return hipErrorInvalidValue;
-            attr_done.store(true);
-        }
-        hipLaunchKernelGGL((gemm_q4_mfma_kernel<EPI_F16, MF, NF, FP16W, WM, WN, Q3>), grid, dim3(kThreadsG), lds, stream, a);
-        return hipGetLastError();
-    }
     if (!attr_done.load()) {
-        const void *ks[4] = {(const void *)gemm_q4_mfma_kernel<EPI_F16, MF, NF, false, WM, WN>, (const void *)gemm_q4_mfma_kernel<EPI_RESID_F32, MF, NF, false, WM, WN>,
-                             (const void *)gemm_q4_mfma_kernel<EPI_RESID_F16, MF, NF, false, WM, WN>, (const void *)gemm_q4_mfma_kernel<EPI_SWIGLU, MF, NF, false, WM, WN>};
-        for (const void *kf : ks)
-            if (hipFuncSetAttribute(kf, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess) return hipErrorInvalidValue;
+        if (hipFuncSetAttribute((const void *)gemm_mfma_kernel<MF, NF, FP16W, WM, WN>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
+            return hipErrorInvalidValue;
         attr_done.store(true);
     }
-    switch (a.epi) {
-    case EPI_F16: hipLaunchKernelGGL((gemm_q4_mfma_kernel<EPI_F16, MF, NF, false, WM, WN>), grid, dim3(kThreadsG), lds, stream, a); break;
-    case EPI_RESID_F32: hipLaunchKernelGGL((gemm_q4_mfma_kernel<EPI_RESID_F32, MF, NF, false, WM, WN>), grid, dim3(kThreadsG), lds, stream, a); break;
-    case EPI_RESID_F16: hipLaunchKernelGGL((gemm_q4_mfma_kernel<EPI_RESID_F16, MF, NF, false, WM, WN>), grid, dim3(kThreadsG), lds, stream, a); break;
-    case EPI_SWIGLU: hipLaunchKernelGGL((gemm_q4_mfma_kernel<EPI_SWIGLU, MF, NF, false, WM, WN>), grid, dim3(kThreadsG), lds, stream, a); break;
-    default: return hipErrorInvalidValue;
-    }
+    hipLaunchKernelGGL((gemm_mfma_kernel<MF, NF, FP16W, WM, WN>), grid, dim3(kThreadsG), lds, stream, a);
     return hipGetLastError();
 }
 
 }  // namespace
-
-// Test switch ("gemm_waves_per_simd"): the 256 x 256 tile runs as eight wavefronts of 64 x 128 (2, the default) or as four of
-// 128 x 128 (1).  Same arithmetic per output element in the same order either way: results are identical.
-void gemm_set_waves_per_simd(int v) { g_waves_per_simd.store(v == 1 ? 1 : 2); }
 
 // Whether the MFMA path can serve this matrix (k in whole 128-blocks, 16-byte aligned rows, 4-row store granules).
 bool gemm_mfma_eligible(const relax_qmat &w, const void *x, int epi)
@@ -664,12 +496,12 @@ hipError_t launch_gemm_q3(const uint16_t *x, const relax_qmat &w, int n, uint16_
     a.x = x, a.q = w.q, a.s = w.s, a.gshift = 0, a.n = n, a.m = w.m, a.k = w.k, a.epi = EPI_F16, a.out_f16 = out, a.partial = partial;
     const TilePlan p = tile_plan(W_Q3, w.m, w.k, n, EPI_F16, partial ? partial_floats : 0);
     a.kb_per_split = p.kb_per_split;
-    if (p.mf == 4 && p.nf == 4) return launch_tile<2, 4, false, 4, 2, true>(a, stream, p.splits);
-    if (p.mf == 4) return launch_tile<2, 3, false, 4, 2, true>(a, stream, p.splits);
-    if (p.nf == 4) return launch_tile<2, 4, false, 2, 2, true>(a, stream, p.splits);
-    if (p.nf == 3) return launch_tile<2, 3, false, 2, 2, true>(a, stream, p.splits);
-    if (p.nf == 2) return launch_tile<2, 2, false, 2, 2, true>(a, stream, p.splits);
-    return launch_tile<2, 1, false, 2, 2, true>(a, stream, p.splits);
+    if (p.mf == 4 && p.nf == 4) return launch_tile<2, 4, false, 4>(a, stream, p.splits);
+    if (p.mf == 4) return launch_tile<2, 3, false, 4>(a, stream, p.splits);
+    if (p.nf == 4) return launch_tile<2, 4, false>(a, stream, p.splits);
+    if (p.nf == 3) return launch_tile<2, 3, false>(a, stream, p.splits);
+    if (p.nf == 2) return launch_tile<2, 2, false>(a, stream, p.splits);
+    return launch_tile<2, 1, false>(a, stream, p.splits);
 }
 
 // k splits of the two launches above with this much workspace: more than one leaves partial rows for launch_skinny_finish
@@ -687,12 +519,11 @@ hipError_t launch_gemm_mfma(const uint16_t *x, const relax_qmat &w, int n, int e
     a.partial = p.splits > 1 ? partial : nullptr;
     a.kb_per_split = p.kb_per_split;
     hipError_t e;
-    const bool eight = g_waves_per_simd.load() == 2;
     if (p.m_big > 0 && p.splits == 1 && epi != EPI_SWIGLU) {
         // rows [0, m_big) on wide tiles, rows [m_big, m) on the narrow ones: two launches on the same stream
         GemmArgs b = a;
         b.m = p.m_big, b.ldm = w.m;
-        e = eight ? launch_tile<2, 4, false, 4, 2>(b, stream, 1) : launch_tile<4, 4>(b, stream, 1);
+        e = launch_packed_tile(b, 4, 4, 1, stream);
         if (e != hipSuccess) return e;
         GemmArgs c = a;
         const size_t skip = (size_t)p.m_big;
@@ -701,14 +532,9 @@ hipError_t launch_gemm_mfma(const uint16_t *x, const relax_qmat &w, int n, int e
         if (c.out_f16) c.out_f16 = a.out_f16 + skip;
         if (c.out_f32) c.out_f32 = a.out_f32 + skip;
         if (c.resid) c.resid = (epi == EPI_RESID_F32) ? (const void *)((const uint16_t *)a.resid + skip) : (const void *)((const float *)a.resid + skip);
-        return launch_tile<2, 4>(c, stream, 1);
+        return launch_packed_tile(c, 2, 4, 1, stream);
     }
-    if (p.mf == 4 && p.nf == 4) e = eight ? launch_tile<2, 4, false, 4, 2>(a, stream, p.splits) : launch_tile<4, 4>(a, stream, p.splits);
-    else if (p.mf == 4) e = eight ? launch_tile<2, 3, false, 4, 2>(a, stream, p.splits) : launch_tile<4, 3>(a, stream, p.splits);
-    else if (p.nf == 3) e = launch_tile<2, 3>(a, stream, p.splits);
-    else if (p.nf == 4) e = launch_tile<2, 4>(a, stream, p.splits);        // 128 x 256: four wavefronts of 64 x 128 beat eight of 64 x 64 by 4 to 11 %
-    else if (p.nf == 2) e = launch_tile<2, 2>(a, stream, p.splits);
-    else e = launch_tile<2, 1>(a, stream, p.splits);
+    e = launch_packed_tile(a, p.mf, p.nf, p.splits, stream);
     if (e != hipSuccess || p.splits < 2) return e;
     return launch_skinny_finish(partial, p.splits, n, w.m, epi, out_f16, out_f32, resid, stream, fuse);
 }

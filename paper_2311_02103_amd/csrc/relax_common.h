@@ -384,7 +384,6 @@ hipError_t launch_swiglu_rows(const uint16_t *gu, uint16_t *act, int n, int F, h
 // MFMA GEMM for large n (gemm_q4_mfma.hip)
 constexpr int kGemmMinN = 16;        // rows from which the MFMA GEMM replaces one matvec pass per row
 bool gemm_mfma_eligible(const relax_qmat &w, const void *x, int epi);
-void gemm_set_waves_per_simd(int v);     // test switch: 2 (default) = eight wavefronts per 256 x 256 tile, 1 = four
 constexpr int kSplitKMax = 8;         // k splits of the tiled GEMM at most
 constexpr int kSplitKMaxN = 512;      // ... and only up to this many rows (the partial tiles are splits * n * m floats)
 size_t gemm_splitk_partial_floats(int m, int k, int n, int epi);
