@@ -255,8 +255,10 @@ relax_status build_seqs(const relax_seqs *sq, const relax_layer_dims &dm, int32_
 // Large batches: the descriptor goes to the device table at the front of the workspace, 128 sequences per launch of a small
 // kernel that carries them in its arguments (the extra symbolic arguments of Sec. 3.3): no host buffer has to outlive the
 // call, nothing is copied from pageable memory, the host never waits, and the launches can be captured in a graph.
-relax_status upload_table(SeqTable &st, const relax_seqs *sq, bool need_table, void *ws, const WsPlan &pl, hipStream_t stream)
+// carry: a table of one launch is left to the caller, who hands it to the first norm of the layer.
+relax_status upload_table(SeqTable &st, const relax_seqs *sq, bool need_table, void *ws, const WsPlan &pl, hipStream_t stream, TableCarry *carry = nullptr)
 {
+    if (carry) carry->table = nullptr;
     if (!need_table) return RELAX_OK;
     int32_t *dev = reinterpret_cast<int32_t *>(static_cast<char *>(ws) + pl.table);
     TableChunk c = {};
@@ -270,7 +272,8 @@ relax_status upload_table(SeqTable &st, const relax_seqs *sq, bool need_table, v
             c.q_start[j] = start, c.q_len[j] = sq->q_lens[b], c.kv_len[j] = sq->kv_lens[b], c.slot[j] = sq->slots ? sq->slots[b] : b;
             start += sq->q_lens[b];
         }
-        if (launch_table_write(dev, c, stream) != hipSuccess) return RELAX_ERR_HIP;
+        if (carry && sq->B <= kTableChunk) carry->table = dev, carry->chunk = c;
+        else if (launch_table_write(dev, c, stream) != hipSuccess) return RELAX_ERR_HIP;
     }
     st.dev = dev;
     return RELAX_OK;
@@ -677,13 +680,20 @@ relax_status check_layer(const relax_layer_dims &dm, const relax_layer_weights *
     return RELAX_OK;
 }
 
+// The first norm of a layer, and with it the descriptor table if that is still to be written
+hipError_t first_norm(const uint16_t *x, const uint16_t *w, uint16_t *y, int32_t n, const relax_layer_dims &dm, const TableCarry *carry, hipStream_t st_)
+{
+    if (carry && carry->table) return launch_rmsnorm_table(x, w, y, n, dm.hidden, dm.rms_eps, *carry, st_);
+    return launch_rmsnorm(x, w, y, n, dm.hidden, dm.rms_eps, st_);
+}
+
 // Enqueues one decoder layer.  Everything has been validated; st is the kernel-side ragged descriptor (its device
-// table, if any, already uploaded); base/pl are the layer workspace and its plan.
+// table, if any, already uploaded or in carry); base/pl are the layer workspace and its plan.
 // next_norm (optional): the RMSNorm weights of the layer that follows; when the few-row path can, it leaves RMSNorm(out) * next_norm in the
 // workspace and sets *xn_done, and the next call passes xn_ready to skip its own first RMSNorm.
 relax_status layer_enqueue(const relax_layer_dims &dm, const relax_layer_weights *wt, const uint16_t *x, const relax_kv_cache *cache,
                            const SeqTable &st, int32_t L_max, uint16_t *out, int32_t n, char *base, const WsPlan &pl, hipStream_t st_,
-                           const uint16_t *next_norm = nullptr, bool xn_ready = false, bool *xn_done = nullptr)
+                           const uint16_t *next_norm = nullptr, bool xn_ready = false, bool *xn_done = nullptr, const TableCarry *carry = nullptr)
 {
     if (xn_done) *xn_done = false;
     const int32_t hd = dm.n_heads * dm.head_dim, qkvw = (dm.n_heads + 2 * dm.n_kv_heads) * dm.head_dim;
@@ -755,7 +765,7 @@ relax_status layer_enqueue(const relax_layer_dims &dm, const relax_layer_weights
             return false;
         };
         timer.before(0);
-        if (!xn_ready && launch_rmsnorm(x, wt->norm_attn, xn, n, dm.hidden, dm.rms_eps, st_) != hipSuccess) return RELAX_ERR_HIP;
+        if (!xn_ready && first_norm(x, wt->norm_attn, xn, n, dm, carry, st_) != hipSuccess) return RELAX_ERR_HIP;
         SkinnyFuse fq = {};
         fq.dm = &dm, fq.cache = cache, fq.st = &st;
         if (!fused(xn, wt->wqkv, EPI_F16, qkv, nullptr, nullptr, fq)) {
@@ -788,6 +798,7 @@ relax_status layer_enqueue(const relax_layer_dims &dm, const relax_layer_weights
         timer.after(4);
         return RELAX_OK;
     }
+    if (carry && carry->table && launch_table_write(carry->table, carry->chunk, st_) != hipSuccess) return RELAX_ERR_HIP;
 
     uint16_t *qbuf = reinterpret_cast<uint16_t *>(base + pl.qbuf);
     uint16_t *attn = reinterpret_cast<uint16_t *>(base + pl.attn);
@@ -888,9 +899,10 @@ relax_status relax_decoder_layer(const relax_layer_dims *dims, const relax_layer
     if (rc != RELAX_OK) return rc;
     const WsPlan pl = plan_ws(dm, n, L_max, seqs->B);
     if (ws_bytes < pl.total || (reinterpret_cast<uintptr_t>(ws) & 255) != 0) return RELAX_ERR_WORKSPACE;
-    rc = upload_table(st, seqs, need_table, ws, pl, st_);
+    TableCarry carry;
+    rc = upload_table(st, seqs, need_table, ws, pl, st_, &carry);
     if (rc != RELAX_OK) return rc;
-    return layer_enqueue(dm, wt, x, cache, st, L_max, out, n, static_cast<char *>(ws), pl, st_);
+    return layer_enqueue(dm, wt, x, cache, st, L_max, out, n, static_cast<char *>(ws), pl, st_, nullptr, false, nullptr, &carry);
 }
 
 }  // extern "C"
@@ -956,7 +968,7 @@ hipError_t q3_matmul(const uint16_t *x, const relax_qmat &w, int32_t n, uint16_t
 template <typename Plain, typename Ranges, typename Streamed>
 relax_status flat_layer(const relax_layer_dims &dm, const uint16_t *norm_attn, const uint16_t *norm_ffn, const uint16_t *x, const relax_kv_cache &cache,
                         const SeqTable &st, int32_t L_max, uint16_t *out, int32_t n, char *base, const Q3Plan &pl, const Plain &plain,
-                        const Ranges &ranges, const Streamed &streamed, hipStream_t st_)
+                        const Ranges &ranges, const Streamed &streamed, const TableCarry &carry, hipStream_t st_)
 {
     uint16_t *xn = reinterpret_cast<uint16_t *>(base + pl.ws.xn), *qkv = reinterpret_cast<uint16_t *>(base + pl.ws.qkv);
     uint16_t *attn = reinterpret_cast<uint16_t *>(base + pl.ws.attn), *act = reinterpret_cast<uint16_t *>(base + pl.ws.act);
@@ -967,7 +979,7 @@ relax_status flat_layer(const relax_layer_dims &dm, const uint16_t *norm_attn, c
     const int32_t hd = dm.n_heads * dm.head_dim, qkvw = hd + 2 * dm.n_kv_heads * dm.head_dim;
     const size_t nh = (size_t)n * dm.hidden;
 #define RELAX_TRY(call) do { if ((call) != hipSuccess) return RELAX_ERR_HIP; } while (0)
-    RELAX_TRY(launch_rmsnorm(x, norm_attn, xn, n, dm.hidden, dm.rms_eps, st_));
+    RELAX_TRY(first_norm(x, norm_attn, xn, n, dm, &carry, st_));
     SkinnyFuse fq = {};
     fq.dm = &dm, fq.cache = &cache, fq.st = &st;
     const relax_qmat qkv_shape = {nullptr, nullptr, qkvw, dm.hidden, 32};
@@ -1040,7 +1052,8 @@ relax_status relax_decoder_layer_q3(const relax_layer_dims *dims, const relax_la
     if (rc != RELAX_OK) return rc;
     const Q3Plan pl = plan_q3(dm, n, L_max, seqs->B);
     if (ws_bytes < pl.total || (reinterpret_cast<uintptr_t>(ws) & 255) != 0) return RELAX_ERR_WORKSPACE;
-    rc = upload_table(st, seqs, need_table, ws, pl.ws, st_);
+    TableCarry carry;
+    rc = upload_table(st, seqs, need_table, ws, pl.ws, st_, &carry);
     if (rc != RELAX_OK) return rc;
 
     char *base = static_cast<char *>(ws);
@@ -1102,7 +1115,7 @@ relax_status relax_decoder_layer_q3(const relax_layer_dims *dims, const relax_la
         }
         return launch_fewrow_q3(xin, *mats[i], n, epi, kr, o16, o32, resid, part, st_, f);
     };
-    return flat_layer(dm, wt->norm_attn, wt->norm_ffn, x, *cache, st, L_max, out, n, base, pl, plain, ranges, streamed, st_);
+    return flat_layer(dm, wt->norm_attn, wt->norm_ffn, x, *cache, st, L_max, out, n, base, pl, plain, ranges, streamed, carry, st_);
 }
 
 // ---- the same sequence on plain fp16 weights (the fp16 models of the paper's LLM evaluation, Sec. 5.1) -----------------
@@ -1135,7 +1148,8 @@ relax_status relax_decoder_layer_f16(const relax_layer_dims *dims, const relax_l
     if (rc != RELAX_OK) return rc;
     const Q3Plan pl = plan_q3(dm, n, L_max, seqs->B);
     if (ws_bytes < pl.total || (reinterpret_cast<uintptr_t>(ws) & 255) != 0) return RELAX_ERR_WORKSPACE;
-    rc = upload_table(st, seqs, need_table, ws, pl.ws, st_);
+    TableCarry carry;
+    rc = upload_table(st, seqs, need_table, ws, pl.ws, st_, &carry);
     if (rc != RELAX_OK) return rc;
 
     char *base = static_cast<char *>(ws);
@@ -1198,7 +1212,7 @@ relax_status relax_decoder_layer_f16(const relax_layer_dims *dims, const relax_l
         }
         return launch_fewrow_f16(xin, mats[i], n, ms[i], ks[i], epi, kr, o16, o32, resid, part, st_, f);
     };
-    return flat_layer(dm, wt->norm_attn, wt->norm_ffn, x, *cache, st, L_max, out, n, base, pl, plain, ranges, streamed, st_);
+    return flat_layer(dm, wt->norm_attn, wt->norm_ffn, x, *cache, st, L_max, out, n, base, pl, plain, ranges, streamed, carry, st_);
 }
 
 }  // extern "C"

@@ -510,6 +510,12 @@ struct TableChunk {
     int32_t q_start[kTableChunk], q_len[kTableChunk], kv_len[kTableChunk], slot[kTableChunk];
 };
 hipError_t launch_table_write(int32_t *table, const TableChunk &chunk, hipStream_t stream);
+// A chunk that is the whole table, still to be written: the first norm of the layer can take it along (launch_rmsnorm_table).
+struct TableCarry {
+    int32_t *table;                    // nullptr: nothing to write
+    TableChunk chunk;
+};
+hipError_t launch_rmsnorm_table(const uint16_t *x, const uint16_t *w, uint16_t *y, int n, int H, float eps, const TableCarry &t, hipStream_t stream);
 
 // A quantised matrix as the streaming kernels pass it around
 struct DLMat {
