@@ -758,8 +758,9 @@ relax_status layer_enqueue(const relax_layer_dims &dm, const relax_layer_weights
                 fuse_err = launch_gemm_skinny(xin, wq, n, epi, o16, o32, resid, skinny_ws, st_, &f);
                 return true;
             }
-            if (n >= kGemmMinN && gemm_mfma_eligible(wq, xin, epi) && gemm_mfma_splits(wq, n, epi, skinny_ws, pl.mm_floats) > 1) {
-                fuse_err = launch_gemm_mfma(xin, wq, n, epi, o16, o32, resid, st_, skinny_ws, pl.mm_floats, &f);    // k-split tiled GEMM
+            if (n >= kGemmMinN && gemm_mfma_eligible(wq, xin, epi) &&
+                (gemm_mfma_splits(wq, n, epi, skinny_ws, pl.mm_floats) > 1 || (epi == EPI_F16 && gemm_rope_fuse_ok(dm, *cache, wq)))) {
+                fuse_err = launch_gemm_mfma(xin, wq, n, epi, o16, o32, resid, st_, skinny_ws, pl.mm_floats, &f);    // tiled GEMM
                 return true;
             }
             return false;

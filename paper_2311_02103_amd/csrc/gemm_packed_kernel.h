@@ -81,6 +81,15 @@ __device__ __forceinline__ uint32_t byte_perm(uint32_t hi, uint32_t lo, uint32_t
     return r;
 }
 
+// fp16(a x + c), x fp16, rounded once: what the compiler makes of the sums of products in rope_append_kernel, whose second product it rounds.  Left
+// to contract here, it fuses the other product of the second sum, and results differ in the last place now and then.
+__device__ __forceinline__ uint16_t fma_to_half(float a, uint16_t x, float c)
+{
+    uint32_t r;
+    asm("v_fma_mixlo_f16 %0, %1, %2, %3 op_sel_hi:[0,1,0]" : "=v"(r) : "v"(a), "v"((uint32_t)x), "v"(c));
+    return (uint16_t)r;
+}
+
 // eight bytes at the alignment of a scale
 struct __attribute__((packed, aligned(2))) Load8 { uint32_t lo, hi; };
 
@@ -234,9 +243,14 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_packed_kernel(GemmArgs a)
     };
 
     // ---- MFMA roles.  Quarter q of the lanes holds columns 16 q .. 16 q + 15 of a block: eight for each of its two k steps ----
-    // fragment f: rows (wm MF + f) 16 .. of the tile, EPI_SWIGLU: half of the fragments in the gate half, half in the up half
-    const int arow = wm * (EPI == EPI_SWIGLU ? MF / 2 : MF) * 16 + row16;
-    auto frag_row = [](int f) { return EPI == EPI_SWIGLU ? f / (MF / 2) * (BM / 2) + f % (MF / 2) * 16 : f * 16; };
+    // Fragment f: rows (wm MF + f) 16 .. of the tile.  EPI_SWIGLU: half of the fragments in the gate half, half in the up half.  EPI_ROPE_KV:
+    // half of them in the lower half of a head of 128 rows, half in its upper half, so that a lane holds both values of a rotation.
+    constexpr int W2 = MF / 2 * 16;                       // rows of a wavefront in either half
+    const int wrow = EPI == EPI_SWIGLU ? wm * W2 : EPI == EPI_ROPE_KV ? wm * W2 / 64 * 128 + wm * W2 % 64 : wm * MF * 16;
+    const int arow = wrow + row16;
+    auto frag_row = [](int f) {
+        return EPI == EPI_SWIGLU ? f / (MF / 2) * (BM / 2) + f % (MF / 2) * 16 : EPI == EPI_ROPE_KV ? f / (MF / 2) * 64 + f % (MF / 2) * 16 : f * 16;
+    };
     uint32_t wrd = kWs + arow * kWPitch + quarter * 8, srd = kSs + arow * 16 + (quarter >> 1) * 2;
     int wrd_step = kWBuf, srd_step = kSBuf;
     uint32_t xrd[2];
@@ -408,6 +422,47 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_packed_kernel(GemmArgs a)
         }
         return;
     }
+    if constexpr (EPI == EPI_ROPE_KV) {
+        // rotary embedding and KV append with the arithmetic of the kernel that does it alone (on values rounded to fp16): a layer call of the 7B
+        // shape 275 -> 268 us with 300 prompt rows and 20 decode rows, 837.6 -> 834.9 at 2048 rows, where the pieces of 32 bytes that a
+        // quarter of the lanes writes cost most of what the separate launch did.  Position and slot of the tile's x rows are looked up once, a thread per row.
+        int2 *const rows = (int2 *)lds;
+        __syncthreads();
+        for (int t = tid; t < BN; t += T) {
+            const RowInfo ri = row_info(a.seqs, min(n0 + t, a.n - 1));
+            rows[t] = make_int2(ri.pos, ri.slot);
+        }
+        __syncthreads();
+        const int head = (a.first_row + row0 + wrow) >> 7, t0 = (wrow & 127) + off;
+        if (head >= a.h + 2 * a.g) return;
+#pragma unroll
+        for (int j = 0; j < NF; ++j) {
+            const int local = (wn * NF + j) * 16 + row16, xrow = n0 + local;
+            if (xrow >= a.n) continue;
+            const int2 at = rows[local];
+            const size_t token = (size_t)at.y * a.kv_capacity + at.x;
+            uint16_t *dst = head < a.h ? a.out_f16 + (size_t)xrow * ldm + (row0 + wrow) / 128 * 128
+                                       : head < a.h + a.g ? a.kcache + (token * a.g + head - a.h) * 128 : a.vcache + (token * a.g + head - a.h - a.g) * 128;
+#pragma unroll
+            for (int f = 0; f < MF / 2; ++f) {
+                const int t = t0 + f * 16;
+                uint16_t lo[4], hi[4];
+#pragma unroll
+                for (int v = 0; v < 4; ++v) lo[v] = f2h(acc[f][j][v]), hi[v] = f2h(acc[f + MF / 2][j][v]);
+                if (head < a.h + a.g) {
+                    const float4 cs[2] = {*(const float4 *)(a.rope + ((size_t)at.x * 64 + t) * 2), *(const float4 *)(a.rope + ((size_t)at.x * 64 + t + 2) * 2)};
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        const float x1 = h2f(hi[v]), co = v % 2 ? cs[v / 2].z : cs[v / 2].x, si = v % 2 ? cs[v / 2].w : cs[v / 2].y;
+                        hi[v] = fma_to_half(si, lo[v], co * x1), lo[v] = fma_to_half(co, lo[v], -(si * x1));
+                    }
+                }
+                *(uint2 *)(dst + t) = make_uint2(lo[0] | ((uint32_t)lo[1] << 16), lo[2] | ((uint32_t)lo[3] << 16));
+                *(uint2 *)(dst + 64 + t) = make_uint2(hi[0] | ((uint32_t)hi[1] << 16), hi[2] | ((uint32_t)hi[3] << 16));
+            }
+        }
+        return;
+    }
 #pragma unroll
     for (int j = 0; j < NF; ++j) {
         const int xrow = n0 + (wn * NF + j) * 16 + row16;
@@ -462,6 +517,7 @@ hipError_t launch_packed(const GemmArgs &a_in, int splits, hipStream_t stream)
     const dim3 grid(gemm_tile_grid(a, 16 * MF * WM, 16 * NF * WN, splits)), block(WM * WN * 64);
     switch (a.epi) {
     case EPI_F16: hipLaunchKernelGGL((gemm_packed_kernel<EPI_F16, MF, NF, WM, WN>), grid, block, 0, stream, a); break;
+    case EPI_ROPE_KV: hipLaunchKernelGGL((gemm_packed_kernel<EPI_ROPE_KV, MF, NF, WM, WN>), grid, block, 0, stream, a); break;
     case EPI_RESID_F32: hipLaunchKernelGGL((gemm_packed_kernel<EPI_RESID_F32, MF, NF, WM, WN>), grid, block, 0, stream, a); break;
     case EPI_RESID_F16: hipLaunchKernelGGL((gemm_packed_kernel<EPI_RESID_F16, MF, NF, WM, WN>), grid, block, 0, stream, a); break;
     case EPI_SWIGLU: hipLaunchKernelGGL((gemm_packed_kernel<EPI_SWIGLU, MF, NF, WM, WN>), grid, block, 0, stream, a); break;

@@ -507,6 +507,13 @@ hipError_t launch_gemm_q3(const uint16_t *x, const relax_qmat &w, int n, uint16_
 // k splits of the two launches above with this much workspace: more than one leaves partial rows for launch_skinny_finish
 int gemm_flat_splits(int wmode, int n, int m, int k, size_t partial_floats) { return k % (2 * BK) == 0 ? tile_plan(wmode, m, k, n, EPI_F16, partial_floats).splits : 1; }
 
+// Whether the one-pass launch on this QKV matrix can rotate q and k and append k and v in its epilogue
+bool gemm_rope_fuse_ok(const relax_layer_dims &dm, const relax_kv_cache &cache, const relax_qmat &w)
+{
+    return dm.head_dim == 128 && w.m == (dm.n_heads + 2 * dm.n_kv_heads) * 128 &&
+           ((reinterpret_cast<uintptr_t>(cache.k) | reinterpret_cast<uintptr_t>(cache.v)) & 7) == 0 && (reinterpret_cast<uintptr_t>(cache.rope) & 15) == 0;
+}
+
 hipError_t launch_gemm_mfma(const uint16_t *x, const relax_qmat &w, int n, int epi, uint16_t *out_f16, float *out_f32, const void *resid,
                             hipStream_t stream, float *partial, size_t partial_floats, const SkinnyFuse *fuse)
 {
@@ -515,7 +522,12 @@ hipError_t launch_gemm_mfma(const uint16_t *x, const relax_qmat &w, int n, int e
     a.x = x, a.q = w.q, a.s = w.s, a.gshift = gshift_of(w.group), a.n = n, a.m = w.m, a.k = w.k, a.epi = epi;
     a.out_f16 = out_f16, a.out_f32 = out_f32, a.resid = resid;
     const TilePlan p = tile_plan(W_Q4, w.m, w.k, n, epi, partial && (reinterpret_cast<uintptr_t>(partial) & 15) == 0 ? partial_floats : 0);
-    if (fuse && p.splits < 2) return hipErrorInvalidValue;        // a folded light step needs the finishing pass
+    if (fuse && p.splits < 2) {                                   // one pass over k: the rotary step of a QKV matrix is an epilogue, a norm is not
+        if (epi != EPI_F16 || !fuse->dm || !gemm_rope_fuse_ok(*fuse->dm, *fuse->cache, w)) return hipErrorInvalidValue;
+        a.epi = EPI_ROPE_KV;
+        a.h = fuse->dm->n_heads, a.g = fuse->dm->n_kv_heads, a.kv_capacity = fuse->dm->kv_capacity;
+        a.kcache = fuse->cache->k, a.vcache = fuse->cache->v, a.rope = fuse->cache->rope, a.seqs = *fuse->st;
+    }
     a.partial = p.splits > 1 ? partial : nullptr;
     a.kb_per_split = p.kb_per_split;
     hipError_t e;
@@ -528,7 +540,7 @@ hipError_t launch_gemm_mfma(const uint16_t *x, const relax_qmat &w, int n, int e
         GemmArgs c = a;
         const size_t skip = (size_t)p.m_big;
         c.q = a.q + skip * (size_t)(w.k / 8), c.s = a.s + skip * (size_t)scales_per_row(w.k, a.gshift);
-        c.m = w.m - p.m_big, c.ldm = w.m;
+        c.m = w.m - p.m_big, c.ldm = w.m, c.first_row = p.m_big;
         if (c.out_f16) c.out_f16 = a.out_f16 + skip;
         if (c.out_f32) c.out_f32 = a.out_f32 + skip;
         if (c.resid) c.resid = (epi == EPI_RESID_F32) ? (const void *)((const uint16_t *)a.resid + skip) : (const void *)((const float *)a.resid + skip);

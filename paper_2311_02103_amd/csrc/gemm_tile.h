@@ -24,6 +24,12 @@ struct GemmArgs {
     uint16_t *out_f16;       // EPI_F16: [n,m]; EPI_RESID_F16: [n,m]; EPI_SWIGLU: [n,m/2]
     float *out_f32;          // EPI_RESID_F32: [n,m]
     const void *resid;       // EPI_RESID_F32: fp16 [n,m]; EPI_RESID_F16: fp32 [n,m]
+    // EPI_ROPE_KV (a QKV matrix, heads of 128): rotated q goes to out_f16, rotated k and v to the cache
+    int32_t first_row;       // matrix row of the launch's row 0
+    int32_t h, g, kv_capacity;
+    uint16_t *kcache, *vcache;
+    const float *rope;
+    SeqTable seqs;
 };
 
 // Tile counts of a launch and its grid; splits < 2: one pass over k, no partial tiles.

@@ -398,7 +398,9 @@ double gemm_tile_us(int m, int k, int n, int epi, size_t partial_floats);      /
 void gemm_tile_plan(int wmode, int m, int k, int n, int epi, size_t partial_floats, relax_matmul_plan *plan);      // tile and cut of a launch
 struct SkinnyFuse;
 int gemm_mfma_splits(const relax_qmat &w, int n, int epi, const float *partial, size_t partial_floats);
-// fuse: only for a launch that splits (gemm_mfma_splits > 1): the light step folded into its finishing pass
+bool gemm_rope_fuse_ok(const relax_layer_dims &dm, const relax_kv_cache &cache, const relax_qmat &w);
+// fuse: the light step folded into the finishing pass of a launch that splits (gemm_mfma_splits > 1), or rotary + append in the epilogue of
+// one that does not (gemm_rope_fuse_ok)
 hipError_t launch_gemm_mfma(const uint16_t *x, const relax_qmat &w, int n, int epi, uint16_t *out_f16, float *out_f32, const void *resid,
                             hipStream_t stream, float *partial = nullptr, size_t partial_floats = 0, const SkinnyFuse *fuse = nullptr);
 // MFMA matmul for a few rows, split-K with partial tiles in the workspace (gemm_q4_skinny.hip)

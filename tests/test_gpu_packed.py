@@ -38,3 +38,39 @@ def test_ends_of_rounds_and_tiles(rx, m, k, n, group):
     want = x.double() @ (dense.double() * s.double().repeat_interleave(group, 1)).t()
     assert float((out[:n].double() - want).norm() / want.norm()) < REL
     assert bool(out[n].isnan().all())
+
+
+@pytest.mark.parametrize("hidden,heads,kv_heads,q_lens,past", [
+    (1024, 6, 1, [513], [0]),                               # one prompt; the last tile holds one head
+    (1024, 12, 4, [530] + [1] * 20, [37] + [5 * b for b in range(20)]),     # grouped heads, more sequences than ride in kernel arguments
+    (1024, 6, 3, [200, 1, 320, 7], [0, 90, 64, 11]),
+    (4096, 112, 8, [1200], [3]),                            # two launches: whole rounds of 256 x 256 tiles and 128 x 256 tiles for the rest
+])
+def test_rotary_epilogue_equals_the_separate_launch(rx, hidden, heads, kv_heads, q_lens, past):
+    """Rotary + append in the QKV GEMM's epilogue against the GEMM and rope_append_kernel: output and caches bit for bit."""
+    import numpy as np
+    from paper_2311_02103_amd.runtime import DeviceLayer
+    rng = np.random.default_rng(hidden + heads)
+    d, ffn, n = 128, 256, sum(q_lens)
+    host = {}
+    for name, m, k in (("wqkv", (heads + 2 * kv_heads) * d, hidden), ("wo", hidden, heads * d), ("wgu", 2 * ffn, hidden), ("wdown", hidden, ffn)):
+        host[name + ".q"] = rng.integers(0, 2 ** 32, (m, k // 8), dtype=np.uint32)
+        host[name + ".s"] = (rng.random((m, k // 32)) * 0.003 + 0.001).astype(np.float16).view(np.uint16)
+    for name in ("norm_attn", "norm_ffn"):
+        host[name] = np.ones(hidden, np.float16).view(np.uint16)
+    kv_lens = [q + p for q, p in zip(q_lens, past)]
+    layer = DeviceLayer(host, hidden=hidden, n_heads=heads, n_kv_heads=kv_heads, head_dim=d, ffn=ffn, kv_capacity=max(kv_lens), kv_slots=len(q_lens),
+                        n_max=n, rms_eps=1e-5, rope_base=10000.0, group=32)
+    x = torch.from_numpy(rng.standard_normal((n, hidden)).astype(np.float16)).cuda()
+    results = []
+    try:
+        for fused in (0, 1):
+            rx.check(rx.relax_set_option("fuse_finish", fused))
+            for cache in (layer.k, layer.v):
+                cache.copy_(torch.arange(cache.numel(), device="cuda").remainder(7).view(cache.shape).half())
+            out = layer.forward(x, q_lens, kv_lens)
+            results.append([t.clone().view(torch.int16) for t in (out, layer.k, layer.v)])
+    finally:
+        rx.check(rx.relax_set_option("fuse_finish", 1))
+    for a, b in zip(*results):
+        assert torch.equal(a, b)
