@@ -45,12 +45,14 @@ inline int gemm_tile_grid(GemmArgs &a, int tile_rows, int tile_cols, int splits)
 // 4-bit weights (gemm_packed_kernel.h): weight rows x rows of x of a tile
 hipError_t launch_packed_256x256(const GemmArgs &a, int splits, hipStream_t stream);
 hipError_t launch_packed_256x192(const GemmArgs &a, int splits, hipStream_t stream);
+hipError_t launch_packed_256x128(const GemmArgs &a, int splits, hipStream_t stream);
 hipError_t launch_packed_128x256(const GemmArgs &a, int splits, hipStream_t stream);
 hipError_t launch_packed_128x192(const GemmArgs &a, int splits, hipStream_t stream);
 hipError_t launch_packed_128x128(const GemmArgs &a, int splits, hipStream_t stream);
 hipError_t launch_packed_128x64(const GemmArgs &a, int splits, hipStream_t stream);
 inline hipError_t launch_packed_tile(const GemmArgs &a, int mf, int nf, int splits, hipStream_t stream)
 {
+    if (mf == 4 && nf == 2) return launch_packed_256x128(a, splits, stream);
     if (mf == 4) return nf == 4 ? launch_packed_256x256(a, splits, stream) : launch_packed_256x192(a, splits, stream);
     if (nf == 4) return launch_packed_128x256(a, splits, stream);
     if (nf == 3) return launch_packed_128x192(a, splits, stream);
