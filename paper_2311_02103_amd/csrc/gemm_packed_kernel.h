@@ -95,14 +95,12 @@ struct __attribute__((packed, aligned(2))) Load8 { uint32_t lo, hi; };
 
 // acc += A B on v_mfma_f32_16x16x32_f16, in place in the accumulation registers.  The builtin leaves result and addend free to differ,
 // and with an accumulator in every register of that half of the file the allocator moved them about (1000 moves per 256 MFMAs).  What the
-// compiler would see to for a builtin: an operand must not be written by a vector operation in the two issue slots before (decode_pair is kept
-// three MFMAs away), and the accumulators must not be read before the pipe has drained, nor multiplied into right behind their
+// compiler would see to for a builtin: an operand must not be written by a vector operation in the two issue slots before (the decode of a k step ends
+// two MFMAs before it; the build checks the distances in the listing), and the accumulators must not be read before the pipe has drained, nor multiplied into right behind their
 // initialisation (settle: in front of the first MFMA and behind the last one).
-template <bool FIRST>
 __device__ __forceinline__ void mfma(float4_t &acc, const uint4_t &a, const half8_t &b)
 {
-    if (FIRST) asm volatile("s_nop 1\n\tv_mfma_f32_16x16x32_f16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
-    else asm volatile("v_mfma_f32_16x16x32_f16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
+    asm volatile("v_mfma_f32_16x16x32_f16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
 }
 // one wait for all fragments of a phase, not one per MFMA
 __device__ __forceinline__ void arrived(half8_t (&b)[2]) { asm volatile("" ::"v"(b[0]), "v"(b[1])); }
@@ -300,8 +298,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_packed_kernel(GemmArgs a)
             constexpr int at = decltype(slot)::value, phase = at / PH, ks = phase / 2, h = phase % 2, f = at % PH / NH, i = at % NH;
             if (at == 3 * PH) lds_barrier();              // in front of the last phase, which reads the first x fragments of the next block
             if (at % PH == 0) arrived(bf[h]);
-            if (i == 0 && h == 0) mfma<true>(acc[f][h * NH + i], af[ks][f], bf[h][i]);
-            else mfma<false>(acc[f][h * NH + i], af[ks][f], bf[h][i]);
+            mfma(acc[f][h * NH + i], af[ks][f], bf[h][i]);
 
             // (all in the first three quarters of the phase, so that they are there when it ends)
             each([&](auto ic) {
