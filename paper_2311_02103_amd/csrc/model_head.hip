@@ -156,54 +156,67 @@ __global__ __launch_bounds__(256) void lm_head_kernel(const uint16_t *__restrict
     }
 }
 
-// ids[b] = lowest index among the maxima of logits[b, :] (fp16 values compared as floats); one workgroup per row.
+// ids[b] = lowest index among the maxima of logits[b, :] (fp16 values compared as floats, NaNs never the maximum); one workgroup per row.
+// One workgroup on 64 KB is a chain of latencies, so the pass over the row is as short as it gets: packed maxima alone, 16 operations per
+// thread at V = 32000; only then the threads that hold the row's maximum look for its first index (carrying value and index along, compare
+// and select for every element, took 6.2 us at V = 32000).
+typedef _Float16 logit2_t __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t pk_max(uint32_t a, uint32_t b)
+{
+    return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(logit2_t, a), __builtin_bit_cast(logit2_t, b)));
+}
 __global__ __launch_bounds__(1024) void argmax_kernel(const uint16_t *__restrict__ logits, int32_t *__restrict__ ids, int V)
 {
-    __shared__ float bv[16];
-    __shared__ int bi[16];
+    __shared__ float red[16];
+    __shared__ int first;
     const uint16_t *row = logits + (size_t)blockIdx.x * V;
-    float best = -INFINITY;
-    int idx = 0x7FFFFFFF;
-    auto take = [&](float v, int c) {
-        if (v > best || (v == best && c < idx)) best = v, idx = c;
+    const int tid = threadIdx.x, packets = V >> 3;
+    const bool vec = V % 8 == 0 && (reinterpret_cast<uintptr_t>(logits) & 15) == 0;
+    if (tid == 0) first = 0x7FFFFFFF;
+    uint4 raw[4];                                          // a round: four 16-byte packets per thread, all in flight; the last packet again past the end
+    auto load = [&](int p0) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) raw[j] = *(const uint4 *)(row + (size_t)min(p0 + j * 1024, packets - 1) * 8);
     };
-    if (V % 8 == 0 && (reinterpret_cast<uintptr_t>(logits) & 15) == 0) {
-        // 16-byte packets, four of them in flight per thread and round
-        const int packets = V >> 3;
-        for (int p0 = threadIdx.x; p0 < packets; p0 += 4 * 1024) {
-            uint4 raw[4];
+    float best = -INFINITY;
+    if (vec) {
+        uint32_t m = 0xFC00FC00u;                          // (-inf, -inf)
+        for (int p0 = tid; p0 < packets; p0 += 4 * 1024) {
+            load(p0);
 #pragma unroll
-            for (int j = 0; j < 4; ++j) raw[j] = stream_load((const uint4 *)(row + (size_t)min(p0 + j * 1024, packets - 1) * 8));
+            for (int j = 0; j < 4; ++j) m = pk_max(m, pk_max(pk_max(raw[j].x, raw[j].y), pk_max(raw[j].z, raw[j].w)));
+        }
+        best = fmaxf(h2f((uint16_t)(m & 0xFFFFu)), h2f((uint16_t)(m >> 16)));
+    } else {
+        for (int c = tid; c < V; c += 1024) best = fmaxf(best, h2f(row[c]));
+    }
+    const float mine = best;
+    best = wave_max(best);
+    if ((tid & 63) == 0) red[tid >> 6] = best;
+    __syncthreads();
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int pk = p0 + j * 1024;
-                if (pk < packets) {
-                    const uint32_t wv[4] = {raw[j].x, raw[j].y, raw[j].z, raw[j].w};
+    for (int w = 0; w < 16; ++w) best = fmaxf(best, red[w]);
+    if (mine == best) {
+        int idx = 0x7FFFFFFF;
+        if (vec) {
+            for (int p0 = tid; p0 < packets; p0 += 4 * 1024) {
+                if (packets > 4 * 1024) load(p0);          // (one round: still in registers)
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        take(h2f((uint16_t)(wv[e] & 0xFFFFu)), pk * 8 + 2 * e);
-                        take(h2f((uint16_t)(wv[e] >> 16)), pk * 8 + 2 * e + 1);
-                    }
+                for (int j = 3; j >= 0; --j) {
+                    const uint32_t w[4] = {raw[j].x, raw[j].y, raw[j].z, raw[j].w};
+#pragma unroll
+                    for (int e = 7; e >= 0; --e)
+                        if (h2f((uint16_t)(w[e >> 1] >> (16 * (e & 1)))) == best) idx = min(idx, min(p0 + j * 1024, packets - 1) * 8 + e);
                 }
             }
+        } else {
+            for (int c = tid; c < V; c += 1024)
+                if (h2f(row[c]) == best) idx = min(idx, c);
         }
-    } else {
-        for (int c = threadIdx.x; c < V; c += 1024) take(h2f(row[c]), c);
+        atomicMin(&first, idx);
     }
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-        const float ov = __shfl_xor(best, off, kWave);
-        const int oi = __shfl_xor(idx, off, kWave);
-        if (ov > best || (ov == best && oi < idx)) best = ov, idx = oi;
-    }
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    if (lane == 0) bv[wave] = best, bi[wave] = idx;
     __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int w = 1; w < 16; ++w)
-            if (bv[w] > best || (bv[w] == best && bi[w] < idx)) best = bv[w], idx = bi[w];
-        ids[blockIdx.x] = idx == 0x7FFFFFFF ? 0 : idx;         // a row of NaNs / -inf only: index 0
-    }
+    if (tid == 0) ids[blockIdx.x] = first == 0x7FFFFFFF ? 0 : first;       // a row of NaNs only: index 0
 }
 
 template <int NB>
