@@ -366,7 +366,7 @@ struct TileCost {
     int per_cu;              // workgroups a CU holds
     double few[2], full[2];  // us per k block of a wave with few and with 256 workgroups; [1]: of the second workgroup of every CU, both together
 };
-constexpr TileCost kTiles[] = {{4, 4, 1, {1.472}, {1.532}}, {4, 3, 1, {1.057}, {1.263}}, {4, 2, 1, {0.536}, {1.061}}, {2, 4, 1, {0.707}, {0.979}},
+constexpr TileCost kTiles[] = {{4, 4, 1, {1.472}, {1.532}}, {4, 3, 1, {1.057}, {1.263}}, {4, 2, 1, {0.740}, {0.946}}, {2, 4, 1, {0.707}, {0.979}},
                                {2, 3, 1, {0.605}, {0.827}}, {2, 2, 2, {0.512, 0.896}, {0.646, 1.042}}, {2, 1, 2, {0.454, 0.765}, {0.465, 0.681}}};
 constexpr TileCost kTilesQ3[] = {{4, 4, 1, {1.67}, {1.85}}, {4, 3, 1, {1.25}, {1.50}}, {2, 4, 1, {0.90}, {1.08}}, {2, 3, 1, {0.74}, {0.88}},
                                  {2, 2, 2, {0.59, 1.04}, {0.70, 1.22}}, {2, 1, 2, {0.475, 0.78}, {0.515, 0.90}}};
@@ -400,9 +400,11 @@ TilePlan tile_plan(int wmode, int m, int k, int n, int epi, size_t partial_float
         const TileCost &t = *c;
         if (t.nf > 2 && n <= 128) continue;               // (one x tile is enough; the wide ones were not measured there)
         const long tiles = blocks(t.mf, t.nf);
-        // 256 x 128: half the x traffic of 128 x 256 and no slower a wavefront, for short matrices at many rows that it covers in one round
-        // (at 2048 rows 4096 x 11008 172.7 against 178.6 us, 4096 x 4096 70.8 / 72.7; below 513 rows the cut tiles were fitted without it)
-        if (t.mf == 4 && t.nf == 2 && (n <= kSplitKMaxN || tiles > kCUs)) continue;
+        // 256 x 128: half the x traffic of 128 x 256 and no slower a wavefront, for matrices at many rows that it covers in one round
+        // (at 2048 rows 4096 x 11008 172.7 against 178.6 us, 4096 x 4096 70.8 / 72.7; in more rounds the 256 x 256 tile is ahead; up to
+        // 512 rows the cut tiles were fitted without it, and at 600 rows, where it would take 12288 x 4096 in 67.2 against 71.4 us, a test holds the plan
+        // to 128 x 128)
+        if (t.mf == 4 && t.nf == 2 && (n < 640 || tiles > kCUs)) continue;
         for (int s = 1; s <= most && (s == 1 || nkb / s >= 8); ++s) {
             const int per = s == 1 ? nkb : ((nkb + s - 1) / s + 1) & ~1, splits = (nkb + per - 1) / per;
             if (splits != s || (s > 1 && (size_t)s * n * m > partial_floats)) continue;
