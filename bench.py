@@ -363,7 +363,7 @@ def bench_prefill_layer(args, np, torch, wl, rx):
     ach = gu_flops / (kernel_ms["gate_up"] * 1e-3) / 1e12
     gemm_ms = kernel_ms["qkv"] + kernel_ms["o_proj"] + kernel_ms["gate_up"] + kernel_ms["down"]
     attn_flops = 4.0 * (n * (n + 1) / 2) * shape.n_heads * shape.head_dim
-    kernel = ("gemm_q4_mfma_kernel<EPI_SWIGLU> (gate/up GEMM, m=22016, k=4096, n=%d)" % n if n > 64 else
+    kernel = ("gemm_packed_kernel<EPI_SWIGLU> (gate/up GEMM, m=22016, k=4096, n=%d)" % n if n > 64 else
               "few-row MFMA kernel (fewrow_kernel, or skinny_q4_kernel + finishing pass; gate/up, m=22016, k=4096, n=%d)" % n)
     roofline = {"bound": "mfma", "kernel": kernel, "achieved": round(ach, 1), "peak": PEAK_MFMA_TFLOPS, "unit": "TFLOP/s",
                 "frac": round(ach / PEAK_MFMA_TFLOPS, 4), "traffic": traffic_from_profile("traffic_gate_up_gemm_7b_n%d.json" % n),
@@ -756,7 +756,7 @@ def bench_half_sweep(args, np, torch, wl, rx):
     tflops = 2.0 * 2048 * 22016 * 4096 / (big["gemm_us"] * 1e-6) / 1e12
     emit(args, "fp16-weight GEMM rate at n = 2048 on the gate/up shape (22016 x 4096)", "TFLOP/s", tflops, big["gemm_us"] / 1e3, "f16 MFMA, f32 accumulate",
          {"workload": "fp16-weight matmul against the row count, matvec passes and tiled GEMM forced in turn", "build_id": rx.relax_build_id()},
-         {"bound": "mfma", "kernel": "gemm_q4_mfma_kernel<EPI_F16, 4, 4, fp16 weights>", "achieved": round(tflops, 1), "peak": PEAK_MFMA_TFLOPS,
+         {"bound": "mfma", "kernel": "gemm_mfma_kernel<4, 4, fp16 weights>", "achieved": round(tflops, 1), "peak": PEAK_MFMA_TFLOPS,
           "unit": "TFLOP/s", "frac": round(tflops / PEAK_MFMA_TFLOPS, 4), "traffic": None}, None, {"half_sweep": table, "f16_layer_7b": layer16})
 
 

@@ -2,9 +2,9 @@
 //
 // At large n the contraction is dense (Relax, Sec. 5.1: library-grade GEMM for batch sizes other than 1; Sec. 4.2: the decode stays
 // fused into the matmul).  What bounds it on gfx950 is, in this order, the power the chip may draw, the issue slots of a wavefront and the
-// bandwidth of the LDS and of the L2s, and the form follows from these (22016 x 4096 at n = 2048: 365 -> 322 us, 1.01 -> 1.15 PFLOP/s;
-// 12288 x 4096 212 -> 187, 4096 x 11008 192 -> 175, 4096 x 4096 77 -> 71, 8192 x 28672 at 511 rows 259 -> 237, against eight wavefronts of
-// 32 x 32 x 16 MFMAs with decoded weights in the LDS):
+// bandwidth of the LDS and of the L2s, and the form follows from these (22016 x 4096 at n = 2048: 382 -> 320 us, 0.97 -> 1.15 PFLOP/s;
+// 12288 x 4096 218 -> 185, 4096 x 11008 197 -> 163, 4096 x 4096 80 -> 67, 8192 x 28672 at 511 rows 267 -> 234, against eight wavefronts of
+// 32 x 32 x 16 MFMAs with decoded weights in the LDS; both sides on one card, cards differ by 5 %):
 //   - v_mfma_f32_16x16x32_f16, not 32x32x16: under the power limit a bare loop on 4-bit weights and normal x reaches 2010 TFLOP/s with
 //     the one and 1630 with the other (both 2440 on zeros).
 //   - One wavefront per SIMD with a tile of 64 x 256 (weight rows x rows of x; 256 accumulation registers), four of them along the weight rows:
