@@ -172,9 +172,10 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_packed_kernel(GemmArgs a)
     const int nkb = min(a.kb_per_split, a.k / BK - kb0);
 
     // ---- staging roles.  Rows of the weight tile: matrix rows from row0 on, or (EPI_SWIGLU) half of them gate rows from row0 on and
-    // half the matching up rows F + row0 ..; clamped to the matrix.  A thread stages piece tid % 8 of row tid / 8 of each quarter. ----
+    // half the matching up rows F + row0 ..; clamped to the matrix.  A thread stages piece tid % 8 of row tid / 8 of each quarter.  Offsets
+    // are counted from the tile's first row (the matrix may hold more bytes than 32 bits count). ----
     const int row0 = EPI == EPI_SWIGLU ? tile_m * (BM / 2) : tile_m * BM;
-    const int last_row = (EPI == EPI_SWIGLU ? F : a.m) - 1 - row0;
+    const int last_row = min((EPI == EPI_SWIGLU ? F : a.m) - row0, EPI == EPI_SWIGLU ? BM / 2 : BM) - 1;
     const uint32_t row_bytes = (uint32_t)a.k >> 1;
     const uint32_t piece16 = (tid & 7) * 16, woff0 = (uint32_t)(tid >> 3) * row_bytes, last_off = (uint32_t)last_row * row_bytes;
     const char *const wbase = (const char *)a.q + (size_t)row0 * row_bytes;
@@ -197,14 +198,15 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_packed_kernel(GemmArgs a)
 #pragma unroll
     for (int h = 0; h < KW; ++h) {
         const int srow = (tid + h * T) >> 1;
-        sat0[h] = (uint32_t)(EPI == EPI_SWIGLU ? (srow < BM / 2 ? row0 + min(srow, last_row) : F + row0 + min(srow - BM / 2, last_row)) : row0 + min(srow, last_row)) * nsc +
+        sat0[h] = (uint32_t)(EPI == EPI_SWIGLU && srow >= BM / 2 ? F + min(srow - BM / 2, last_row) : min(srow, last_row)) * nsc +
                   ((sub0 + 4 * (tid & 1)) >> a.gshift);
     }
-    const uint32_t last_s = (uint32_t)a.m * nsc - 4;
+    const uint16_t *const sbase = a.s + (size_t)row0 * nsc;
+    const uint32_t last_s = (uint32_t)min((int64_t)(a.m - row0) * nsc - 4, (int64_t)1 << 30);
     const uint32_t sel_lo = a.gshift == 0 ? 0x03020100u : 0x01000100u, sel_hi = a.gshift == 0 ? 0x07060504u : a.gshift == 1 ? 0x03020302u : 0x01000100u;
     auto load_s = [&](int round, int h) {
         const uint32_t from = min(sat0[h] + ((8 * round) >> a.gshift), last_s);
-        const Load8 v = *(const Load8 *)(a.s + from);
+        const Load8 v = *(const Load8 *)((const char *)sbase + 2 * from);
         return ((uint64_t)v.hi << 32) | v.lo;
     };
     const uint32_t sst = kSs + tid * 8;

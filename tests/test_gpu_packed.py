@@ -41,6 +41,32 @@ def test_ends_of_rounds_and_tiles(rx, m, k, n, group):
     assert bool(out[n].isnan().all())
 
 
+@pytest.mark.parametrize("m,k", [
+    (1048976, 8192),                                        # 4 GiB of codes and 400 rows more
+    (4793664, 28672),                                       # more than 2^32 scales
+])
+def test_matrices_beyond_32_bits_of_offset(rx, m, k):
+    """Rows of the first tiles, of the last ones and of the tiles where offsets counted in 32 bits wrap (the others hold what the memory held)."""
+    n, group = 65, 32
+    g = torch.Generator(device="cuda")
+    g.manual_seed(m)
+    q, s = torch.empty(m, k // 8, dtype=torch.int32, device="cuda"), torch.empty(m, k // group, dtype=torch.float16, device="cuda")
+    wraps = [m - 2 ** 32 // (k // 2), 2 ** 32 // (k // group)]
+    ranges = sorted({(max(0, min(r - 300, m - 600)), max(0, min(r - 300, m - 600)) + 600) for r in [0, m] + [r for r in wraps if 0 < r < m]})
+    x = torch.randn(n, k, device="cuda", generator=g).half()
+    for a, b in ranges:
+        q[a:b] = torch.randint(-2 ** 31, 2 ** 31 - 1, (b - a, k // 8), device="cuda", dtype=torch.int32, generator=g)
+        s[a:b] = (torch.rand(b - a, k // group, device="cuda", generator=g) * 0.01 + 0.001).half()
+    out = torch.empty(n, m, device="cuda", dtype=torch.float16)
+    assert rx.relax_plan_matmul("q4", n, m, k)[1] == rx.KERNEL_TILED
+    rx.check(rx.relax_dequant_matmul(x, rx.QMat(q, s, m, k, group), out, n))
+    for a, b in ranges:
+        dense = torch.empty(b - a, k, dtype=torch.int8, device="cuda")
+        rx.check(rx.relax_unpack_int4(rx.QMat(q[a:b], s[a:b], b - a, k, group), dense))
+        want = x.double() @ (dense.double() * s[a:b].double().repeat_interleave(group, 1)).t()
+        assert float((out[:, a:b].double() - want).norm() / want.norm()) < REL, (a, b)
+
+
 @pytest.mark.parametrize("hidden,heads,kv_heads,q_lens,past", [
     (1024, 6, 1, [513], [0]),                               # one prompt; the last tile holds one head
     (1024, 12, 4, [530] + [1] * 20, [37] + [5 * b for b in range(20)]),     # grouped heads, more sequences than ride in kernel arguments
