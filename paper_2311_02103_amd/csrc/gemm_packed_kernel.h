@@ -146,6 +146,11 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_packed_kernel(GemmArgs a)
     constexpr int NH = NF / 2;                            // x fragments of a phase: half of a k step's
     constexpr int PH = MF * NH;                           // MFMAs of a phase, four phases a block
     static_assert(2 * PH - PH / 2 - 3 > 0 && NF % 2 == 0 && XP >= 1 && 3 * PH / XP >= 5, "staging roles");
+    // k blocks between a load and its way to LDS.  A block of the 64-column tile is shorter than the way to memory, so a launch that leaves most of
+    // the chip idle, as every call without a workspace at few rows does, waited for each of its loads: 4096 x 4096 at 65 rows 40.6 -> 26.3 us,
+    // 2048 x 5632 at 17 rows 54.7 -> 33.7.  Wider tiles gain nothing, or lose on a full chip what they gain on long rows (128 columns: 5120 x 5120 at
+    // 640 rows 44.9 against 46.4 us, 4096 x 11008 at 129 rows 101 against 84).
+    constexpr int AHEAD = BN == 64 ? 2 : 1;
     // two buffers each of the x tile of a block, of the codes of a round and of its scales, one for every sub-group of 32 columns
     constexpr uint32_t kXBuf = BN * kXPitch, kWBuf = BM * kWPitch, kSBuf = BM * 16;
     constexpr uint32_t kWs = 2 * kXBuf, kSs = kWs + 2 * kWBuf;
@@ -268,8 +273,8 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_packed_kernel(GemmArgs a)
     uint32_t raw[MF][2], sc[MF];
     uint4_t af[2][MF];
     half8_t bf[2][NH];
-    uint4_t xr[XP];
-    uint4 wr[KW];
+    uint4_t xr[AHEAD][XP];
+    uint4 wr[AHEAD][KW];
     uint64_t sr[KW];
 
     auto read_raw = [&](int j, int f) {                   // block j of the round that wrd and srd stand at
@@ -293,7 +298,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_packed_kernel(GemmArgs a)
     // their successors are requested.  A phase is half of the x fragments of a k step against all weight fragments; the next phase's are read
     // under it, evenly, as are all other steps: behind an MFMA a wavefront has three issue slots until the pipe takes the next.
     auto block = [&](auto jc, int r) {
-        constexpr int j = decltype(jc)::value, buf = j & 1;
+        constexpr int j = decltype(jc)::value, buf = j & 1, set = (j + 1) % AHEAD;
         const int kb = 4 * r + j;
         uint4_t packed = {};
         each([&](auto slot) {
@@ -315,20 +320,20 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_packed_kernel(GemmArgs a)
             for (int q = 0; q < KW; ++q) {
                 if (at == PH / 2 + q) {
                     if (q == 0 && j == 3) wst += wst_step, wst_step = -wst_step;
-                    store_w(wr[q], j + 1, q);
-                    wr[q] = load_w(kb + 6, q);
+                    store_w(wr[set][q], j + 1, q);
+                    wr[set][q] = load_w(kb + 5 + AHEAD, q);
                 }
                 if (j == 0 && at == PH + 1 + q * PH / 2) sr[q] = load_s(r + 1, q);
-                if (j == 1 && at == PH + 1 + q * PH / 2) store_s(sr[q], r + 1, q);
+                if (j == AHEAD && at == PH + 1 + q * PH / 2) store_s(sr[q], r + 1, q);
             }
 #pragma unroll
             for (int p = 0; p < XP; ++p) {
                 const int first = p * (3 * PH) / XP;
 #pragma unroll
                 for (int i4 = 0; i4 < 4; ++i4)
-                    if (at == first + i4) pack_x(packed, xr[p], i4);
+                    if (at == first + i4) pack_x(packed, xr[set][p], i4);
                 if (at == first + 3) store_x(packed, buf ^ 1, p);
-                if (at == first + 4) xr[p] = load_x(kb + 2, p);
+                if (at == first + 4) xr[set][p] = load_x(kb + 1 + AHEAD, p);
             }
             // k step 1 is decoded under k step 0; the next block's k step 0 under k step 1, from half a phase behind the reads of its codes on
             constexpr int D = 4 * MF, from = at < 2 * PH ? 0 : 2 * PH + PH / 2, span = at < 2 * PH ? 2 * PH - 3 : 2 * PH - PH / 2 - 3;
@@ -347,6 +352,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_packed_kernel(GemmArgs a)
     // ---- prologue: round 0, a quarter of round 1 and block 0 in LDS, the next quarter and block 1 on their way ----
     {
         uint4 w0[5][KW];
+        uint4_t x0[XP];
 #pragma unroll
         for (int u = 0; u < 5; ++u)
 #pragma unroll
@@ -354,7 +360,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_packed_kernel(GemmArgs a)
 #pragma unroll
         for (int h = 0; h < KW; ++h) sr[h] = load_s(0, h);
 #pragma unroll
-        for (int p = 0; p < XP; ++p) xr[p] = load_x(0, p);
+        for (int p = 0; p < XP; ++p) x0[p] = load_x(0, p);
 #pragma unroll
         for (int u = 0; u < 5; ++u) {
             if (u == 4) wst += wst_step, wst_step = -wst_step;
@@ -362,14 +368,20 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_packed_kernel(GemmArgs a)
             for (int h = 0; h < KW; ++h) store_w(w0[u][h], u, h);
         }
 #pragma unroll
-        for (int h = 0; h < KW; ++h) store_s(sr[h], 0, h), wr[h] = load_w(5, h);
+        for (int h = 0; h < KW; ++h) store_s(sr[h], 0, h), wr[1 % AHEAD][h] = load_w(5, h);
 #pragma unroll
         for (int p = 0; p < XP; ++p) {
             uint4_t o;
 #pragma unroll
-            for (int i4 = 0; i4 < 4; ++i4) pack_x(o, xr[p], i4);
+            for (int i4 = 0; i4 < 4; ++i4) pack_x(o, x0[p], i4);
             store_x(o, 0, p);
-            xr[p] = load_x(1, p);
+            xr[1 % AHEAD][p] = load_x(1, p);
+        }
+        if constexpr (AHEAD > 1) {
+#pragma unroll
+            for (int h = 0; h < KW; ++h) wr[0][h] = load_w(6, h);
+#pragma unroll
+            for (int p = 0; p < XP; ++p) xr[0][p] = load_x(2, p);
         }
     }
     lds_barrier();
