@@ -346,13 +346,14 @@ bool gemm_mfma_eligible(const relax_qmat &w, const void *x, int epi)
 // Tile and cut of a launch: the least estimated time over the tiles (weight rows x x-rows) and over k splits, of which there
 // may be up to kSplitKMax of at least 8 k blocks each for up to kSplitKMaxN rows; the fp32 partial tiles of a split launch go to
 // the caller's workspace (it has to hold them) and the finishing pass of the few-row kernel adds them in order and applies the
-// epilogue: 1.1 us, 0.4 per split and the partial rows twice over at 5 TB/s.
+// epilogue: 0.6 us, 0.3 per split and the partial rows twice over at 5 TB/s.
 // A k block of a wave of 256 workgroups takes longer the more of them there are (clock and fabric), and the two small tiles fit a
 // CU twice, so a launch of 257 to 512 of them is still one round.  The figures are the ones whose choice is closest to the fastest launch:
-// of 4-bit weights over 17 matrices from 2048 x 5632 to 57344 x 8192 at 65 to 2048 rows, every tile, and every split up to 512 rows, 0.4 % off
-// on average and 13 % at most (the figures of the kernel before it 0.8 and 18 %); of 3-bit and fp16 weights over 28 matrices 0.3 % and 0.1 %.
-// With one figure per tile, taken on a full chip, 256 x 192 tiles were preferred to 144 of 256 x 256 or 480 of 128 x 128 (12288 x 4096
-// at 600 rows 99 against 85 us).  Fp16 weights have no tiles of 256 weight rows: their staging needs more registers than two wavefronts
+// of 4-bit weights over 27 matrices from 768 x 256 to 57344 x 8192 at 65 to 2048 rows, every tile, every split up to 512 rows and two launches,
+// with and without a workspace, 0.5 % off on average and 9 % at most (the figures before them, under which 256 x 128 tiles were held to matrices
+// of one round at 640 rows and more, 1.0 %: 12288 x 4096 at 600 rows 64.3 against 70.2 us); of 3-bit and fp16 weights over 28 matrices 0.3 % and 0.1 %.
+// With one figure per tile, taken on a full chip, 256 x 192 tiles were preferred to 144 of 256 x 256 or 480 of 128 x 128 (12288 x 4096 of 3-bit weights
+// at 640 rows 97 against 86 us).  Fp16 weights have no tiles of 256 weight rows: their staging needs more registers than two wavefronts
 // per SIMD leave, and as four wavefronts they lost to two of 128 rows on all but the longest rows (27648 x 5120 at 2048 rows 741 to 882
 // against 667 us; 8192 x 28672 at 1200 877 against 943).
 namespace {
@@ -366,8 +367,8 @@ struct TileCost {
     int per_cu;              // workgroups a CU holds
     double few[2], full[2];  // us per k block of a wave with few and with 256 workgroups; [1]: of the second workgroup of every CU, both together
 };
-constexpr TileCost kTiles[] = {{4, 4, 1, {1.472}, {1.532}}, {4, 3, 1, {1.057}, {1.263}}, {4, 2, 1, {0.740}, {0.946}}, {2, 4, 1, {0.707}, {0.979}},
-                               {2, 3, 1, {0.605}, {0.827}}, {2, 2, 2, {0.512, 0.896}, {0.646, 1.042}}, {2, 1, 2, {0.454, 0.765}, {0.465, 0.681}}};
+constexpr TileCost kTiles[] = {{4, 4, 1, {1.376}, {1.729}}, {4, 3, 1, {0.803}, {1.377}}, {4, 2, 1, {0.716}, {1.029}}, {2, 4, 1, {0.569}, {1.076}},
+                               {2, 3, 1, {0.563}, {0.841}}, {2, 2, 2, {0.418, 0.938}, {0.671, 1.142}}, {2, 1, 2, {0.296, 0.707}, {0.464, 0.707}}};
 constexpr TileCost kTilesQ3[] = {{4, 4, 1, {1.67}, {1.85}}, {4, 3, 1, {1.25}, {1.50}}, {2, 4, 1, {0.90}, {1.08}}, {2, 3, 1, {0.74}, {0.88}},
                                  {2, 2, 2, {0.59, 1.04}, {0.70, 1.22}}, {2, 1, 2, {0.475, 0.78}, {0.515, 0.90}}};
 constexpr TileCost kTilesF16[] = {{2, 4, 1, {0.985}, {1.13}}, {2, 3, 1, {0.85}, {0.96}}, {2, 2, 2, {0.70, 1.45}, {0.82, 1.60}}, {2, 1, 2, {0.58, 1.05}, {0.67, 1.43}}};
@@ -393,18 +394,13 @@ TilePlan tile_plan(int wmode, int m, int k, int n, int epi, size_t partial_float
     const int most = n <= kSplitKMaxN ? kSplitKMax : 1;
     TilePlan p = {2, 1, 1, nkb, 0, 0.0};
     double best_us = 0.0;
-    const double finish0 = wmode == W_Q4 ? 1.1 : 1.6, finish1 = wmode == W_Q4 ? 0.43 : 0.4;
+    const double finish0 = wmode == W_Q4 ? 0.58 : 1.6, finish1 = wmode == W_Q4 ? 0.27 : 0.4;
     const TileCost *const first = wmode == W_F16 ? std::begin(kTilesF16) : wmode == W_Q3 ? std::begin(kTilesQ3) : std::begin(kTiles);
     const TileCost *const last = wmode == W_F16 ? std::end(kTilesF16) : wmode == W_Q3 ? std::end(kTilesQ3) : std::end(kTiles);
     for (const TileCost *c = first; c != last; ++c) {
         const TileCost &t = *c;
         if (t.nf > 2 && n <= 128) continue;               // (one x tile is enough; the wide ones were not measured there)
         const long tiles = blocks(t.mf, t.nf);
-        // 256 x 128: half the x traffic of 128 x 256 and no slower a wavefront, for matrices at many rows that it covers in one round
-        // (at 2048 rows 4096 x 11008 172.7 against 178.6 us, 4096 x 4096 70.8 / 72.7; in more rounds the 256 x 256 tile is ahead; up to
-        // 512 rows the cut tiles were fitted without it, and at 600 rows, where it would take 12288 x 4096 in 67.2 against 71.4 us, a test holds the plan
-        // to 128 x 128)
-        if (t.mf == 4 && t.nf == 2 && (n < 640 || tiles > kCUs)) continue;
         for (int s = 1; s <= most && (s == 1 || nkb / s >= 8); ++s) {
             const int per = s == 1 ? nkb : ((nkb + s - 1) / s + 1) & ~1, splits = (nkb + per - 1) / per;
             if (splits != s || (s > 1 && (size_t)s * n * m > partial_floats)) continue;
@@ -412,12 +408,12 @@ TilePlan tile_plan(int wmode, int m, int k, int n, int epi, size_t partial_float
             if (best_us == 0.0 || us < best_us) best_us = us, p.mf = t.mf, p.nf = t.nf, p.splits = s, p.kb_per_split = per;
         }
     }
-    // Or two launches (4-bit, plain rows): whole rounds of 256 x 256 tiles on the first weight rows, 128 x 256 tiles on the rest, and 5 us
-    // for the second launch (7B QKV at n = 2048: 227 -> 217 us; 27648 x 5120 at n = 2048 588 against 628 in one launch).
+    // Or two launches (4-bit, plain rows): whole rounds of 256 x 256 tiles on the first weight rows, 128 x 256 tiles on the rest, and 3.3 us
+    // for the second launch (7B QKV at n = 2048: 194 -> 185 us; 27648 x 5120 at n = 2048 491 against 515 in one launch).
     const long tn = (n + 255) / 256, rows_round = kCUs / std::min(tn, kCUs) * 256;      // weight rows of one round of wide tiles
     if (wmode == W_Q4 && epi != EPI_SWIGLU && n > 128 && tn <= kCUs)
         for (long big = rows_round; big < rows; big += rows_round) {
-            const double us = (double)(big / rows_round) * kTiles[0].full[0] * nkb + tile_us(kTiles[3], (rows - big + 127) / 128 * tn, nkb) + 5.0;
+            const double us = (double)(big / rows_round) * kTiles[0].full[0] * nkb + tile_us(kTiles[3], (rows - big + 127) / 128 * tn, nkb) + 3.3;
             if (us < best_us) best_us = us, p = {2, 4, 1, nkb, (int)big, 0.0};
         }
     p.us = best_us;

@@ -53,7 +53,8 @@ def test_row_counts_around_the_tile_edges(rx, m, k, group, with_ws):
 ONE_PASS = [(132, 256, 33, 128, 64, 1, 0), (16388, 256, 65, 128, 128, 1, 0), (16388, 256, 129, 128, 192, 1, 0), (16388, 256, 200, 128, 256, 1, 0),
             (22020, 256, 257, 256, 192, 1, 0), (16388, 256, 600, 256, 256, 1, 0), (16388, 4096, 1200, 128, 256, 1, 13056)]
 SPLIT = [(132, 1024, 65, 128, 64, 2, 0), (132, 4096, 65, 128, 64, 8, 0), (4100, 2048, 65, 128, 128, 4, 0), (4100, 5632, 128, 128, 128, 5, 0),
-         (8196, 4096, 129, 128, 192, 2, 0), (4100, 11008, 129, 128, 192, 6, 0), (8196, 11008, 200, 128, 256, 3, 0), (12292, 11008, 257, 256, 192, 2, 0)]
+         (8196, 4096, 129, 128, 192, 2, 0), (4100, 11008, 129, 128, 192, 6, 0), (8196, 11008, 200, 128, 256, 3, 0), (12292, 11008, 257, 256, 192, 2, 0),
+         (16388, 4096, 65, 256, 128, 2, 0)]
 
 
 @pytest.mark.parametrize("fmt,case", [("q4", c) for c in ONE_PASS + SPLIT] + [("q3", c) for c in ONE_PASS[:6]] + [("f16", c) for c in ONE_PASS[:4]])

@@ -79,11 +79,11 @@ def test_calls_without_a_workspace_take_the_faster_kernel(fmt, m, k, n, stream, 
 # The tiled GEMM's tiles (weight rows, rows of x, k splits) with their measured times in us: the fastest ones, and the one that one
 # figure per tile would pick.  The plan has to be within a tenth of the fastest.
 TILES = [
-    ("q4", 12288, 4096, 600, {(128, 128, 1): 85, (256, 192, 1): 99, (128, 192, 1): 115}),
-    ("q4", 22016, 4096, 560, {(128, 128, 1): 155, (128, 192, 1): 173, (256, 192, 1): 185}),
-    ("q4", 4096, 11008, 300, {(128, 192, 4): 52, (256, 192, 8): 54, (128, 128, 5): 57}),
-    ("q4", 8192, 28672, 511, {(256, 256, 4): 254, (128, 256, 2): 267, (256, 256, 8): 269}),
-    ("q4", 10240, 8192, 200, {(128, 256, 3): 61, (256, 256, 6): 65, (128, 128, 3): 66}),
+    ("q4", 12288, 4096, 600, {(256, 128, 1): 64, (128, 128, 1): 70, (256, 192, 1): 79, (128, 192, 1): 97}),
+    ("q4", 22016, 4096, 560, {(256, 128, 1): 120, (128, 128, 1): 128, (128, 192, 1): 145, (256, 192, 1): 154}),
+    ("q4", 4096, 11008, 300, {(128, 192, 4): 46.9, (128, 64, 3): 47.3, (256, 128, 5): 47.7, (256, 192, 8): 47.9, (128, 128, 5): 50.6}),
+    ("q4", 8192, 28672, 511, {(256, 256, 4): 205, (256, 128, 2): 215, (256, 256, 8): 222, (128, 256, 2): 227}),
+    ("q4", 10240, 8192, 200, {(256, 128, 3): 54.1, (128, 256, 3): 54.7, (256, 256, 6): 57.4, (128, 128, 3): 58.1}),
     ("q3", 12288, 4096, 640, {(128, 128, 1): 86, (256, 192, 1): 97, (128, 192, 1): 117}),
     ("q3", 22016, 4096, 513, {(128, 128, 1): 152, (128, 192, 1): 174, (256, 192, 1): 181}),
     ("f16", 12288, 4096, 600, {(128, 128, 1): 96, (128, 192, 1): 112, (256, 192, 1): 118}),
@@ -102,7 +102,7 @@ def test_tile_plan_picks_a_fast_tile(fmt, m, k, n, us):
 
 
 # Two launches, whole rounds of 256 x 256 tiles first (us: two launches, the best single one): 4-bit only.
-TWO_LAUNCHES = [(12288, 4096, 2048, 8192, 217, 227), (27648, 5120, 2048, 24576, 588, 628), (22016, 4096, 1700, 18432, 343, 372), (32000, 4096, 1700, 27648, 476, 503)]
+TWO_LAUNCHES = [(12288, 4096, 2048, 8192, 185, 194), (27648, 5120, 2048, 24576, 491, 515), (22016, 4096, 1700, 18432, 288, 310), (32000, 4096, 1700, 27648, 400, 415)]
 
 
 @pytest.mark.parametrize("m,k,n,wide,us_two,us_one", TWO_LAUNCHES)
