@@ -161,7 +161,7 @@ int fewrow_ranges(int wmode, int n, int m, int k, int epi, bool folded, size_t p
     if (wmode == W_Q4 && kr > 0 && gemm_skinny_partial_floats(m, k, n) > 0 && partial_floats >= gemm_skinny_partial_floats(m, k, n) &&
         split_us(n, m, k) - (folded ? kFolded : 0.0) < us)
         return 0;
-    // ... and on matrices that fill the chip with tiles through the tiled GEMM (48 rows: 49152 x 2048 32.6 against 44.5 us)
+    // ... and on matrices that fill the chip with tiles through the tiled GEMM (48 rows: 49152 x 2048 26.5 against 45.3 us, 57344 x 8192 87 against 99)
     if (wmode == W_Q4 && gemm_prefers_tiled(m, n) && gemm_tile_us(m, k, n, epi, partial_floats) < us) return 0;
     return kr;
 }

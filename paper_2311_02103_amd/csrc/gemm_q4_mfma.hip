@@ -454,8 +454,7 @@ size_t gemm_splitk_partial_floats(int m, int k, int n, int epi)
     return worst;
 }
 
-// (up to 64 rows: on the figures that the few-row kernels' estimates were fitted beside)
-double gemm_tile_us(int m, int k, int n, int epi, size_t partial_floats) { return 4.5 + tile_plan(W_Q3, m, k, n, epi, partial_floats).us; }
+double gemm_tile_us(int m, int k, int n, int epi, size_t partial_floats) { return 5.1 + tile_plan(W_Q4, m, k, n, epi, partial_floats).us; }
 
 void gemm_tile_plan(int wmode, int m, int k, int n, int epi, size_t partial_floats, relax_matmul_plan *plan)
 {

@@ -394,7 +394,7 @@ bool gemm_f16_eligible(const void *x, const void *w, const void *out, int m, int
 hipError_t launch_gemm_f16(const uint16_t *x, const uint16_t *w, int n, int m, int k, uint16_t *out, hipStream_t stream, float *partial = nullptr,
                            size_t partial_floats = 0);
 int gemm_flat_splits(int wmode, int n, int m, int k, size_t partial_floats);
-double gemm_tile_us(int m, int k, int n, int epi, size_t partial_floats);      // estimated time of a 4-bit launch
+double gemm_tile_us(int m, int k, int n, int epi, size_t partial_floats);      // estimated time of a 4-bit launch, of every kernel in it
 void gemm_tile_plan(int wmode, int m, int k, int n, int epi, size_t partial_floats, relax_matmul_plan *plan);      // tile and cut of a launch
 struct SkinnyFuse;
 int gemm_mfma_splits(const relax_qmat &w, int n, int epi, const float *partial, size_t partial_floats);
@@ -411,8 +411,9 @@ bool gemm_skinny_eligible(const relax_qmat &w, const void *x, int n, int epi);
 // Whether the tiled GEMM takes n rows before the split-K few-row kernel (Sec. 5.1: the dispatch follows the runtime value of the
 // symbolic dim): from 65 rows on, where a launch cut along k keeps its tiles wide (128 rows, few-row kernel against tiled: 8192 x 28672
 // 126 / 95 us, 5120 x 13824 57 / 40, 10240 x 8192 63 / 45, 12288 x 4096 36.8 / 34.6; layers 7B 236 / 232, 13B 325 / 289, 70B 455 / 393),
-// and from 48 rows on matrices that fill the chip with tiles (57344 x 8192: 124 against 139 us).  Up to 64 rows the streaming kernel comes
-// before either where its estimate is lower (57344 x 8192 at 48 to 64 rows: 108 us, tiled 128).
+// and from 48 rows on matrices that fill the chip with tiles (57344 x 8192 at 48 rows: 143 / 87 us), where the streaming kernel comes before it if its
+// estimate is lower (57344 x 8192 99 us, 49152 x 2048 45 against 26).  Plain matmuls on other matrices are ahead on the tiled GEMM too at 33 to 64
+// rows (4096 x 4096 at 64 rows 15.1 us, stream and split-K 18.0; 27648 x 5120 37.9, 47.3 and 52.8); the rule leaves that unused, whole layers there are unmeasured.
 inline bool gemm_prefers_tiled(int m, int n) { return n > 64 || (n >= 48 && m >= 49152); }
 size_t gemm_skinny_partial_floats(int m, int k, int n);
 void gemm_skinny_cut(int m, int k, int *tiles_m, int *splits, int *rounds);      // its workgroups: row tiles x k splits, rounds of 256 columns each

@@ -111,12 +111,12 @@ def test_tall_matrices_are_cut_into_two_launches(m, k, n, wide, us_two, us_one):
     assert plan("q3", n, m, k)[4] == plan("f16", n, m, k)[4] == 0
 
 
-@pytest.mark.parametrize("n", [47, 48, 56, 64])
-def test_tall_matrices_stay_on_the_streaming_kernel_up_to_64_rows(n):
-    """57344 x 8192 at 48 rows: the stream 108 us, the tiled GEMM 128, the split-K kernel 139."""
-    assert plan("q4", n, 57344, 8192, workspace(n, 57344, 8192))[0] == rx.KERNEL_STREAM
+# Tall matrices at up to 64 rows: the streaming kernel, the split-K kernel and the tiled GEMM in us.  The tiled GEMM is a candidate from 48 rows on.
+TALL = [(57344, 8192, 47, None, None, None), (57344, 8192, 48, 99, 143, 87), (57344, 8192, 56, 102, 147, 88), (57344, 8192, 64, 105, 151, 90),
+        (49152, 2048, 48, 45.3, 41.2, 26.5), (51200, 5120, 48, 67, 95, 56), (128256, 4096, 64, 117, 156, 97)]
 
 
-def test_short_rows_of_tall_matrices_go_to_the_tiled_gemm_at_48_rows():
-    """49152 x 2048 at 48 rows: the tiled GEMM 32.6 us, the stream 44.5."""
-    assert plan("q4", 48, 49152, 2048, workspace(48, 49152, 2048))[0] == rx.KERNEL_TILED
+@pytest.mark.parametrize("m,k,n,stream,split,tiled", TALL)
+def test_tall_matrices_go_to_the_tiled_gemm_from_48_rows(m, k, n, stream, split, tiled):
+    assert n < 48 or tiled < min(stream, split)
+    assert plan("q4", n, m, k, workspace(n, m, k))[0] == (rx.KERNEL_STREAM if n < 48 else rx.KERNEL_TILED)
