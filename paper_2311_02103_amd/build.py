@@ -56,39 +56,91 @@ RESULT_SLOTS = 18        # ... and between an MFMA and another instruction that 
 
 
 def _registers(operand: str):
-    m = re.match(r"^([va])(?:\[(\d+):(\d+)\]|(\d+))$", operand)
+    """The vector and accumulation registers of an operand, whatever modifiers stand around it."""
+    m = re.search(r"\b([va])(?:\[(\d+):(\d+)\]|(\d+))(?!\w)", operand.split()[0] if operand.split() else "")
     if not m:
         return set()
     lo, hi = (int(m[2]), int(m[3])) if m[2] else (int(m[4]), int(m[4]))
     return {(m[1], i) for i in range(lo, hi + 1)}
 
 
-def mfma_hazards(assembly: str):
-    """Instructions of an assembly listing that come too soon behind or in front of an MFMA, as texts."""
-    bad, recent = [], []                                     # recent: (name, operands, text), oldest first
+class _Instruction:
+    def __init__(self, text: str):
+        self.text = text
+        self.name, _, rest = text.partition(" ")
+        ops = [o.strip() for o in rest.split(",")]
+        regs = [_registers(o) for o in ops]
+        self.touched = set().union(*regs)
+        self.mfma = self.name.startswith("v_mfma")
+        self.written = (regs[0] | regs[1] if self.name.startswith("v_swap") else regs[0]) if self.name.startswith("v_") else set()
+        self.slots = int(ops[0], 0) + 1 if self.name == "s_nop" else 1
+        self.target = ops[0] if self.name.startswith(("s_branch", "s_cbranch")) else None
+        self.falls_through = self.name not in ("s_branch", "s_endpgm")
+
+
+def _listing(assembly: str):
+    """(instructions, {label: index of the instruction behind it}) of an assembly listing."""
+    code, labels = [], {}
     for line in assembly.splitlines():
         text = line.split(";")[0].strip()
-        if not text or text.startswith(".") or text.endswith(":"):
+        if text.endswith(":"):
+            labels[text[:-1]] = len(code)
+        elif text and not text.startswith("."):
+            code.append(_Instruction(text))
+    return code, labels
+
+
+def mfma_hazards(assembly: str):
+    """Instructions of an assembly listing that come too soon behind or in front of an MFMA on some path, loops' back edges among them, as texts."""
+    code, labels = _listing(assembly)
+    bad = []
+    for i, first in enumerate(code):
+        if not first.mfma and not first.written:
             continue
-        name, _, rest = text.partition(" ")
-        ops = [o.strip() for o in rest.split(",")]
-        touched = set().union(*(_registers(o) for o in ops))
-        is_mfma = name.startswith("v_mfma")
-        slots = 0
-        for pname, pops, ptext in reversed(recent):
-            if slots >= RESULT_SLOTS:
-                break
-            if pname == "s_nop":
-                slots += int(pops[0], 0) + 1
+        limit = RESULT_SLOTS if first.mfma else OPERAND_SLOTS
+        todo = [(i, 0)]                                      # (instruction, issue slots from the first one to it)
+        while todo:
+            at, slots = todo.pop()
+            ins = code[at]
+            if at != i or slots:
+                if first.mfma:
+                    hit = not ins.mfma and first.written & ins.touched
+                else:
+                    hit = ins.mfma and first.written & ins.touched
+                if hit:
+                    bad.append("%s -> %s" % (first.text, ins.text))
+                slots += ins.slots
+            if slots >= limit:
                 continue
-            if pname.startswith("v_mfma"):
-                if not is_mfma and _registers(pops[0]) & touched:
-                    bad.append("%s -> %s" % (ptext, text))
-            elif is_mfma and slots < OPERAND_SLOTS and pname.startswith("v_") and not pname.startswith("v_cmp") and _registers(pops[0]) & touched:
-                bad.append("%s -> %s" % (ptext, text))
-            slots += 1
-        recent = (recent + [(name, ops, text)])[-RESULT_SLOTS - 2:]
+            slots = max(slots, 0)
+            if ins.falls_through and at + 1 < len(code):
+                todo.append((at + 1, slots))
+            if ins.target in labels and labels[ins.target] < len(code):
+                todo.append((labels[ins.target], slots))
     return bad
+
+
+def mfma_loop_scratch(assembly: str):
+    """Accesses to scratch memory inside loops that hold MFMAs, as texts."""
+    code, labels = _listing(assembly)
+    bad = []
+    for i, ins in enumerate(code):
+        if ins.target in labels and labels[ins.target] <= i:
+            loop = code[labels[ins.target]:i + 1]
+            if any(x.mfma for x in loop):
+                bad += [x.text for x in loop if x.name.startswith("scratch_")]
+    return bad
+
+
+def check_mfma_listing(src: str, assembly: str) -> None:
+    if "v_mfma" not in assembly:
+        raise RuntimeError("%s: no MFMA in the assembly listing" % src)
+    bad = mfma_hazards(assembly)
+    if bad:
+        raise RuntimeError("%s: instructions too close to an MFMA: %s" % (src, "; ".join(bad[:8])))
+    bad = mfma_loop_scratch(assembly)
+    if bad:
+        raise RuntimeError("%s: scratch memory in a loop of MFMAs: %s" % (src, "; ".join(bad[:8])))
 
 
 def _check_mfma_asm(src: str, folder: str) -> None:
@@ -96,9 +148,7 @@ def _check_mfma_asm(src: str, folder: str) -> None:
     if len(listings) != 1:
         raise RuntimeError("%s: no assembly listing to check (%s)" % (src, ", ".join(listings)))
     with open(os.path.join(folder, listings[0])) as f:
-        bad = mfma_hazards(f.read())
-    if bad:
-        raise RuntimeError("%s: instructions too close to an MFMA: %s" % (src, "; ".join(bad[:8])))
+        check_mfma_listing(src, f.read())
 
 
 def _compile(src: str) -> str:
