@@ -756,7 +756,7 @@ def bench_half_sweep(args, np, torch, wl, rx):
     tflops = 2.0 * 2048 * 22016 * 4096 / (big["gemm_us"] * 1e-6) / 1e12
     emit(args, "fp16-weight GEMM rate at n = 2048 on the gate/up shape (22016 x 4096)", "TFLOP/s", tflops, big["gemm_us"] / 1e3, "f16 MFMA, f32 accumulate",
          {"workload": "fp16-weight matmul against the row count, matvec passes and tiled GEMM forced in turn", "build_id": rx.relax_build_id()},
-         {"bound": "mfma", "kernel": "gemm_mfma_kernel<4, 4, fp16 weights>", "achieved": round(tflops, 1), "peak": PEAK_MFMA_TFLOPS,
+         {"bound": "mfma", "kernel": "gemm_mfma_kernel<4, fp16 weights> (128 x 256 tiles)", "achieved": round(tflops, 1), "peak": PEAK_MFMA_TFLOPS,
           "unit": "TFLOP/s", "frac": round(tflops / PEAK_MFMA_TFLOPS, 4), "traffic": None}, None, {"half_sweep": table, "f16_layer_7b": layer16})
 
 

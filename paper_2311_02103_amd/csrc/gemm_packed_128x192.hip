@@ -3,6 +3,6 @@
 
 namespace relax {
 
-hipError_t launch_packed_128x192(const GemmArgs &a, int splits, hipStream_t stream) { return packed::launch_packed<2, 12, 4, 1>(a, splits, stream); }
+hipError_t launch_packed_128x192(const GemmArgs &a, int splits, hipStream_t stream) { return packed::launch_packed<2, 12>(a, splits, stream); }
 
 }  // namespace relax

@@ -3,6 +3,6 @@
 
 namespace relax {
 
-hipError_t launch_packed_256x128(const GemmArgs &a, int splits, hipStream_t stream) { return packed::launch_packed<4, 8, 4, 1>(a, splits, stream); }
+hipError_t launch_packed_256x128(const GemmArgs &a, int splits, hipStream_t stream) { return packed::launch_packed<4, 8>(a, splits, stream); }
 
 }  // namespace relax

@@ -133,12 +133,13 @@ __device__ __forceinline__ void each(Fn &&f, std::integer_sequence<int, I...>)
     (f(Int<I>{}), ...);
 }
 
-// One-dimensional grid of tiles_m * tiles_n * splits workgroups.  WM x WN wavefronts along the weight rows and along the x rows, each with
-// four fragments of 16 weight rows and NF fragments of 16 x rows.
-template <int EPI, int MF, int NF, int WM, int WN>
-__global__ __launch_bounds__(WM * WN * 64) void gemm_packed_kernel(GemmArgs a)
+// One-dimensional grid of tiles_m * tiles_n * splits workgroups of four wavefronts along the weight rows, each with MF fragments of 16 weight
+// rows and NF fragments of 16 x rows.
+constexpr int WM = 4;
+template <int EPI, int MF, int NF>
+__global__ __launch_bounds__(WM * 64) void gemm_packed_kernel(GemmArgs a)
 {
-    constexpr int T = WM * WN * 64, BM = 16 * MF * WM, BN = 16 * NF * WN;
+    constexpr int T = WM * 64, BM = 16 * MF * WM, BN = 16 * NF;
     constexpr int KW = 2 * BM / T;                        // pieces of codes a thread stages per k block, pieces of scales per round
     constexpr int kRows = T / 8;                          // weight rows of T pieces of codes
     static_assert(KW >= 1 && KW <= 2 && KW * T == 2 * BM, "staging roles");
@@ -156,9 +157,8 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_packed_kernel(GemmArgs a)
     constexpr uint32_t kWs = 2 * kXBuf, kSs = kWs + 2 * kWBuf;
     __shared__ __align__(16) char lds[kSs + 2 * kSBuf];
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wm = tid >> 6;
     const int row16 = lane & 15, quarter = lane >> 4;
-    const int wm = wave % WM, wn = wave / WM;
     // Workgroups are handed to the 8 XCDs round-robin by linear id, and each XCD has its own L2.  Renumber them so
     // that an XCD owns a contiguous run of tiles: the x tiles a workgroup streams are then fetched into one L2 instead of eight.
     const int nb = gridDim.x, xcd = blockIdx.x & 7, idx = blockIdx.x >> 3;
@@ -260,7 +260,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_packed_kernel(GemmArgs a)
     int wrd_step = kWBuf, srd_step = kSBuf;
     uint32_t xrd[2];
 #pragma unroll
-    for (int ks = 0; ks < 2; ++ks) xrd[ks] = (wn * NF * 16 + row16) * kXPitch + ((quarter + 4 * ks) ^ (row16 >> 1)) * 16;
+    for (int ks = 0; ks < 2; ++ks) xrd[ks] = row16 * kXPitch + ((quarter + 4 * ks) ^ (row16 >> 1)) * 16;
 
     float4_t acc[MF][NF];
 #pragma unroll
@@ -408,14 +408,14 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_packed_kernel(GemmArgs a)
 
     settle(acc);
 
-    // ---- epilogue.  acc[f][j][v]: tile row of fragment f + 4 (lane / 16) + v, x row n0 + 16 (NF wn + j) + lane % 16 ----
+    // ---- epilogue.  acc[f][j][v]: tile row of fragment f + 4 (lane / 16) + v, x row n0 + 16 j + lane % 16 ----
     const int off = quarter * 4;
     if (a.partial) {
         // k split: the raw fp32 tile goes to partial[split][x row][weight row] (gate rows first, up rows from F on, as in the
         // matrix), and the finishing pass adds the splits in order and applies the epilogue
 #pragma unroll
         for (int j = 0; j < NF; ++j) {
-            const int xrow = n0 + (wn * NF + j) * 16 + row16;
+            const int xrow = n0 + j * 16 + row16;
             if (xrow >= a.n) continue;
             float *dst = a.partial + ((size_t)split * a.n + xrow) * a.m;
 #pragma unroll
@@ -448,7 +448,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_packed_kernel(GemmArgs a)
         if (head >= a.h + 2 * a.g) return;
 #pragma unroll
         for (int j = 0; j < NF; ++j) {
-            const int local = (wn * NF + j) * 16 + row16, xrow = n0 + local;
+            const int local = j * 16 + row16, xrow = n0 + local;
             if (xrow >= a.n) continue;
             const int2 at = rows[local];
             const size_t token = (size_t)at.y * a.kv_capacity + at.x;
@@ -476,7 +476,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_packed_kernel(GemmArgs a)
     }
 #pragma unroll
     for (int j = 0; j < NF; ++j) {
-        const int xrow = n0 + (wn * NF + j) * 16 + row16;
+        const int xrow = n0 + j * 16 + row16;
         if (xrow >= a.n) continue;
         if (EPI == EPI_SWIGLU) {
 #pragma unroll
@@ -521,17 +521,17 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_packed_kernel(GemmArgs a)
 }
 
 // a launcher of gemm_tile.h for this tile
-template <int MF, int NF, int WM, int WN>
+template <int MF, int NF>
 hipError_t launch_packed(const GemmArgs &a_in, int splits, hipStream_t stream)
 {
     GemmArgs a = a_in;
-    const dim3 grid(gemm_tile_grid(a, 16 * MF * WM, 16 * NF * WN, splits)), block(WM * WN * 64);
+    const dim3 grid(gemm_tile_grid(a, 16 * MF * WM, 16 * NF, splits)), block(WM * 64);
     switch (a.epi) {
-    case EPI_F16: hipLaunchKernelGGL((gemm_packed_kernel<EPI_F16, MF, NF, WM, WN>), grid, block, 0, stream, a); break;
-    case EPI_ROPE_KV: hipLaunchKernelGGL((gemm_packed_kernel<EPI_ROPE_KV, MF, NF, WM, WN>), grid, block, 0, stream, a); break;
-    case EPI_RESID_F32: hipLaunchKernelGGL((gemm_packed_kernel<EPI_RESID_F32, MF, NF, WM, WN>), grid, block, 0, stream, a); break;
-    case EPI_RESID_F16: hipLaunchKernelGGL((gemm_packed_kernel<EPI_RESID_F16, MF, NF, WM, WN>), grid, block, 0, stream, a); break;
-    case EPI_SWIGLU: hipLaunchKernelGGL((gemm_packed_kernel<EPI_SWIGLU, MF, NF, WM, WN>), grid, block, 0, stream, a); break;
+    case EPI_F16: hipLaunchKernelGGL((gemm_packed_kernel<EPI_F16, MF, NF>), grid, block, 0, stream, a); break;
+    case EPI_ROPE_KV: hipLaunchKernelGGL((gemm_packed_kernel<EPI_ROPE_KV, MF, NF>), grid, block, 0, stream, a); break;
+    case EPI_RESID_F32: hipLaunchKernelGGL((gemm_packed_kernel<EPI_RESID_F32, MF, NF>), grid, block, 0, stream, a); break;
+    case EPI_RESID_F16: hipLaunchKernelGGL((gemm_packed_kernel<EPI_RESID_F16, MF, NF>), grid, block, 0, stream, a); break;
+    case EPI_SWIGLU: hipLaunchKernelGGL((gemm_packed_kernel<EPI_SWIGLU, MF, NF>), grid, block, 0, stream, a); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();

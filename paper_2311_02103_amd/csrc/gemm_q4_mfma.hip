@@ -1,5 +1,5 @@
 // Tiled MFMA GEMM on native 3-bit and on plain fp16 weights for large n (prefill), out[i,r] = sum_c x[i,c] * W(r,c), and the tile plan of
-// these and of the 4-bit kernel (gemm_packed.hip).
+// these and of the 4-bit kernel (gemm_packed_kernel.h).
 //
 //   - v_mfma_f32_32x32x16_f16, fp32 accumulate.  The 256-row tiles (weight rows x x-rows) run as eight wavefronts,
 //     two per SIMD with up to 256 registers each, so that one wavefront's decode, LDS
@@ -87,25 +87,22 @@ __device__ __forceinline__ half8_t decode_q3_packet(uint32_t w0, uint32_t w1, ui
 // One-dimensional grid of tiles_m * (x-row tiles) workgroups.  Wavefront w owns MF fragments of 32 weight rows (w % WM picks which)
 // and NF fragments of 32 x-rows (w / WM picks which) of the workgroup tile of 32 MF WM weight rows x 32 NF WN x-rows.
 // FP16W: plain fp16 weights (the fp16-weight configurations of the paper's LLM charts, Sec. 5.1): the staging copies 16-byte packets.
-// Otherwise 3-bit weights in the native word layout (Sec. 5.3 of the paper deploys 3-bit models): a thread stages whole groups of 32
+// Otherwise 3-bit weights in the native word layout (Sec. 5.3 of the paper deploys 3-bit models): a thread stages a whole group of 32
 // columns (three words), the decode yields the columns in natural order, so the x tile is staged unpermuted.
-// WM x WN: wavefronts along the weight rows and along the x rows.  2 x 2: four wavefronts, one per SIMD, each with up to 512
-// registers.  4 x 2: eight wavefronts, two per SIMD with up to 256 registers each.
-template <int MF, int NF, bool FP16W, int WM = 2, int WN = 2>
-__global__ __launch_bounds__(WM * WN * 64) void gemm_mfma_kernel(GemmArgs a)
+// WM = 2: four wavefronts, one per SIMD, each with up to 512 registers.  WM = 4: eight wavefronts, two per SIMD with up to 256 registers each.
+template <int NF, bool FP16W, int WM = 2>
+__global__ __launch_bounds__(WM * 128) void gemm_mfma_kernel(GemmArgs a)
 {
     constexpr bool Q3 = !FP16W;
+    constexpr int MF = 2, WN = 2;
     constexpr int ST = 2;                                 // register stages; four were measured and gained nothing
     constexpr int kThreadsG = WM * WN * 64;
     constexpr int BM = 32 * MF * WM, BN = 32 * NF * WN;
-    // packed words a thread decodes per k block: its share of the BM x 8 words of the weight tile (2, 4 or 8: every thread
-    // stages weights, so the staging has no branch for the compiler's wait-count pass to merge across)
-    constexpr int W = BM * 8 / kThreadsG;
-    constexpr int TPR = 8 / W;                            // threads per weight row
+    // packets of 8 columns a thread stages per k block: its share of the BM x 8 of the weight tile (every thread stages weights, so
+    // the staging has no branch for the compiler's wait-count pass to merge across)
+    constexpr int W = 4, TPR = 8 / W;                     // ... and threads per weight row
+    static_assert(W * kThreadsG == BM * 8, "staging roles");
     constexpr int XP = BN * 8 / kThreadsG;                // 16-byte x packets a thread stages per k block
-    static_assert((W == 2 || W == 4 || W == 8) && XP >= 1, "staging roles");
-    static_assert(!Q3 || W >= 4, "a thread stages whole 3-bit groups");
-    constexpr int WV = W < 4 ? 1 : W / 4;                 // 16-byte (W = 2: 8-byte) loads of packed words per thread and k block
     constexpr int kABuf = BM * kPitch, kBBuf = BN * kPitch;
     extern __shared__ __align__(16) uint16_t lds[];       // A[2][BM][kPitch], B[2][BN][kPitch]
     uint16_t *const As = lds, *const Bs = lds + 2 * kABuf;
@@ -127,12 +124,11 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_mfma_kernel(GemmArgs a)
     const int n0 = tile_n * BN;
 
     // ---- staging roles ----
-    const int arow = tid / TPR, aword0 = (tid % TPR) * W;
+    const int arow = tid / TPR, apart = tid % TPR, acol0 = apart * W * 8;
     const int grow = min(tile_m * BM + arow, a.m - 1);
-    const uint32_t *qsrc = FP16W ? nullptr : a.q + ((size_t)grow * (a.k >> 5) + (aword0 >> 2)) * 3;
+    const uint32_t *qsrc = FP16W ? nullptr : a.q + ((size_t)grow * (a.k >> 5) + apart) * 3;
     const uint16_t *ssrc = FP16W ? nullptr : a.s + (size_t)grow * scales_per_row(a.k, a.gshift);
-    const int sub0 = aword0 >> 2;                         // first 32-column sub-group of this thread's words inside a k block
-    const uint16_t *hsrc = FP16W ? a.wh + (size_t)grow * a.k + aword0 * 8 : nullptr;
+    const uint16_t *hsrc = FP16W ? a.wh + (size_t)grow * a.k + acol0 : nullptr;
     const uint16_t *xsrc[XP];
 #pragma unroll
     for (int p = 0; p < XP; ++p) {
@@ -142,7 +138,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_mfma_kernel(GemmArgs a)
 
     // Staged registers of one k block: packed codes + scales of this thread's weight row part, and its x packets.
     struct Stage {
-        uint4 wq[FP16W ? W : WV];                         // packed words (W = 2: in .x, .y), or one 16-byte packet of fp16 weights per word
+        uint4 wq[FP16W ? W : 1];                          // 16-byte packets of fp16 weights, or the three words of a 3-bit group
         uint32_t wsc;
         uint4 xr[XP];
     };
@@ -157,20 +153,13 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_mfma_kernel(GemmArgs a)
         if (FP16W) {
 #pragma unroll
             for (int i = 0; i < W; ++i)
-                if (i * 4 / W == part) S.wq[i] = *(const uint4 *)(hsrc + kb * BK + i * 8);
+                if (i == part) S.wq[i] = *(const uint4 *)(hsrc + kb * BK + i * 8);
         } else {
-#pragma unroll
-            for (int i = 0; i < WV; ++i) {
-                if (i * 2 != part) continue;
-                const uint32_t *g3 = qsrc + (kb * (BK / 32) + i) * 3;      // group i of this thread: three words, 4-byte aligned
-                S.wq[i].x = g3[0], S.wq[i].y = g3[1], S.wq[i].z = g3[2];
+            if (part == 0) {
+                const uint32_t *g3 = qsrc + kb * (BK / 32) * 3;            // 4-byte aligned
+                S.wq[0].x = g3[0], S.wq[0].y = g3[1], S.wq[0].z = g3[2];
             }
-            if (part == 1) {
-                // scale of sub-group g: ssrc[g >> gshift] (neighbouring sub-groups share it when the group is wider than 32)
-                const int g = kb * (BK / 32) + sub0;
-                if (W == 8) S.wsc = (uint32_t)ssrc[g >> a.gshift] | ((uint32_t)ssrc[(g + 1) >> a.gshift] << 16);
-                else S.wsc = ssrc[g >> a.gshift];
-            }
+            if (part == 1) S.wsc = ssrc[(kb * (BK / 32) + apart) >> a.gshift];
         }
 #pragma unroll
         for (int p = 0; p < XP; ++p)
@@ -187,10 +176,10 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_mfma_kernel(GemmArgs a)
     };
     // quarter `part` (0..3) of the decode + LDS write of a staged block
     auto stage_store = [&](const Stage &S, int buf, int part) {
-        uint16_t *ad = As + buf * kABuf + arow * kPitch + aword0 * 8;
+        uint16_t *ad = As + buf * kABuf + arow * kPitch + acol0;
 #pragma unroll
         for (int i = 0; i < W; ++i) {
-            if (i * 4 / W != part) continue;
+            if (i != part) continue;
             if (FP16W) {                                  // same packet order as the decode and the x tile
                 const uint4 &h = S.wq[FP16W ? i : 0];
                 uint4 o;
@@ -201,9 +190,8 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_mfma_kernel(GemmArgs a)
                 *(uint4 *)(ad + i * 8) = o;
                 continue;
             }
-            const uint4 &wv = S.wq[i >> 2];
-            const uint32_t sc = (W == 8 && i >= 4) ? (S.wsc >> 16) : (S.wsc & 0xFFFFu);
-            *(half8_t *)(ad + i * 8) = decode_q3_packet(wv.x, wv.y, wv.z, i & 3, sc | (sc << 16));
+            const uint4 &wv = S.wq[0];
+            *(half8_t *)(ad + i * 8) = decode_q3_packet(wv.x, wv.y, wv.z, i, S.wsc | (S.wsc << 16));
         }
         uint16_t *bd = Bs + buf * kBBuf;
 #pragma unroll
@@ -313,21 +301,21 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_mfma_kernel(GemmArgs a)
     }
 }
 
-template <int MF, int NF, bool FP16W, int WM = 2, int WN = 2>
+template <int NF, bool FP16W, int WM = 2>
 hipError_t launch_tile(const GemmArgs &a_in, hipStream_t stream, int splits)
 {
-    constexpr int BM = 32 * MF * WM, BN = 32 * NF * WN, kThreadsG = WM * WN * 64;
+    constexpr int BM = 64 * WM, BN = 64 * NF, kThreadsG = WM * 128;
     GemmArgs a = a_in;
     if (a.epi != EPI_F16) return hipErrorInvalidValue;   // plain matmuls only: a split launch's epilogue is the finishing pass
     const dim3 grid(gemm_tile_grid(a, BM, BN, splits));
     const size_t lds = 2 * (size_t)(BM + BN) * kPitch * sizeof(uint16_t);    // up to 147456 bytes: one workgroup per CU
     static std::atomic<bool> attr_done{false};   // setting the attribute twice is harmless; the flag only has to be a defined read
     if (!attr_done.load()) {
-        if (hipFuncSetAttribute((const void *)gemm_mfma_kernel<MF, NF, FP16W, WM, WN>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
+        if (hipFuncSetAttribute((const void *)gemm_mfma_kernel<NF, FP16W, WM>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
             return hipErrorInvalidValue;
         attr_done.store(true);
     }
-    hipLaunchKernelGGL((gemm_mfma_kernel<MF, NF, FP16W, WM, WN>), grid, dim3(kThreadsG), lds, stream, a);
+    hipLaunchKernelGGL((gemm_mfma_kernel<NF, FP16W, WM>), grid, dim3(kThreadsG), lds, stream, a);
     return hipGetLastError();
 }
 
@@ -481,10 +469,10 @@ hipError_t launch_gemm_f16(const uint16_t *x, const uint16_t *w, int n, int m, i
     a.x = x, a.wh = w, a.n = n, a.m = m, a.k = k, a.epi = EPI_F16, a.out_f16 = out, a.partial = partial;
     const TilePlan p = tile_plan(W_F16, m, k, n, EPI_F16, partial ? partial_floats : 0);
     a.kb_per_split = p.kb_per_split;
-    if (p.nf == 4) return launch_tile<2, 4, true>(a, stream, p.splits);
-    if (p.nf == 3) return launch_tile<2, 3, true>(a, stream, p.splits);
-    if (p.nf == 2) return launch_tile<2, 2, true>(a, stream, p.splits);
-    return launch_tile<2, 1, true>(a, stream, p.splits);
+    if (p.nf == 4) return launch_tile<4, true>(a, stream, p.splits);
+    if (p.nf == 3) return launch_tile<3, true>(a, stream, p.splits);
+    if (p.nf == 2) return launch_tile<2, true>(a, stream, p.splits);
+    return launch_tile<1, true>(a, stream, p.splits);
 }
 
 // out[n,m] = x[n,k] . w[m,k]^T with 3-bit weights in the native word layout (group 32): the same tiles, one pass over k
@@ -500,12 +488,12 @@ hipError_t launch_gemm_q3(const uint16_t *x, const relax_qmat &w, int n, uint16_
     a.x = x, a.q = w.q, a.s = w.s, a.gshift = 0, a.n = n, a.m = w.m, a.k = w.k, a.epi = EPI_F16, a.out_f16 = out, a.partial = partial;
     const TilePlan p = tile_plan(W_Q3, w.m, w.k, n, EPI_F16, partial ? partial_floats : 0);
     a.kb_per_split = p.kb_per_split;
-    if (p.mf == 4 && p.nf == 4) return launch_tile<2, 4, false, 4>(a, stream, p.splits);
-    if (p.mf == 4) return launch_tile<2, 3, false, 4>(a, stream, p.splits);
-    if (p.nf == 4) return launch_tile<2, 4, false>(a, stream, p.splits);
-    if (p.nf == 3) return launch_tile<2, 3, false>(a, stream, p.splits);
-    if (p.nf == 2) return launch_tile<2, 2, false>(a, stream, p.splits);
-    return launch_tile<2, 1, false>(a, stream, p.splits);
+    if (p.mf == 4 && p.nf == 4) return launch_tile<4, false, 4>(a, stream, p.splits);
+    if (p.mf == 4) return launch_tile<3, false, 4>(a, stream, p.splits);
+    if (p.nf == 4) return launch_tile<4, false>(a, stream, p.splits);
+    if (p.nf == 3) return launch_tile<3, false>(a, stream, p.splits);
+    if (p.nf == 2) return launch_tile<2, false>(a, stream, p.splits);
+    return launch_tile<1, false>(a, stream, p.splits);
 }
 
 // k splits of the two launches above with this much workspace: more than one leaves partial rows for launch_skinny_finish
