@@ -20,8 +20,8 @@ REL = 1e-3
 @pytest.mark.parametrize("k", [128, 256, 384, 640, 1152])
 @pytest.mark.parametrize("m,n", [(4, 65), (132, 20), (68, 130), (260, 193), (1028, 260), (16388, 600), (4092, 2000)])
 def test_ends_of_rounds_and_tiles(rx, m, k, n, group):
-    """Rows of half a round and of one and a half, matrices of one granule, scales read up to the last one of the matrix: the codes and
-    scales end where their buffers end, and what lies behind them is poison."""
+    """Rows of half a round and of one and a half, matrices of one granule, scales read up to the last one of the matrix: behind the scales lie NaNs, and
+    other words behind the codes change nothing."""
     g = torch.Generator(device="cuda")
     g.manual_seed(m + k + n + group)
     codes = torch.randint(-2 ** 31, 2 ** 31 - 1, (m * k // 8 + 64,), device="cuda", dtype=torch.int32, generator=g)
@@ -39,6 +39,10 @@ def test_ends_of_rounds_and_tiles(rx, m, k, n, group):
     want = x.double() @ (dense.double() * s.double().repeat_interleave(group, 1)).t()
     assert float((out[:n].double() - want).norm() / want.norm()) < REL
     assert bool(out[n].isnan().all())
+    codes[m * k // 8:] ^= -1
+    again = torch.empty(n, m, device="cuda", dtype=torch.float16)
+    rx.check(rx.relax_dequant_matmul(x, w, again, n))
+    assert torch.equal(again, out[:n])
 
 
 @pytest.mark.parametrize("m,k", [
