@@ -367,6 +367,7 @@ def bench_prefill_layer(args, np, torch, wl, rx):
               "few-row MFMA kernel (fewrow_kernel, or skinny_q4_kernel + finishing pass; gate/up, m=22016, k=4096, n=%d)" % n)
     roofline = {"bound": "mfma", "kernel": kernel, "achieved": round(ach, 1), "peak": PEAK_MFMA_TFLOPS, "unit": "TFLOP/s",
                 "frac": round(ach / PEAK_MFMA_TFLOPS, 4), "traffic": traffic_from_profile("traffic_gate_up_gemm_7b_n%d.json" % n),
+                "traffic_source": "stored value, not measured in this run: profiles/traffic_gate_up_gemm_7b_n%d.json" % n,
                 "algorithmic_flops_per_launch": gu_flops, "avg_launch_ms": round(kernel_ms["gate_up"], 5)}
 
     cpu = None
@@ -598,8 +599,7 @@ def bench_batch_sweep(args, np, torch, wl, rx):
             calls[i % sets](stream.cuda_stream)
         stream.synchronize()
         us = (time.perf_counter() - t0) * 1e6 / steps
-        matmuls = ("matvec" if n == 1 else "matvec, 2 or 4 rows per pass" if n <= 4 else "few-row MFMA" if n <= 64 else
-                   "few-row MFMA, tiled GEMM for gate/up" if n <= 128 else "tiled GEMM")
+        matmuls = ("matvec" if n == 1 else "matvec, 2 or 4 rows per pass" if n <= 4 else "few-row MFMA" if n <= 64 else "tiled GEMM")
         rows.append({"n": n, "us_per_call": round(us, 1), "layer_tokens_per_s": round(n / us * 1e6, 0), "matmul_kernels": matmuls})
     best = max(rows, key=lambda r: r["layer_tokens_per_s"])
     emit(args, "layer-tokens/s of one 7B-shaped int4 layer call against the number of decode rows (best point)", "tokens/s",

@@ -165,7 +165,8 @@ __global__ __launch_bounds__(WM * 64) void gemm_packed_kernel(GemmArgs a)
     const int tile = xcd * (nb >> 3) + min(xcd, nb & 7) + idx;
     // Inside an XCD's run the x-row tile changes fastest within a PAIR of x-row tiles: a round of 32 workgroups then is 16
     // weight-row tiles x 2 x-row tiles, and an XCD streams half of the weight matrix instead of all of it (requests of the L2s
-    // to the fabric on the 7B gate/up shape at n = 2048: 304 MB against 456 MB; neither operand fits a 4 MB L2).
+    // to the fabric on the 7B gate/up shape at n = 2048: 324 MB; the kernel before this one 304 MB, without the pairs 456; neither operand
+    // fits a 4 MB L2).
     const int per_split = a.tiles_m * a.tiles_n, split = tile / per_split, t2 = tile - split * per_split;
     const int pair = t2 / (2 * a.tiles_m), r2 = t2 - pair * 2 * a.tiles_m;
     const bool whole = 2 * pair + 1 < a.tiles_n;          // the last pair of an odd count is a single tile

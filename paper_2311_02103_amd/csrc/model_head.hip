@@ -157,9 +157,9 @@ __global__ __launch_bounds__(256) void lm_head_kernel(const uint16_t *__restrict
 }
 
 // ids[b] = lowest index among the maxima of logits[b, :] (fp16 values compared as floats, NaNs never the maximum); one workgroup per row.
-// One workgroup on 64 KB is a chain of latencies, so the pass over the row is as short as it gets: packed maxima alone, 16 operations per
-// thread at V = 32000; only then the threads that hold the row's maximum look for its first index (carrying value and index along, compare
-// and select for every element, took 6.2 us at V = 32000).
+// One workgroup on 64 KB is a chain of latencies, so the pass over the row is as short as it gets: packed maxima alone, 33 instructions per
+// thread at V = 32000 (16 maxima, and one each that quiets an operand); only then the threads that hold the row's maximum look for its first
+// index (4.3 us at V = 32000; carrying value and index along, compare and select for every element, 6.2).
 typedef _Float16 logit2_t __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ uint32_t pk_max(uint32_t a, uint32_t b)
 {
