@@ -199,8 +199,8 @@ relax_status relax_dequant_matmul(const uint16_t *x, const relax_qmat *w, uint16
 /* The same matmul with plain fp16 weights (the fp16-weight configurations of the paper's LLM evaluation,
  * Sec. 5.1): out[i,r] = sum_c x[i,c] * w[r,c], x [n,k] fp16, w [m,k] fp16 row-major, out [n,m] fp16, fp32
  * accumulation, dispatched on the runtime n like the int4 call: passes of up to 8 rows through the fp16
- * matrix-vector kernel (the one the LM head uses) for a few rows, the tiled MFMA GEMM without its decode
- * step (k % 128 == 0, m % 4 == 0) from the row count on at which its estimated time falls below that of the
+ * matrix-vector kernel (the one the LM head uses) for a few rows, the tiled MFMA GEMM of the 3-bit format
+ * without its decode step (k % 128 == 0, m % 4 == 0) from the row count on at which its estimated time falls below that of the
  * passes -- 24 rows on a 4096 x 4096 matrix, 8 on 22016 x 4096 (measured: bench.py --workload half_sweep).
  * 2 .. 32 rows of up to 6144 or of 7169 .. 8192 columns (k % 128 == 0, m % 4 == 0, out 8-byte aligned; up to 4096 from
  * 17 rows on) take the streaming few-row kernel instead of either, one pass over the matrix, unless 2, 4 or 8 rows are
@@ -329,8 +329,8 @@ relax_status relax_dequant_matmul_q3(const uint16_t *x, const relax_qmat *w, uin
  * within what a launch without workspace holds: 12288 up to 16 rows, 6144 up to 32, 2048 beyond), m % 4 == 0, s 4-byte and
  * out 8-byte aligned take the streaming few-row MFMA kernel, one pass, except where one matrix-vector pass or the GEMM is
  * faster (two rows of up to 8192 columns, small matrices).  Else, from 16 rows on, a matrix with
- * k % 128 == 0 and m % 4 == 0 (out 8-byte aligned) goes through the tiled MFMA GEMM that serves the 4-bit format at
- * large n, its decode step replaced by the 3-bit one: the matrix is read once whatever n is, and k is not limited.
+ * k % 128 == 0 and m % 4 == 0 (out 8-byte aligned) goes through a tiled MFMA GEMM that decodes the weights on
+ * their way into LDS: the matrix is read once whatever n is, and k is not limited.
  * x 16-byte aligned; errors as the canonical call. */
 relax_status relax_repack_q3(const relax_qmat *canonical, uint32_t *native_q, relax_stream stream);
 relax_status relax_unpack_q3_native(const relax_qmat *w, int8_t *out, relax_stream stream);

@@ -386,9 +386,9 @@ constexpr int kGemmMinN = 16;        // rows from which the MFMA GEMM replaces o
 bool gemm_mfma_eligible(const relax_qmat &w, const void *x, int epi);
 constexpr int kSplitKMax = 8;         // k splits of the tiled GEMM at most
 constexpr int kSplitKMaxN = 512;      // ... and only up to this many rows (the partial tiles are splits * n * m floats)
+// fp32 elements of workspace for the k-split form (without it a launch makes one pass over k)
 size_t gemm_splitk_partial_floats(int m, int k, int n, int epi);
-// partial: optional workspace of partial_floats fp32 for the k-split form (without it the launch makes one pass over k)
-// the same tiled kernel on plain fp16 weights [m,k] (no decode)
+// the tiled kernel on plain fp16 weights [m,k]
 bool gemm_f16_eligible(const void *x, const void *w, const void *out, int m, int k);
 // partial: with room for the partial rows of more than one k split (gemm_flat_splits) they go there and the caller finishes them
 hipError_t launch_gemm_f16(const uint16_t *x, const uint16_t *w, int n, int m, int k, uint16_t *out, hipStream_t stream, float *partial = nullptr,
