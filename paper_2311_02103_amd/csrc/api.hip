@@ -17,13 +17,13 @@ inline bool aligned(const void *p, size_t bytes) { return (reinterpret_cast<uint
 // k ranges of the streaming few-row kernel for a packed matrix at n rows, with at most `partial_floats` floats for the partial rows
 // of a launch that is cut along k; 0: it does not take the call.  out: whatever the epilogue writes or adds (8-byte accesses).
 // The kernel reads codes and scales at 4-byte alignment.  4-bit matrices have to be aligned as the split-K kernel wants them all
-// the same: it rounds a weight to fp16, and calls that no MFMA kernel took for their alignment stay on the matvec kernels, which
-// apply the scale in fp32.
-int stream_ranges(int wmode, const relax_qmat &w, const void *x, const void *out, int n, int epi, size_t partial_floats, bool folded = false)
+// the same: beyond 16 rows it rounds a weight to fp16, and calls that no MFMA kernel took for their alignment stay on the matvec
+// kernels, which apply the scale in fp32.
+int stream_ranges(int wmode, const relax_qmat &w, const void *x, const void *out, int n, int epi, size_t partial_floats, bool folded = false, bool alone = false)
 {
     const size_t wa = wmode == W_Q4 ? 16 : 4;
     if (!aligned(x, 16) || !aligned(w.q, wa) || !aligned(w.s, wa) || !aligned(out, 8)) return 0;
-    return fewrow_ranges(wmode, n, w.m, w.k, epi, folded, partial_floats);
+    return fewrow_ranges(wmode, wmode == W_Q4 ? gshift_of(w.group) : 0, n, w.m, w.k, epi, folded, alone, partial_floats);
 }
 
 // The kernel a plain matmul takes, and for the streaming few-row kernel its k ranges (Sec. 5.1: the dispatch follows the runtime value
@@ -39,7 +39,7 @@ Route q4_route(const uint16_t *x, const relax_qmat &w, const uint16_t *out, int 
 {
     const bool tiled_first = gemm_prefers_tiled(w.m, n) && gemm_mfma_eligible(w, x, EPI_F16);
     const bool ws_fits = ws && aligned(ws, 16) && n <= kSkinnyMaxN && ws_bytes >= sizeof(float) * gemm_skinny_partial_floats(w.m, w.k, n);
-    const int kr = !ws_fits ? 0 : stream_ranges(W_Q4, w, x, out, n, EPI_F16, ws_bytes / sizeof(float));
+    const int kr = !ws_fits ? 0 : stream_ranges(W_Q4, w, x, out, n, EPI_F16, ws_bytes / sizeof(float), false, true);
     if (kr > 0) return {RELAX_KERNEL_STREAM, kr};
     if (!tiled_first && n >= kSkinnyMinN && n <= kSkinnyMaxN && ws_fits && gemm_skinny_eligible(w, x, n, EPI_F16)) return {RELAX_KERNEL_SPLIT_K, 0};
     if (n >= kGemmMinN && gemm_mfma_eligible(w, x, EPI_F16)) return {RELAX_KERNEL_TILED, 0};
@@ -342,7 +342,7 @@ Route f16_route(const uint16_t *x, const uint16_t *w, const uint16_t *out, int n
 {
     bool use_gemm;
     const int gemm_rows = g_opt_half_gemm_rows.load();
-    if (gemm_rows == 0 && aligned(x, 16) && aligned(w, 16) && aligned(out, 8) && fewrow_ranges(W_F16, n, m, k, EPI_F16, false, 0) &&
+    if (gemm_rows == 0 && aligned(x, 16) && aligned(w, 16) && aligned(out, 8) && fewrow_ranges(W_F16, 0, n, m, k, EPI_F16, false, true, 0) &&
         fewrow_pays_alone(W_F16, n, m, k))
         return {RELAX_KERNEL_STREAM, 1};
     if (gemm_rows > 0) {
@@ -715,7 +715,9 @@ relax_status layer_enqueue(const relax_layer_dims &dm, const relax_layer_weights
         return stream(wq, xin, epi) || (n <= kSkinnyMaxN && gemm_skinny_eligible(wq, xin, n, epi)) || (n >= kGemmMinN && gemm_mfma_eligible(wq, xin, epi));
     };
     auto few_row = [&](const relax_qmat &wq, const void *xin, int epi) {      // the split-K few-row kernel takes this matmul, if the stream does not
-        if (gemm_prefers_tiled(wq.m, n) && n >= kGemmMinN && gemm_mfma_eligible(wq, xin, epi)) return false;
+        if (gemm_mfma_eligible(wq, xin, epi) && (gemm_prefers_tiled(wq.m, n) ||
+                                                 (n > 32 && gemm_tile_us(wq.m, wq.k, n, epi, pl.mm_floats) < gemm_skinny_us(n, wq.m, wq.k, gshift_of(wq.group)))))
+            return false;
         return n <= kSkinnyMaxN && gemm_skinny_eligible(wq, xin, n, epi);
     };
     auto matmul = [&](const uint16_t *xin, const relax_qmat &wq, int epi, uint16_t *o16, float *o32, const void *resid) {
@@ -732,7 +734,12 @@ relax_status layer_enqueue(const relax_layer_dims &dm, const relax_layer_weights
     // Two rows share one pass over the weights on every model size (measured per layer at L = 512: 13B shape 65 against 90 us on
     // the matrix path, 70B shape 112 against 167 us); three and four rows need a second pass where a lane cannot hold four rows
     // of x, which pays only while the matrices mostly stay in the last-level cache (13B: 94 against 92 us, 70B: 178 against 155).
-    const bool rows_as_matvecs = n >= 2 && n <= g_opt_matvec_rows.load() && (n == 2 || largest <= ((size_t)g_opt_matvec_mb.load() << 20));
+    // Three and four rows take the streaming kernel where it serves all four matrices: as exact, and faster or the same from the 7B shape on (us
+    // per layer at L = 300, matvec / stream, groups of 32 and 128: 7B 59 / 58 and 59 / 55 at three rows, 62 / 60 and 62 / 57 at four; 13B 87 / 76
+    // and 87 / 70, 88 / 78 and 89 / 73).
+    const bool streams = n > 2 && n <= kRopeOnce && stream(wt->wqkv, x, EPI_F16) && stream(wt->wo, x, EPI_RESID_F32) && stream(wt->wgu, x, EPI_SWIGLU) &&
+                         stream(wt->wdown, x, EPI_RESID_F16) && fewrow_fuse_ok(dm, *cache);
+    const bool rows_as_matvecs = n >= 2 && n <= g_opt_matvec_rows.load() && (n == 2 || (largest <= ((size_t)g_opt_matvec_mb.load() << 20) && !streams));
     if (n >= kSkinnyMinN && !rows_as_matvecs && mat_ok(wt->wqkv, x, EPI_F16) && mat_ok(wt->wo, x, EPI_RESID_F32) && mat_ok(wt->wgu, x, EPI_SWIGLU) &&
         mat_ok(wt->wdown, x, EPI_RESID_F16)) {
         uint16_t *xn = reinterpret_cast<uint16_t *>(base + pl.xn), *qkv = reinterpret_cast<uint16_t *>(base + pl.qkv);
@@ -1201,7 +1208,7 @@ relax_status relax_decoder_layer_f16(const relax_layer_dims *dims, const relax_l
     auto plain = [&](int i, const uint16_t *xin, uint16_t *o) { return half_matmul_enqueue(xin, mats[i], o, n, ms[i], ks[i], st_); };
     auto ranges = [&](int i, const void *xin, const void *o, int epi, size_t floats, bool folded) {      // every pointer was checked for 16 bytes above
         if (g_opt_half_gemm_rows.load() != 0) return 0;
-        const int kr = fewrow_ranges(W_F16, n, ms[i], ks[i], epi, folded, floats);
+        const int kr = fewrow_ranges(W_F16, 0, n, ms[i], ks[i], epi, folded, false, floats);
         if (kr > 0 || n < kGemmMinN || !gemm_f16_eligible(xin, mats[i], o, ms[i], ks[i])) return kr;
         const int splits = gemm_flat_splits(W_F16, n, ms[i], ks[i], floats);
         return splits > 1 ? -splits : 0;

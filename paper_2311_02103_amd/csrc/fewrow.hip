@@ -15,35 +15,38 @@ namespace {
 
 using namespace fewrow;
 
-bool uw_built(bool f16, int nb, int uw)                   // the instances of launch_nb
+bool uw_built(int fmt, int nb, int uw)                    // the instances of launch_nb
 {
-    if (f16) return uw >= 1 && (nb == 1 ? uw <= 6 || uw == 8 : nb == 2 && uw <= 4);
-    return uw >= 1 && uw <= (nb == 1 ? 6 : nb == 2 ? 3 : 1);
+    if (fmt == F_F16) return uw >= 1 && (nb == 1 ? uw <= 6 || uw == 8 : nb == 2 && uw <= 4);
+    if (fmt == F_Q3) return uw >= 1 && uw <= (nb == 1 ? 6 : nb == 2 ? 3 : 1);
+    if (fmt == F_Q4G32) return uw >= 1 && uw <= (nb == 1 ? 5 : nb == 2 ? 3 : 1);
+    return uw >= 1 && uw <= (nb == 1 ? 5 : nb == 2 ? 2 : 0);
 }
 
-int lds_tiles(int nb) { return (int)(kLdsBytes / ((size_t)kWaves * nb * 1024)); }
+int lds_tiles(int fmt, int nb, int uw) { return (int)((kLdsBytes - offset_bytes(fmt, nb, uw)) / ((size_t)kWaves * nb * 1024)); }
 
 int blocks_of(int n) { return n <= 16 ? 1 : n <= 32 ? 2 : 4; }
 
 int tiles_of(int m, int epi) { return epi == EPI_SWIGLU ? (m / 2 + 7) / 8 : (m + kTileRows - 1) / kTileRows; }
 
 // The cut into kg k ranges; false: no instance of the kernel for it.
-bool cut(bool f16, int nb, int m, int k, int epi, int kg, Plan &p)
+bool cut(int fmt, int nb, int m, int k, int epi, int kg, Plan &p)
 {
+    const bool f16 = fmt == F_F16;
     const int units = k / unit_columns(f16);
     p.kg = kg, p.uw = (units + kWaves * kg - 1) / (kWaves * kg);
-    if (!uw_built(f16, nb, p.uw)) return false;
+    if (!uw_built(fmt, nb, p.uw)) return false;
     p.tiles = tiles_of(m, kg > 1 ? (int)EPI_F16 : epi);
     p.rg = std::min(p.tiles, 256 / kg);
     // a workgroup whose epilogue is not plain partial rows keeps the sums of all its tiles in LDS: more workgroups if they don't fit
     if (kg == 1 || nb == 1)
-        while ((p.tiles + p.rg - 1) / p.rg > lds_tiles(nb)) p.rg = std::min(p.tiles, p.rg + 256 / kg);
+        while ((p.tiles + p.rg - 1) / p.rg > lds_tiles(fmt, nb, p.uw)) p.rg = std::min(p.tiles, p.rg + 256 / kg);
     return true;
 }
 
-// What a launch takes, in us, for blocks of 16, 32 and 64 rows of x: fitted to 73 matrices from 256 x 256 to 128256 x 4096 and 12288 x
-// 12288 at 2 to 64 rows, weights cold, every k range the kernel is built for.  What the 4-bit figures and the ones of the split-K kernel
-// below choose is 0.4, 0.6 and 0.6 % off the fastest launch on average, 15, 13 and 11 % at most.
+// What a launch takes, in us, for blocks of 16, 32 and 64 rows of x: fitted to 22 matrices from 1024 x 4096 to 57344 x 8192 (groups of 32 beyond
+// 16 rows: to 73) at 2 to 64 rows, weights cold, every k range the kernel is built for.  What the 4-bit figures choose is 0.3 % off the fastest k
+// range on average for blocks of 16, 0.6 % for 32, 9 and 10 % at most; the estimates are within 4 % of the times on average.
 //   launch                 the launch, the first data and the sums over the wavefronts
 //   tb_per_s               the stream of the weights, or, where few row tiles or uneven slices leave it to the slowest workgroup,
 //   unit, tile             ... per row tile of a workgroup: its longest slice's units, and the sums
@@ -55,7 +58,11 @@ bool cut(bool f16, int nb, int m, int k, int epi, int kg, Plan &p)
 struct Cost {
     double launch, tb_per_s, unit, tile, x, finish, range, partial, full, round;
 };
-constexpr Cost kCostQ4[3] = {{4.2, 9.5, 0.65, 0.17, 35, 3.1, 0.33, 3.3, 3.4}, {4.6, 5.4, 0.79, 0.0, 32, 2.2, 0.57, 2.7, 0.0, 8.0}, {4.8, 3.1, 1.39, 0.05, 25, 2.6, 0.79, 38}};
+constexpr Cost kCostQ4[3] = {{4.1, 6.2, 0.62, 0.31, 23, 2.0, 0.32, 7.9, 1.4, 6.6}, {4.6, 5.4, 0.79, 0.0, 32, 2.2, 0.57, 2.7, 0.0, 8.0}, {4.8, 3.1, 1.39, 0.05, 25, 2.6, 0.79, 38}};
+// ... of a plain matmul of up to 16 rows: the same launches at what they took with two and three row tiles in flight.  Where the estimates of
+// the two kernels lie closer than the stream has gained since (a tenth) the call stays where it was.
+constexpr Cost kCostQ4Alone = {4.2, 9.5, 0.65, 0.17, 35, 3.1, 0.33, 3.3, 3.4};
+constexpr Cost kCostQ4Coarse[2] = {{4.1, 6.8, 0.64, 0.06, 22, 1.9, 0.32, 2.7, 1.6, 6.9}, {4.8, 36, 0.49, 0.42, 27, 1.5, 0.34, 2.8, 9.3, 2.2}};
 // 3-bit and fp16 matrices: the rates of the stream alone (what is estimated for them only picks the k ranges of a layer's matrices)
 constexpr Cost kCostQ3[3] = {{5.8, 5.9, 0.46, 0.0, 25, 3.1, 0.0, 5.8}, {5.8, 5.35, 0.51, 0.0, 27, 3.4, 0.0, 5.3}, {5.8, 4.7, 0.58, 0.0, 31, 3.9, 0.0, 4.6}};
 constexpr Cost kCostF16[2] = {{5.8, 5.9, 1.05, 0.0, 25, 3.1, 0.0, 5.8}, {5.8, 5.35, 1.17, 0.0, 27, 3.4, 0.0, 5.3}};
@@ -64,16 +71,16 @@ constexpr double kFolded = 2.5;                           // a finishing pass th
 int block_class(int n) { return n <= 16 ? 0 : n <= 32 ? 1 : 2; }
 
 // The number of k ranges with the least estimated time (`folded`: the finishing pass is also the RMSNorm of the result).
-int best_ranges(int fmt, int n, int m, int k, int epi, bool folded, size_t partial_floats, double *time_us)
+int best_ranges(int fmt, int n, int m, int k, int epi, bool folded, bool alone, size_t partial_floats, double *time_us)
 {
     const bool f16 = fmt == F_F16;
-    const Cost &c = (f16 ? kCostF16 : fmt == F_Q3 ? kCostQ3 : kCostQ4)[block_class(n)];
-    const double bytes = (double)m * k * (f16 ? 2.0 : fmt == F_Q3 ? 0.4375 : 0.5625);
+    const Cost &c = alone && fmt == F_Q4G32 && n <= 16 ? kCostQ4Alone : (f16 ? kCostF16 : fmt == F_Q3 ? kCostQ3 : fmt == F_Q4G32 ? kCostQ4 : kCostQ4Coarse)[block_class(n)];
+    const double bytes = (double)m * k * (f16 ? 2.0 : fmt == F_Q3 ? 0.4375 : fmt == F_Q4G32 ? 0.5625 : fmt == F_Q4G64 ? 0.53125 : 0.515625);
     double best_us = 0.0;
     int best = 0;
     for (int kg = 1; kg <= 16 && (kg == 1 || (size_t)kg * n * m <= partial_floats); ++kg) {
         Plan p;
-        if (!cut(f16, blocks_of(n), m, k, epi, kg, p)) continue;
+        if (!cut(fmt, blocks_of(n), m, k, epi, kg, p)) continue;
         const double per = (p.tiles + p.rg - 1) / p.rg, rounds = (p.rg * kg + 255) / 256;
         double us = std::max(bytes / (c.tb_per_s * 1e6), rounds * per * (p.uw * c.unit + c.tile)) + rounds * n * ((double)k / kg) * 2e-6 * c.x + (rounds - 1) * c.round;
         if (p.uw >= 4 && k / unit_columns(f16) == p.uw * kWaves * kg) us += c.full;
@@ -101,6 +108,8 @@ double split_us(int n, int m, int k)
            (double)splits * n * m * 8e-6 / c.partial;
 }
 
+constexpr double kSplitCoarse = 1.1;                      // groups of 64 and 128: its scale staging is made for groups of 32
+
 bool shape_ok(bool f16, int n, int m, int k, int epi)
 {
     if (n < kFewRowMin || n > kFewRowMax || k < 1 || k % unit_columns(f16) != 0) return false;
@@ -114,7 +123,7 @@ hipError_t launch(int fmt, const uint16_t *x, const void *w, size_t w_bytes, con
 {
     Plan p;
     const int nb = blocks_of(n);
-    if (!cut(fmt == F_F16, nb, m, k, epi, k_ranges, p)) return hipErrorInvalidValue;
+    if (!cut(fmt, nb, m, k, epi, k_ranges, p)) return hipErrorInvalidValue;
     Args a = {};
     a.x = x, a.w = w, a.s = s, a.x_bytes = (uint32_t)((size_t)n * k * 2), a.w_bytes = (uint32_t)w_bytes, a.s_bytes = (uint32_t)s_bytes;
     a.n = n, a.m = m, a.k = k, a.kg = p.kg, a.rg = p.rg, a.tiles = p.tiles;
@@ -132,7 +141,7 @@ hipError_t launch(int fmt, const uint16_t *x, const void *w, size_t w_bytes, con
         a.epi = epi;
         if (epi == EPI_SWIGLU) a.delta = m / 2;
     }
-    a.batch = std::min((p.tiles + p.rg - 1) / p.rg, lds_tiles(nb));
+    a.batch = std::min((p.tiles + p.rg - 1) / p.rg, lds_tiles(fmt, nb, p.uw));
     hipError_t e;
     switch (fmt) {
     case F_Q4G32: e = launch_q4g32(nb, p.uw, a, a.batch, stream); break;
@@ -147,22 +156,28 @@ hipError_t launch(int fmt, const uint16_t *x, const void *w, size_t w_bytes, con
 
 }  // namespace
 
-int fewrow_ranges(int wmode, int n, int m, int k, int epi, bool folded, size_t partial_floats)
+double gemm_skinny_us(int n, int m, int k, int gshift) { return split_us(n, m, k) * (gshift == 0 ? 1.0 : kSplitCoarse); }
+
+int fewrow_ranges(int wmode, int gshift, int n, int m, int k, int epi, bool folded, bool alone, size_t partial_floats)
 {
-    if (!shape_ok(wmode == W_F16, n, m, k, epi) || (wmode == W_F16 && n > 32)) return 0;
+    const int fmt = wmode == W_F16 ? F_F16 : wmode == W_Q3 ? F_Q3 : gshift == 0 ? F_Q4G32 : gshift == 1 ? F_Q4G64 : F_Q4G128;
+    if (!shape_ok(fmt == F_F16, n, m, k, epi) || (n > 32 && (fmt == F_F16 || fmt == F_Q4G64 || fmt == F_Q4G128))) return 0;
     const size_t row = wmode == W_F16 ? (size_t)k * 2 : wmode == W_Q3 ? (size_t)k / 32 * 12 : (size_t)k / 2;
     if ((size_t)m * row > kMaxBuffer) return 0;
     double us = 0.0;
-    const int kr = best_ranges(wmode == W_F16 ? F_F16 : wmode == W_Q3 ? F_Q3 : F_Q4G32, n, m, k, epi, folded, partial_floats, &us);
+    const int kr = best_ranges(fmt, n, m, k, epi, folded, alone, partial_floats, &us);
     // A 4-bit matrix may also go through the split-K few-row kernel, whose workgroups own 128 rows and an eighth of k: an eighth of the
     // x traffic, a lower rate.  It is the better one where its workgroups fill the chip and rows are long or x has many rows (8192 x
     // 8192 at 16 rows 16.5 against 18.6 us, 5120 x 13824 17.8 against 20.0, 15360 x 5120 at 64 rows 29.9 against 35.4), the stream
     // on the others (22016 x 4096 at 16 rows 19.1 against 23.4, 57344 x 8192 58 against 74).
-    if (wmode == W_Q4 && kr > 0 && gemm_skinny_partial_floats(m, k, n) > 0 && partial_floats >= gemm_skinny_partial_floats(m, k, n) &&
-        split_us(n, m, k) - (folded ? kFolded : 0.0) < us)
+    // Up to kRopeOnce rows of a layer stay here: that kernel rounds the weights, which the matvec kernels do not.
+    if (wmode == W_Q4 && kr > 0 && (alone || n > kRopeOnce) && gemm_skinny_partial_floats(m, k, n) > 0 && partial_floats >= gemm_skinny_partial_floats(m, k, n) &&
+        gemm_skinny_us(n, m, k, gshift) - (folded ? kFolded : 0.0) < us)
         return 0;
-    // ... and on matrices that fill the chip with tiles through the tiled GEMM (48 rows: 49152 x 2048 26.5 against 45.3 us, 57344 x 8192 87 against 99)
-    if (wmode == W_Q4 && gemm_prefers_tiled(m, n) && gemm_tile_us(m, k, n, epi, partial_floats) < us) return 0;
+    // ... and on matrices that fill the chip with tiles through the tiled GEMM (48 rows: 49152 x 2048 26.5 against 45.3 us, 57344 x 8192 87 against 99),
+    // in a layer from 33 rows on wherever that is estimated faster (64 rows, stream / split-K / tiled: 22016 x 4096 33 / 39 / 30, 27648 x 5120 47 / 53
+    // / 40, 4096 x 4096 16.8 / 17.4 / 15.2; a 7B layer on 64 rows of 300 tokens 157 -> 145 us, 13B 199 -> 180, 70B 244 -> 231)
+    if (wmode == W_Q4 && (gemm_prefers_tiled(m, n) || (!alone && n > 32)) && gemm_tile_us(m, k, n, epi, partial_floats) < us) return 0;
     return kr;
 }
 

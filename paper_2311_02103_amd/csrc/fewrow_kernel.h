@@ -8,14 +8,25 @@
 //     COLUMNS (UW units of 256, fp16: 128) for good: its share of x sits in registers as ready MFMA operands, read once, and it
 //     streams its slice of row tile after row tile (16 weight rows) of the workgroup's range.  Nothing is shared inside the loop:
 //     no LDS staging, no barrier, the only memory operations in flight are weights and scales.
-//   - v_mfma_f32_16x16x32_f16 with the weights as the A operand straight from global memory.  A load takes whole 128-byte
-//     lines: 8 rows x 8 lanes, rows 0..7 and 8..15 of a tile by two loads; exchanging the two registers between the lanes
+//   - Little in flight: one row tile (32 to 64 KB per CU).  A bare read of 235 MB in this pattern takes 39.4 us with 64 KB per CU and 42.5
+//     with 128 (lines of 128, 256 or 512 bytes per row and load: the same; neighbouring tiles dealt out over the CUs: slower), and the
+//     kernels gain more than that (us, two or three tiles / one: 4 bits, 16 rows 22016 x 4096 18.2 / 16.5, 57344 x 8192 60.5 / 56.6, 8192 x
+//     28672 39.7 / 35.3; 3 bits, 8 rows 22016 x 4096 21.3 / 18.7; fp16, 8 rows of 8192 x 8192 four units / two 35.6 / 31.3).
+//   - v_mfma_f32_16x16x32_f16 with the weights as the A operand (4-bit sums, below: B) straight from global memory.  A load takes whole
+//     128-byte lines: 8 rows x 8 lanes, rows 0..7 and 8..15 of a tile by two loads; exchanging the two registers between the lanes
 //     l and l ^ 8 (one DPP move each) leaves lane l with row l % 16 and pieces 2 q and 2 q + 1 of the row's line, q = l / 16: the
 //     A layout, with the columns of a unit dealt to the quarters in pairs of sub-groups.  Because every line is touched by one
 //     instruction only, the loads carry the non-temporal hint (27648 x 5120 in fp16, two rows: 55 -> 50 us; loads of 16 rows x
 //     64 bytes got slower with it).  3-bit rows are 96 bytes per unit: no hint there.
 //   - A 16-byte piece is one sub-group of 32 columns and gives four MFMA steps, one per word; scales come as one load per lane
 //     and four units and are dealt to the quarters with v_permlane swaps.
+//   - 4-bit scales meet the fp32 sums of their groups, not the codes (all groups at up to 16 rows, 64 and 128 up to 32): permlane swaps put columns
+//     of one group into all quarters of an MFMA, whose result has x rows in registers and the weight row in the lane, so one scale per lane
+//     does for a group; the codes go in as 64 + u, and what that adds leaves with three small MFMAs of the scales per four units.  Nothing is
+//     rounded before the result (2.07e-4 off the 64-bit one at 4096 x 5120, the rounding of the result itself; scaled codes 2.78e-4), and a
+//     word costs 9 (128) to 13 (32) vector operations instead of 18: 16 rows, groups of 128 / 32, 5120 x 5120 14.6 / 13.2 -> 11.6 / 12.2 us, 15360 x
+//     5120 20.9 / 19.4 -> 15.6 / 16.4, 22016 x 4096 18.1 / 18.4 -> 15.1 / 16.6, 57344 x 8192 57 / 59 -> 53 / 57 (little in flight included).  Beyond,
+//     groups of 32 would need more operations for the sums of 32 x rows than for the codes.
 //   - The order of k inside an MFMA is free as long as A and B agree: x is put into the order the decode yields.  What x
 //     costs is its bytes (256 workgroups x n rows from the L2s, 13 TB/s), not the pattern: fetching it in 64-byte pieces per row
 //     and transposing in registers took the same time.
@@ -46,10 +57,16 @@ typedef uint32_t u32x3_t __attribute__((ext_vector_type(3)));
 enum { F_Q4G32 = 0, F_Q4G64 = 1, F_Q4G128 = 2, F_Q3 = 3, F_F16 = 4 };
 
 constexpr int kWaves = 8, kThreads = kWaves * 64;
+// 4-bit: whether a group's scale meets the fp32 sum of its products (exact), or its codes (one rounding per weight)
+constexpr bool scale_sums(int fmt, int nb) { return fmt == F_Q4G64 || fmt == F_Q4G128 || (fmt == F_Q4G32 && nb == 1); }
 constexpr int unit_columns(bool f16) { return f16 ? 128 : 256; }      // a row's share of a unit: 128 bytes, 96 (3-bit) or 2 x 128 (fp16)
 constexpr int kTileRows = 16;
 constexpr uint32_t kNowhere = 0x80000000u;                // an offset past every buffer (they are at most 2^31 - 1 bytes)
-constexpr size_t kLdsBytes = 152 * 1024;                  // partial tiles of a batch
+constexpr size_t kLdsBytes = 152 * 1024;                  // partial tiles of a batch, and the offsets of 4-bit codes
+constexpr size_t offset_bytes(int fmt, int nb, int uw)
+{
+    return scale_sums(fmt, nb) ? (size_t)kWaves * nb * ((uw + 3) / 4) * 3 * (fmt == F_Q4G32 ? 1024 : fmt == F_Q4G64 ? 512 : 256) : 0;
+}
 
 struct Args {
     const uint16_t *x;       // [n,k] fp16
@@ -85,14 +102,20 @@ __device__ __forceinline__ uint32_t pk_fma(uint32_t a, uint32_t b, uint32_t c)
     half2_t r = __builtin_elementwise_fma(__builtin_bit_cast(half2_t, a), __builtin_bit_cast(half2_t, b), __builtin_bit_cast(half2_t, c));
     return __builtin_bit_cast(uint32_t, r);
 }
-// one packed 4-bit word -> its 8 codes less 8 as fp16, in the order [e0 e4 e1 e5 e2 e6 e3 e7]: 1024 + u - 1032, (1024 + 16 u) / 16 - 72
+// one packed 4-bit word -> its 8 codes u (0..15) as fp16 64 + u in the order [e0 e4 e1 e5 e2 e6 e3 e7]: a nibble at bits 4..7 of fp16
+// 64 counts ones.  (Without the shift of the first pair, at the bottom of 1024, the fp32 sums of 1024 + u were 2.2e-5 off, where the matvec kernels
+// are 1.1e-5 off and 64 + u is below 2e-6.)
+__device__ __forceinline__ half8_t raw_q4(uint32_t w)
+{
+    const uint32_t mask = 0x00F000F0u, base = 0x54005400u;
+    return __builtin_bit_cast(half8_t, u32x4_t{and_or3(w << 4, mask, base), and_or3(w, mask, base), and_or3(w >> 4, mask, base), and_or3(w >> 8, mask, base)});
+}
+constexpr uint32_t kOffset = 0x54805480u, kNegOffset = 0xD480D480u;    // the codes mean u - 8: 72 is in every one too many
+// the same without it, exactly
 __device__ __forceinline__ u32x4_t decode_q4(uint32_t w)
 {
-    const uint32_t w8 = w >> 8;
-    const uint32_t a0 = and_or3(w, 0x000F000Fu, 0x64006400u), a1 = and_or3(w, 0x00F000F0u, 0x64006400u);
-    const uint32_t a2 = and_or3(w8, 0x000F000Fu, 0x64006400u), a3 = and_or3(w8, 0x00F000F0u, 0x64006400u);
-    const uint32_t kNeg1032 = 0xE408E408u, kSixteenth = 0x2C002C00u, kNeg72 = 0xD480D480u;
-    return u32x4_t{pk_add(a0, kNeg1032), pk_fma(a1, kSixteenth, kNeg72), pk_add(a2, kNeg1032), pk_fma(a3, kSixteenth, kNeg72)};
+    const u32x4_t r = __builtin_bit_cast(u32x4_t, raw_q4(w));
+    return u32x4_t{pk_add(r[0], kNegOffset), pk_add(r[1], kNegOffset), pk_add(r[2], kNegOffset), pk_add(r[3], kNegOffset)};
 }
 // packet j (columns 8j .. 8j+7) of a 3-bit group from its three words -> its codes less 4 as fp16: pairs (1024 + f u) with f = 1, 8
 // or 64 by class, one packed fma removes weight and offset exactly ((1024 + f u) / f - (1024 / f + 4) = u - 4).
@@ -122,6 +145,14 @@ __device__ __forceinline__ u32x4_t decode_q3(const u32x3_t &w, int j)
 __device__ __forceinline__ half8_t scaled(const u32x4_t &v, uint32_t s2)
 {
     return __builtin_bit_cast(half8_t, u32x4_t{pk_mul(v[0], s2), pk_mul(v[1], s2), pk_mul(v[2], s2), pk_mul(v[3], s2)});
+}
+
+// a b + c rounded to fp16 once: what the compiler makes of the stand-alone rotary kernel's expression, whose bits the epilogue repeats
+__device__ __forceinline__ uint16_t fma_f16(float a, float b, float c)
+{
+    uint32_t r = 0;
+    asm("v_fma_mixlo_f16 %0, %1, %2, %3" : "+v"(r) : "v"(a), "v"(b), "v"(c));
+    return (uint16_t)r;
 }
 
 // orders LDS only: requests in flight stay in flight across it
@@ -162,6 +193,9 @@ __global__ __launch_bounds__(kThreads) void fewrow_kernel(Args a)
     // of a 7B layer was 3.20e-4 off the 64-bit result instead of 2.95e-4 (the split costs 4 us of 62).  Elsewhere the products are
     // rounded once, as in the split-K kernel and the tiled GEMM.
     constexpr bool EXACT = NB == 1 && Q3;
+    constexpr bool SUMS = scale_sums(FMT, NB);
+    constexpr int GU = SUMS ? 256 / SG : 1;               // groups of a unit: one, two or four MFMA steps each
+    constexpr int GS = ST / GU;
     extern __shared__ __align__(16) float4_t red[];       // [tile of the batch][wavefront][NB][64]
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -184,19 +218,24 @@ __global__ __launch_bounds__(kThreads) void fewrow_kernel(Args a)
 
     // ---- x of the wavefront's columns, in the order the decode yields ----
     // step s of a packed unit: word s % 4 of piece 2 q + s / 4; of an fp16 unit: piece 2 q + s % 2 of line s / 2
+    // of a 4-bit unit: what set_to_steps makes of the sets of pieces 0..3 and 4..7
+    auto x_step = [](int s) {
+        return F16 || (SUMS && SG == 64) ? (s >> 1) * 128 + (s & 1) * 16 : !SUMS ? s * 16 : SG == 128 ? (s >> 2) * 256 + (s & 3) * 16 : s * 64;
+    };
     u32x4_t X[UW][ST][NB];
     {
         const __amdgpu_buffer_rsrc_t xr = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(a.x), 0, a.x_bytes, 0x00020000);
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) {
             const uint32_t row = (uint32_t)(16 * nb + r16);
-            const uint32_t xo = row < (uint32_t)a.n ? row * (uint32_t)a.k * 2 + (uint32_t)(u0 * kUnit) * 2 + qd * (F16 ? 32 : 128) : kNowhere;
+            const uint32_t xq = F16 ? qd * 32 : !SUMS ? qd * 128 : SG == 32 ? qd * 16 : SG == 64 ? (qd & 1) * 64 + (qd >> 1) * 32 : qd * 64;
+            const uint32_t xo = row < (uint32_t)a.n ? row * (uint32_t)a.k * 2 + (uint32_t)(u0 * kUnit) * 2 + xq : kNowhere;
             const uint32_t xo_last = nu < UW ? kNowhere : xo + (UW - 1) * kUnit * 2;
 #pragma unroll
             for (int u = 0; u < UW; ++u)
 #pragma unroll
                 for (int s = 0; s < ST; ++s)
-                    X[u][s][nb] = __builtin_amdgcn_raw_buffer_load_b128(xr, (u == UW - 1 ? xo_last : xo + u * kUnit * 2) + (F16 ? (s >> 1) * 128 + (s & 1) * 16 : s * 16), 0, 0);
+                    X[u][s][nb] = __builtin_amdgcn_raw_buffer_load_b128(xr, (u == UW - 1 ? xo_last : xo + u * kUnit * 2) + x_step(s), 0, 0);
         }
     }
 
@@ -207,10 +246,12 @@ __global__ __launch_bounds__(kThreads) void fewrow_kernel(Args a)
     };
     const uint32_t wpitch = F16 ? (uint32_t)a.k * 2 : Q3 ? (uint32_t)(a.k / 32) * 12 : (uint32_t)a.k / 2;
     const uint32_t spitch = (uint32_t)(a.k / SG) * 2;
-    const uint32_t wo0 = (uint32_t)(lane & 7) * wpitch + (uint32_t)u0 * kUnitBytes + (lane >> 3) * kPiece, wo1 = wo0 + (uint32_t)a.delta * wpitch;
+    const uint32_t piece = SUMS ? (uint32_t)((lane >> 3) & 1) * 4 + qd : (uint32_t)(lane >> 3);
+    const uint32_t wo0 = (uint32_t)(lane & 7) * wpitch + (uint32_t)u0 * kUnitBytes + piece * kPiece, wo1 = wo0 + (uint32_t)a.delta * wpitch;
     const uint32_t wo0_last = nu < UW ? kNowhere : wo0 + (UW - 1) * kUnitBytes, wo1_last = nu < UW ? kNowhere : wo1 + (UW - 1) * kUnitBytes;
     // scale load of pack p: quarter q brings the scales of unit 4 p + q
     const uint32_t so = ((r16 & 7) + (r16 >> 3) * (uint32_t)a.delta) * spitch + (uint32_t)(u0 + qd) * (SW * 4);
+    const uint32_t so_last = SUMS && (SP - 1) * 4 + qd >= nu ? kNowhere : so + (SP - 1) * (4 * SW * 4);      // 0 for units that are not the wavefront's
     struct Where {                                        // the rest of the matrix from one row tile on; empty for a tile past the range
         __amdgpu_buffer_rsrc_t w, s;
     };
@@ -233,7 +274,7 @@ __global__ __launch_bounds__(kThreads) void fewrow_kernel(Args a)
             }
     };
     auto load_scales = [&](Tile &b, const Where &at, int p) {
-        const uint32_t o = so + p * (4 * SW * 4);
+        const uint32_t o = p == SP - 1 ? so_last : so + p * (4 * SW * 4);
         if (SW == 4) {
             b.s[p] = __builtin_amdgcn_raw_buffer_load_b128(at.s, o, 0, 0);
         } else if (SW == 2) {
@@ -248,28 +289,43 @@ __global__ __launch_bounds__(kThreads) void fewrow_kernel(Args a)
         const auto r = __builtin_amdgcn_permlane16_swap(va, vb, false, false);
         ra = r[0], rb = r[1];
     };
-    // the scale pairs of units 4 p .. 4 p + 3 for this lane's sub-groups 2 q and 2 q + 1
-    const uint32_t sel = (SW == 2 ? qd & 1 : qd >> 1) ? 0x03020302u : 0x01000100u;
+    // 4 x 4 transpose over words and quarters: word q of what quarter i holds -> r[i]
+    auto transpose4 = [&](const uint32_t (&v)[4], uint32_t (&r)[4]) {
+        const auto p02 = __builtin_amdgcn_permlane32_swap(v[0], v[2], false, false), p13 = __builtin_amdgcn_permlane32_swap(v[1], v[3], false, false);
+        swap16(p02[0], p13[0], r[0], r[1]);
+        swap16(p02[1], p13[1], r[2], r[3]);
+    };
+    // scales on codes: the scale pairs of units 4 p .. 4 p + 3 for this lane's sub-groups 2 q and 2 q + 1
     auto unpack_scales = [&](const u32x4_t v, uint32_t (*s2)[2]) {
+        const uint32_t vv[4] = {v[0], v[1], v[2], v[3]};
         uint32_t c4[4];
-        if (SW == 4) {                                    // word q of unit i: a 4 x 4 transpose over words and quarters
-            const auto p02 = __builtin_amdgcn_permlane32_swap(v[0], v[2], false, false), p13 = __builtin_amdgcn_permlane32_swap(v[1], v[3], false, false);
-            swap16(p02[0], p13[0], c4[0], c4[1]);
-            swap16(p02[1], p13[1], c4[2], c4[3]);
-        } else {                                          // two words: quarters 0, 1 need word 0 of a unit, quarters 2, 3 word 1; or one for all
-            const auto r = __builtin_amdgcn_permlane32_swap(v[0], SW == 2 ? v[1] : v[0], false, false);
-            const uint32_t lo = r[0], hi = r[1];          // units 4 p, 4 p + 1 and 4 p + 2, 4 p + 3 in the even and odd rows of 16 lanes
-            swap16(lo, lo, c4[0], c4[1]);
-            swap16(hi, hi, c4[2], c4[3]);
-        }
+        transpose4(vv, c4);
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            if (SW == 4) {
-                s2[i][0] = __builtin_amdgcn_perm(c4[i], c4[i], 0x01000100u);
-                s2[i][1] = __builtin_amdgcn_perm(c4[i], c4[i], 0x03020302u);
-            } else {
-                s2[i][0] = s2[i][1] = __builtin_amdgcn_perm(c4[i], c4[i], sel);
-            }
+            s2[i][0] = __builtin_amdgcn_perm(c4[i], c4[i], 0x01000100u);
+            s2[i][1] = __builtin_amdgcn_perm(c4[i], c4[i], 0x03020302u);
+        }
+    };
+    // 4-bit: the scales of units 4 p + 2 half and the next, as loaded by the quarters, for all quarters
+    auto spread_scales = [&](const u32x4_t v, int half, uint32_t (*su)[SW]) {
+#pragma unroll
+        for (int i = 0; i < SW; ++i) {
+            const auto r = __builtin_amdgcn_permlane32_swap(v[i], v[i], false, false);
+            swap16(r[half], r[half], su[0][i], su[1][i]);
+        }
+    };
+    // 4-bit, pieces 0..3 (or 4..7) of a unit, piece q in quarter q -> one word per MFMA step, such that the quarters of a step hold columns of
+    // one group: groups of 32 are four quarters of a piece, groups of 64 two halves of two pieces, groups of 128 the four pieces as they are
+    auto set_to_steps = [&](const u32x4_t v, uint32_t (&r)[4]) {
+        if (SG == 32) {
+            const uint32_t vv[4] = {v[0], v[1], v[2], v[3]};
+            transpose4(vv, r);
+        } else if (SG == 64) {
+            const auto p02 = __builtin_amdgcn_permlane32_swap(v[0], v[2], false, false), p13 = __builtin_amdgcn_permlane32_swap(v[1], v[3], false, false);
+            r[0] = p02[0], r[1] = p13[0], r[2] = p02[1], r[3] = p13[1];
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) r[j] = v[j];
         }
     };
 
@@ -295,6 +351,47 @@ __global__ __launch_bounds__(kThreads) void fewrow_kernel(Args a)
                 }
     }
 
+    // 4-bit: what the offsets of the codes add to a group's sum for x row r16, negated, in the lanes that load the scales of the group's unit, as three fp16
+    // parts (2^-13 or less of it, so that no x overflows; the next part scaled by 2^11).  The contraction over the groups with the
+    // scales as they are loaded takes the offsets out of a tile: three MFMAs per four units.
+    constexpr float kDown = SG == 32 ? 0x1p-13f : SG == 64 ? 0x1p-14f : 0x1p-15f;
+    // They wait in LDS (a slot of each wavefront's own): the registers are x's.
+    typedef _Float16 part_t __attribute__((ext_vector_type(GU > 1 ? GU : 2)));
+    part_t *const off = reinterpret_cast<part_t *>(red + (size_t)a.batch * (kWaves * NB * 64)) + wave * (NB * SP * 3 * 64) + lane;
+    if constexpr (SUMS) {
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+            for (int p = 0; p < SP; ++p) {
+                // rows of a constant matrix: those of quarter u % 4 hold what unit u's columns count, so that a lane gets its own units' sums
+                float o[GU];
+#pragma unroll
+                for (int j = 0; j < GU; ++j) {
+                    float4_t d = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+                    for (int u = 4 * p; u < UW && u < 4 * p + 4; ++u) {
+                        const uint32_t c1 = (r16 >> 2) == (u & 3) ? kOffset : 0u;
+                        const u32x4_t c = {c1, c1, c1, c1};
+#pragma unroll
+                        for (int s = j * GS; s < (j + 1) * GS; ++s)
+                            d = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, c), __builtin_bit_cast(half8_t, X[u][s][nb]), d, 0, 0, 0);
+                    }
+                    o[j] = d[0];
+                }
+#pragma unroll
+                for (int i = 0; i < 3; ++i) {
+                    part_t part;
+#pragma unroll
+                    for (int j = 0; j < GU; ++j) {
+                        const float v = o[j] * (i == 0 ? -kDown : 1.0f);
+                        part[j] = (_Float16)v;
+                        o[j] = (v - (float)part[j]) * 0x1p11f;
+                    }
+                    off[((nb * SP + p) * 3 + i) * 64] = part;
+                }
+            }
+    }
+
     // one row tile: its MFMAs, unit by unit, each unit's registers re-requested for tile t + T as soon as it is consumed
     auto consume = [&](Tile &b, int t, int at_batch) {
         float4_t acc[NB];
@@ -302,12 +399,44 @@ __global__ __launch_bounds__(kThreads) void fewrow_kernel(Args a)
         for (int nb = 0; nb < NB; ++nb) acc[nb] = float4_t{0.0f, 0.0f, 0.0f, 0.0f};
         float4_t rest = {0.0f, 0.0f, 0.0f, 0.0f};
         const Where next = where(t + T), cur = D < UW ? where(t) : next;
-        uint32_t s2[4][2];
+        uint32_t s2[SUMS ? 1 : 4][2], su[2][SW];
 #pragma unroll
         for (int u = 0; u < UW; ++u) {
+            float4_t d[2][NB];                            // 4-bit: sums of two groups
+            auto apply_scale = [&](int grp) {
+                const float sc = (float)__builtin_bit_cast(half2_t, su[u % 2][grp / 2])[grp % 2];
+#pragma unroll
+                for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) acc[nb][e] = fmaf(d[grp % 2][nb][e], sc, acc[nb][e]);
+            };
             if (SP && u % 4 == 0) {
-                unpack_scales(b.s[SP ? u / 4 : 0], s2);
-                load_scales(b, next, u / 4);
+                if constexpr (SUMS) {
+                    const u32x4_t v = b.s[SP ? u / 4 : 0];
+                    uint32_t zero = 0;
+                    asm volatile("" : "+v"(zero));        // read per tile: as loop invariants the parts would be kept in registers, or spilled
+                    const half8_t sv = __builtin_bit_cast(half8_t, u32x4_t{v[0], SW >= 2 ? v[1] : 0u, SW == 4 ? v[2] : 0u, SW == 4 ? v[3] : 0u});
+#pragma unroll
+                    for (int nb = 0; nb < NB; ++nb) {
+                        float4_t d = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+                        for (int i = 2; i >= 0; --i) {
+                            const part_t part = off[((nb * SP + u / 4) * 3 + i) * 64 + zero];
+                            half8_t pf;
+#pragma unroll
+                            for (int j = 0; j < 8; ++j) pf[j] = j < GU ? part[j < GU ? j : 0] : (_Float16)0.0f;
+                            d = __builtin_amdgcn_mfma_f32_16x16x32_f16(pf, sv, d, 0, 0, 0) * (i > 0 ? 0x1p-11f : 1.0f / kDown);
+                        }
+                        acc[nb] += d;
+                    }
+                } else {
+                    unpack_scales(b.s[SP ? u / 4 : 0], s2);
+                    load_scales(b, next, u / 4);
+                }
+            }
+            if (SUMS && u % 2 == 0) {
+                spread_scales(b.s[SP ? u / 4 : 0], u % 4 / 2, su);
+                if (u % 4 == 2 || u + 2 >= UW) load_scales(b, next, u / 4);
             }
             if (u < UW - 1 || nu == UW) {                 // wavefront-uniform, no memory operation inside
 #pragma unroll
@@ -328,13 +457,31 @@ __global__ __launch_bounds__(kThreads) void fewrow_kernel(Args a)
                         }
                     }
                 }
+                if constexpr (SUMS) {
+                    // x rows times weight rows: lane l holds weight row l % 16 of a group's sum and meets it with that row's scale in fp32, while the
+                    // next group's first MFMA runs (left to itself the compiler waits for every MFMA: 8 of 18 slots per step)
+                    uint32_t word[4];
 #pragma unroll
-                for (int s = 0; s < ST; ++s) {
+                    for (int s = 0; s < ST; ++s) {
+                        if (s % 4 == 0) set_to_steps(b.w[u % D][0][s / 4], word);
+                        const half8_t wf = raw_q4(word[s % 4]);
+#pragma unroll
+                        for (int nb = 0; nb < NB; ++nb)
+                            d[s / GS % 2][nb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, X[u][s][nb]), wf,
+                                                                                       s % GS == 0 ? float4_t{0.0f, 0.0f, 0.0f, 0.0f} : d[s / GS % 2][nb], 0, 0, 0);
+                        __builtin_amdgcn_sched_barrier(0);
+                        if (s >= GS && s % GS == 0) apply_scale(s / GS - 1);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                    apply_scale(GU - 1);
+                }
+#pragma unroll
+                for (int s = 0; s < (SUMS ? 0 : ST); ++s) {
                     half8_t af;
                     if (F16) {
                         af = __builtin_bit_cast(half8_t, b.w[Q3 ? 0 : u % D][F16 ? s >> 1 : 0][s & 1]);
                     } else {
-                        const uint32_t sc = s2[u % 4][(s >> 2) & 1];
+                        const uint32_t sc = s2[SUMS ? 0 : u % 4][(s >> 2) & 1];
                         const u32x4_t codes = Q3 ? decode_q3<EXACT>(b.w3[Q3 ? u % D : 0][(s >> 2) & 1], s & 3) : decode_q4(b.w[Q3 ? 0 : u % D][0][(s >> 2) & 1][s & 3]);
                         if (EXACT) {
                             const uint32_t upper = sc & 0xFFF8FFF8u;
@@ -355,9 +502,21 @@ __global__ __launch_bounds__(kThreads) void fewrow_kernel(Args a)
             __builtin_amdgcn_sched_barrier(0);            // keeps decodes of later units (and their registers) out of this one
         }
         if (EXACT) acc[0] = (acc[0] + rest * 0x1p-8f) * 4.0f;
+        if constexpr (SUMS) {
+            // lane l holds x rows 4 (l / 16) .. + 3 of weight row l % 16: into the layout that finish reads (float4 lane & 15 of row group
+            // l / 16 there is one x row's four weight rows), its lanes permuted so that the four stores meet no bank twice
 #pragma unroll
-        for (int nb = 0; nb < NB; ++nb) red[((at_batch * kWaves + wave) * NB + nb) * 64 + lane] = acc[nb];
+            for (int nb = 0; nb < NB; ++nb) {
+                float *dst = (float *)&red[((at_batch * kWaves + wave) * NB + nb) * 64];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) dst[(16 * (r16 >> 2) + ((4 * qd + e) ^ (r16 >> 2))) * 4 + (r16 & 3)] = acc[nb][e];
+            }
+        } else {
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) red[((at_batch * kWaves + wave) * NB + nb) * 64 + lane] = acc[nb];
+        }
     };
+    const int at_lane = SUMS ? lane ^ qd : lane;
 
     // ---- the wavefronts' shares of `count` tiles from t0 + first on: sum in order, epilogue ----
     // value layout of a tile block: lane l holds x row l % 16 of the block and tile rows 4 (l / 16) .. + 3; tile rows 0..7 are the
@@ -367,9 +526,9 @@ __global__ __launch_bounds__(kThreads) void fewrow_kernel(Args a)
             const int bt = it / NB, nb = it - bt * NB, t = t0 + first + bt;
             const int i = nb * 16 + r16, half = lane >> 5;
             if (nb * 16 >= a.n) continue;
-            float4_t v = red[(bt * kWaves * NB + nb) * 64 + lane];
+            float4_t v = red[(bt * kWaves * NB + nb) * 64 + at_lane];
 #pragma unroll
-            for (int w = 1; w < kWaves; ++w) v += red[((bt * kWaves + w) * NB + nb) * 64 + lane];
+            for (int w = 1; w < kWaves; ++w) v += red[((bt * kWaves + w) * NB + nb) * 64 + at_lane];
             const int row = tile_row(t) + (qd & 1) * 4 + half * a.delta;       // matrix row of v[0]
             if (a.epi == EPI_SWIGLU) {
                 float o[4];
@@ -383,7 +542,7 @@ __global__ __launch_bounds__(kThreads) void fewrow_kernel(Args a)
                 continue;
             }
             if (a.epi == EPI_ROPE_KV) {
-                // the fp16 rounding of the plain epilogue comes first; then both members of each rotation pair in either lane
+                // the fp16 rounding of the plain epilogue comes first (beyond kRopeOnce rows); then both members of each rotation pair in either lane
                 const uint32_t h01 = f2h(v[0]) | ((uint32_t)f2h(v[1]) << 16), h23 = f2h(v[2]) | ((uint32_t)f2h(v[3]) << 16);
                 const auto p01 = __builtin_amdgcn_permlane32_swap(h01, h01, false, false), p23 = __builtin_amdgcn_permlane32_swap(h23, h23, false, false);
                 const uint32_t ab[4] = {p01[0], p23[0], p01[1], p23[1]};
@@ -392,6 +551,13 @@ __global__ __launch_bounds__(kThreads) void fewrow_kernel(Args a)
                 for (int e = 0; e < 2; ++e) {
                     pa[2 * e] = h2f((uint16_t)(ab[e] & 0xFFFFu)), pa[2 * e + 1] = h2f((uint16_t)(ab[e] >> 16));
                     pb[2 * e] = h2f((uint16_t)(ab[2 + e] & 0xFFFFu)), pb[2 * e + 1] = h2f((uint16_t)(ab[2 + e] >> 16));
+                }
+                if (a.n <= kRopeOnce) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const float2 p = pair_xor32(v[e]);
+                        pa[e] = p.x, pb[e] = p.y;
+                    }
                 }
                 if (i >= a.n) continue;
                 const RowInfo ri = row_info(a.st, i);
@@ -402,8 +568,7 @@ __global__ __launch_bounds__(kThreads) void fewrow_kernel(Args a)
                     const float4_t c01 = *(const float4_t *)cs, c23 = *(const float4_t *)(cs + 4);
                     const float co[4] = {c01.x, c01.z, c23.x, c23.z}, si[4] = {c01.y, c01.w, c23.y, c23.w};
 #pragma unroll
-                    for (int e = 0; e < 4; ++e)           // contracted and rounded (once) as in the stand-alone rotary kernel: same bits
-                        o[e] = f2h(fmaf(pa[e], half ? si[e] : co[e], pb[e] * (half ? co[e] : -si[e])));
+                    for (int e = 0; e < 4; ++e) o[e] = fma_f16(pa[e], half ? si[e] : co[e], pb[e] * (half ? co[e] : -si[e]));
                 } else {
 #pragma unroll
                     for (int e = 0; e < 4; ++e) o[e] = f2h(v[e]);
@@ -441,9 +606,9 @@ __global__ __launch_bounds__(kThreads) void fewrow_kernel(Args a)
         for (int it = wave; it < count * NB; it += kWaves) {
             const int bt = it / NB, nb = it - bt * NB, i = nb * 16 + r16, row = (t0 + first + bt) * 16 + qd * 4;
             if (i >= a.n || row >= a.m) continue;
-            float4_t v = red[(bt * kWaves * NB + nb) * 64 + lane];
+            float4_t v = red[(bt * kWaves * NB + nb) * 64 + at_lane];
 #pragma unroll 1
-            for (int w = 1; w < kWaves; ++w) v += red[((bt * kWaves + w) * NB + nb) * 64 + lane];
+            for (int w = 1; w < kWaves; ++w) v += red[((bt * kWaves + w) * NB + nb) * 64 + at_lane];
             *(float4_t *)(a.out_f32 + ((size_t)kgi * a.n + i) * a.m + row) = v;
         }
     };
@@ -477,20 +642,16 @@ struct Plan {
     int kg, rg, uw, tiles;
 };
 
-// row tiles in flight (packed formats: 8 registers per unit, 1 KB per load), as far as the registers allow; the fp16 stream has
-// whole slices of 4 KB units in flight, and a long slice half of it
+// row tiles in flight (packed formats: 8 registers per unit, 1 KB per load), and units of a tile: 8 KB per wavefront are enough, fp16 16 KB
 template <int FMT, int NB, int UW>
 constexpr int tiles_in_flight()
 {
-    if (FMT == F_F16) return UW == 1 ? 2 : 1;
-    const int want = UW >= 5 ? 1 : UW >= 3 ? 2 : UW == 2 ? 3 : 4;
-    const int room = (216 - UW * 32 * NB) / (UW * 8 + 4 * ((UW + 3) / 4));
-    return want < room ? want : room < 1 ? 1 : room;
+    return UW == 1 ? 2 : 1;
 }
 template <int FMT, int NB, int UW>
 constexpr int units_in_flight()
 {
-    if (FMT == F_F16) return UW % 2 == 0 && UW * NB >= 6 ? UW / 2 : UW;
+    if (FMT == F_F16) return UW >= 6 ? 2 : UW % 2 == 0 && UW * NB >= 6 ? UW / 2 : UW;
     return UW == 6 ? 2 : UW;
 }
 
@@ -504,7 +665,7 @@ hipError_t launch_one(const Args &a, int lds_tiles, hipStream_t stream)
             return hipErrorInvalidValue;
         attr_done.store(true);
     }
-    hipLaunchKernelGGL((fewrow_kernel<FMT, NB, UW, T, D>), dim3(a.kg * a.rg), dim3(kThreads), (size_t)lds_tiles * kWaves * NB * 1024, stream, a);
+    hipLaunchKernelGGL((fewrow_kernel<FMT, NB, UW, T, D>), dim3(a.kg * a.rg), dim3(kThreads), (size_t)lds_tiles * kWaves * NB * 1024 + offset_bytes(FMT, NB, UW), stream, a);
     return hipGetLastError();
 }
 
@@ -524,6 +685,10 @@ hipError_t launch_nb(int nb, int uw, const Args &a, int lds_tiles, hipStream_t s
     if constexpr (FMT == F_F16) {
         if (nb == 1) return launch_uw<FMT, 1, 1, 2, 3, 4, 5, 6, 8>(uw, a, lds_tiles, stream);
         return launch_uw<FMT, 2, 1, 2, 3, 4>(uw, a, lds_tiles, stream);
+    } else if constexpr (FMT != F_Q3) {
+        if (nb == 1) return launch_uw<FMT, 1, 1, 2, 3, 4, 5>(uw, a, lds_tiles, stream);
+        if constexpr (FMT == F_Q4G32) return nb == 2 ? launch_uw<FMT, 2, 1, 2, 3>(uw, a, lds_tiles, stream) : launch_uw<FMT, 4, 1>(uw, a, lds_tiles, stream);
+        else return nb == 2 ? launch_uw<FMT, 2, 1, 2>(uw, a, lds_tiles, stream) : hipErrorInvalidValue;
     } else {
         if (nb == 1) return launch_uw<FMT, 1, 1, 2, 3, 4, 5, 6>(uw, a, lds_tiles, stream);
         if (nb == 2) return launch_uw<FMT, 2, 1, 2, 3>(uw, a, lds_tiles, stream);

@@ -264,3 +264,53 @@ def test_wide_layers_against_the_first_rows_of_a_larger_call(rx, fmt, shape, row
         got = layer.forward(x[:n].contiguous(), [n], [n]).double()
         assert float((got - want[:n]).norm() / want[:n].norm()) < 4e-3, (fmt, n)
         assert float((layer.k[0, :n].double() - k_all[0, :n].double()).norm() / k_all[0, :n].double().norm()) < 2e-3
+
+
+# Units per wavefront 1 (some wavefronts without any) to 5, whole and ragged; rows around a tile; one, two and three packs of scales
+EXACT_Q4 = [(20, 256), (40, 1280), (72, 4352), (520, 8192), (36, 9984), (40, 13824)]
+
+
+@pytest.mark.parametrize("m,k", EXACT_Q4)
+@pytest.mark.parametrize("group", [32, 64, 128])
+def test_4bit_scales_meet_fp32_sums(rx, group, m, k):
+    """Up to 16 rows of groups of 32 and 32 rows of longer ones are exact but for the fp32 sums and the rounding of the result, for scales of any size,
+    for x far from zero and for small x: the codes go in as u + 64, so a group's terms are at most 79 / 8 of those of its largest codes."""
+    g = _gen(m + k + group)
+    w, _ = _packed(rx, "q4", m, k, group, g)
+    codes = torch.empty(m, k, dtype=torch.int8, device="cuda")
+    rx.check(rx.relax_unpack_int4(w, codes))
+    size = rx.relax_matmul_workspace_bytes(w, 64)
+    ws = torch.empty(size, dtype=torch.uint8, device="cuda")
+    for low, high, mean, std in ((2.0 ** -24, 2.0 ** -14, 0.0, 1.0), (2.0 ** -8, 1.0, 0.5, 0.01), (1e-3, 1e-2, 0.0, 3e-4)):
+        s = torch.exp(torch.empty(m, k // group, device="cuda").uniform_(float(np.log(low)), float(np.log(high)), generator=g)).clamp(low, high).half()
+        w = rx.QMat(w.q, s, m, k, group)
+        ref = codes.double() * s.double().repeat_interleave(group, 1)
+        largest = 79 * s.double().repeat_interleave(group, 1)
+        for n in (2, 5, 16) + ((17, 32) if group > 32 else ()):
+            if rx.relax_plan_matmul("q4", n, m, k, size)[1] != rx.KERNEL_STREAM:      # (plans are for groups of 32; where the split-K kernel is near)
+                continue
+            x = (torch.randn(n, k, device="cuda", generator=g) * std + mean).half()
+            out = torch.empty(n, m, device="cuda", dtype=torch.float16)
+            rx.check(rx.relax_dequant_matmul(x, w, out, n, ws, size))
+            want, terms = x.double() @ ref.t(), x.double().abs() @ largest.t()
+            # 2^-25: half of the smallest fp16 step; at most 128 roundings lie on the way of a term (MFMAs of its group, its wavefront's groups, wavefronts)
+            bound = 2.0 ** -11 * want.abs() + 2.0 ** -25 + 128 * 2.0 ** -24 * terms
+            assert bool(((out.double() - want).abs() <= bound).all()), (n, low)
+
+
+@pytest.mark.parametrize("group", [32, 64, 128])
+def test_4bit_infinite_scales_stay_in_their_row(rx, group):
+    """... also next to units that a wavefront does not have, where the scales of the next row lie."""
+    m, k, n, g = 40, 1280, 5, _gen(5)
+    w, _ = _packed(rx, "q4", m, k, group, g)
+    size = rx.relax_matmul_workspace_bytes(w, 64)
+    ws = torch.empty(size, dtype=torch.uint8, device="cuda")
+    x = torch.randn(n, k, device="cuda", generator=g).half()
+    clean, out = (torch.empty(n, m, device="cuda", dtype=torch.float16) for _ in range(2))
+    rx.check(rx.relax_dequant_matmul(x, w, clean, n, ws, size))
+    s = w.s.clone()
+    s[7, 0], s[20] = float("inf"), float("nan")
+    rx.check(rx.relax_dequant_matmul(x, rx.QMat(w.q, s, m, k, group), out, n, ws, size))
+    rows = (torch.arange(m) != 7) & (torch.arange(m) != 20)
+    assert torch.equal(out[:, rows], clean[:, rows])
+    assert not torch.isfinite(out[:, ~rows].float()).any()
