@@ -28,7 +28,7 @@
 //   - Workgroups of the longest prefixes are first in dispatch order (causal work grows with the q position).
 //   - Cache rows past a sequence's length are never read (loads are clamped to its last row); masked scores are
 //     replaced, not multiplied, so stale cache contents cannot leak in.
-#include "relax_common.h"
+#include "attn_device.h"
 
 namespace relax {
 
@@ -69,13 +69,49 @@ __device__ __forceinline__ void lds_barrier()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
+// A sequence with one row beside a prompt: the eight wavefronts stream its cache like the split kernel of the decode calls do, one workgroup per
+// head, nothing staged; the states meet in LDS (float [wavefront][D + 2]).  As a 128-query tile with one live query it waited for
+// every 64-token tile: a 7B call of a 300-row chunk on 1201 tokens beside 20 rows on 90 to 1173 took 72 us, now 49; its K and V alone are 37.
+template <int D, int WAVES>
+__device__ __forceinline__ void decode_row(const uint16_t *q, const uint16_t *kc, const uint16_t *vc, uint16_t *out, const SeqInfo &si, int h, int g, int kvh, int cap,
+                                           float *sm)
+{
+    constexpr int LPT = D / 8, NL = D == 128 ? 4 : 2;         // heads of 64 have half the registers
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), e0 = (lane % LPT) * 8;
+    const size_t base = ((size_t)si.slot * cap * g + kvh) * D;
+    const char *ks = (const char *)(kc + base), *vs = (const char *)(vc + base);
+    auto load_q = [&] { return *(const u32x4a_t *)(q + e0); };
+    float m, l, acc[8];
+    if (h == g) attend_tokens<D, WAVES, NL, true>(ks, vs, (uint32_t)g * D * 2, 0, si.kv_len, wave, lane, load_q, m, l, acc);
+    else attend_tokens<D, WAVES, NL, false>(ks, vs, (uint32_t)g * D * 2, 0, si.kv_len, wave, lane, load_q, m, l, acc);
+    if (lane < LPT) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) sm[wave * (D + 2) + e0 + e] = acc[e];
+        if (lane == 0) sm[wave * (D + 2) + D] = m, sm[wave * (D + 2) + D + 1] = l;
+    }
+    __syncthreads();
+    if (tid < D) {
+        float mm = -INFINITY, num = 0.0f, den = 0.0f;
+#pragma unroll
+        for (int w = 0; w < WAVES; ++w) mm = fmaxf(mm, sm[w * (D + 2) + D]);
+#pragma unroll
+        for (int w = 0; w < WAVES; ++w) {
+            const float *src = sm + w * (D + 2);
+            const float sc = src[D] == -INFINITY ? 0.0f : __expf(src[D] - mm);     // a wavefront without a token
+            num += src[tid] * sc;
+            den += src[D + 1] * sc;
+        }
+        out[tid] = f2h(num / den);
+    }
+}
+
 // grid: x = query head, y = q tile (reversed: longest prefix first), z = sequence
 // MINW: wavefronts per SIMD the registers have to leave room for.  Heads of 64 fit two workgroups on a CU (4 per SIMD), which calls of
 // many short sequences live on.
 template <int D, int NWV, int KVS, int MINW>
 __global__ __launch_bounds__(64 * NWV, MINW) void attn_prefill_kernel(const uint16_t *__restrict__ q, int q_stride,
                                                                  const uint16_t *__restrict__ kc, const uint16_t *__restrict__ vc,
-                                                                 uint16_t *__restrict__ out, SeqTable st, int h, int g, int cap)
+                                                                 uint16_t *__restrict__ out, SeqTable st, int h, int g, int cap, int stream_rows)
 {
     // NWV wavefronts = QW query groups x KVS groups along the KV length: wavefront (qw, kg) owns queries qw WQ .. + WQ of the
     // workgroup and every KVS-th 32-token sub-tile (the longest prefix is then KVS times fewer steps per wavefront);
@@ -104,6 +140,11 @@ __global__ __launch_bounds__(64 * NWV, MINW) void attn_prefill_kernel(const uint
     // heads in an order that deals the KV heads out to the XCDs (workgroups go to them round-robin): the query heads of a KV head meet
     // in one L2
     const int kvh = blockIdx.x % g, head = kvh * (h / g) + blockIdx.x / g;
+    if (si.q_len == 1 && stream_rows) {
+        decode_row<D, NWV>(q + (size_t)si.q_start * q_stride + (size_t)head * D, kc, vc, out + ((size_t)si.q_start * h + head) * D, si, h, g, kvh, cap,
+                           reinterpret_cast<float *>(smem));
+        return;
+    }
     const int past = si.kv_len - si.q_len;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, qw = wave % QW, kg = wave / QW;
     const int i32 = lane & 31, hf = lane >> 5;
@@ -325,8 +366,10 @@ hipError_t launch_one(const uint16_t *q, int32_t q_stride, const relax_kv_cache 
 {
     const int queries = NWV / KVS * 32;
     const dim3 grid(dm.n_heads, (st.q_max + queries - 1) / queries, st.B);
+    // attend_tokens: 32-bit byte offsets inside a slot of the cache, and the two steps of all wavefronts that it counts past the end
+    const int stream_rows = ((size_t)dm.kv_capacity + 1024) * dm.n_kv_heads * D * 2 < ((size_t)1 << 31);
     hipLaunchKernelGGL((attn_prefill_kernel<D, NWV, KVS, MINW>), grid, dim3(64 * NWV), 0, stream, q, q_stride, cache.k, cache.v, out, st, dm.n_heads,
-                       dm.n_kv_heads, dm.kv_capacity);
+                       dm.n_kv_heads, dm.kv_capacity, stream_rows);
     return hipGetLastError();
 }
 
