@@ -5,14 +5,18 @@
 //
 // A workgroup is one (row, KV head, split along L); each of its four wavefronts walks its own 32-token tiles with no
 // workgroup barrier in the loop:
-//   S^T[t, head] = K[t, :] . Q[head, :]   A operand = the K tile straight from global memory (lane = token t % 32;
-//                                          k step ks takes d = 16 ks + 8 (l / 32) .. + 8), B operand = the query
-//                                          heads in the same order, read from LDS (written once per workgroup);
+//   S^T[t, head] = K[t, :] . Q[head, :]   A operand = the K tile (lane = token t % 32; k step ks takes d = 16 ks +
+//                                          8 (l / 32) .. + 8), B operand = the query heads in the same order, read
+//                                          from LDS (written once per workgroup);
 //   online softmax per column (= per head) inside a lane plus one exchange with lane ^ 32;
 //   O^T[d, head] += V^T[d, t] . P^T[t, head]   A operand = the V tile, staged in a wavefront-private LDS region and
 //                                          read with the LDS transpose read of gfx950 (lane r of a 16-lane block
 //                                          addresses V[t0 + r/4][d0 + 4 (r%4)], lane L receives V[t0..t0+3][d0 + L]);
 //                                          B operand = the probabilities the lane already holds.
+// Bound by the K / V stream.  Both tiles come in as whole rows with the non-temporal hint and go through the wavefront's LDS region, K first; with
+// K straight from global memory as the A operand a line was touched by four load instructions and the hint hurt.  64 / 8 heads of 128, with
+// the merge: 16 rows on 100 to 7990 tokens 69.0 -> 59.4 us (3.9 -> 4.5 TB/s), 32 rows on 2000 to 2620 81.4 -> 69.0.  Chunks of 384 to 1024
+// tokens are within 3 % of 512; three workgroups per CU spill (101 us).
 // Columns beyond the number of heads per group re-read the last head and are dropped.
 #include "relax_common.h"
 
@@ -36,6 +40,7 @@ __global__ __launch_bounds__(256, 2) void attn_gqa_kernel(const uint16_t *__rest
     constexpr int KS = D / 16;       // k steps of K Q^T
     constexpr int DB = D / 32;       // 32-wide blocks of the head dimension in O^T
     constexpr int VP = D + 32;       // V tile pitch in halfs (distinct banks for the transpose reads of a 32-lane half)
+    constexpr int KP = D + 8;        // K tile pitch in halfs: 16-byte reads of eight rows hit distinct banks
     constexpr int VPK = 32 * (D / 8) / 64;          // 16-byte V packets per lane and tile
     __shared__ __align__(16) uint16_t vs_all[4 * 32 * VP];
 
@@ -54,16 +59,15 @@ __global__ __launch_bounds__(256, 2) void attn_gqa_kernel(const uint16_t *__rest
     const size_t slot_base = (size_t)ri.slot * cap;
     const int tr_row = hf * 4 + ((lane & 15) >> 2), tr_col = ((lane >> 4) & 1) * 16 + (lane & 3) * 4;
 
-    // registers of one tile in flight: the lane's run of its K row (KS packets) and its share of the V tile
-    u32x4_t kreg[KS], vreg[VPK];
+    // registers of one tile in flight: the lane's shares of the K and of the V tile, whole rows per load instruction
+    u32x4_t kreg[VPK], vreg[VPK];
     auto tile_load = [&](int t0) {                             // rows are clamped to the split: masked later
-        const size_t krow = ((slot_base + min(t0 + col, t_end - 1)) * g + kvh) * D + hf * 8;
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) kreg[ks] = *(const u32x4_t *)(kc + krow + ks * 16);
 #pragma unroll
         for (int p = 0; p < VPK; ++p) {
             const int pk = lane + p * 64, r = pk / (D / 8), c = pk % (D / 8);
-            vreg[p] = stream_load((const u32x4_t *)(vc + ((slot_base + min(t0 + r, t_end - 1)) * g + kvh) * D + c * 8));
+            const size_t at = ((slot_base + min(t0 + r, t_end - 1)) * g + kvh) * D + c * 8;
+            kreg[p] = stream_load((const u32x4_t *)(kc + at));
+            vreg[p] = stream_load((const u32x4_t *)(vc + at));
         }
     };
 
@@ -91,18 +95,28 @@ __global__ __launch_bounds__(256, 2) void attn_gqa_kernel(const uint16_t *__rest
     float m_run = -INFINITY, l_run = 0.0f;
 
     for (int t0 = t_first; t0 < t_end; t0 += 128) {
-        // ---- S^T = K Q^T on the tile in registers; V tile to the wavefront's LDS region ----
+        // ---- K tile to the wavefront's LDS region and back as A operands: S^T = K Q^T; then the V tile in its place ----
+#pragma unroll
+        for (int p = 0; p < VPK; ++p) {
+            const int pk = lane + p * 64, r = pk / (D / 8), c = pk % (D / 8);
+            *(u32x4_t *)(vs + r * KP + c * 8) = kreg[p];
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup", "local");      // the wavefront's own LDS traffic is in order
+        half8_t kf[KS];
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) kf[ks] = *(const half8_t *)(vs + col * KP + hf * 8 + ks * 16);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup", "local");
         float16_t S;
 #pragma unroll
         for (int v = 0; v < 16; ++v) S[v] = 0.0f;
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) S = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(half8_t, kreg[ks]), *(const half8_t *)(q_lds + (ks * 64 + lane) * 8), S, 0, 0, 0);
+        for (int ks = 0; ks < KS; ++ks) S = __builtin_amdgcn_mfma_f32_32x32x16_f16(kf[ks], *(const half8_t *)(q_lds + (ks * 64 + lane) * 8), S, 0, 0, 0);
 #pragma unroll
         for (int p = 0; p < VPK; ++p) {
             const int pk = lane + p * 64, r = pk / (D / 8), c = pk % (D / 8);
             *(u32x4_t *)(vs + r * VP + c * 8) = vreg[p];
         }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");      // the wavefront's own LDS traffic is in order
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
         if (t0 + 128 < t_end) tile_load(t0 + 128);
         // ---- mask, online softmax per column; P^T packed as the B operand of the second product ----
         float mx = -INFINITY;

@@ -1,4 +1,5 @@
-"""GPU test of relax_attention on calls that carry decode rows beside a prompt chunk: the prefill kernel's form for sequences with one row."""
+"""GPU tests of relax_attention: calls that carry decode rows beside a prompt chunk (the prefill kernel's form for sequences with one row), and
+calls of decode rows alone with grouped heads."""
 import math
 
 import pytest
@@ -14,9 +15,19 @@ LENGTHS = [1, 2, 15, 16, 17, 127, 128, 129, 255, 256, 257, 300, 384, 511, 640, 1
 @pytest.mark.parametrize("h,g,d", [(4, 4, 128), (8, 2, 128), (6, 2, 64), (4, 4, 64)])
 @pytest.mark.parametrize("first", [True, False])
 def test_decode_rows_beside_a_prompt_against_float64(h, g, d, first):
+    prompt = (40, 200)
+    _check(h, g, d, [prompt] + [(1, L) for L in LENGTHS] if first else [(1, L) for L in LENGTHS[::-1]] + [prompt, (1, 3)])
+
+
+# Tiles of 32 tokens, four wavefronts, splits of up to 512 tokens: lengths around each; the largest group of query heads, and heads of 64
+@pytest.mark.parametrize("h,g,d", [(16, 2, 128), (16, 1, 128), (16, 4, 64)])
+def test_grouped_decode_rows_against_float64(h, g, d):
+    _check(h, g, d, [(1, L) for L in (1, 31, 32, 33, 64, 65, 96, 127, 128, 129, 160, 511, 512, 513, 1000)])
+
+
+def _check(h, g, d, seqs):
     from paper_2311_02103_amd import binding as rx
-    cap, prompt = 1024, (40, 200)
-    seqs = [prompt] + [(1, L) for L in LENGTHS] if first else [(1, L) for L in LENGTHS[::-1]] + [prompt, (1, 3)]
+    cap = 1024
     q_lens, kv_lens = [s[0] for s in seqs], [s[1] for s in seqs]
     gen = torch.Generator(device="cuda")
     gen.manual_seed(h * d + g)
