@@ -15,8 +15,8 @@
 //     (ds_read_b64_tr_b16) delivers from the untransposed tile: inside a block of 16 lanes, lane r supplies the
 //     address of 4 halfs and lane L receives half (L % 4) of the rows supplied by lanes L/4 + 4j, j = 0..3.
 //     With lane r pointing at V[t0 + r/4][d0 + 4 (r%4)], lane L receives V[t0 + 0..3][d0 + L].
-//   - A workgroup is 128 queries of one (sequence, head) on 8 wavefronts: 4 query groups of 32 x 2 groups along the
-//     KV length (a wavefront takes every second 32-token sub-tile; the two states of a query group are merged
+//   - A workgroup is 128 queries of one (sequence, head) on 8 wavefronts (calls with few of them: 64 queries and 4 KV groups): 4 query
+//     groups of 32 x 2 groups along the KV length (a wavefront takes every second 32-token sub-tile; the two states of a query group are merged
 //     through LDS at the end).  The step count of the longest prefix sets the kernel time, and this halves it; fewer
 //     queries per workgroup cost more than they give because every workgroup stages every K/V tile of its prefix.
 //     A wavefront keeps its 32 queries' Q fragments in registers, O^T (32 x d fp32) in accumulators.  KV tiles of
@@ -378,8 +378,18 @@ hipError_t launch_one(const uint16_t *q, int32_t q_stride, const relax_kv_cache 
 bool attn_prefill_supported(const relax_layer_dims &dm) { return dm.head_dim == 128 || dm.head_dim == 64; }
 
 hipError_t launch_attention_prefill(const uint16_t *q, int32_t q_stride, const relax_kv_cache &cache, const relax_layer_dims &dm,
-                                    const SeqTable &st, uint16_t *out, hipStream_t stream)
+                                    const SeqTable &st, int32_t L_max, uint16_t *out, hipStream_t stream)
 {
+    // A call whose tiles of 64 queries leave no CU with two takes them, with 4 KV groups (tiles of 128 tokens, 152 KB; heads of 64: 86 KB): half the
+    // steps of the longest prefix, and the CUs it takes stood idle (us, 128 queries x 2 groups / 64 x 4: 7B heads, 100 rows on 0, 500 and 1500
+    // cached tokens 9.1 / 8.2, 17.2 / 14.4, 32.8 / 27.5; 511 rows 16.1 / 13.8, 25.4 / 21.9, 40.6 / 33.3; 32 / 8 heads of 64, 300 rows on 1500 27.0 /
+    // 18.9).  One more tile per CU and the other form is the faster one (7B heads, 700 rows on 1500 42.7 / 56.1), as it is on short
+    // prefixes of up to 64 queries, where both have one tile (64 rows on none 7.2 / 8.0, on 500 14.8 / 14.2).
+    const long long tiles = (long long)dm.n_heads * st.B * ((st.q_max + 63) / 64);
+    if (tiles <= 256 && (st.q_max > 64 || L_max >= 400)) {
+        if (dm.head_dim == 128) return launch_one<128, 8, 4, 2>(q, q_stride, cache, dm, st, out, stream);
+        if (dm.head_dim == 64) return launch_one<64, 8, 4, 2>(q, q_stride, cache, dm, st, out, stream);
+    }
     // 8 wavefronts = 4 query groups of 32 x 2 KV groups, two tiles of 64 tokens in LDS (76 KB; heads of 64: 43 KB).  Measured, against one
     // tile of 64 tokens with the softmax in units of e and masks on every tile, and against two tiles of 128 tokens (152 KB, 86 KB):
     //   4096 rows, 32 / 8 heads of 128               181 us   214   188

@@ -493,7 +493,7 @@ hipError_t launch_attention_gqa_split(const uint16_t *q, int32_t q_stride, const
 constexpr int kPrefillMinQ = 16;     // longest q_len from which launch_attention takes the MFMA kernel
 bool attn_prefill_supported(const relax_layer_dims &dm);
 hipError_t launch_attention_prefill(const uint16_t *q, int32_t q_stride, const relax_kv_cache &cache, const relax_layer_dims &dm,
-                                    const SeqTable &st, uint16_t *out, hipStream_t stream);
+                                    const SeqTable &st, int32_t L_max, uint16_t *out, hipStream_t stream);
 
 // Model wrapper steps (model_head.hip)
 hipError_t launch_embed(const int32_t *ids, const uint16_t *E, uint16_t *x, int n, int H, int V, uint32_t *err, hipStream_t stream);
