@@ -19,8 +19,7 @@ bool uw_built(int fmt, int nb, int uw)                    // the instances of la
 {
     if (fmt == F_F16) return uw >= 1 && (nb == 1 ? uw <= 6 || uw == 8 : nb == 2 && uw <= 4);
     if (fmt == F_Q3) return uw >= 1 && uw <= (nb == 1 ? 6 : nb == 2 ? 3 : 1);
-    if (fmt == F_Q4G32) return uw >= 1 && uw <= (nb == 1 ? 5 : nb == 2 ? 3 : 1);
-    return uw >= 1 && uw <= (nb == 1 ? 5 : nb == 2 ? 2 : 0);
+    return uw >= 1 && uw <= (nb == 1 ? 5 : nb == 2 ? 3 : fmt == F_Q4G32 ? 1 : 0);
 }
 
 int lds_tiles(int fmt, int nb, int uw) { return (int)((kLdsBytes - offset_bytes(fmt, nb, uw)) / ((size_t)kWaves * nb * 1024)); }
@@ -108,6 +107,11 @@ double split_us(int n, int m, int k)
            (double)splits * n * m * 8e-6 / c.partial;
 }
 
+// Up to 16 rows of a layer's output and down projections, where both kernels need the finishing pass: by themselves they tie on many matrices
+// (5120 x 13824 at 16 rows 17.7 against 17.5), inside a layer the split-K kernel, with less x traffic, is ahead of its estimate (13B: 14 rows
+// of the down projection 17.0 us against 20.0, 6 of the output projection 14.2 against 14.6; the QKV matrix of the 70B shape is not: 20.3
+// against 22.0 with the rotary step, nor is its down projection, 33 against 38 at 4 rows).
+constexpr double kCutTie = 1.5;
 constexpr double kSplitCoarse = 1.1;                      // groups of 64 and 128: its scale staging is made for groups of 32
 
 bool shape_ok(bool f16, int n, int m, int k, int epi)
@@ -172,7 +176,7 @@ int fewrow_ranges(int wmode, int gshift, int n, int m, int k, int epi, bool fold
     // on the others (22016 x 4096 at 16 rows 19.1 against 23.4, 57344 x 8192 58 against 74).
     // Up to kRopeOnce rows of a layer stay here: that kernel rounds the weights, which the matvec kernels do not.
     if (wmode == W_Q4 && kr > 0 && (alone || n > kRopeOnce) && gemm_skinny_partial_floats(m, k, n) > 0 && partial_floats >= gemm_skinny_partial_floats(m, k, n) &&
-        gemm_skinny_us(n, m, k, gshift) - (folded ? kFolded : 0.0) < us)
+        gemm_skinny_us(n, m, k, gshift) - (folded ? kFolded : 0.0) < us + (!alone && n <= 16 && kr > 1 && epi != EPI_F16 ? kCutTie : 0.0))
         return 0;
     // ... and on matrices that fill the chip with tiles through the tiled GEMM (48 rows: 49152 x 2048 26.5 against 45.3 us, 57344 x 8192 87 against 99),
     // in a layer from 33 rows on wherever that is estimated faster (64 rows, stream / split-K / tiled: 22016 x 4096 33 / 39 / 30, 27648 x 5120 47 / 53

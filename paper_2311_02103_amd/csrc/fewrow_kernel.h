@@ -57,15 +57,16 @@ typedef uint32_t u32x3_t __attribute__((ext_vector_type(3)));
 enum { F_Q4G32 = 0, F_Q4G64 = 1, F_Q4G128 = 2, F_Q3 = 3, F_F16 = 4 };
 
 constexpr int kWaves = 8, kThreads = kWaves * 64;
-// 4-bit: whether a group's scale meets the fp32 sum of its products (exact), or its codes (one rounding per weight)
-constexpr bool scale_sums(int fmt, int nb) { return fmt == F_Q4G64 || fmt == F_Q4G128 || (fmt == F_Q4G32 && nb == 1); }
+// 4-bit: whether a group's scale meets the fp32 sum of its products (exact), or its codes (one rounding per weight; three units of 32 x rows leave
+// no registers for sums, and in two k ranges instead a 13B layer of 17 rows with groups of 64 took 123 us, so 120)
+constexpr bool scale_sums(int fmt, int nb, int uw) { return fmt == F_Q4G64 || fmt == F_Q4G128 ? uw * nb < 6 : fmt == F_Q4G32 && nb == 1; }
 constexpr int unit_columns(bool f16) { return f16 ? 128 : 256; }      // a row's share of a unit: 128 bytes, 96 (3-bit) or 2 x 128 (fp16)
 constexpr int kTileRows = 16;
 constexpr uint32_t kNowhere = 0x80000000u;                // an offset past every buffer (they are at most 2^31 - 1 bytes)
 constexpr size_t kLdsBytes = 152 * 1024;                  // partial tiles of a batch, and the offsets of 4-bit codes
 constexpr size_t offset_bytes(int fmt, int nb, int uw)
 {
-    return scale_sums(fmt, nb) ? (size_t)kWaves * nb * ((uw + 3) / 4) * 3 * (fmt == F_Q4G32 ? 1024 : fmt == F_Q4G64 ? 512 : 256) : 0;
+    return scale_sums(fmt, nb, uw) ? (size_t)kWaves * nb * ((uw + 3) / 4) * 3 * (fmt == F_Q4G32 ? 1024 : fmt == F_Q4G64 ? 512 : 256) : 0;
 }
 
 struct Args {
@@ -110,12 +111,13 @@ __device__ __forceinline__ half8_t raw_q4(uint32_t w)
     const uint32_t mask = 0x00F000F0u, base = 0x54005400u;
     return __builtin_bit_cast(half8_t, u32x4_t{and_or3(w << 4, mask, base), and_or3(w, mask, base), and_or3(w >> 4, mask, base), and_or3(w >> 8, mask, base)});
 }
-constexpr uint32_t kOffset = 0x54805480u, kNegOffset = 0xD480D480u;    // the codes mean u - 8: 72 is in every one too many
-// the same without it, exactly
+constexpr uint32_t kOffset = 0x54805480u;                              // the codes mean u - 8: 72 is in every one too many
+// its codes less 8, in the same order: 1024 + u - 1032, 64 + u - 72 (two shifts less than raw_q4)
 __device__ __forceinline__ u32x4_t decode_q4(uint32_t w)
 {
-    const u32x4_t r = __builtin_bit_cast(u32x4_t, raw_q4(w));
-    return u32x4_t{pk_add(r[0], kNegOffset), pk_add(r[1], kNegOffset), pk_add(r[2], kNegOffset), pk_add(r[3], kNegOffset)};
+    const uint32_t w8 = w >> 8, kNeg1032 = 0xE408E408u, kNeg72 = 0xD480D480u;
+    return u32x4_t{pk_add(and_or3(w, 0x000F000Fu, 0x64006400u), kNeg1032), pk_add(and_or3(w, 0x00F000F0u, 0x54005400u), kNeg72),
+                   pk_add(and_or3(w8, 0x000F000Fu, 0x64006400u), kNeg1032), pk_add(and_or3(w8, 0x00F000F0u, 0x54005400u), kNeg72)};
 }
 // packet j (columns 8j .. 8j+7) of a 3-bit group from its three words -> its codes less 4 as fp16: pairs (1024 + f u) with f = 1, 8
 // or 64 by class, one packed fma removes weight and offset exactly ((1024 + f u) / f - (1024 / f + 4) = u - 4).
@@ -193,7 +195,7 @@ __global__ __launch_bounds__(kThreads) void fewrow_kernel(Args a)
     // of a 7B layer was 3.20e-4 off the 64-bit result instead of 2.95e-4 (the split costs 4 us of 62).  Elsewhere the products are
     // rounded once, as in the split-K kernel and the tiled GEMM.
     constexpr bool EXACT = NB == 1 && Q3;
-    constexpr bool SUMS = scale_sums(FMT, NB);
+    constexpr bool SUMS = scale_sums(FMT, NB, UW);
     constexpr int GU = SUMS ? 256 / SG : 1;               // groups of a unit: one, two or four MFMA steps each
     constexpr int GS = ST / GU;
     extern __shared__ __align__(16) float4_t red[];       // [tile of the batch][wavefront][NB][64]
@@ -296,14 +298,21 @@ __global__ __launch_bounds__(kThreads) void fewrow_kernel(Args a)
         swap16(p02[1], p13[1], r[2], r[3]);
     };
     // scales on codes: the scale pairs of units 4 p .. 4 p + 3 for this lane's sub-groups 2 q and 2 q + 1
+    const uint32_t sel = (SW == 2 ? qd & 1 : qd >> 1) ? 0x03020302u : 0x01000100u;
     auto unpack_scales = [&](const u32x4_t v, uint32_t (*s2)[2]) {
-        const uint32_t vv[4] = {v[0], v[1], v[2], v[3]};
         uint32_t c4[4];
-        transpose4(vv, c4);
+        if (SW == 4) {
+            const uint32_t vv[4] = {v[0], v[1], v[2], v[3]};
+            transpose4(vv, c4);
+        } else {                                          // two words: quarters 0, 1 need word 0 of a unit, quarters 2, 3 word 1; or one for all
+            const auto r = __builtin_amdgcn_permlane32_swap(v[0], SW == 2 ? v[1] : v[0], false, false);
+            swap16(r[0], r[0], c4[0], c4[1]);             // units 4 p, 4 p + 1 in the even and odd rows of 16 lanes
+            swap16(r[1], r[1], c4[2], c4[3]);
+        }
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            s2[i][0] = __builtin_amdgcn_perm(c4[i], c4[i], 0x01000100u);
-            s2[i][1] = __builtin_amdgcn_perm(c4[i], c4[i], 0x03020302u);
+            s2[i][0] = __builtin_amdgcn_perm(c4[i], c4[i], SW == 4 ? 0x01000100u : sel);
+            s2[i][1] = __builtin_amdgcn_perm(c4[i], c4[i], SW == 4 ? 0x03020302u : sel);
         }
     };
     // 4-bit: the scales of units 4 p + 2 half and the next, as loaded by the quarters, for all quarters
@@ -687,8 +696,9 @@ hipError_t launch_nb(int nb, int uw, const Args &a, int lds_tiles, hipStream_t s
         return launch_uw<FMT, 2, 1, 2, 3, 4>(uw, a, lds_tiles, stream);
     } else if constexpr (FMT != F_Q3) {
         if (nb == 1) return launch_uw<FMT, 1, 1, 2, 3, 4, 5>(uw, a, lds_tiles, stream);
-        if constexpr (FMT == F_Q4G32) return nb == 2 ? launch_uw<FMT, 2, 1, 2, 3>(uw, a, lds_tiles, stream) : launch_uw<FMT, 4, 1>(uw, a, lds_tiles, stream);
-        else return nb == 2 ? launch_uw<FMT, 2, 1, 2>(uw, a, lds_tiles, stream) : hipErrorInvalidValue;
+        if (nb == 2) return launch_uw<FMT, 2, 1, 2, 3>(uw, a, lds_tiles, stream);
+        if constexpr (FMT == F_Q4G32) return launch_uw<FMT, 4, 1>(uw, a, lds_tiles, stream);
+        else return hipErrorInvalidValue;
     } else {
         if (nb == 1) return launch_uw<FMT, 1, 1, 2, 3, 4, 5, 6>(uw, a, lds_tiles, stream);
         if (nb == 2) return launch_uw<FMT, 2, 1, 2, 3>(uw, a, lds_tiles, stream);
