@@ -523,7 +523,7 @@ def bench_model(args, np, torch, wl, rx, big):
     m, k = shape.matrices()["wgu"]
     gu_bytes = m * (k // 2) + m * (k // 32) * 2
     ach = gu_bytes / (kernel_ms["gate_up"] * 1e-3) / 1e9
-    kernel = ("fewrow_kernel<F_Q4G32, 1, 4, 2, 4> (gate/up with SwiGLU, m=57344, k=8192, n=16)" if big else
+    kernel = ("fewrow_kernel<F_Q4G32, 1, 4, 1, 4> (gate/up with SwiGLU, m=57344, k=8192, n=16)" if big else
               "gemv_q4_reg_kernel<X_F32_NORM, EPI_SWIGLU, 2> (gate/up matvec, m=22016, k=4096)")
     roofline = {"bound": "hbm", "kernel": kernel, "achieved": round(ach, 1), "peak": PEAK_HBM_GBS, "unit": "GB/s",
                 "frac": round(ach / PEAK_HBM_GBS, 4),
@@ -599,7 +599,7 @@ def bench_batch_sweep(args, np, torch, wl, rx):
             calls[i % sets](stream.cuda_stream)
         stream.synchronize()
         us = (time.perf_counter() - t0) * 1e6 / steps
-        matmuls = ("matvec" if n == 1 else "matvec, 2 or 4 rows per pass" if n <= 4 else "few-row MFMA" if n <= 64 else "tiled GEMM")
+        matmuls = ("matvec" if n == 1 else "matvec, 2 rows per pass" if n == 2 else "few-row MFMA" if n <= 32 else "few-row MFMA or tiled GEMM" if n <= 64 else "tiled GEMM")
         rows.append({"n": n, "us_per_call": round(us, 1), "layer_tokens_per_s": round(n / us * 1e6, 0), "matmul_kernels": matmuls})
     best = max(rows, key=lambda r: r["layer_tokens_per_s"])
     emit(args, "layer-tokens/s of one 7B-shaped int4 layer call against the number of decode rows (best point)", "tokens/s",
