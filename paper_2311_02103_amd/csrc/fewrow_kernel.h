@@ -367,9 +367,12 @@ __global__ __launch_bounds__(kThreads) void fewrow_kernel(Args a)
     // They wait in LDS (a slot of each wavefront's own): the registers are x's.
     typedef _Float16 part_t __attribute__((ext_vector_type(GU > 1 ? GU : 2)));
     part_t *const off = reinterpret_cast<part_t *>(red + (size_t)a.batch * (kWaves * NB * 64)) + wave * (NB * SP * 3 * 64) + lane;
+    uint32_t odd = 0;                                     // bits of the x rows whose sums are not finite in the wavefront's columns (see redo)
+    static_assert(!SUMS || NB <= 2, "a bit per row");
     if constexpr (SUMS) {
 #pragma unroll
-        for (int nb = 0; nb < NB; ++nb)
+        for (int nb = 0; nb < NB; ++nb) {
+            float nan = 0.0f;
 #pragma unroll
             for (int p = 0; p < SP; ++p) {
                 // rows of a constant matrix: those of quarter u % 4 hold what unit u's columns count, so that a lane gets its own units' sums
@@ -386,6 +389,7 @@ __global__ __launch_bounds__(kThreads) void fewrow_kernel(Args a)
                             d = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, c), __builtin_bit_cast(half8_t, X[u][s][nb]), d, 0, 0, 0);
                     }
                     o[j] = d[0];
+                    nan = fmaf(o[j], 0.0f, nan);
                 }
 #pragma unroll
                 for (int i = 0; i < 3; ++i) {
@@ -399,6 +403,9 @@ __global__ __launch_bounds__(kThreads) void fewrow_kernel(Args a)
                     off[((nb * SP + p) * 3 + i) * 64] = part;
                 }
             }
+            const uint64_t lanes = __ballot(nan != nan);
+            odd |= ((uint32_t)(lanes | lanes >> 16 | lanes >> 32 | lanes >> 48) & 0xFFFFu) << (nb * 16 % 32);
+        }
     }
 
     // one row tile: its MFMAs, unit by unit, each unit's registers re-requested for tile t + T as soon as it is consumed
@@ -622,6 +629,37 @@ __global__ __launch_bounds__(kThreads) void fewrow_kernel(Args a)
         }
     };
 
+    // 4-bit rows of x with an infinity or a NaN: the sums of 64 + u lose an infinity to the offset (inf - inf), where its product with a code less 8 is
+    // infinite.  The wavefront that holds one computes its shares of these rows once more from codes less 8, in plain fp32 (40 us per row and
+    // tile at most); the rows beside them keep their bits, the calls without pay 0.1 us for the look.
+    auto redo = [&](int first, int count) {
+#pragma unroll 1
+        for (int it = 0; it < count * NB; ++it) {
+            const int bt = it / NB, nb = it - bt * NB;
+            const Where at = where(first + bt);
+            const uint32_t row = (r16 & 7) + (r16 >> 3) * (uint32_t)a.delta;
+            float *dst = (float *)&red[((bt * kWaves + wave) * NB + nb) * 64];
+#pragma unroll 1
+            for (uint32_t todo = odd >> (nb * 16 % 32) & 0xFFFFu; todo; todo &= todo - 1) {
+                const int i = __builtin_ctz(todo);
+                float sum = 0.0f;
+#pragma unroll 1
+                for (int c = u0 * kUnit + qd * 8; c < (u0 + nu) * kUnit; c += 32) {
+                    const uint32_t w = __builtin_amdgcn_raw_buffer_load_b32(at.w, row * wpitch + (uint32_t)c / 2, 0, 0);
+                    const uint16_t sc = __builtin_amdgcn_raw_buffer_load_b16(at.s, row * spitch + (uint32_t)(c / SG) * 2, 0, 0);
+                    const half8_t xv = *(const half8_t *)(a.x + (size_t)(nb * 16 + i) * a.k + c);
+                    float part = 0.0f;
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) part = fmaf((float)((int)(w >> (4 * e) & 15u) - 8), (float)xv[e], part);
+                    sum = fmaf(part, h2f(sc), sum);
+                }
+                sum += __shfl_xor(sum, 16, kWave);
+                sum += __shfl_xor(sum, 32, kWave);
+                if (qd == 0) dst[(16 * (r16 >> 2) + (i ^ (r16 >> 2))) * 4 + (r16 & 3)] = sum;
+            }
+        }
+    };
+
     int first = 0, filled = 0;                            // tiles first .. first + filled - 1 of the range sit in LDS
     for (int t = 0;; t += T) {
         bool done = false;
@@ -634,6 +672,8 @@ __global__ __launch_bounds__(kThreads) void fewrow_kernel(Args a)
                 break;
             }
             if (NB > 1 && filled == a.batch) {            // more tiles than LDS holds (partial rows only: the launcher sees to it)
+                if constexpr (SUMS)
+                    if (odd) redo(first, filled);
                 lds_barrier();
                 flush(first, filled);
                 lds_barrier();
@@ -642,6 +682,8 @@ __global__ __launch_bounds__(kThreads) void fewrow_kernel(Args a)
         }
         if (done) break;
     }
+    if constexpr (SUMS)
+        if (odd) redo(first, filled);
     lds_barrier();
     finish(first, filled);
 }

@@ -314,3 +314,28 @@ def test_4bit_infinite_scales_stay_in_their_row(rx, group):
     rows = (torch.arange(m) != 7) & (torch.arange(m) != 20)
     assert torch.equal(out[:, rows], clean[:, rows])
     assert not torch.isfinite(out[:, ~rows].float()).any()
+
+
+@pytest.mark.parametrize("m,k", [(40, 1280), (24, 13824)])
+@pytest.mark.parametrize("n", [5, 16, 32])
+@pytest.mark.parametrize("group", [32, 64, 128])
+def test_4bit_infinite_x_keeps_its_sign(rx, group, n, m, k):
+    """An infinity in x times a code is an infinity of that sign, times code 0 a NaN, however the codes' offset is taken out; and the row's alone."""
+    g = _gen(m + k + group)
+    w, ref = _packed(rx, "q4", m, k, group, g)
+    size = rx.relax_matmul_workspace_bytes(w, 64)
+    assert rx.relax_plan_matmul("q4", n, m, k, size)[1] == rx.KERNEL_STREAM
+    ws = torch.empty(size, dtype=torch.uint8, device="cuda")
+    x = torch.randn(n, k, device="cuda", generator=g).half()
+    clean, out = (torch.empty(n, m, device="cuda", dtype=torch.float16) for _ in range(2))
+    rx.check(rx.relax_dequant_matmul(x, w, clean, n, ws, size))
+    inf = float("inf")
+    x[1, 77], x[2, k - 1], x[n - 1, 300], x[3, 5] = inf, -inf, inf, float("nan")
+    rx.check(rx.relax_dequant_matmul(x, w, out, n, ws, size))
+    for i, column, sign in ((1, 77, 1.0), (2, k - 1, -1.0), (n - 1, 300, 1.0)):
+        want = (ref[:, column] * (sign * inf)).half()
+        assert torch.equal(torch.isnan(out[i]), torch.isnan(want)), i
+        assert torch.equal(out[i][~torch.isnan(want)], want[~torch.isnan(want)]), i
+    assert torch.isnan(out[3]).all()
+    others = [i for i in range(n) if i not in (1, 2, 3, n - 1)]
+    assert torch.equal(out[others], clean[others])
