@@ -19,7 +19,8 @@ extern "C" {
  * pass of a matmul that is cut along k, or the epilogue of a streaming one, also does the light step that follows it (rotary
  * embedding + KV append after QKV; in a finishing pass the RMSNorm after the output projection, and in relax_model_step
  * the first RMSNorm of the next layer after the down projection: Sec. 4.2 operator fusion); 0 runs them as launches of
- * their own.  Results are identical bit for bit either way.
+ * their own (three and four rows that the streaming kernel takes from the matrix-vector kernels: not the rotary step, which
+ * rounds q and k once there, as those kernels do).  Results are identical bit for bit either way.
  * "gemm_waves_per_simd" (1 or 2): accepted, without effect (the tiled GEMM has one form per tile).
  * "layer_matvec_rows" (default 4, 1 .. 64): relax_decoder_layer and relax_model_step keep a call of up to this many rows on
  * the matrix-vector kernels (two or four rows of x share one pass over the weights): two rows on every model, more when

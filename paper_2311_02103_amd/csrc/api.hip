@@ -737,9 +737,13 @@ relax_status layer_enqueue(const relax_layer_dims &dm, const relax_layer_weights
     // Three and four rows take the streaming kernel where it serves all four matrices: as exact, and faster or the same from the 7B shape on (us
     // per layer at L = 300, matvec / stream, groups of 32 and 128: 7B 59 / 58 and 59 / 55 at three rows, 62 / 60 and 62 / 57 at four; 13B 87 / 76
     // and 87 / 70, 88 / 78 and 89 / 73).
-    const bool streams = n > 2 && n <= kRopeOnce && stream(wt->wqkv, x, EPI_F16) && stream(wt->wo, x, EPI_RESID_F32) && stream(wt->wgu, x, EPI_SWIGLU) &&
-                         stream(wt->wdown, x, EPI_RESID_F16) && fewrow_fuse_ok(dm, *cache);
-    const bool rows_as_matvecs = n >= 2 && n <= g_opt_matvec_rows.load() && (n == 2 || (largest <= ((size_t)g_opt_matvec_mb.load() << 20) && !streams));
+    const bool matvec_call = n >= 2 && n <= g_opt_matvec_rows.load() && (n == 2 || largest <= ((size_t)g_opt_matvec_mb.load() << 20));
+    SkinnyFuse fq = {};
+    fq.dm = &dm, fq.cache = cache, fq.st = &st;
+    const int qkv_ranges = stream(wt->wqkv, x, EPI_F16);
+    fq.rope_once = matvec_call && n > 2 && n <= kMatvecRows && qkv_ranges && stream(wt->wo, x, EPI_RESID_F32) && stream(wt->wgu, x, EPI_SWIGLU) &&
+                   stream(wt->wdown, x, EPI_RESID_F16) && fewrow_fuse_ok(dm, *cache) && (qkv_ranges == 1 || gemm_skinny_fuse_ok(wt->wqkv, EPI_F16, fq));
+    const bool rows_as_matvecs = matvec_call && !fq.rope_once;
     if (n >= kSkinnyMinN && !rows_as_matvecs && mat_ok(wt->wqkv, x, EPI_F16) && mat_ok(wt->wo, x, EPI_RESID_F32) && mat_ok(wt->wgu, x, EPI_SWIGLU) &&
         mat_ok(wt->wdown, x, EPI_RESID_F16)) {
         uint16_t *xn = reinterpret_cast<uint16_t *>(base + pl.xn), *qkv = reinterpret_cast<uint16_t *>(base + pl.qkv);
@@ -749,7 +753,7 @@ relax_status layer_enqueue(const relax_layer_dims &dm, const relax_layer_weights
         hipError_t fuse_err = hipSuccess;
         const bool fuse_finish = g_opt_fuse_finish.load() != 0;
         auto fused = [&](const uint16_t *xin, const relax_qmat &wq, int epi, uint16_t *o16, float *o32, const void *resid, const SkinnyFuse &f) {
-            if (!fuse_finish) return false;
+            if (!fuse_finish && !(fq.rope_once && epi == EPI_F16)) return false;
             const int kr = stream(wq, xin, epi);
             if (kr == 1) {   // no finishing pass: rotary + append is its epilogue, a norm is not
                 if (epi != EPI_F16 || !fewrow_fuse_ok(dm, *cache)) return false;
@@ -774,8 +778,6 @@ relax_status layer_enqueue(const relax_layer_dims &dm, const relax_layer_weights
         };
         timer.before(0);
         if (!xn_ready && first_norm(x, wt->norm_attn, xn, n, dm, carry, st_) != hipSuccess) return RELAX_ERR_HIP;
-        SkinnyFuse fq = {};
-        fq.dm = &dm, fq.cache = cache, fq.st = &st;
         if (!fused(xn, wt->wqkv, EPI_F16, qkv, nullptr, nullptr, fq)) {
             if (matmul(xn, wt->wqkv, EPI_F16, qkv, nullptr, nullptr) != hipSuccess) return RELAX_ERR_HIP;
             if (launch_rope_append(qkv, dm, *cache, st, st_) != hipSuccess) return RELAX_ERR_HIP;

@@ -140,7 +140,7 @@ hipError_t launch(int fmt, const uint16_t *x, const void *w, size_t w_bytes, con
         const relax_layer_dims &dm = *fuse->dm;
         a.epi = EPI_ROPE_KV, a.delta = dm.head_dim / 2, a.ropeshift = dm.head_dim == 128 ? 3 : 2;
         a.kc = fuse->cache->k, a.vc = fuse->cache->v, a.rope = fuse->cache->rope;
-        a.h = dm.n_heads, a.g = dm.n_kv_heads, a.d = dm.head_dim, a.cap = dm.kv_capacity, a.st = *fuse->st;
+        a.h = dm.n_heads, a.g = dm.n_kv_heads, a.d = dm.head_dim, a.cap = dm.kv_capacity, a.rope_once = fuse->rope_once, a.st = *fuse->st;
     } else {
         a.epi = epi;
         if (epi == EPI_SWIGLU) a.delta = m / 2;
@@ -174,8 +174,8 @@ int fewrow_ranges(int wmode, int gshift, int n, int m, int k, int epi, bool fold
     // x traffic, a lower rate.  It is the better one where its workgroups fill the chip and rows are long or x has many rows (8192 x
     // 8192 at 16 rows 16.5 against 18.6 us, 5120 x 13824 17.8 against 20.0, 15360 x 5120 at 64 rows 29.9 against 35.4), the stream
     // on the others (22016 x 4096 at 16 rows 19.1 against 23.4, 57344 x 8192 58 against 74).
-    // Up to kRopeOnce rows of a layer stay here: that kernel rounds the weights, which the matvec kernels do not.
-    if (wmode == W_Q4 && kr > 0 && (alone || n > kRopeOnce) && gemm_skinny_partial_floats(m, k, n) > 0 && partial_floats >= gemm_skinny_partial_floats(m, k, n) &&
+    // Up to kMatvecRows rows of a layer stay here: that kernel rounds the weights, which the matvec kernels do not.
+    if (wmode == W_Q4 && kr > 0 && (alone || n > kMatvecRows) && gemm_skinny_partial_floats(m, k, n) > 0 && partial_floats >= gemm_skinny_partial_floats(m, k, n) &&
         gemm_skinny_us(n, m, k, gshift) - (folded ? kFolded : 0.0) < us + (!alone && n <= 16 && kr > 1 && epi != EPI_F16 ? kCutTie : 0.0))
         return 0;
     // ... and on matrices that fill the chip with tiles through the tiled GEMM (48 rows: 49152 x 2048 26.5 against 45.3 us, 57344 x 8192 87 against 99),

@@ -85,7 +85,7 @@ struct Args {
     const void *resid;
     uint16_t *kc, *vc;       // EPI_ROPE_KV: cache and rotary table; out_f16 is the qkv buffer [n,m] (q part written)
     const float *rope;
-    int32_t h, g, d, cap;
+    int32_t h, g, d, cap, rope_once;
     SeqTable st;
 };
 constexpr int kPartial = 100;
@@ -558,7 +558,7 @@ __global__ __launch_bounds__(kThreads) void fewrow_kernel(Args a)
                 continue;
             }
             if (a.epi == EPI_ROPE_KV) {
-                // the fp16 rounding of the plain epilogue comes first (beyond kRopeOnce rows); then both members of each rotation pair in either lane
+                // the fp16 rounding of the plain epilogue comes first (rope_once: does not); then both members of each rotation pair in either lane
                 const uint32_t h01 = f2h(v[0]) | ((uint32_t)f2h(v[1]) << 16), h23 = f2h(v[2]) | ((uint32_t)f2h(v[3]) << 16);
                 const auto p01 = __builtin_amdgcn_permlane32_swap(h01, h01, false, false), p23 = __builtin_amdgcn_permlane32_swap(h23, h23, false, false);
                 const uint32_t ab[4] = {p01[0], p23[0], p01[1], p23[1]};
@@ -568,7 +568,7 @@ __global__ __launch_bounds__(kThreads) void fewrow_kernel(Args a)
                     pa[2 * e] = h2f((uint16_t)(ab[e] & 0xFFFFu)), pa[2 * e + 1] = h2f((uint16_t)(ab[e] >> 16));
                     pb[2 * e] = h2f((uint16_t)(ab[2 + e] & 0xFFFFu)), pb[2 * e + 1] = h2f((uint16_t)(ab[2 + e] >> 16));
                 }
-                if (a.n <= kRopeOnce) {
+                if (a.rope_once) {
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
                         const float2 p = pair_xor32(v[e]);

@@ -378,7 +378,7 @@ __global__ __launch_bounds__(1024) void skinny_finish_norm_kernel(const float *_
 // Plain fp16 epilogue of the QKV matmul + rotary embedding of the q and k heads + append of k (rotated) and v to the
 // cache at each row's position.  grid (row, slice of the heads); a thread owns eight consecutive rotation pairs of one
 // head, or eight v elements.  q goes to its place in qkv (the attention kernel reads it there), k and v to the cache only.
-// ONCE: q and k are rounded behind the rotation only (kRopeOnce); a form of its own, because the other one's bits, those of the stand-alone
+// ONCE: q and k are rounded behind the rotation only (SkinnyFuse::rope_once); a form of its own, because the other one's bits, those of the stand-alone
 // rotary kernel, depend on the products and the rounding to fp16 being one instruction.
 template <bool ONCE>
 __global__ __launch_bounds__(256) void skinny_finish_rope_kernel(const float *__restrict__ partial, int splits, int n, int m,
@@ -539,7 +539,7 @@ hipError_t launch_skinny_finish(const float *partial, int splits, int n, int m, 
         else if (epi == EPI_F16) {
             const relax_layer_dims &dm = *fuse->dm;
             const int items = (dm.n_heads + dm.n_kv_heads) * (dm.head_dim / 16);
-            hipLaunchKernelGGL(n <= kRopeOnce ? skinny_finish_rope_kernel<true> : skinny_finish_rope_kernel<false>, dim3(n, (items + 255) / 256), dim3(256), 0,
+            hipLaunchKernelGGL(fuse->rope_once ? skinny_finish_rope_kernel<true> : skinny_finish_rope_kernel<false>, dim3(n, (items + 255) / 256), dim3(256), 0,
                                stream, partial, splits, n, w.m, out_f16, fuse->cache->k, fuse->cache->v, fuse->cache->rope, dm.n_heads, dm.n_kv_heads,
                                dm.head_dim, dm.kv_capacity, *fuse->st);
         }

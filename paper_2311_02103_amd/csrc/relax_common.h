@@ -427,6 +427,7 @@ struct SkinnyFuse {
     const relax_layer_dims *dm;
     const relax_kv_cache *cache;
     const SeqTable *st;
+    bool rope_once;          // q and k are rounded to fp16 behind the rotary embedding only, as the matvec kernels do, not in front of it too
 };
 bool gemm_skinny_fuse_ok(const relax_qmat &w, int epi, const SkinnyFuse &f);
 hipError_t launch_skinny_finish(const float *partial, int splits, int n, int m, int epi, uint16_t *out_f16, float *out_f32, const void *resid,
@@ -439,10 +440,10 @@ hipError_t launch_gemm_skinny(const uint16_t *x, const relax_qmat &w, int n, int
 // k_ranges * n * m floats and the finishing pass of the split-K kernel follows.  folded: that pass replaces a launch of its own
 // (the RMSNorm of the result), so cutting along k costs next to nothing.
 constexpr int kFewRowMin = 2, kFewRowMax = 64;
-// Calls of up to this many rows round q and k once, behind the rotary embedding, on every path: the matvec kernels, which serve these
-// calls where the matrices do not suit the matrix path, do.  With more rows the rotary step is a launch of its own on some paths, and
-// the plain epilogue's rounding comes first on all of them.
-constexpr int kRopeOnce = 4;
+// Rows up to which the matvec kernels take a 4-bit layer by default.  Where the streaming kernel takes such a call from them it is as exact:
+// scales on sums, and q and k rounded once, behind the rotary embedding (SkinnyFuse::rope_once).  Everywhere else on the matrix path the plain
+// epilogue's rounding comes first, whether the rotary step is part of a matmul or a launch of its own.
+constexpr int kMatvecRows = 4;
 double gemm_skinny_us(int n, int m, int k, int gshift);      // estimated time of the split-K few-row kernel
 int fewrow_ranges(int wmode, int gshift, int n, int m, int k, int epi, bool folded, bool alone, size_t partial_floats);
 bool fewrow_pays_alone(int wmode, int n, int m, int k);      // 3-bit, fp16: as fast as the other kernels without an epilogue to save a launch

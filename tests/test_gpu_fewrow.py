@@ -339,3 +339,39 @@ def test_4bit_infinite_x_keeps_its_sign(rx, group, n, m, k):
     assert torch.isnan(out[3]).all()
     others = [i for i in range(n) if i not in (1, 2, 3, n - 1)]
     assert torch.equal(out[others], clean[others])
+
+
+# Weights of the last one: a layer whose three and four rows the streaming kernel takes from the matvec kernels
+FUSED = [(LAYERS[0], 32, 0), (LAYERS[1], 32, 0), (LAYERS[1], 128, 0), (wl.LayerShape("w", hidden=5120, n_heads=40, n_kv_heads=8, head_dim=128, ffn=13824), 128, 96)]
+
+
+@pytest.mark.parametrize("shape,group,matvec_mb", FUSED)
+def test_fused_light_steps_change_no_bit_at_two_to_four_rows(rx, shape, group, matvec_mb):
+    """fuse_finish on and off, on the matrix path (matvec_mb = 0: in place of the matvec kernels) and for the calls that it takes by itself."""
+    from paper_2311_02103_amd.runtime import DeviceLayer
+    layer = DeviceLayer(_random_layer(shape, group), hidden=shape.hidden, n_heads=shape.n_heads, n_kv_heads=shape.n_kv_heads, head_dim=shape.head_dim,
+                        ffn=shape.ffn, kv_capacity=64, n_max=16, group=group)
+    x = torch.from_numpy(wl.activations(shape, 4, 0, 4).view(np.int16)).view(torch.float16).cuda()
+    try:
+        rx.check(rx.relax_set_option("layer_matvec_mb", matvec_mb))
+        for n in (2, 3, 4):
+            rx.check(rx.relax_set_option("layer_matvec_rows", 1 if n == 2 and matvec_mb == 0 else 4))
+            got = []
+            for fused in (0, 1):
+                rx.check(rx.relax_set_option("fuse_finish", fused))
+                layer.k.zero_(), layer.v.zero_()
+                got.append((layer.forward(x[:n].contiguous(), [n], [n]).clone(), layer.k.clone(), layer.v.clone()))
+            for a, b in zip(*got):
+                assert torch.equal(a.view(torch.int16), b.view(torch.int16)), n
+    finally:
+        for name, value in (("layer_matvec_mb", 96), ("layer_matvec_rows", 4), ("fuse_finish", 1)):
+            rx.check(rx.relax_set_option(name, value))
+
+
+def _random_layer(shape, group):
+    r, host = np.random.RandomState(7), {}
+    for name, (m, k) in shape.matrices().items():
+        host[name + ".q"] = np.frombuffer(bytearray(r.bytes(m * k // 2)), dtype=np.uint32).reshape(m, k // 8)
+        host[name + ".s"] = (r.random_sample((m, k // group)) * 0.006 + 0.001).astype(np.float16).view(np.uint16)
+    host.update({name: wl.normal_f16_bits(4, 10 + i, (shape.hidden,), std=0.1, mean=1.0) for i, name in enumerate(("norm_attn", "norm_ffn"))})
+    return host
