@@ -46,6 +46,18 @@ __device__ inline void unpack8(const uint4 &raw, float *f)
     }
 }
 
+// merge state b into state a (running max m, running sum l, accumulator acc[8])
+__device__ inline void merge_state(float &ma, float &la, float *acca, float mb, float lb, const float *accb)
+{
+    const float mn = fmaxf(ma, mb);
+    const float sa = (ma == -INFINITY) ? 0.0f : __expf(ma - mn);
+    const float sb = (mb == -INFINITY) ? 0.0f : __expf(mb - mn);
+    la = la * sa + lb * sb;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) acca[e] = acca[e] * sa + accb[e] * sb;
+    ma = mn;
+}
+
 // grid: x = KV head * (rep/REP) + head sub-group, y = split along L, z = row of the call
 template <int D, int REP>
 __global__ __launch_bounds__(256) void attn_split_kernel(const uint16_t *__restrict__ q, const uint16_t *__restrict__ kc,

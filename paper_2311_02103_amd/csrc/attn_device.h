@@ -5,18 +5,6 @@
 
 namespace relax {
 
-// merge state b into state a (running max m, running sum l, accumulator acc[8])
-__device__ inline void merge_state(float &ma, float &la, float *acca, float mb, float lb, const float *accb)
-{
-    const float mn = fmaxf(ma, mb);
-    const float sa = (ma == -INFINITY) ? 0.0f : __expf(ma - mn);
-    const float sb = (mb == -INFINITY) ? 0.0f : __expf(mb - mn);
-    la = la * sa + lb * sb;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) acca[e] = acca[e] * sa + accb[e] * sb;
-    ma = mn;
-}
-
 typedef uint32_t u32x4a_t __attribute__((ext_vector_type(4)));
 typedef _Float16 half2a_t __attribute__((ext_vector_type(2)));
 
@@ -38,7 +26,7 @@ __device__ __forceinline__ u32x4a_t row_load(const char *p)
 // rows are read by this workgroup alone.  NL: K (and V) loads per step.
 template <int D, int WAVES, int NL, bool NT, typename LoadQ>
 __device__ __forceinline__ void attend_tokens(const char *kslot, const char *vslot, uint32_t row_bytes, int t_begin, int t_end, int wave, int lane,
-                                              const LoadQ &load_q, float &m, float &l, float (&acc)[8])
+                                              const LoadQ &load_q, float &m_out, float &l_out, float (&acc_out)[8])
 {
     constexpr int LPT = D / 8;        // lanes that share one token (each owns 8 of its d elements)
     constexpr int TPW = kWave / LPT;  // tokens per load instruction of a wavefront
@@ -79,7 +67,8 @@ __device__ __forceinline__ void attend_tokens(const char *kslot, const char *vsl
     step_load(sb, 1);
     const u32x4a_t qv = load_q();
 
-    m = -INFINITY, l = 0.0f;
+    // locals: on the references the compiler pairs other products and sums into multiply-adds, and takes three registers more
+    float acc[8], m = -INFINITY, l = 0.0f;
 #pragma unroll
     for (int e = 0; e < 8; ++e) acc[e] = 0.0f;
 
@@ -158,8 +147,15 @@ __device__ __forceinline__ void attend_tokens(const char *kslot, const char *vsl
         float mb = __shfl_xor(m, off, kWave), lb = __shfl_xor(l, off, kWave), accb[8];
 #pragma unroll
         for (int e = 0; e < 8; ++e) accb[e] = __shfl_xor(acc[e], off, kWave);
-        merge_state(m, l, acc, mb, lb, accb);
+        const float mn = fmaxf(m, mb), sa = m == -INFINITY ? 0.0f : __expf(m - mn), sb = mb == -INFINITY ? 0.0f : __expf(mb - mn);
+        l = fmaf(l, sa, lb * sb);                              // multiply-adds written out: which product is rounded is not the compiler's choice
+#pragma unroll
+        for (int e = 0; e < 8; ++e) acc[e] = fmaf(accb[e], sb, acc[e] * sa);
+        m = mn;
     }
+    m_out = m, l_out = l;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) acc_out[e] = acc[e];
 }
 
 }  // namespace relax
