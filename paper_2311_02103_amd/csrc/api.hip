@@ -734,14 +734,22 @@ relax_status layer_enqueue(const relax_layer_dims &dm, const relax_layer_weights
     // Two rows share one pass over the weights on every model size (measured per layer at L = 512: 13B shape 65 against 90 us on
     // the matrix path, 70B shape 112 against 167 us); three and four rows need a second pass where a lane cannot hold four rows
     // of x, which pays only while the matrices mostly stay in the last-level cache (13B: 94 against 92 us, 70B: 178 against 155).
-    // Three and four rows take the streaming kernel where it serves all four matrices: as exact, and faster or the same from the 7B shape on (us
-    // per layer at L = 300, matvec / stream, groups of 32 and 128: 7B 59 / 58 and 59 / 55 at three rows, 62 / 60 and 62 / 57 at four; 13B 87 / 76
-    // and 87 / 70, 88 / 78 and 89 / 73).
+    // Three and four rows take the streaming kernel where it serves all four matrices, as exact, and the layer is large: it needs nine launches
+    // for the matvec path's five or six, which the second pass over the weights has to outweigh (us per layer at L = 300, weights cold, matvec /
+    // stream at four rows; groups of 32, 64, 128):
+    //   hidden, ffn, heads (M weights)           2048, 5632, 16 / 16 (51)     34.6 / 44.5   34.5 / 43.4   34.7 / 41.1
+    //   3072, 8192, 24 / 8 (101)     47.8 / 52.3   47.8 / 52.3   47.9 / 51.1   4096, 8192, 32 / 32 (168)    54.5 / 57.0   54.0 / 55.4   53.9 / 54.2
+    //   5120, 8192, 40 / 8 (189)     62.3 / 64.9   62.2 / 63.0   61.9 / 60.8   4096, 11008, 32 / 32 (202)   61.8 / 61.7   61.8 / 60.0   61.6 / 58.2
+    //   4096, 14336, 32 / 8 (218)    60.6 / 62.2   61.1 / 60.5   61.1 / 59.5   5120, 8192, 40 / 40 (231)    74.5 / 71.4   73.8 / 69.6   73.5 / 67.0
+    //   3584, 18944, 28 / 4 (233)    70.6 / 70.2   70.7 / 67.5   71.0 / 65.8   5120, 13824, 40 / 40 (317)   91.9 / 83.3   93.0 / 79.4   94.3 / 77.0
+    // A switch above the default keeps these calls on the matvec kernels.
     const bool matvec_call = n >= 2 && n <= g_opt_matvec_rows.load() && (n == 2 || largest <= ((size_t)g_opt_matvec_mb.load() << 20));
+    const double weights = (double)wt->wqkv.m * wt->wqkv.k + (double)wt->wo.m * wt->wo.k + (double)wt->wgu.m * wt->wgu.k + (double)wt->wdown.m * wt->wdown.k;
+    const bool large = weights >= (gshift_of(wt->wqkv.group) == 0 ? 225e6 : 195e6);
     SkinnyFuse fq = {};
     fq.dm = &dm, fq.cache = cache, fq.st = &st;
     const int qkv_ranges = stream(wt->wqkv, x, EPI_F16);
-    fq.rope_once = matvec_call && n > 2 && n <= kMatvecRows && qkv_ranges && stream(wt->wo, x, EPI_RESID_F32) && stream(wt->wgu, x, EPI_SWIGLU) &&
+    fq.rope_once = matvec_call && n > 2 && n <= kMatvecRows && g_opt_matvec_rows.load() <= kMatvecRows && large && qkv_ranges && stream(wt->wo, x, EPI_RESID_F32) && stream(wt->wgu, x, EPI_SWIGLU) &&
                    stream(wt->wdown, x, EPI_RESID_F16) && fewrow_fuse_ok(dm, *cache) && (qkv_ranges == 1 || gemm_skinny_fuse_ok(wt->wqkv, EPI_F16, fq));
     const bool rows_as_matvecs = matvec_call && !fq.rope_once;
     if (n >= kSkinnyMinN && !rows_as_matvecs && mat_ok(wt->wqkv, x, EPI_F16) && mat_ok(wt->wo, x, EPI_RESID_F32) && mat_ok(wt->wgu, x, EPI_SWIGLU) &&

@@ -368,6 +368,27 @@ def test_fused_light_steps_change_no_bit_at_two_to_four_rows(rx, shape, group, m
             rx.check(rx.relax_set_option(name, value))
 
 
+@pytest.mark.parametrize("shape,group,rows_switch,matvec", [(LAYERS[0], 32, 4, True), (LAYERS[1], 128, 4, True), (FUSED[3][0], 128, 4, False),
+                                                            (FUSED[3][0], 128, 64, True)])
+def test_three_and_four_rows_leave_the_matvec_kernels_in_large_layers_only(rx, shape, group, rows_switch, matvec):
+    """A rotary table aligned to 8 bytes keeps a call on the matvec kernels: the same bits where an aligned one stays there too, close to them where not."""
+    from paper_2311_02103_amd.runtime import DeviceLayer
+    layer = DeviceLayer(_random_layer(shape, group), hidden=shape.hidden, n_heads=shape.n_heads, n_kv_heads=shape.n_kv_heads, head_dim=shape.head_dim,
+                        ffn=shape.ffn, kv_capacity=64, n_max=16, group=group)
+    x = torch.from_numpy(wl.activations(shape, 4, 0, 4).view(np.int16)).view(torch.float16).cuda()
+    try:
+        rx.check(rx.relax_set_option("layer_matvec_rows", rows_switch))
+        got = [layer.forward(x[:n].contiguous(), [n], [n]).clone() for n in (3, 4)]
+        layer.cache = rx.KVCache(layer.k, layer.v, _shifted(layer.rope, 2))
+        want = [layer.forward(x[:n].contiguous(), [n], [n]) for n in (3, 4)]
+    finally:
+        rx.check(rx.relax_set_option("layer_matvec_rows", 4))
+    for a, b in zip(got, want):
+        assert torch.equal(a.view(torch.int16), b.view(torch.int16)) == matvec
+        # seven fp16 roundings (2^-11 each) on each side, independent where the two paths round at other points
+        assert float((a.double() - b.double()).norm() / b.double().norm()) < 4e-3
+
+
 def _random_layer(shape, group):
     r, host = np.random.RandomState(7), {}
     for name, (m, k) in shape.matrices().items():
