@@ -15,7 +15,8 @@
 //                                          B operand = the probabilities the lane already holds.
 // Bound by the K / V stream.  Both tiles come in as whole rows with the non-temporal hint and go through the wavefront's LDS region, K first; with
 // K straight from global memory as the A operand a line was touched by four load instructions and the hint hurt.  64 / 8 heads of 128, with
-// the merge: 16 rows on 100 to 7990 tokens 69.0 -> 59.4 us (3.9 -> 4.5 TB/s), 32 rows on 2000 to 2620 81.4 -> 69.0.  Chunks of 384 to 1024
+// the merge: 16 rows on 100 to 7990 tokens 69.0 -> 59.4 us (3.9 -> 4.5 TB/s), 32 rows on 2000 to 2620 81.4 -> 69.0; one or two tiles per
+// wavefront pay 0.2 us for the way through LDS (4 rows of 40 tokens 7.9 -> 8.1, of 300 9.2 -> 9.4, of 4000 26.2 -> 25.2).  Chunks of 384 to 1024
 // tokens are within 3 % of 512; three workgroups per CU spill (101 us).
 // Columns beyond the number of heads per group re-read the last head and are dropped.
 #include "relax_common.h"

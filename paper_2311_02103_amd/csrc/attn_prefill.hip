@@ -384,9 +384,11 @@ hipError_t launch_attention_prefill(const uint16_t *q, int32_t q_stride, const r
     // steps of the longest prefix, and the CUs it takes stood idle (us, 128 queries x 2 groups / 64 x 4: 7B heads, 100 rows on 0, 500 and 1500
     // cached tokens 9.1 / 8.2, 17.2 / 14.4, 32.8 / 27.5; 511 rows 16.1 / 13.8, 25.4 / 21.9, 40.6 / 33.3; 32 / 8 heads of 64, 300 rows on 1500 27.0 /
     // 18.9).  One more tile per CU and the other form is the faster one (7B heads, 700 rows on 1500 42.7 / 56.1), as it is on short
-    // prefixes of up to 64 queries, where both have one tile (64 rows on none 7.2 / 8.0, on 500 14.8 / 14.2).
+    // prefixes of up to 64 queries, where both have one tile (7B heads, 64 rows with a total of 200, 400, 450, 640 and 1000 tokens 10.0 / 10.5, 13.0 /
+    // 13.6, 13.9 / 13.8, 16.0 / 15.7, 21.6 / 20.1; 17 rows 8.9 / 9.2, 12.0 / 12.1, 13.0 / 12.5, 15.0 / 14.2, 20.6 / 18.8): from seven tiles of 64 tokens
+    // on.  Heads of 64 gain earlier (32 / 8, 64 rows, 400 tokens 9.2 / 8.3).
     const long long tiles = (long long)dm.n_heads * st.B * ((st.q_max + 63) / 64);
-    if (tiles <= 256 && (st.q_max > 64 || L_max >= 400)) {
+    if (tiles <= 256 && (st.q_max > 64 || L_max >= (dm.head_dim == 64 ? 400 : 449))) {
         if (dm.head_dim == 128) return launch_one<128, 8, 4, 2>(q, q_stride, cache, dm, st, out, stream);
         if (dm.head_dim == 64) return launch_one<64, 8, 4, 2>(q, q_stride, cache, dm, st, out, stream);
     }

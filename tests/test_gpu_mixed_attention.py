@@ -27,7 +27,7 @@ def test_grouped_decode_rows_against_float64(h, g, d):
 
 # 64 queries and four KV groups per workgroup (few workgroups, more than 64 rows or 400 tokens) and the calls next to them
 @pytest.mark.parametrize("h,g,d", [(4, 4, 128), (8, 2, 128), (4, 2, 64)])
-@pytest.mark.parametrize("seqs", [[(65, 65)], [(64, 399)], [(64, 400)], [(17, 1000)], [(16, 463)], [(100, 129)], [(128, 1000)], [(129, 257)], [(512, 1000)],
+@pytest.mark.parametrize("seqs", [[(65, 65)], [(64, 399)], [(64, 400)], [(64, 448)], [(64, 449)], [(17, 1000)], [(16, 463)], [(100, 129)], [(128, 1000)], [(129, 257)], [(512, 1000)],
                                   [(70, 70), (2, 600), (1, 1), (1, 500)]])
 def test_few_tiles_against_float64(h, g, d, seqs):
     _check(h, g, d, seqs)
