@@ -43,6 +43,8 @@ typedef struct {
     int32_t kernel, k_ranges, tile_rows, tile_cols, wide_rows;
 } relax_matmul_plan;
 relax_status relax_plan_matmul(int32_t format, int32_t n, int32_t m, int32_t k, size_t ws_bytes, relax_matmul_plan *plan);
+/* The same for a 4-bit matrix with groups of 32, 64 or 128 (other formats: 32; anything else UNSUPPORTED). */
+relax_status relax_plan_matmul_group(int32_t format, int32_t group, int32_t n, int32_t m, int32_t k, size_t ws_bytes, relax_matmul_plan *plan);
 
 /* Measurement aids for the roofline figures: what the device at hand reaches on a plain
  * streaming read and on a bare loop of fp16 matrix-core instructions (the published

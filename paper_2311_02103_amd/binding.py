@@ -85,6 +85,7 @@ _SIGNATURES = {
     "relax_build_id": (C.c_char_p, []),
     "relax_set_option": (C.c_int32, [C.c_char_p, C.c_int32]),
     "relax_plan_matmul": (C.c_int32, [C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.c_size_t, C.POINTER(MatmulPlanC)]),
+    "relax_plan_matmul_group": (C.c_int32, [C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.c_size_t, C.POINTER(MatmulPlanC)]),
     "relax_profile_alt_gate_up": (None, [C.c_void_p, C.c_void_p]),
     "relax_workspace_init": (C.c_int32, [C.POINTER(LayerDims), C.c_void_p, C.c_size_t, C.c_void_p]),
     "relax_workspace_error": (C.c_int32, [C.POINTER(LayerDims), C.c_void_p, C.POINTER(C.c_int32)]),
@@ -440,10 +441,10 @@ def relax_set_option(name: str, value: int) -> int:
     return lib().relax_set_option(name.encode(), value)
 
 
-def relax_plan_matmul(fmt: str, n: int, m: int, k: int, ws_bytes: int = 0):
+def relax_plan_matmul(fmt: str, n: int, m: int, k: int, ws_bytes: int = 0, group: int = 32):
     """(status, kernel, k_ranges, tile_rows, tile_cols, wide_rows) of a plain matmul; fmt "q4", "q3" or "f16".  Host only."""
     p = MatmulPlanC()
-    rc = lib().relax_plan_matmul({"q4": 4, "q3": 3, "f16": 16}.get(fmt, 0), n, m, k, ws_bytes, C.byref(p))
+    rc = lib().relax_plan_matmul_group({"q4": 4, "q3": 3, "f16": 16}.get(fmt, 0), group, n, m, k, ws_bytes, C.byref(p))
     return rc, p.kernel, p.k_ranges, p.tile_rows, p.tile_cols, p.wide_rows
 
 

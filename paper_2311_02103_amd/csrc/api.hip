@@ -443,12 +443,18 @@ relax_status relax_set_option(const char *name, int32_t value)
 
 relax_status relax_plan_matmul(int32_t format, int32_t n, int32_t m, int32_t k, size_t ws_bytes, relax_matmul_plan *plan)
 {
+    return relax_plan_matmul_group(format, kGroup, n, m, k, ws_bytes, plan);
+}
+
+relax_status relax_plan_matmul_group(int32_t format, int32_t group, int32_t n, int32_t m, int32_t k, size_t ws_bytes, relax_matmul_plan *plan)
+{
     if (!plan) return RELAX_ERR_NULL;
     if (n < 1 || m < 1 || k < 32 || k % 32 != 0) return RELAX_ERR_SHAPE;
     if (format != 3 && format != 4 && format != 16) return RELAX_ERR_UNSUPPORTED;
+    if (gshift_of(group) < 0 || (format != 4 && group != kGroup)) return RELAX_ERR_UNSUPPORTED;
     // the dispatch looks at nothing but the alignment of pointers
     uint16_t *const p = reinterpret_cast<uint16_t *>(static_cast<uintptr_t>(256));
-    const relax_qmat w = {reinterpret_cast<const uint32_t *>(p), p, m, k, 32};
+    const relax_qmat w = {reinterpret_cast<const uint32_t *>(p), p, m, k, group};
     const Route r = format == 4 ? q4_route(p, w, p, n, ws_bytes ? p : nullptr, ws_bytes) : format == 3 ? q3_route(p, w, p, n) : f16_route(p, p, p, n, m, k);
     *plan = {r.kernel, r.ranges, 0, 0, 0};
     if (r.kernel == RELAX_KERNEL_TILED) gemm_tile_plan(format == 16 ? W_F16 : format == 3 ? W_Q3 : W_Q4, m, k, n, EPI_F16, format == 4 ? ws_bytes / sizeof(float) : 0, plan);

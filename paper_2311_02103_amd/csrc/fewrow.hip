@@ -18,8 +18,7 @@ using namespace fewrow;
 bool uw_built(int fmt, int nb, int uw)                    // the instances of launch_nb
 {
     if (fmt == F_F16) return uw >= 1 && (nb == 1 ? uw <= 6 || uw == 8 : nb == 2 && uw <= 4);
-    if (fmt == F_Q3) return uw >= 1 && uw <= (nb == 1 ? 6 : nb == 2 ? 3 : 1);
-    return uw >= 1 && uw <= (nb == 1 ? 5 : nb == 2 ? 3 : fmt == F_Q4G32 ? 1 : 0);
+    return uw >= 1 && uw <= (nb == 1 ? (fmt == F_Q3 ? 6 : 5) : nb == 2 ? 3 : 1);
 }
 
 int lds_tiles(int fmt, int nb, int uw) { return (int)((kLdsBytes - offset_bytes(fmt, nb, uw)) / ((size_t)kWaves * nb * 1024)); }
@@ -112,7 +111,10 @@ double split_us(int n, int m, int k)
 // of the down projection 17.0 us against 20.0, 6 of the output projection 14.2 against 14.6; the QKV matrix of the 70B shape is not: 20.3
 // against 22.0 with the rotary step, nor is its down projection, 33 against 38 at 4 rows).
 constexpr double kCutTie = 1.5;
-constexpr double kSplitCoarse = 1.1;                      // groups of 64 and 128: its scale staging is made for groups of 32
+// Groups of 64 and 128: its scale staging is made for groups of 32 (us at 6, 16 and 32 rows, groups of 32 / 64 / 128: 4096 x 4096 11.6 / 13.1 / 12.9,
+// 12.0 / 13.5 / 13.4, 13.5 / 14.8 / 14.7; 5120 x 13824 16.5 / 19.5 / 18.9, 17.3 / 21.4 / 19.8, 19.5 / 22.0 / 21.8; 22016 x 4096 22.5 / 25.9 / 25.0, 23.4 /
+// 26.2 / 26.0, 26.7 / 29.3 / 29.4; without the factor a 13B layer of 8 rows takes 79.3 us with groups of 64, so 77.2).
+constexpr double kSplitCoarse = 1.1;
 
 bool shape_ok(bool f16, int n, int m, int k, int epi)
 {
@@ -164,8 +166,11 @@ double gemm_skinny_us(int n, int m, int k, int gshift) { return split_us(n, m, k
 
 int fewrow_ranges(int wmode, int gshift, int n, int m, int k, int epi, bool folded, bool alone, size_t partial_floats)
 {
+    // From 33 rows on all groups are decoded alike (scales on codes) and one estimate serves them (us at 33 and 64 rows, groups of 32 / 128: 22016 x 4096
+    // 29.5 / 29.6 and 32.9 / 34.7, 27648 x 5120 43 / 44 and 48 / 46, 57344 x 8192 95 / 96 and 97 / 98, 8192 x 28672 56 / 57 and 64 / 62).
+    if (n > 32) gshift = 0;
     const int fmt = wmode == W_F16 ? F_F16 : wmode == W_Q3 ? F_Q3 : gshift == 0 ? F_Q4G32 : gshift == 1 ? F_Q4G64 : F_Q4G128;
-    if (!shape_ok(fmt == F_F16, n, m, k, epi) || (n > 32 && (fmt == F_F16 || fmt == F_Q4G64 || fmt == F_Q4G128))) return 0;
+    if (!shape_ok(fmt == F_F16, n, m, k, epi) || (n > 32 && fmt == F_F16)) return 0;
     const size_t row = wmode == W_F16 ? (size_t)k * 2 : wmode == W_Q3 ? (size_t)k / 32 * 12 : (size_t)k / 2;
     if ((size_t)m * row > kMaxBuffer) return 0;
     double us = 0.0;

@@ -59,7 +59,7 @@ enum { F_Q4G32 = 0, F_Q4G64 = 1, F_Q4G128 = 2, F_Q3 = 3, F_F16 = 4 };
 constexpr int kWaves = 8, kThreads = kWaves * 64;
 // 4-bit: whether a group's scale meets the fp32 sum of its products (exact), or its codes (one rounding per weight; three units of 32 x rows leave
 // no registers for sums, and in two k ranges instead a 13B layer of 17 rows with groups of 64 took 123 us, so 120)
-constexpr bool scale_sums(int fmt, int nb, int uw) { return fmt == F_Q4G64 || fmt == F_Q4G128 ? uw * nb < 6 : fmt == F_Q4G32 && nb == 1; }
+constexpr bool scale_sums(int fmt, int nb, int uw) { return fmt == F_Q4G64 || fmt == F_Q4G128 ? nb <= 2 && uw * nb < 6 : fmt == F_Q4G32 && nb == 1; }
 constexpr int unit_columns(bool f16) { return f16 ? 128 : 256; }      // a row's share of a unit: 128 bytes, 96 (3-bit) or 2 x 128 (fp16)
 constexpr int kTileRows = 16;
 constexpr uint32_t kNowhere = 0x80000000u;                // an offset past every buffer (they are at most 2^31 - 1 bytes)
@@ -739,8 +739,7 @@ hipError_t launch_nb(int nb, int uw, const Args &a, int lds_tiles, hipStream_t s
     } else if constexpr (FMT != F_Q3) {
         if (nb == 1) return launch_uw<FMT, 1, 1, 2, 3, 4, 5>(uw, a, lds_tiles, stream);
         if (nb == 2) return launch_uw<FMT, 2, 1, 2, 3>(uw, a, lds_tiles, stream);
-        if constexpr (FMT == F_Q4G32) return launch_uw<FMT, 4, 1>(uw, a, lds_tiles, stream);
-        else return hipErrorInvalidValue;
+        return launch_uw<FMT, 4, 1>(uw, a, lds_tiles, stream);
     } else {
         if (nb == 1) return launch_uw<FMT, 1, 1, 2, 3, 4, 5, 6>(uw, a, lds_tiles, stream);
         if (nb == 2) return launch_uw<FMT, 2, 1, 2, 3>(uw, a, lds_tiles, stream);
