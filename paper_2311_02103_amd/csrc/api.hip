@@ -19,11 +19,11 @@ inline bool aligned(const void *p, size_t bytes) { return (reinterpret_cast<uint
 // The kernel reads codes and scales at 4-byte alignment.  4-bit matrices have to be aligned as the split-K kernel wants them all
 // the same: beyond 16 rows it rounds a weight to fp16, and calls that no MFMA kernel took for their alignment stay on the matvec
 // kernels, which apply the scale in fp32.
-int stream_ranges(int wmode, const relax_qmat &w, const void *x, const void *out, int n, int epi, size_t partial_floats, bool folded = false, bool alone = false)
+int stream_ranges(int wmode, const relax_qmat &w, const void *x, const void *out, int n, int epi, size_t partial_floats, bool folded = false, bool alone = false, bool exact = false)
 {
     const size_t wa = wmode == W_Q4 ? 16 : 4;
     if (!aligned(x, 16) || !aligned(w.q, wa) || !aligned(w.s, wa) || !aligned(out, 8)) return 0;
-    return fewrow_ranges(wmode, wmode == W_Q4 ? gshift_of(w.group) : 0, n, w.m, w.k, epi, folded, alone, partial_floats);
+    return fewrow_ranges(wmode, wmode == W_Q4 ? gshift_of(w.group) : 0, n, w.m, w.k, epi, folded, alone, exact, partial_floats);
 }
 
 // The kernel a plain matmul takes, and for the streaming few-row kernel its k ranges (Sec. 5.1: the dispatch follows the runtime value
@@ -342,7 +342,7 @@ Route f16_route(const uint16_t *x, const uint16_t *w, const uint16_t *out, int n
 {
     bool use_gemm;
     const int gemm_rows = g_opt_half_gemm_rows.load();
-    if (gemm_rows == 0 && aligned(x, 16) && aligned(w, 16) && aligned(out, 8) && fewrow_ranges(W_F16, 0, n, m, k, EPI_F16, false, true, 0) &&
+    if (gemm_rows == 0 && aligned(x, 16) && aligned(w, 16) && aligned(out, 8) && fewrow_ranges(W_F16, 0, n, m, k, EPI_F16, false, true, false, 0) &&
         fewrow_pays_alone(W_F16, n, m, k))
         return {RELAX_KERNEL_STREAM, 1};
     if (gemm_rows > 0) {
@@ -707,30 +707,6 @@ relax_status layer_enqueue(const relax_layer_dims &dm, const relax_layer_weights
 
     float *partials = reinterpret_cast<float *>(base + pl.partials);
 
-    // More than one row: matrix path (same entry point, same binary) -- the matmuls run on MFMA: up to kSkinnyMaxN rows the streaming
-    // or the split-K few-row kernel, whichever is estimated faster for a matrix, the tiled GEMM above; the light steps ride in their
-    // epilogues and finishing passes or are kernels of their own.
-    float *skinny_ws = reinterpret_cast<float *>(base + pl.skinny);
-    // k ranges of the streaming few-row kernel where it takes this matmul (0: it does not).  Its finishing pass, if any, is the RMSNorm
-    // launch behind the output projection (and behind the down projection when the next layer's norm is known).
-    auto folds = [&](int epi) { return epi == EPI_RESID_F32 || (epi == EPI_RESID_F16 && next_norm && xn_done); };
-    auto stream = [&](const relax_qmat &wq, const void *xin, int epi) {
-        return stream_ranges(W_Q4, wq, xin, epi == EPI_RESID_F16 ? (const void *)out : epi == EPI_RESID_F32 ? (const void *)x : nullptr, n, epi, pl.mm_floats, folds(epi));
-    };
-    auto mat_ok = [&](const relax_qmat &wq, const void *xin, int epi) {
-        return stream(wq, xin, epi) || (n <= kSkinnyMaxN && gemm_skinny_eligible(wq, xin, n, epi)) || (n >= kGemmMinN && gemm_mfma_eligible(wq, xin, epi));
-    };
-    auto few_row = [&](const relax_qmat &wq, const void *xin, int epi) {      // the split-K few-row kernel takes this matmul, if the stream does not
-        if (gemm_mfma_eligible(wq, xin, epi) && (gemm_prefers_tiled(wq.m, n) ||
-                                                 (n > 32 && gemm_tile_us(wq.m, wq.k, n, epi, pl.mm_floats) < gemm_skinny_us(n, wq.m, wq.k, gshift_of(wq.group)))))
-            return false;
-        return n <= kSkinnyMaxN && gemm_skinny_eligible(wq, xin, n, epi);
-    };
-    auto matmul = [&](const uint16_t *xin, const relax_qmat &wq, int epi, uint16_t *o16, float *o32, const void *resid) {
-        if (const int kr = stream(wq, xin, epi)) return launch_fewrow_q4(xin, wq, n, epi, kr, o16, o32, resid, skinny_ws, st_);
-        if (few_row(wq, xin, epi)) return launch_gemm_skinny(xin, wq, n, epi, o16, o32, resid, skinny_ws, st_);
-        return launch_gemm_mfma(xin, wq, n, epi, o16, o32, resid, st_, skinny_ws, pl.mm_floats);
-    };
     // Up to four rows of a small model stay on the matvec kernels: two or four rows of x share one pass over the weights
     // (k <= 4096: four, k <= 8192: two; taller rows go one by one and find most of a matrix of this size in the last-level
     // cache), and the matvec path needs no separate norm / finishing launches.  Measured on the 7B layer shape, 256 cached
@@ -752,10 +728,36 @@ relax_status layer_enqueue(const relax_layer_dims &dm, const relax_layer_weights
     const bool matvec_call = n >= 2 && n <= g_opt_matvec_rows.load() && (n == 2 || largest <= ((size_t)g_opt_matvec_mb.load() << 20));
     const double weights = (double)wt->wqkv.m * wt->wqkv.k + (double)wt->wo.m * wt->wo.k + (double)wt->wgu.m * wt->wgu.k + (double)wt->wdown.m * wt->wdown.k;
     const bool large = weights >= (gshift_of(wt->wqkv.group) == 0 ? 225e6 : 195e6);
+    const bool streamable = matvec_call && n > 2 && n <= kMatvecRows && g_opt_matvec_rows.load() <= kMatvecRows && large;
+
+    // More than one row: matrix path (same entry point, same binary) -- the matmuls run on MFMA: up to kSkinnyMaxN rows the streaming
+    // or the split-K few-row kernel, whichever is estimated faster for a matrix, the tiled GEMM above; the light steps ride in their
+    // epilogues and finishing passes or are kernels of their own.
+    float *skinny_ws = reinterpret_cast<float *>(base + pl.skinny);
+    // k ranges of the streaming few-row kernel where it takes this matmul (0: it does not).  Its finishing pass, if any, is the RMSNorm
+    // launch behind the output projection (and behind the down projection when the next layer's norm is known).
+    auto folds = [&](int epi) { return epi == EPI_RESID_F32 || (epi == EPI_RESID_F16 && next_norm && xn_done); };
+    auto stream = [&](const relax_qmat &wq, const void *xin, int epi) {
+        return stream_ranges(W_Q4, wq, xin, epi == EPI_RESID_F16 ? (const void *)out : epi == EPI_RESID_F32 ? (const void *)x : nullptr, n, epi, pl.mm_floats, folds(epi), false, streamable);
+    };
+    auto mat_ok = [&](const relax_qmat &wq, const void *xin, int epi) {
+        return stream(wq, xin, epi) || (n <= kSkinnyMaxN && gemm_skinny_eligible(wq, xin, n, epi)) || (n >= kGemmMinN && gemm_mfma_eligible(wq, xin, epi));
+    };
+    auto few_row = [&](const relax_qmat &wq, const void *xin, int epi) {      // the split-K few-row kernel takes this matmul, if the stream does not
+        if (gemm_mfma_eligible(wq, xin, epi) && (gemm_prefers_tiled(wq.m, n) ||
+                                                 (n > 32 && gemm_tile_us(wq.m, wq.k, n, epi, pl.mm_floats) < gemm_skinny_us(n, wq.m, wq.k, gshift_of(wq.group)))))
+            return false;
+        return n <= kSkinnyMaxN && gemm_skinny_eligible(wq, xin, n, epi);
+    };
+    auto matmul = [&](const uint16_t *xin, const relax_qmat &wq, int epi, uint16_t *o16, float *o32, const void *resid) {
+        if (const int kr = stream(wq, xin, epi)) return launch_fewrow_q4(xin, wq, n, epi, kr, o16, o32, resid, skinny_ws, st_);
+        if (few_row(wq, xin, epi)) return launch_gemm_skinny(xin, wq, n, epi, o16, o32, resid, skinny_ws, st_);
+        return launch_gemm_mfma(xin, wq, n, epi, o16, o32, resid, st_, skinny_ws, pl.mm_floats);
+    };
     SkinnyFuse fq = {};
     fq.dm = &dm, fq.cache = cache, fq.st = &st;
     const int qkv_ranges = stream(wt->wqkv, x, EPI_F16);
-    fq.rope_once = matvec_call && n > 2 && n <= kMatvecRows && g_opt_matvec_rows.load() <= kMatvecRows && large && qkv_ranges && stream(wt->wo, x, EPI_RESID_F32) && stream(wt->wgu, x, EPI_SWIGLU) &&
+    fq.rope_once = streamable && qkv_ranges && stream(wt->wo, x, EPI_RESID_F32) && stream(wt->wgu, x, EPI_SWIGLU) &&
                    stream(wt->wdown, x, EPI_RESID_F16) && fewrow_fuse_ok(dm, *cache) && (qkv_ranges == 1 || gemm_skinny_fuse_ok(wt->wqkv, EPI_F16, fq));
     const bool rows_as_matvecs = matvec_call && !fq.rope_once;
     if (n >= kSkinnyMinN && !rows_as_matvecs && mat_ok(wt->wqkv, x, EPI_F16) && mat_ok(wt->wo, x, EPI_RESID_F32) && mat_ok(wt->wgu, x, EPI_SWIGLU) &&
@@ -1224,7 +1226,7 @@ relax_status relax_decoder_layer_f16(const relax_layer_dims *dims, const relax_l
     auto plain = [&](int i, const uint16_t *xin, uint16_t *o) { return half_matmul_enqueue(xin, mats[i], o, n, ms[i], ks[i], st_); };
     auto ranges = [&](int i, const void *xin, const void *o, int epi, size_t floats, bool folded) {      // every pointer was checked for 16 bytes above
         if (g_opt_half_gemm_rows.load() != 0) return 0;
-        const int kr = fewrow_ranges(W_F16, 0, n, ms[i], ks[i], epi, folded, false, floats);
+        const int kr = fewrow_ranges(W_F16, 0, n, ms[i], ks[i], epi, folded, false, false, floats);
         if (kr > 0 || n < kGemmMinN || !gemm_f16_eligible(xin, mats[i], o, ms[i], ks[i])) return kr;
         const int splits = gemm_flat_splits(W_F16, n, ms[i], ks[i], floats);
         return splits > 1 ? -splits : 0;

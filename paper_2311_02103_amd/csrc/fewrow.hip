@@ -4,11 +4,11 @@
 namespace relax {
 
 namespace fewrow {
-hipError_t launch_q4g32(int nb, int uw, const Args &a, int lds_tiles, hipStream_t stream);
-hipError_t launch_q4g64(int nb, int uw, const Args &a, int lds_tiles, hipStream_t stream);
-hipError_t launch_q4g128(int nb, int uw, const Args &a, int lds_tiles, hipStream_t stream);
-hipError_t launch_q3(int nb, int uw, const Args &a, int lds_tiles, hipStream_t stream);
-hipError_t launch_f16(int nb, int uw, const Args &a, int lds_tiles, hipStream_t stream);
+hipError_t launch_q4g32(int nb, int uw, const Args &a, size_t lds_bytes, bool wait, hipStream_t stream);
+hipError_t launch_q4g64(int nb, int uw, const Args &a, size_t lds_bytes, bool wait, hipStream_t stream);
+hipError_t launch_q4g128(int nb, int uw, const Args &a, size_t lds_bytes, bool wait, hipStream_t stream);
+hipError_t launch_q3(int nb, int uw, const Args &a, size_t lds_bytes, bool wait, hipStream_t stream);
+hipError_t launch_f16(int nb, int uw, const Args &a, size_t lds_bytes, bool wait, hipStream_t stream);
 }  // namespace fewrow
 
 namespace {
@@ -18,10 +18,15 @@ using namespace fewrow;
 bool uw_built(int fmt, int nb, int uw)                    // the instances of launch_nb
 {
     if (fmt == F_F16) return uw >= 1 && (nb == 1 ? uw <= 6 || uw == 8 : nb == 2 && uw <= 4);
-    return uw >= 1 && uw <= (nb == 1 ? (fmt == F_Q3 ? 6 : 5) : nb == 2 ? 3 : 1);
+    return uw >= 1 && uw <= (nb == 1 ? 6 : nb == 2 ? 3 : 1);
 }
 
-int lds_tiles(int fmt, int nb, int uw) { return (int)((kLdsBytes - offset_bytes(fmt, nb, uw)) / ((size_t)kWaves * nb * 1024)); }
+// Row tiles whose shares the LDS of a workgroup holds at a time (wait: beside the sums of all its `per` tiles, 1 KB each)
+int lds_tiles(int fmt, int nb, int uw, bool wait = false, int per = 0)
+{
+    const size_t room = (scale_sums(fmt, nb, uw) && nb == 1 ? kLdsBytes : kShareBytes) - offset_bytes(fmt, nb, uw, wait) - (wait ? (size_t)per * 1024 : 0);
+    return (int)(room / ((size_t)kWaves * nb * 1024));
+}
 
 int blocks_of(int n) { return n <= 16 ? 1 : n <= 32 ? 2 : 4; }
 
@@ -36,9 +41,10 @@ bool cut(int fmt, int nb, int m, int k, int epi, int kg, Plan &p)
     if (!uw_built(fmt, nb, p.uw)) return false;
     p.tiles = tiles_of(m, kg > 1 ? (int)EPI_F16 : epi);
     p.rg = std::min(p.tiles, 256 / kg);
-    // a workgroup whose epilogue is not plain partial rows keeps the sums of all its tiles in LDS: more workgroups if they don't fit
+    // a workgroup whose epilogue is not plain partial rows keeps all its tiles in LDS (one block of x rows: any): more workgroups if they don't fit
+    const int most = std::max(lds_tiles(fmt, nb, p.uw), sums_wait(fmt, nb, p.uw) ? kMostTiles : 0);
     if (kg == 1 || nb == 1)
-        while ((p.tiles + p.rg - 1) / p.rg > lds_tiles(fmt, nb, p.uw)) p.rg = std::min(p.tiles, p.rg + 256 / kg);
+        while ((p.tiles + p.rg - 1) / p.rg > most) p.rg = std::min(p.tiles, p.rg + 256 / kg);
     return true;
 }
 
@@ -50,15 +56,14 @@ bool cut(int fmt, int nb, int m, int k, int epi, int kg, Plan &p)
 //   unit, tile             ... per row tile of a workgroup: its longest slice's units, and the sums
 //   x                      per MB of x a workgroup fetches from its L2: long rows and many rows of x want k ranges
 //   finish, range, partial the finishing launch, per k range of it, and the partial rows at TB/s
-//   full                   more where every wavefront holds four units of x or more, which leaves it two row tiles in flight (8192 columns
-//                          in one range: 8192 x 8192 at 6 rows 16.5 us, the split-K kernel 15.4)
+//   full                   more where every wavefront holds four units of x or more and none has one to spare (8192 columns in one range)
 //   round                  more per wave of workgroups behind the first, which begins with x and the first data again
 struct Cost {
     double launch, tb_per_s, unit, tile, x, finish, range, partial, full, round;
 };
 constexpr Cost kCostQ4[3] = {{4.1, 6.2, 0.62, 0.31, 23, 2.0, 0.32, 7.9, 1.4, 6.6}, {4.6, 5.4, 0.79, 0.0, 32, 2.2, 0.57, 2.7, 0.0, 8.0}, {4.8, 3.1, 1.39, 0.05, 25, 2.6, 0.79, 38}};
-// ... of a plain matmul of up to 16 rows: the same launches at what they took with two and three row tiles in flight.  Where the estimates of
-// the two kernels lie closer than the stream has gained since (a tenth) the call stays where it was.
+// ... of a plain matmul of up to 16 rows, and of six units with scales on codes: the kernel with two and three row tiles in flight and scales on
+// codes, which six units still are.
 constexpr Cost kCostQ4Alone = {4.2, 9.5, 0.65, 0.17, 35, 3.1, 0.33, 3.3, 3.4};
 constexpr Cost kCostQ4Coarse[2] = {{4.1, 6.8, 0.64, 0.06, 22, 1.9, 0.32, 2.7, 1.6, 6.9}, {4.8, 36, 0.49, 0.42, 27, 1.5, 0.34, 2.8, 9.3, 2.2}};
 // 3-bit and fp16 matrices: the rates of the stream alone (what is estimated for them only picks the k ranges of a layer's matrices)
@@ -68,25 +73,27 @@ constexpr double kFolded = 2.5;                           // a finishing pass th
 
 int block_class(int n) { return n <= 16 ? 0 : n <= 32 ? 1 : 2; }
 
-// The number of k ranges with the least estimated time (`folded`: the finishing pass is also the RMSNorm of the result).
-int best_ranges(int fmt, int n, int m, int k, int epi, bool folded, bool alone, size_t partial_floats, double *time_us)
+// The number of k ranges with the least estimated time (`folded`: the finishing pass is also the RMSNorm of the result; `exact`: scales on sums only).
+int best_ranges(int fmt, int n, int m, int k, int epi, bool folded, bool alone, bool exact, size_t partial_floats, double *time_us)
 {
-    const bool f16 = fmt == F_F16;
-    const Cost &c = alone && fmt == F_Q4G32 && n <= 16 ? kCostQ4Alone : (f16 ? kCostF16 : fmt == F_Q3 ? kCostQ3 : fmt == F_Q4G32 ? kCostQ4 : kCostQ4Coarse)[block_class(n)];
+    const bool f16 = fmt == F_F16, q4 = !f16 && fmt != F_Q3;
+    const Cost &cost = alone && fmt == F_Q4G32 && n <= 16 ? kCostQ4Alone : (f16 ? kCostF16 : fmt == F_Q3 ? kCostQ3 : fmt == F_Q4G32 ? kCostQ4 : kCostQ4Coarse)[block_class(n)];
     const double bytes = (double)m * k * (f16 ? 2.0 : fmt == F_Q3 ? 0.4375 : fmt == F_Q4G32 ? 0.5625 : fmt == F_Q4G64 ? 0.53125 : 0.515625);
     double best_us = 0.0;
     int best = 0;
     for (int kg = 1; kg <= 16 && (kg == 1 || (size_t)kg * n * m <= partial_floats); ++kg) {
         Plan p;
-        if (!cut(fmt, blocks_of(n), m, k, epi, kg, p)) continue;
+        if (!cut(fmt, blocks_of(n), m, k, epi, kg, p) || (exact && !scale_sums(fmt, blocks_of(n), p.uw))) continue;
+        const Cost &c = q4 && p.uw == 6 ? kCostQ4Alone : cost;
         const double per = (p.tiles + p.rg - 1) / p.rg, rounds = (p.rg * kg + 255) / 256;
         double us = std::max(bytes / (c.tb_per_s * 1e6), rounds * per * (p.uw * c.unit + c.tile)) + rounds * n * ((double)k / kg) * 2e-6 * c.x + (rounds - 1) * c.round;
         if (p.uw >= 4 && k / unit_columns(f16) == p.uw * kWaves * kg) us += c.full;
         if (kg > 1) us += c.finish + kg * c.range + (double)kg * n * m * 8e-6 / c.partial - (folded ? kFolded : 0.0);
+        us += c.launch;
         if (best == 0 || us < best_us) best = kg, best_us = us;
         if (p.uw == 1) break;
     }
-    *time_us = c.launch + best_us;
+    *time_us = best_us;
     return best;
 }
 
@@ -147,14 +154,17 @@ hipError_t launch(int fmt, const uint16_t *x, const void *w, size_t w_bytes, con
         a.epi = epi;
         if (epi == EPI_SWIGLU) a.delta = m / 2;
     }
-    a.batch = std::min((p.tiles + p.rg - 1) / p.rg, lds_tiles(fmt, nb, p.uw));
+    const int per = (p.tiles + p.rg - 1) / p.rg;
+    const bool wait = sums_wait(fmt, nb, p.uw) && per > lds_tiles(fmt, nb, p.uw);
+    a.batch = std::min(per, lds_tiles(fmt, nb, p.uw, wait, per));
+    const size_t lds = (size_t)a.batch * kWaves * nb * 1024 + offset_bytes(fmt, nb, p.uw, wait) + (wait ? (size_t)per * 1024 : 0);
     hipError_t e;
     switch (fmt) {
-    case F_Q4G32: e = launch_q4g32(nb, p.uw, a, a.batch, stream); break;
-    case F_Q4G64: e = launch_q4g64(nb, p.uw, a, a.batch, stream); break;
-    case F_Q4G128: e = launch_q4g128(nb, p.uw, a, a.batch, stream); break;
-    case F_Q3: e = launch_q3(nb, p.uw, a, a.batch, stream); break;
-    default: e = launch_f16(nb, p.uw, a, a.batch, stream); break;
+    case F_Q4G32: e = launch_q4g32(nb, p.uw, a, lds, wait, stream); break;
+    case F_Q4G64: e = launch_q4g64(nb, p.uw, a, lds, wait, stream); break;
+    case F_Q4G128: e = launch_q4g128(nb, p.uw, a, lds, wait, stream); break;
+    case F_Q3: e = launch_q3(nb, p.uw, a, lds, wait, stream); break;
+    default: e = launch_f16(nb, p.uw, a, lds, wait, stream); break;
     }
     if (e != hipSuccess || p.kg == 1) return e;
     return launch_skinny_finish(partial, p.kg, n, m, epi, out_f16, out_f32, resid, stream, fuse);
@@ -164,7 +174,7 @@ hipError_t launch(int fmt, const uint16_t *x, const void *w, size_t w_bytes, con
 
 double gemm_skinny_us(int n, int m, int k, int gshift) { return split_us(n, m, k) * (gshift == 0 ? 1.0 : kSplitCoarse); }
 
-int fewrow_ranges(int wmode, int gshift, int n, int m, int k, int epi, bool folded, bool alone, size_t partial_floats)
+int fewrow_ranges(int wmode, int gshift, int n, int m, int k, int epi, bool folded, bool alone, bool exact, size_t partial_floats)
 {
     // From 33 rows on all groups are decoded alike (scales on codes) and one estimate serves them (us at 33 and 64 rows, groups of 32 / 128: 22016 x 4096
     // 29.5 / 29.6 and 32.9 / 34.7, 27648 x 5120 43 / 44 and 48 / 46, 57344 x 8192 95 / 96 and 97 / 98, 8192 x 28672 56 / 57 and 64 / 62).
@@ -174,7 +184,7 @@ int fewrow_ranges(int wmode, int gshift, int n, int m, int k, int epi, bool fold
     const size_t row = wmode == W_F16 ? (size_t)k * 2 : wmode == W_Q3 ? (size_t)k / 32 * 12 : (size_t)k / 2;
     if ((size_t)m * row > kMaxBuffer) return 0;
     double us = 0.0;
-    const int kr = best_ranges(fmt, n, m, k, epi, folded, alone, partial_floats, &us);
+    const int kr = best_ranges(fmt, n, m, k, epi, folded, alone, exact, partial_floats, &us);
     // A 4-bit matrix may also go through the split-K few-row kernel, whose workgroups own 128 rows and an eighth of k: an eighth of the
     // x traffic, a lower rate.  It is the better one where its workgroups fill the chip and rows are long or x has many rows (8192 x
     // 8192 at 16 rows 16.5 against 18.6 us, 5120 x 13824 17.8 against 20.0, 15360 x 5120 at 64 rows 29.9 against 35.4), the stream

@@ -3,6 +3,6 @@
 
 namespace relax {
 namespace fewrow {
-hipError_t launch_f16(int nb, int uw, const Args &a, int lds_tiles, hipStream_t stream) { return launch_nb<F_F16>(nb, uw, a, lds_tiles, stream); }
+hipError_t launch_f16(int nb, int uw, const Args &a, size_t lds_bytes, bool wait, hipStream_t stream) { return launch_nb<F_F16>(nb, uw, a, lds_bytes, wait, stream); }
 }  // namespace fewrow
 }  // namespace relax

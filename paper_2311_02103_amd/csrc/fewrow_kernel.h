@@ -58,16 +58,28 @@ enum { F_Q4G32 = 0, F_Q4G64 = 1, F_Q4G128 = 2, F_Q3 = 3, F_F16 = 4 };
 
 constexpr int kWaves = 8, kThreads = kWaves * 64;
 // 4-bit: whether a group's scale meets the fp32 sum of its products (exact), or its codes (one rounding per weight; three units of 32 x rows leave
-// no registers for sums, and in two k ranges instead a 13B layer of 17 rows with groups of 64 took 123 us, so 120)
-constexpr bool scale_sums(int fmt, int nb, int uw) { return fmt == F_Q4G64 || fmt == F_Q4G128 ? nb <= 2 && uw * nb < 6 : fmt == F_Q4G32 && nb == 1; }
+// no registers for sums, and in two k ranges instead a 13B layer of 17 rows with groups of 64 took 123 us, so 120; nor do six of 16: in two
+// or three ranges 57344 x 12288 with groups of 32 took 88 us at 12 rows, so 83, 4096 x 11008 at two rows 12.8, so 11.6)
+constexpr bool scale_sums(int fmt, int nb, int uw) { return fmt == F_Q4G64 || fmt == F_Q4G128 ? nb <= 2 && uw * nb < 6 : fmt == F_Q4G32 && nb == 1 && uw < 6; }
 constexpr int unit_columns(bool f16) { return f16 ? 128 : 256; }      // a row's share of a unit: 128 bytes, 96 (3-bit) or 2 x 128 (fp16)
 constexpr int kTileRows = 16;
 constexpr uint32_t kNowhere = 0x80000000u;                // an offset past every buffer (they are at most 2^31 - 1 bytes)
-constexpr size_t kLdsBytes = 152 * 1024;                  // partial tiles of a batch, and the offsets of 4-bit codes
-constexpr size_t offset_bytes(int fmt, int nb, int uw)
+constexpr size_t kLdsBytes = 160 * 1024, kShareBytes = 152 * 1024;        // the CU's; of the wavefronts' shares where there are no offsets
+// Offsets of 4-bit codes, per wavefront and block of x rows: three parts of 16 rows for four units a pack, or, where row tiles need the space, for the
+// units that there are (and a place for what the lanes of the others write)
+constexpr bool dense_offsets(int fmt, int uw, bool wait) { return wait || (fmt == F_Q4G32 && uw == 5); }
+constexpr size_t offset_bytes(int fmt, int nb, int uw, bool wait)
 {
-    return scale_sums(fmt, nb, uw) ? (size_t)kWaves * nb * ((uw + 3) / 4) * 3 * (fmt == F_Q4G32 ? 1024 : fmt == F_Q4G64 ? 512 : 256) : 0;
+    const int units = dense_offsets(fmt, uw, wait) ? nb * uw * 3 + 1 : nb * ((uw + 3) / 4) * 12;
+    return scale_sums(fmt, nb, uw) ? (size_t)kWaves * units * (fmt == F_Q4G32 ? 256 : fmt == F_Q4G64 ? 128 : 64) : 0;
 }
+
+// One block of x rows with scales on sums: whether there is a form of the kernel (WAIT) that takes the shares of a batch of tiles together inside the
+// loop, so that as many row tiles fit a workgroup (kMostTiles) as without offsets.  A second wave of workgroups instead, with x and the first data
+// once more, cost 8 to 20 % (16 rows, groups of 32: 77824 x 4096 46 us, so 41, 36864 x 14336 83, so 68); the other launches keep the form
+// without, which is 0.2 us (three units: 1.2) faster on 5120 x 5120.  Five units leave no registers for it.
+constexpr bool sums_wait(int fmt, int nb, int uw) { return scale_sums(fmt, nb, uw) && nb == 1 && uw <= 4; }
+constexpr int kMostTiles = (int)(kShareBytes / (kWaves * 1024));
 
 struct Args {
     const uint16_t *x;       // [n,k] fp16
@@ -76,7 +88,7 @@ struct Args {
     uint32_t x_bytes, w_bytes, s_bytes;
     int32_t n, m, k;
     int32_t kg, rg;          // workgroups along k, row ranges
-    int32_t tiles, batch;    // row tiles of the matrix; tiles whose partial sums fit LDS together
+    int32_t tiles, batch;    // row tiles of the matrix; tiles whose wavefronts' shares fit LDS together
     int32_t epi;             // Epilogue, or kPartial
     int32_t delta;           // the second eight rows of a tile start delta rows after the first eight
     int32_t ropeshift;       // EPI_ROPE_KV: log2(head_dim / 16)
@@ -174,7 +186,8 @@ __device__ __forceinline__ void rows_to_lanes(uint32_t &a, uint32_t &b)
 }
 
 // UW units per wavefront, NB blocks of 16 x rows; in flight per wavefront: T row tiles (D == UW), or D units (T == 1, D < UW).
-template <int FMT, int NB, int UW, int T, int D>
+// WAIT: the shares of a full batch of tiles are taken together inside the loop (sums_wait).
+template <int FMT, int NB, int UW, int T, int D, bool WAIT>
 __global__ __launch_bounds__(kThreads) void fewrow_kernel(Args a)
 {
     constexpr bool Q3 = FMT == F_Q3, F16 = FMT == F_F16;
@@ -366,7 +379,12 @@ __global__ __launch_bounds__(kThreads) void fewrow_kernel(Args a)
     constexpr float kDown = SG == 32 ? 0x1p-13f : SG == 64 ? 0x1p-14f : 0x1p-15f;
     // They wait in LDS (a slot of each wavefront's own): the registers are x's.
     typedef _Float16 part_t __attribute__((ext_vector_type(GU > 1 ? GU : 2)));
-    part_t *const off = reinterpret_cast<part_t *>(red + (size_t)a.batch * (kWaves * NB * 64)) + wave * (NB * SP * 3 * 64) + lane;
+    part_t *const off = reinterpret_cast<part_t *>(red + (size_t)a.batch * (kWaves * NB * 64)) + wave * (int)(offset_bytes(FMT, NB, UW, WAIT) / (kWaves * sizeof(part_t)));
+    constexpr bool DENSE = dense_offsets(FMT, UW, WAIT);
+    auto part_at = [&](int l, int nb, int p, int i) {     // part i of lane l's unit of pack p (a unit that the pack does not have: another's, times scales of 0)
+        const int unit = 4 * p + 3 < UW ? 4 * p + (l >> 4) : 4 * p + 1 == UW ? 4 * p : min(4 * p + (l >> 4), UW - 1);
+        return DENSE ? ((nb * UW + unit) * 3 + i) * 16 + (l & 15) : ((nb * SP + p) * 3 + i) * 64 + l;
+    };
     uint32_t odd = 0;                                     // bits of the x rows whose sums are not finite in the wavefront's columns (see redo)
     static_assert(!SUMS || NB <= 2, "a bit per row");
     if constexpr (SUMS) {
@@ -400,7 +418,7 @@ __global__ __launch_bounds__(kThreads) void fewrow_kernel(Args a)
                         part[j] = (_Float16)v;
                         o[j] = (v - (float)part[j]) * 0x1p11f;
                     }
-                    off[((nb * SP + p) * 3 + i) * 64] = part;
+                    off[!DENSE || 4 * p + 3 < UW || 4 * p + qd < UW ? part_at(lane, nb, p, i) : NB * UW * 3 * 16 + r16] = part;
                 }
             }
             const uint64_t lanes = __ballot(nan != nan);
@@ -429,15 +447,15 @@ __global__ __launch_bounds__(kThreads) void fewrow_kernel(Args a)
             if (SP && u % 4 == 0) {
                 if constexpr (SUMS) {
                     const u32x4_t v = b.s[SP ? u / 4 : 0];
-                    uint32_t zero = 0;
-                    asm volatile("" : "+v"(zero));        // read per tile: as loop invariants the parts would be kept in registers, or spilled
+                    int l = lane;
+                    asm volatile("" : "+v"(l));           // read per tile: as loop invariants the parts, or their addresses, would be kept in registers, or spilled
                     const half8_t sv = __builtin_bit_cast(half8_t, u32x4_t{v[0], SW >= 2 ? v[1] : 0u, SW == 4 ? v[2] : 0u, SW == 4 ? v[3] : 0u});
 #pragma unroll
                     for (int nb = 0; nb < NB; ++nb) {
                         float4_t d = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
                         for (int i = 2; i >= 0; --i) {
-                            const part_t part = off[((nb * SP + u / 4) * 3 + i) * 64 + zero];
+                            const part_t part = off[part_at(l, nb, u / 4, i)];
                             half8_t pf;
 #pragma unroll
                             for (int j = 0; j < 8; ++j) pf[j] = j < GU ? part[j < GU ? j : 0] : (_Float16)0.0f;
@@ -537,14 +555,21 @@ __global__ __launch_bounds__(kThreads) void fewrow_kernel(Args a)
     // ---- the wavefronts' shares of `count` tiles from t0 + first on: sum in order, epilogue ----
     // value layout of a tile block: lane l holds x row l % 16 of the block and tile rows 4 (l / 16) .. + 3; tile rows 0..7 are the
     // first half of the tile, 8..15 the second, so lane l and lane l ^ 32 hold the two members of a pair
+    // WAIT: the sums of the tiles before `first`, behind the offsets
+    float4_t *const sums = (float4_t *)((char *)(red + (size_t)a.batch * (kWaves * NB * 64)) + offset_bytes(FMT, NB, UW, WAIT));
     auto finish = [&](int first, int count) {
-        for (int it = wave; it < count * NB; it += kWaves) {
-            const int bt = it / NB, nb = it - bt * NB, t = t0 + first + bt;
+        for (int it = (WAIT ? -first : 0) + wave; it < count * NB; it += kWaves) {
+            const int bt = NB == 1 ? it : it / NB, nb = NB == 1 ? 0 : it - bt * NB, t = t0 + first + bt;
             const int i = nb * 16 + r16, half = lane >> 5;
             if (nb * 16 >= a.n) continue;
-            float4_t v = red[(bt * kWaves * NB + nb) * 64 + at_lane];
+            float4_t v;
+            if (WAIT && it < 0) {
+                v = sums[(first + it) * 64 + lane];
+            } else {
+                v = red[(bt * kWaves * NB + nb) * 64 + at_lane];
 #pragma unroll
-            for (int w = 1; w < kWaves; ++w) v += red[((bt * kWaves + w) * NB + nb) * 64 + at_lane];
+                for (int w = 1; w < kWaves; ++w) v += red[((bt * kWaves + w) * NB + nb) * 64 + at_lane];
+            }
             const int row = tile_row(t) + (qd & 1) * 4 + half * a.delta;       // matrix row of v[0]
             if (a.epi == EPI_SWIGLU) {
                 float o[4];
@@ -671,7 +696,20 @@ __global__ __launch_bounds__(kThreads) void fewrow_kernel(Args a)
                 done = true;
                 break;
             }
-            if (NB > 1 && filled == a.batch) {            // more tiles than LDS holds (partial rows only: the launcher sees to it)
+            if (WAIT && filled == a.batch) {              // more tiles than LDS holds shares of
+                if constexpr (SUMS)
+                    if (odd) redo(first, filled);
+                lds_barrier();
+                for (int it = wave; it < filled; it += kWaves) {
+                    float4_t v = red[it * kWaves * 64 + at_lane];
+#pragma unroll 1
+                    for (int w = 1; w < kWaves; ++w) v += red[(it * kWaves + w) * 64 + at_lane];
+                    sums[(first + it) * 64 + lane] = v;
+                }
+                lds_barrier();
+                first += filled, filled = 0;
+            }
+            if (NB > 1 && filled == a.batch) {            // (partial rows only: the launcher sees to it)
                 if constexpr (SUMS)
                     if (odd) redo(first, filled);
                 lds_barrier();
@@ -706,44 +744,42 @@ constexpr int units_in_flight()
     return UW == 6 ? 2 : UW;
 }
 
-template <int FMT, int NB, int UW>
-hipError_t launch_one(const Args &a, int lds_tiles, hipStream_t stream)
+template <int FMT, int NB, int UW, bool WAIT = false>
+hipError_t launch_one(const Args &a, size_t lds_bytes, bool wait, hipStream_t stream)
 {
+    if constexpr (sums_wait(FMT, NB, UW) && !WAIT)
+        if (wait) return launch_one<FMT, NB, UW, true>(a, lds_bytes, wait, stream);
     constexpr int T = tiles_in_flight<FMT, NB, UW>(), D = units_in_flight<FMT, NB, UW>();
     static std::atomic<bool> attr_done{false};            // setting the attribute twice is harmless; the flag only has to be a defined read
     if (!attr_done.load()) {
-        if (hipFuncSetAttribute((const void *)fewrow_kernel<FMT, NB, UW, T, D>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsBytes) != hipSuccess)
+        if (hipFuncSetAttribute((const void *)fewrow_kernel<FMT, NB, UW, T, D, WAIT>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsBytes) != hipSuccess)
             return hipErrorInvalidValue;
         attr_done.store(true);
     }
-    hipLaunchKernelGGL((fewrow_kernel<FMT, NB, UW, T, D>), dim3(a.kg * a.rg), dim3(kThreads), (size_t)lds_tiles * kWaves * NB * 1024 + offset_bytes(FMT, NB, UW), stream, a);
+    hipLaunchKernelGGL((fewrow_kernel<FMT, NB, UW, T, D, WAIT>), dim3(a.kg * a.rg), dim3(kThreads), lds_bytes, stream, a);
     return hipGetLastError();
 }
 
 template <int FMT, int NB, int... UWS>
-hipError_t launch_uw(int uw, const Args &a, int lds_tiles, hipStream_t stream)
+hipError_t launch_uw(int uw, const Args &a, size_t lds_bytes, bool wait, hipStream_t stream)
 {
     hipError_t e = hipErrorInvalidValue;
-    (void)((uw == UWS ? (e = launch_one<FMT, NB, UWS>(a, lds_tiles, stream), true) : false) || ...);
+    (void)((uw == UWS ? (e = launch_one<FMT, NB, UWS>(a, lds_bytes, wait, stream), true) : false) || ...);
     return e;
 }
 
 // units per wavefront the kernels are built for (registers: 32 NB per unit of x, fp16 16 NB; 8 resp. 16 per unit of weights in
 // flight): {16 x rows, 32, 64}
 template <int FMT>
-hipError_t launch_nb(int nb, int uw, const Args &a, int lds_tiles, hipStream_t stream)
+hipError_t launch_nb(int nb, int uw, const Args &a, size_t lds_bytes, bool wait, hipStream_t stream)
 {
     if constexpr (FMT == F_F16) {
-        if (nb == 1) return launch_uw<FMT, 1, 1, 2, 3, 4, 5, 6, 8>(uw, a, lds_tiles, stream);
-        return launch_uw<FMT, 2, 1, 2, 3, 4>(uw, a, lds_tiles, stream);
-    } else if constexpr (FMT != F_Q3) {
-        if (nb == 1) return launch_uw<FMT, 1, 1, 2, 3, 4, 5>(uw, a, lds_tiles, stream);
-        if (nb == 2) return launch_uw<FMT, 2, 1, 2, 3>(uw, a, lds_tiles, stream);
-        return launch_uw<FMT, 4, 1>(uw, a, lds_tiles, stream);
+        if (nb == 1) return launch_uw<FMT, 1, 1, 2, 3, 4, 5, 6, 8>(uw, a, lds_bytes, wait, stream);
+        return launch_uw<FMT, 2, 1, 2, 3, 4>(uw, a, lds_bytes, wait, stream);
     } else {
-        if (nb == 1) return launch_uw<FMT, 1, 1, 2, 3, 4, 5, 6>(uw, a, lds_tiles, stream);
-        if (nb == 2) return launch_uw<FMT, 2, 1, 2, 3>(uw, a, lds_tiles, stream);
-        return launch_uw<FMT, 4, 1>(uw, a, lds_tiles, stream);
+        if (nb == 1) return launch_uw<FMT, 1, 1, 2, 3, 4, 5, 6>(uw, a, lds_bytes, wait, stream);
+        if (nb == 2) return launch_uw<FMT, 2, 1, 2, 3>(uw, a, lds_bytes, wait, stream);
+        return launch_uw<FMT, 4, 1>(uw, a, lds_bytes, wait, stream);
     }
 }
 

@@ -438,14 +438,15 @@ hipError_t launch_gemm_skinny(const uint16_t *x, const relax_qmat &w, int n, int
 // into when partial_floats floats of workspace are at hand; 0: the kernel does not take the shape.  With one range the epilogues
 // (residuals, SwiGLU, and with `fuse` rotary + append) happen in the kernel and `partial` is not used; with more, `partial` holds
 // k_ranges * n * m floats and the finishing pass of the split-K kernel follows.  folded: that pass replaces a launch of its own
-// (the RMSNorm of the result), so cutting along k costs next to nothing.
+// (the RMSNorm of the result), so cutting along k costs next to nothing.  alone: a plain matmul, no layer around it.  exact: only as launches that
+// round no weight (4-bit).
 constexpr int kFewRowMin = 2, kFewRowMax = 64;
 // Rows up to which the matvec kernels take a 4-bit layer by default.  Where the streaming kernel takes such a call from them it is as exact:
 // scales on sums, and q and k rounded once, behind the rotary embedding (SkinnyFuse::rope_once).  Everywhere else on the matrix path the plain
 // epilogue's rounding comes first, whether the rotary step is part of a matmul or a launch of its own.
 constexpr int kMatvecRows = 4;
 double gemm_skinny_us(int n, int m, int k, int gshift);      // estimated time of the split-K few-row kernel
-int fewrow_ranges(int wmode, int gshift, int n, int m, int k, int epi, bool folded, bool alone, size_t partial_floats);
+int fewrow_ranges(int wmode, int gshift, int n, int m, int k, int epi, bool folded, bool alone, bool exact, size_t partial_floats);
 bool fewrow_pays_alone(int wmode, int n, int m, int k);      // 3-bit, fp16: as fast as the other kernels without an epilogue to save a launch
 bool fewrow_fuse_ok(const relax_layer_dims &dm, const relax_kv_cache &cache);
 hipError_t launch_fewrow_q4(const uint16_t *x, const relax_qmat &w, int n, int epi, int k_ranges, uint16_t *out_f16, float *out_f32, const void *resid, float *partial,

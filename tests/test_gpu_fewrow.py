@@ -396,3 +396,42 @@ def _random_layer(shape, group):
         host[name + ".s"] = (r.random_sample((m, k // group)) * 0.006 + 0.001).astype(np.float16).view(np.uint16)
     host.update({name: wl.normal_f16_bits(4, 10 + i, (shape.hidden,), std=0.1, mean=1.0) for i, name in enumerate(("norm_attn", "norm_ffn"))})
     return host
+
+
+# Six units per wavefront and fewer (wavefronts with 5 and 6), row tiles that end early
+@pytest.mark.parametrize("m,k,n,group", [(20, 11008, 2, 32), (520, 10496, 3, 32), (4096, 11008, 4, 64), (4096, 11008, 4, 128), (12288, 12288, 2, 32)])
+def test_six_units_per_wavefront_against_float64(rx, m, k, n, group):
+    g = _gen(m + k + n)
+    w, ref = _packed(rx, "q4", m, k, group, g)
+    size = rx.relax_matmul_workspace_bytes(w, 64)
+    assert rx.relax_plan_matmul("q4", n, m, k, size, group)[:3] == (rx.OK, rx.KERNEL_STREAM, 1)
+    ws = torch.empty(size, dtype=torch.uint8, device="cuda")
+    x = torch.randn(n, k, device="cuda", generator=g).half()
+    out = torch.full((n, m), float("nan"), device="cuda", dtype=torch.float16)
+    rx.check(rx.relax_dequant_matmul(x, w, out, n, ws, size))
+    want = x.double() @ ref.t()
+    assert float((out.double() - want).norm() / want.norm()) < REL
+
+
+# 17 to 19 row tiles per workgroup, or 34 to 38 of one cut in two: more than the LDS holds shares of beside the offsets, sums wait there inside the loop.  One
+# to four units per wavefront; the last row tile has 4 rows.
+@pytest.mark.parametrize("m,k,ranges", [(77748, 1536, 1), (73732, 4096, 1), (77748, 4352, 1), (69652, 6400, 1), (73732, 8192, 1), (38836, 14336, 2)])
+@pytest.mark.parametrize("group", [32, 64, 128])
+def test_more_row_tiles_than_lds_in_one_block_of_rows(rx, group, m, k, ranges):
+    n, g = 5, _gen(m + k)
+    w, ref = _packed(rx, "q4", m, k, group, g)
+    size = rx.relax_matmul_workspace_bytes(w, 16)
+    assert rx.relax_plan_matmul("q4", n, m, k, size, group)[:3] == (rx.OK, rx.KERNEL_STREAM, ranges)
+    ws = torch.empty(size, dtype=torch.uint8, device="cuda")
+    x = torch.randn(n, k, device="cuda", generator=g).half()
+    out = [torch.full((n, m), float("nan"), device="cuda", dtype=torch.float16) for _ in range(3)]
+    for o in out[:2]:
+        rx.check(rx.relax_dequant_matmul(x, w, o, n, ws, size))
+    want = x.double() @ ref.t()
+    # exact but for the rounding of the result (2^-11 of it at most, 0.4 of that in the norm) and fp32 sums
+    assert float((out[0].double() - want).norm() / want.norm()) < 2.5e-4 and torch.equal(out[0], out[1])
+    x[1, 7] = float("inf")
+    rx.check(rx.relax_dequant_matmul(x, w, out[2], n, ws, size))
+    infinite = (ref[:, 7] * float("inf")).half()
+    assert torch.equal(torch.nan_to_num(out[2][1], nan=0.5), torch.nan_to_num(infinite, nan=0.5))
+    assert torch.equal(out[2][[0, 2, 3, 4]], out[0][[0, 2, 3, 4]])

@@ -135,3 +135,14 @@ def test_long_groups_stay_on_the_streaming_kernel_at_33_to_64_rows(group, m, k, 
     assert stream < split and plan("q4", n, m, k, workspace(n, m, k), group)[0] == rx.KERNEL_STREAM
     for rows in range(33, 65):                            # decoded alike: one route for all groups
         assert plan("q4", rows, m, k, workspace(rows, m, k), group) == plan("q4", rows, m, k, workspace(rows, m, k)), rows
+
+
+# Rows of 10241 to 12288 columns in one k range are six units per wavefront: streaming kernel with them, without (two ranges or more) in us, groups of 32.
+SIX_UNITS = [(4096, 11008, 2, 11.6, 12.8), (4096, 11008, 4, 12.5, 13.2), (4096, 11008, 6, 12.9, 14.4), (12288, 11008, 3, 20.9, 22.9),
+             (57344, 12288, 4, 77.0, 83.3), (57344, 12288, 12, 82.5, 89.2), (12288, 12288, 3, 25.6, 24.4), (12288, 11008, 16, 28.5, 25.5)]
+
+
+@pytest.mark.parametrize("m,k,n,six,fewer", SIX_UNITS)
+def test_rows_of_six_units_take_the_faster_cut(m, k, n, six, fewer):
+    kernel, ranges, *_ = plan("q4", n, m, k, workspace(n, m, k))
+    assert kernel == rx.KERNEL_STREAM and (ranges == 1) == (six < fewer)
