@@ -50,7 +50,8 @@ bool cut(int fmt, int nb, int m, int k, int epi, int kg, Plan &p)
 
 // What a launch takes, in us, for blocks of 16, 32 and 64 rows of x: fitted to 22 matrices from 1024 x 4096 to 57344 x 8192 (groups of 32 beyond
 // 16 rows: to 73) at 2 to 64 rows, weights cold, every k range the kernel is built for.  What the 4-bit figures choose is 0.3 % off the fastest k
-// range on average for blocks of 16, 0.6 % for 32, 9 and 10 % at most; the estimates are within 4 % of the times on average.
+// range on average for blocks of 16, 0.6 % for 32, 9 and 10 % at most; the estimates are within 4 % of the times on average (launches with scales on
+// sums of before their arguments were read behind the loop, which takes 0.5 to 1 us off each).
 //   launch                 the launch, the first data and the sums over the wavefronts
 //   tb_per_s               the stream of the weights, or, where few row tiles or uneven slices leave it to the slowest workgroup,
 //   unit, tile             ... per row tile of a workgroup: its longest slice's units, and the sums
@@ -69,6 +70,7 @@ constexpr Cost kCostQ4Coarse[2] = {{4.1, 6.8, 0.64, 0.06, 22, 1.9, 0.32, 2.7, 1.
 // 3-bit and fp16 matrices: the rates of the stream alone (what is estimated for them only picks the k ranges of a layer's matrices)
 constexpr Cost kCostQ3[3] = {{5.8, 5.9, 0.46, 0.0, 25, 3.1, 0.0, 5.8}, {5.8, 5.35, 0.51, 0.0, 27, 3.4, 0.0, 5.3}, {5.8, 4.7, 0.58, 0.0, 31, 3.9, 0.0, 4.6}};
 constexpr Cost kCostF16[2] = {{5.8, 5.9, 1.05, 0.0, 25, 3.1, 0.0, 5.8}, {5.8, 5.35, 1.17, 0.0, 27, 3.4, 0.0, 5.3}};
+constexpr double kSumsWait = 2.0;                         // two ranges whose sums wait in LDS (34816 x 8192 at 8 rows, groups of 64, 37.1 us, one range without 35.4)
 constexpr double kFolded = 2.5;                           // a finishing pass that is also a step of the layer saves that step's launch
 
 int block_class(int n) { return n <= 16 ? 0 : n <= 32 ? 1 : 2; }
@@ -88,6 +90,7 @@ int best_ranges(int fmt, int n, int m, int k, int epi, bool folded, bool alone, 
         const double per = (p.tiles + p.rg - 1) / p.rg, rounds = (p.rg * kg + 255) / 256;
         double us = std::max(bytes / (c.tb_per_s * 1e6), rounds * per * (p.uw * c.unit + c.tile)) + rounds * n * ((double)k / kg) * 2e-6 * c.x + (rounds - 1) * c.round;
         if (p.uw >= 4 && k / unit_columns(f16) == p.uw * kWaves * kg) us += c.full;
+        if (kg > 1 && sums_wait(fmt, blocks_of(n), p.uw) && per > lds_tiles(fmt, blocks_of(n), p.uw)) us += kSumsWait;
         if (kg > 1) us += c.finish + kg * c.range + (double)kg * n * m * 8e-6 / c.partial - (folded ? kFolded : 0.0);
         us += c.launch;
         if (best == 0 || us < best_us) best = kg, best_us = us;

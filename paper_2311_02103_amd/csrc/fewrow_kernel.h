@@ -185,11 +185,85 @@ __device__ __forceinline__ void rows_to_lanes(uint32_t &a, uint32_t &b)
     b = __builtin_amdgcn_update_dpp(b, a0, 0x128, 0xF, 0x3, false);     // ... lower eight
 }
 
+// A wavefront's share of the launch: units u0 .. u0 + nu - 1 of the row tiles t0 .. t0 + nt - 1.  Neighbouring workgroups (they go to different
+// XCDs) take different k ranges of the same rows.
+struct Share {
+    int kgi, nu, u0, nt, t0;
+    template <typename A>
+    __device__ __forceinline__ Share(const A &a, int wave, int unit_cols)
+    {
+        const int rgi = blockIdx.x / a.kg;
+        kgi = blockIdx.x - rgi * a.kg;
+        const int units = a.k / unit_cols, slices = a.kg * kWaves, slice = kgi * kWaves + wave;
+        const int ubase = units / slices, urem = units - ubase * slices;
+        nu = ubase + (slice < urem), u0 = slice * ubase + min(slice, urem);
+        const int tbase = a.tiles / a.rg, trem = a.tiles - tbase * a.rg;
+        nt = tbase + (rgi < trem), t0 = rgi * tbase + min(rgi, trem);
+    }
+};
+// first matrix row of a tile's first half
+template <typename A>
+__device__ __forceinline__ int tile_first_row(const A &a, int t)
+{
+    if (a.epi == EPI_SWIGLU) return t * 8;
+    if (a.epi == EPI_ROPE_KV) return ((t >> a.ropeshift) * a.d) + (t & ((1 << a.ropeshift) - 1)) * 8;
+    return t * 16;
+}
+
+// The kernel's arguments, read again.  What the compiler holds in scalar registers over the loop for the code behind it, it spills: 45 moves in front
+// of the first data, 80 (with redo_rows 280) behind the loop.  Without them a launch takes 0.5 to 1 us less (us: 4 rows, groups of 32, 4096 x
+// 4096 7.1 -> 6.3, 22016 x 4096 16.2 -> 14.9, 57344 x 8192 53.9 -> 53.2; 32 rows, groups of 128, 12288 x 4096 15.9 -> 14.9).
+__device__ __forceinline__ const Args &args_again()
+{
+    const __attribute__((address_space(4))) Args *p = (const __attribute__((address_space(4))) Args *)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    return *(const Args *)p;
+}
+
+// Rows of x with an infinity or a NaN where 4-bit scales meet sums: the sums of 64 + u lose an infinity to the offset (inf - inf), where its product
+// with a code less 8 is infinite.  The wavefront that holds one computes its shares of these rows (bits of `odd`) once more from codes less 8,
+// in plain fp32 (40 us per row and tile at most), for the `count` tiles from `first` of its range on, whose shares are in red; the rows beside them
+// keep their bits, the calls without pay 0.1 us for the look.
+template <int FMT, int NB>
+__device__ __forceinline__ void redo_rows(float4_t *red, uint32_t odd, int first, int count)
+{
+    constexpr int SG = FMT == F_Q4G64 ? 64 : FMT == F_Q4G128 ? 128 : 32, kUnit = unit_columns(false);
+    const Args &a = args_again();
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), r16 = lane & 15, qd = lane >> 4;
+    const int k = a.k;
+    const Share sh(a, wave, kUnit);
+#pragma unroll 1
+    for (int it = 0; it < count * NB; ++it) {
+        const int bt = it / NB, nb = it - bt * NB;
+        // (rows past the matrix: the last one's results, which nobody reads)
+        const size_t row = min(tile_first_row(a, sh.t0 + first + bt) + (r16 & 7) + (r16 >> 3) * a.delta, a.m - 1);
+        float *dst = (float *)&red[((bt * kWaves + wave) * NB + nb) * 64];
+#pragma unroll 1
+        for (uint32_t todo = odd >> (nb * 16 % 32) & 0xFFFFu; todo; todo &= todo - 1) {
+            const int i = __builtin_ctz(todo);
+            float sum = 0.0f;
+#pragma unroll 1
+            for (int c = sh.u0 * kUnit + qd * 8; c < (sh.u0 + sh.nu) * kUnit; c += 32) {
+                const uint32_t w = ((const uint32_t *)a.w)[row * (k / 8) + c / 8];
+                const half8_t xv = *(const half8_t *)(a.x + (size_t)(nb * 16 + i) * k + c);
+                float part = 0.0f;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) part = fmaf((float)((int)(w >> (4 * e) & 15u) - 8), (float)xv[e], part);
+                sum = fmaf(part, h2f(a.s[row * (k / SG) + c / SG]), sum);
+            }
+            sum += __shfl_xor(sum, 16, kWave);
+            sum += __shfl_xor(sum, 32, kWave);
+            if (qd == 0) dst[(16 * (r16 >> 2) + (i ^ (r16 >> 2))) * 4 + (r16 & 3)] = sum;
+        }
+    }
+}
+
 // UW units per wavefront, NB blocks of 16 x rows; in flight per wavefront: T row tiles (D == UW), or D units (T == 1, D < UW).
 // WAIT: the shares of a full batch of tiles are taken together inside the loop (sums_wait).
 template <int FMT, int NB, int UW, int T, int D, bool WAIT>
-__global__ __launch_bounds__(kThreads) void fewrow_kernel(Args a)
+__global__ __launch_bounds__(kThreads) void fewrow_kernel(Args args)
 {
+    const Args &a = args;
     constexpr bool Q3 = FMT == F_Q3, F16 = FMT == F_F16;
     static_assert(D == UW || (T == 1 && UW % D == 0), "ring of units");
     constexpr int NL = F16 ? 2 : 1;                       // lines of a row per unit
@@ -215,21 +289,9 @@ __global__ __launch_bounds__(kThreads) void fewrow_kernel(Args a)
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r16 = lane & 15, qd = lane >> 4;
-    // neighbouring workgroups (they go to different XCDs) take different k ranges of the same rows
-    const int rgi = blockIdx.x / a.kg, kgi = blockIdx.x - rgi * a.kg;
-    const int units = a.k / kUnit, slices = a.kg * kWaves, slice = kgi * kWaves + wave;
-    const int ubase = units / slices, urem = units - ubase * slices;
-    const int nu = ubase + (slice < urem);                // live units of this wavefront: UW or UW - 1
-    const int u0 = slice * ubase + min(slice, urem);
-    const int tbase = a.tiles / a.rg, trem = a.tiles - tbase * a.rg;
-    const int nt = tbase + (rgi < trem), t0 = rgi * tbase + min(rgi, trem);
-
-    // first matrix row of a tile's first half
-    auto tile_row = [&](int t) {
-        if (a.epi == EPI_SWIGLU) return t * 8;
-        if (a.epi == EPI_ROPE_KV) return ((t >> a.ropeshift) * a.d) + (t & ((1 << a.ropeshift) - 1)) * 8;
-        return t * 16;
-    };
+    const Share sh(a, wave, kUnit);
+    const int kgi = sh.kgi, nu = sh.nu, u0 = sh.u0, nt = sh.nt, t0 = sh.t0;      // nu: UW or UW - 1
+    auto tile_row = [&](int t) { return tile_first_row(a, t); };
 
     // ---- x of the wavefront's columns, in the order the decode yields ----
     // step s of a packed unit: word s % 4 of piece 2 q + s / 4; of an fp16 unit: piece 2 q + s % 2 of line s / 2
@@ -385,7 +447,7 @@ __global__ __launch_bounds__(kThreads) void fewrow_kernel(Args a)
         const int unit = 4 * p + 3 < UW ? 4 * p + (l >> 4) : 4 * p + 1 == UW ? 4 * p : min(4 * p + (l >> 4), UW - 1);
         return DENSE ? ((nb * UW + unit) * 3 + i) * 16 + (l & 15) : ((nb * SP + p) * 3 + i) * 64 + l;
     };
-    uint32_t odd = 0;                                     // bits of the x rows whose sums are not finite in the wavefront's columns (see redo)
+    uint32_t odd = 0;                                     // bits of the x rows whose sums are not finite in the wavefront's columns (see redo_rows)
     static_assert(!SUMS || NB <= 2, "a bit per row");
     if constexpr (SUMS) {
 #pragma unroll
@@ -558,6 +620,7 @@ __global__ __launch_bounds__(kThreads) void fewrow_kernel(Args a)
     // WAIT: the sums of the tiles before `first`, behind the offsets
     float4_t *const sums = (float4_t *)((char *)(red + (size_t)a.batch * (kWaves * NB * 64)) + offset_bytes(FMT, NB, UW, WAIT));
     auto finish = [&](int first, int count) {
+        const Args &a = SUMS ? args_again() : args;
         for (int it = (WAIT ? -first : 0) + wave; it < count * NB; it += kWaves) {
             const int bt = NB == 1 ? it : it / NB, nb = NB == 1 ? 0 : it - bt * NB, t = t0 + first + bt;
             const int i = nb * 16 + r16, half = lane >> 5;
@@ -654,37 +717,6 @@ __global__ __launch_bounds__(kThreads) void fewrow_kernel(Args a)
         }
     };
 
-    // 4-bit rows of x with an infinity or a NaN: the sums of 64 + u lose an infinity to the offset (inf - inf), where its product with a code less 8 is
-    // infinite.  The wavefront that holds one computes its shares of these rows once more from codes less 8, in plain fp32 (40 us per row and
-    // tile at most); the rows beside them keep their bits, the calls without pay 0.1 us for the look.
-    auto redo = [&](int first, int count) {
-#pragma unroll 1
-        for (int it = 0; it < count * NB; ++it) {
-            const int bt = it / NB, nb = it - bt * NB;
-            const Where at = where(first + bt);
-            const uint32_t row = (r16 & 7) + (r16 >> 3) * (uint32_t)a.delta;
-            float *dst = (float *)&red[((bt * kWaves + wave) * NB + nb) * 64];
-#pragma unroll 1
-            for (uint32_t todo = odd >> (nb * 16 % 32) & 0xFFFFu; todo; todo &= todo - 1) {
-                const int i = __builtin_ctz(todo);
-                float sum = 0.0f;
-#pragma unroll 1
-                for (int c = u0 * kUnit + qd * 8; c < (u0 + nu) * kUnit; c += 32) {
-                    const uint32_t w = __builtin_amdgcn_raw_buffer_load_b32(at.w, row * wpitch + (uint32_t)c / 2, 0, 0);
-                    const uint16_t sc = __builtin_amdgcn_raw_buffer_load_b16(at.s, row * spitch + (uint32_t)(c / SG) * 2, 0, 0);
-                    const half8_t xv = *(const half8_t *)(a.x + (size_t)(nb * 16 + i) * a.k + c);
-                    float part = 0.0f;
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) part = fmaf((float)((int)(w >> (4 * e) & 15u) - 8), (float)xv[e], part);
-                    sum = fmaf(part, h2f(sc), sum);
-                }
-                sum += __shfl_xor(sum, 16, kWave);
-                sum += __shfl_xor(sum, 32, kWave);
-                if (qd == 0) dst[(16 * (r16 >> 2) + (i ^ (r16 >> 2))) * 4 + (r16 & 3)] = sum;
-            }
-        }
-    };
-
     int first = 0, filled = 0;                            // tiles first .. first + filled - 1 of the range sit in LDS
     for (int t = 0;; t += T) {
         bool done = false;
@@ -698,7 +730,7 @@ __global__ __launch_bounds__(kThreads) void fewrow_kernel(Args a)
             }
             if (WAIT && filled == a.batch) {              // more tiles than LDS holds shares of
                 if constexpr (SUMS)
-                    if (odd) redo(first, filled);
+                    if (odd) redo_rows<FMT, NB>(red, odd, first, filled);
                 lds_barrier();
                 for (int it = wave; it < filled; it += kWaves) {
                     float4_t v = red[it * kWaves * 64 + at_lane];
@@ -711,7 +743,7 @@ __global__ __launch_bounds__(kThreads) void fewrow_kernel(Args a)
             }
             if (NB > 1 && filled == a.batch) {            // (partial rows only: the launcher sees to it)
                 if constexpr (SUMS)
-                    if (odd) redo(first, filled);
+                    if (odd) redo_rows<FMT, NB>(red, odd, first, filled);
                 lds_barrier();
                 flush(first, filled);
                 lds_barrier();
@@ -721,7 +753,7 @@ __global__ __launch_bounds__(kThreads) void fewrow_kernel(Args a)
         if (done) break;
     }
     if constexpr (SUMS)
-        if (odd) redo(first, filled);
+        if (odd) redo_rows<FMT, NB>(red, odd, first, filled);
     lds_barrier();
     finish(first, filled);
 }

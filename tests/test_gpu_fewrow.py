@@ -187,10 +187,17 @@ def test_3bit_scales_over_the_whole_fp16_range(rx, low, high):
         assert bool(((out.double() - want).abs() <= bound).all()), n
 
 
-def _more_tiles_than_lds(n, m, ranges):
-    """Whether a workgroup of the streaming kernel gets more row tiles than its 152 KB of LDS hold sums of."""
-    blocks, tiles = (1 if n <= 16 else 2 if n <= 32 else 4), -(-m // 16)
-    return -(-tiles // min(tiles, 256 // ranges)) > 152 // (8 * blocks)
+def _units(k, ranges):
+    """Units of 256 columns of the wavefront with most of them."""
+    return -(-(k // 256) // (8 * ranges))
+
+
+def _more_tiles_than_lds(n, m, k, ranges, group):
+    """Whether a workgroup of the streaming kernel gets more row tiles than its 152 KB of LDS hold sums of, beside the offsets of 4-bit codes where
+    scales meet sums (more than 16 rows; with fewer the sums wait there instead)."""
+    blocks, tiles, units = (1 if n <= 16 else 2 if n <= 32 else 4), -(-m // 16), _units(k, ranges)
+    offsets = 8 * blocks * -(-units // 4) * 3 * 16 * 1024 // group * 2 if group > 32 and blocks == 2 and units < 3 else 0
+    return blocks > 1 and -(-tiles // min(tiles, 256 // ranges)) > (152 * 1024 - offsets) // (8 * blocks * 1024)
 
 
 # (m, k, n, k ranges, sums flushed inside the loop): blocks of 16, 32 and 64 rows
@@ -198,13 +205,18 @@ RANGES = [(20, 5120, 15, 3, False), (20, 28672, 16, 14, False), (20, 6656, 17, 4
           (12292, 11008, 17, 3, True), (20, 5120, 33, 3, False), (11264, 4096, 33, 2, True), (16388, 2816, 64, 2, True), (11264, 5632, 48, 3, True)]
 
 
-@pytest.mark.parametrize("m,k,n,ranges,flush", RANGES)
-@pytest.mark.parametrize("group", [32, 128])
+# Groups of 64 and 128 up to 32 rows: one and two units of 32 x rows with scales on sums, three with scales on codes
+RANGES_COARSE = [(20, 5120, 15, 3, False), (20, 28672, 16, 8, False), (20, 6656, 17, 4, False), (11264, 6656, 17, 2, False), (12292, 11008, 32, 3, True),
+                 (16400, 8192, 17, 2, True), (16400, 8192, 32, 2, True), (20500, 11008, 17, 2, True)]
+
+
+@pytest.mark.parametrize("group,m,k,n,ranges,flush", [(32,) + r for r in RANGES] +
+                         [(g,) + r for g in (64, 128) for r in RANGES_COARSE + [r for r in RANGES if r[2] > 32]])
 def test_several_k_ranges_against_float64(rx, group, m, k, n, ranges, flush):
     g = _gen(m + k + n)
     w, ref = _packed(rx, "q4", m, k, group, g)
     size = rx.relax_matmul_workspace_bytes(w, 128)
-    assert rx.relax_plan_matmul("q4", n, m, k, size)[:3] == (rx.OK, rx.KERNEL_STREAM, ranges) and _more_tiles_than_lds(n, m, ranges) == flush
+    assert rx.relax_plan_matmul("q4", n, m, k, size, group)[:3] == (rx.OK, rx.KERNEL_STREAM, ranges) and _more_tiles_than_lds(n, m, k, ranges, group) == flush
     ws = torch.full((size + 4096,), 7, dtype=torch.uint8, device="cuda")
     x = torch.randn(n, k, device="cuda", generator=g).half()
     out = [torch.full((n, m), float("nan"), device="cuda", dtype=torch.float16) for _ in range(2)]
@@ -266,13 +278,16 @@ def test_wide_layers_against_the_first_rows_of_a_larger_call(rx, fmt, shape, row
         assert float((layer.k[0, :n].double() - k_all[0, :n].double()).norm() / k_all[0, :n].double().norm()) < 2e-3
 
 
-# Units per wavefront 1 (some wavefronts without any) to 5, whole and ragged; rows around a tile; one, two and three packs of scales
-EXACT_Q4 = [(20, 256), (40, 1280), (72, 4352), (520, 8192), (36, 9984), (40, 13824)]
+# Rows around a tile, whole and ragged slices; units per wavefront at 2 (1: some wavefronts without any), 5 and 16 rows, and at 17 and 32 of groups of
+# 64 and 128 (three units of 32 rows of x take their scales on codes); 0: the groups differ
+EXACT_Q4 = [(20, 256, (1, 1, 1), (1, 1)), (40, 1280, (1, 1, 1), (1, 1)), (72, 4352, (3, 3, 1), (1, 1)), (520, 8192, (1, 1, 1), (1, 1)), (36, 9984, (5, 1, 1), (1, 1)),
+            (40, 13824, (2, 1, 1), (1, 1)), (8200, 4096, (2, 2, 2), (2, 2)), (12292, 6144, (3, 3, 0), (3, 3)), (12292, 6656, (4, 4, 0), (2, 2)),
+            (12292, 9984, (5, 5, 1), (3, 2)), (40976, 8192, (4, 4, 4), (2, 2))]
 
 
-@pytest.mark.parametrize("m,k", EXACT_Q4)
+@pytest.mark.parametrize("m,k,units,units_32", EXACT_Q4)
 @pytest.mark.parametrize("group", [32, 64, 128])
-def test_4bit_scales_meet_fp32_sums(rx, group, m, k):
+def test_4bit_scales_meet_fp32_sums(rx, group, m, k, units, units_32):
     """Up to 16 rows of groups of 32 and 32 rows of longer ones are exact but for the fp32 sums and the rounding of the result, for scales of any size,
     for x far from zero and for small x: the codes go in as u + 64, so a group's terms are at most 79 / 8 of those of its largest codes."""
     g = _gen(m + k + group)
@@ -286,8 +301,12 @@ def test_4bit_scales_meet_fp32_sums(rx, group, m, k):
         w = rx.QMat(w.q, s, m, k, group)
         ref = codes.double() * s.double().repeat_interleave(group, 1)
         largest = 79 * s.double().repeat_interleave(group, 1)
-        for n in (2, 5, 16) + ((17, 32) if group > 32 else ()):
-            if rx.relax_plan_matmul("q4", n, m, k, size)[1] != rx.KERNEL_STREAM:      # (plans are for groups of 32; where the split-K kernel is near)
+        for n, want_units in list(zip((2, 5, 16), units)) + (list(zip((17, 32), units_32)) if group > 32 else []):
+            _, kernel, ranges, *_ = rx.relax_plan_matmul("q4", n, m, k, size, group)
+            if kernel != rx.KERNEL_STREAM and want_units == 0:                        # (the split-K kernel takes it)
+                continue
+            assert kernel == rx.KERNEL_STREAM and (want_units == 0 or _units(k, ranges) == want_units)
+            if n > 16 and want_units > 2:
                 continue
             x = (torch.randn(n, k, device="cuda", generator=g) * std + mean).half()
             out = torch.empty(n, m, device="cuda", dtype=torch.float16)
@@ -316,7 +335,8 @@ def test_4bit_infinite_scales_stay_in_their_row(rx, group):
     assert not torch.isfinite(out[:, ~rows].float()).any()
 
 
-@pytest.mark.parametrize("m,k", [(40, 1280), (24, 13824)])
+# (the last one takes its sums out of LDS inside the loop where groups are long)
+@pytest.mark.parametrize("m,k", [(40, 1280), (24, 13824), (16400, 8192)])
 @pytest.mark.parametrize("n", [5, 16, 32])
 @pytest.mark.parametrize("group", [32, 64, 128])
 def test_4bit_infinite_x_keeps_its_sign(rx, group, n, m, k):
@@ -324,7 +344,7 @@ def test_4bit_infinite_x_keeps_its_sign(rx, group, n, m, k):
     g = _gen(m + k + group)
     w, ref = _packed(rx, "q4", m, k, group, g)
     size = rx.relax_matmul_workspace_bytes(w, 64)
-    assert rx.relax_plan_matmul("q4", n, m, k, size)[1] == rx.KERNEL_STREAM
+    assert rx.relax_plan_matmul("q4", n, m, k, size, group)[1] == rx.KERNEL_STREAM
     ws = torch.empty(size, dtype=torch.uint8, device="cuda")
     x = torch.randn(n, k, device="cuda", generator=g).half()
     clean, out = (torch.empty(n, m, device="cuda", dtype=torch.float16) for _ in range(2))
