@@ -26,7 +26,7 @@ extern "C" {
  * the matrix-vector kernels (two or four rows of x share one pass over the weights): two rows on every model, more when
  * every matrix of the layer is at most "layer_matvec_mb" MB of packed codes (default 96, 0 .. 4096) -- a model that mostly
  * stays in the last-level cache; above it the few-row matrix path takes the call, and three and four rows also below where its
- * streaming kernel serves all four matrices and they hold 225 million weights together (groups of 64 and 128: 195 million), unless the
+ * streaming kernel serves all four matrices and they hold 150 million weights together, unless the
  * value is above the default.  1: matrix path from two rows on.
  * "half_matmul_gemm_rows" (default 0): relax_half_matmul takes the tiled GEMM from this many rows on; 0: by estimate.
  * Unknown name: RELAX_ERR_UNSUPPORTED.                                                                           */

@@ -719,15 +719,15 @@ relax_status layer_enqueue(const relax_layer_dims &dm, const relax_layer_weights
     // Three and four rows take the streaming kernel where it serves all four matrices, as exact, and the layer is large: it needs nine launches
     // for the matvec path's five or six, which the second pass over the weights has to outweigh (us per layer at L = 300, weights cold, matvec /
     // stream at four rows; groups of 32, 64, 128):
-    //   hidden, ffn, heads (M weights)           2048, 5632, 16 / 16 (51)     34.6 / 44.5   34.5 / 43.4   34.7 / 41.1
-    //   3072, 8192, 24 / 8 (101)     47.8 / 52.3   47.8 / 52.3   47.9 / 51.1   4096, 8192, 32 / 32 (168)    54.5 / 57.0   54.0 / 55.4   53.9 / 54.2
-    //   5120, 8192, 40 / 8 (189)     62.3 / 64.9   62.2 / 63.0   61.9 / 60.8   4096, 11008, 32 / 32 (202)   61.8 / 61.7   61.8 / 60.0   61.6 / 58.2
-    //   4096, 14336, 32 / 8 (218)    60.6 / 62.2   61.1 / 60.5   61.1 / 59.5   5120, 8192, 40 / 40 (231)    74.5 / 71.4   73.8 / 69.6   73.5 / 67.0
-    //   3584, 18944, 28 / 4 (233)    70.6 / 70.2   70.7 / 67.5   71.0 / 65.8   5120, 13824, 40 / 40 (317)   91.9 / 83.3   93.0 / 79.4   94.3 / 77.0
+    //   hidden, ffn, heads (M weights)   1024, 2816, 16 / 16 (13)   30.5 / 33.8   30.7 / 33.7   30.6 / 32.8   2048, 5632, 16 / 16 (51)  34.9 / 40.5   34.8 / 39.5   35.2 / 38.7
+    //   3072, 8192, 24 / 8 (101)    48.8 / 50.3   48.5 / 50.2   48.5 / 49.4   4096, 8192, 32 / 8 (143)    49.8 / 51.3   49.7 / 50.3   49.7 / 49.1
+    //   3584, 9728, 28 / 28 (156)   60.1 / 56.8   59.5 / 55.3   59.7 / 53.6   4096, 8192, 32 / 32 (168)   55.5 / 54.1   55.6 / 53.2   55.3 / 52.2
+    //   5120, 8192, 40 / 8 (189)    62.6 / 62.5   62.4 / 60.7   62.3 / 59.1   4096, 11008, 32 / 32 (202)  62.2 / 59.0   62.7 / 58.0   62.8 / 56.2
+    //   4096, 14336, 32 / 8 (218)   62.2 / 59.8   62.1 / 58.8   61.9 / 57.4   5120, 13824, 40 / 40 (317)  92.5 / 79.5   91.3 / 75.7   91.5 / 74.1
     // A switch above the default keeps these calls on the matvec kernels.
     const bool matvec_call = n >= 2 && n <= g_opt_matvec_rows.load() && (n == 2 || largest <= ((size_t)g_opt_matvec_mb.load() << 20));
     const double weights = (double)wt->wqkv.m * wt->wqkv.k + (double)wt->wo.m * wt->wo.k + (double)wt->wgu.m * wt->wgu.k + (double)wt->wdown.m * wt->wdown.k;
-    const bool large = weights >= (gshift_of(wt->wqkv.group) == 0 ? 225e6 : 195e6);
+    const bool large = weights >= 150e6;
     const bool streamable = matvec_call && n > 2 && n <= kMatvecRows && g_opt_matvec_rows.load() <= kMatvecRows && large;
 
     // More than one row: matrix path (same entry point, same binary) -- the matmuls run on MFMA: up to kSkinnyMaxN rows the streaming
