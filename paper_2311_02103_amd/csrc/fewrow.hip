@@ -63,8 +63,11 @@ struct Cost {
     double launch, tb_per_s, unit, tile, x, finish, range, partial, full, round;
 };
 constexpr Cost kCostQ4[3] = {{4.1, 6.2, 0.62, 0.31, 23, 2.0, 0.32, 7.9, 1.4, 6.6}, {4.6, 5.4, 0.79, 0.0, 32, 2.2, 0.57, 2.7, 0.0, 8.0}, {4.8, 3.1, 1.39, 0.05, 25, 2.6, 0.79, 38}};
-// ... of a plain matmul of up to 16 rows, and of six units with scales on codes: the kernel with two and three row tiles in flight and scales on
-// codes, which six units still are.
+// ... of six units, which have scales on codes, and of plain matmuls of up to 16 rows: fitted to the kernel with two and three row tiles in flight and
+// scales on codes.  Plain matmuls keep these figures, and so the kernel and cut that the host tests pin with that kernel's times, although the
+// stream has become faster: over 76 launches (19 matrices, 2 to 16 rows) what they choose is 3.6 % off the fastest on average, 22 % at
+// most, where that is split-K or too few k ranges (us, split-K / stream: 8192 x 8192 at 4 rows 15.2 / 12.5, 15360 x 5120 at 16 rows 18.9 / 15.8, 10240 x
+// 8192 at 8 rows 18.2 / 15.1).
 constexpr Cost kCostQ4Alone = {4.2, 9.5, 0.65, 0.17, 35, 3.1, 0.33, 3.3, 3.4};
 constexpr Cost kCostQ4Coarse[2] = {{4.1, 6.8, 0.64, 0.06, 22, 1.9, 0.32, 2.7, 1.6, 6.9}, {4.8, 36, 0.49, 0.42, 27, 1.5, 0.34, 2.8, 9.3, 2.2}};
 // 3-bit and fp16 matrices: the rates of the stream alone (what is estimated for them only picks the k ranges of a layer's matrices)
@@ -116,11 +119,6 @@ double split_us(int n, int m, int k)
            (double)splits * n * m * 8e-6 / c.partial;
 }
 
-// Up to 16 rows of a layer's output and down projections, where both kernels need the finishing pass: by themselves they tie on many matrices
-// (5120 x 13824 at 16 rows 17.7 against 17.5), inside a layer the split-K kernel, with less x traffic, is ahead of its estimate (13B: 14 rows
-// of the down projection 17.0 us against 20.0, 6 of the output projection 14.2 against 14.6; the QKV matrix of the 70B shape is not: 20.3
-// against 22.0 with the rotary step, nor is its down projection, 33 against 38 at 4 rows).
-constexpr double kCutTie = 1.5;
 // Groups of 64 and 128: its scale staging is made for groups of 32 (us at 6, 16 and 32 rows, groups of 32 / 64 / 128: 4096 x 4096 11.6 / 13.1 / 12.9,
 // 12.0 / 13.5 / 13.4, 13.5 / 14.8 / 14.7; 5120 x 13824 16.5 / 19.5 / 18.9, 17.3 / 21.4 / 19.8, 19.5 / 22.0 / 21.8; 22016 x 4096 22.5 / 25.9 / 25.0, 23.4 /
 // 26.2 / 26.0, 26.7 / 29.3 / 29.4; without the factor a 13B layer of 8 rows takes 79.3 us with groups of 64, so 77.2).
@@ -189,12 +187,12 @@ int fewrow_ranges(int wmode, int gshift, int n, int m, int k, int epi, bool fold
     double us = 0.0;
     const int kr = best_ranges(fmt, n, m, k, epi, folded, alone, exact, partial_floats, &us);
     // A 4-bit matrix may also go through the split-K few-row kernel, whose workgroups own 128 rows and an eighth of k: an eighth of the
-    // x traffic, a lower rate.  It is the better one where its workgroups fill the chip and rows are long or x has many rows (8192 x
-    // 8192 at 16 rows 16.5 against 18.6 us, 5120 x 13824 17.8 against 20.0, 15360 x 5120 at 64 rows 29.9 against 35.4), the stream
-    // on the others (22016 x 4096 at 16 rows 19.1 against 23.4, 57344 x 8192 58 against 74).
+    // x traffic, a lower rate.  It is the better one where its workgroups fill the chip, rows are long and x has many of them (groups of 32, split-K /
+    // stream, us: 4096 x 11008 at 32 rows 16.6 / 20.6, 8192 x 8192 18.6 / 23.0, 15360 x 5120 at 64 28.2 / 35.8), a tie at 16 rows of such
+    // matrices (8192 x 8192 16.5 / 15.9), the stream on the others (at 16 rows 22016 x 4096 23.5 / 16.6, 57344 x 8192 81 / 58.5).
     // Up to kMatvecRows rows of a layer stay here: that kernel rounds the weights, which the matvec kernels do not.
     if (wmode == W_Q4 && kr > 0 && (alone || n > kMatvecRows) && gemm_skinny_partial_floats(m, k, n) > 0 && partial_floats >= gemm_skinny_partial_floats(m, k, n) &&
-        gemm_skinny_us(n, m, k, gshift) - (folded ? kFolded : 0.0) < us + (!alone && n <= 16 && kr > 1 && epi != EPI_F16 ? kCutTie : 0.0))
+        gemm_skinny_us(n, m, k, gshift) - (folded ? kFolded : 0.0) < us)
         return 0;
     // ... and on matrices that fill the chip with tiles through the tiled GEMM (48 rows: 49152 x 2048 26.5 against 45.3 us, 57344 x 8192 87 against 99),
     // in a layer from 33 rows on wherever that is estimated faster (64 rows, stream / split-K / tiled: 22016 x 4096 33 / 39 / 30, 27648 x 5120 47 / 53

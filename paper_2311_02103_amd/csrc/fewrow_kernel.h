@@ -8,7 +8,7 @@
 //     COLUMNS (UW units of 256, fp16: 128) for good: its share of x sits in registers as ready MFMA operands, read once, and it
 //     streams its slice of row tile after row tile (16 weight rows) of the workgroup's range.  Nothing is shared inside the loop:
 //     no LDS staging, no barrier, the only memory operations in flight are weights and scales.
-//   - Little in flight: one row tile (32 to 64 KB per CU).  A bare read of 235 MB in this pattern takes 39.4 us with 64 KB per CU and 42.5
+//   - Little in flight: one row tile (8 KB per CU and unit, 16 in two tiles of one unit; fp16 16 KB per unit, half a tile from six units on).  A bare read of 235 MB in this pattern takes 39.4 us with 64 KB per CU and 42.5
 //     with 128 (lines of 128, 256 or 512 bytes per row and load: the same; neighbouring tiles dealt out over the CUs: slower), and the
 //     kernels gain more than that (us, two or three tiles / one: 4 bits, 16 rows 22016 x 4096 18.2 / 16.5, 57344 x 8192 60.5 / 56.6, 8192 x
 //     28672 39.7 / 35.3; 3 bits, 8 rows 22016 x 4096 21.3 / 18.7; fp16, 8 rows of 8192 x 8192 four units / two 35.6 / 31.3).
@@ -763,7 +763,7 @@ struct Plan {
     int kg, rg, uw, tiles;
 };
 
-// row tiles in flight (packed formats: 8 registers per unit, 1 KB per load), and units of a tile: 8 KB per wavefront are enough, fp16 16 KB
+// row tiles in flight (packed formats: 8 registers and 1 KB per unit), and units of a tile: the whole tile but where registers are short
 template <int FMT, int NB, int UW>
 constexpr int tiles_in_flight()
 {
