@@ -523,7 +523,7 @@ def bench_model(args, np, torch, wl, rx, big):
     m, k = shape.matrices()["wgu"]
     gu_bytes = m * (k // 2) + m * (k // 32) * 2
     ach = gu_bytes / (kernel_ms["gate_up"] * 1e-3) / 1e9
-    kernel = ("fewrow_kernel<F_Q4G32, 1, 4, 1, 4> (gate/up with SwiGLU, m=57344, k=8192, n=16)" if big else
+    kernel = ("fewrow_kernel<F_Q4G32, 1, 4, 1, 4, false> (gate/up with SwiGLU, m=57344, k=8192, n=16)" if big else
               "gemv_q4_reg_kernel<X_F32_NORM, EPI_SWIGLU, 2> (gate/up matvec, m=22016, k=4096)")
     roofline = {"bound": "hbm", "kernel": kernel, "achieved": round(ach, 1), "peak": PEAK_HBM_GBS, "unit": "GB/s",
                 "frac": round(ach / PEAK_HBM_GBS, 4),

@@ -69,6 +69,7 @@ constexpr Cost kCostQ4[3] = {{4.1, 6.2, 0.62, 0.31, 23, 2.0, 0.32, 7.9, 1.4, 6.6
 // most, where that is split-K or too few k ranges (us, split-K / stream: 8192 x 8192 at 4 rows 15.2 / 12.5, 15360 x 5120 at 16 rows 18.9 / 15.8, 10240 x
 // 8192 at 8 rows 18.2 / 15.1).
 constexpr Cost kCostQ4Alone = {4.2, 9.5, 0.65, 0.17, 35, 3.1, 0.33, 3.3, 3.4};
+// ... groups of 64 and 128 (at 32 rows the arithmetic of a unit is what counts: the fit leaves the stream nothing)
 constexpr Cost kCostQ4Coarse[2] = {{4.1, 6.8, 0.64, 0.06, 22, 1.9, 0.32, 2.7, 1.6, 6.9}, {4.8, 36, 0.49, 0.42, 27, 1.5, 0.34, 2.8, 9.3, 2.2}};
 // 3-bit and fp16 matrices: the rates of the stream alone (what is estimated for them only picks the k ranges of a layer's matrices)
 constexpr Cost kCostQ3[3] = {{5.8, 5.9, 0.46, 0.0, 25, 3.1, 0.0, 5.8}, {5.8, 5.35, 0.51, 0.0, 27, 3.4, 0.0, 5.3}, {5.8, 4.7, 0.58, 0.0, 31, 3.9, 0.0, 4.6}};

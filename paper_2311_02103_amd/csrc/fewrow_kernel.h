@@ -210,7 +210,7 @@ __device__ __forceinline__ int tile_first_row(const A &a, int t)
     return t * 16;
 }
 
-// The kernel's arguments, read again.  What the compiler holds in scalar registers over the loop for the code behind it, it spills: 45 moves in front
+// The kernel's arguments, its one parameter, read again from where they were passed.  What the compiler holds in scalar registers over the loop for the code behind it, it spills: 45 moves in front
 // of the first data, 80 (with redo_rows 280) behind the loop.  Without them a launch takes 0.5 to 1 us less (us: 4 rows, groups of 32, 4096 x
 // 4096 7.1 -> 6.3, 22016 x 4096 16.2 -> 14.9, 57344 x 8192 53.9 -> 53.2; 32 rows, groups of 128, 12288 x 4096 15.9 -> 14.9).
 __device__ __forceinline__ const Args &args_again()
